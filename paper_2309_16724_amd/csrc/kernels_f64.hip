@@ -177,27 +177,28 @@ __device__ __forceinline__ void item_f64(const Tile &T, const Seg *__restrict__ 
 // Three wavefronts per SIMD (at most 168 registers, no spills): more loads in
 // flight per SIMD than the two that the register use of an unbounded build
 // allows; four spill.
+constexpr int F64_GRID = 256 * 3;   // resident work groups (three wavefronts per SIMD)
 template <int STAGE>
 __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(3, 3))) stage_f64_kernel(
     const Tile *__restrict__ tiles, const Seg *__restrict__ segs, XcdQueues q, int32_t *__restrict__ counters,
-    const double *const *__restrict__ bases, const double *__restrict__ psi, double *__restrict__ y,
+    int32_t *__restrict__ next_counters, int chunk, const double *const *__restrict__ bases, const double *__restrict__ psi, double *__restrict__ y,
     double *__restrict__ work, double *__restrict__ part) {
   const int lane = threadIdx.x & 63;
   const int r16 = lane & 15, q4 = lane >> 4;
-  const int x = xcc_id();
-  int qi = 0;
-  for (;;) {
-    // the tile index is the same for the whole wavefront: saying so makes the
-    // descriptors scalar loads and the K loops uniform (no exec masking)
-    int v = -1;
-    if (lane == 0) v = queue_next(q, counters, x, qi);
-    const int t = __builtin_amdgcn_readfirstlane(v);
-    if (t < 0) break;
-    const Tile T = tiles[t];
-    if (T.mb == 1) item_f64<1>(T, segs, bases, psi, y, work, part, r16, q4);
-    else if (T.mb == 4) item_f64<4>(T, segs, bases, psi, y, work, part, r16, q4);
-    else item_f64<2>(T, segs, bases, psi, y, work, part, r16, q4);
-  }
+  clear_counters(next_counters);
+  // the tile index is the same for the whole wavefront: saying so makes the
+  // descriptors scalar loads and the K loops uniform (no exec masking)
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD) * WAVES + wave, (int)(gridDim.x / NXCD) * WAVES, chunk);
+  do {
+    wq.request(lane == 0);
+    for (; wq.t < wq.tend; wq.t++) {
+      const Tile T = tiles[wq.t];
+      if (T.mb == 1) item_f64<1>(T, segs, bases, psi, y, work, part, r16, q4);
+      else if (T.mb == 4) item_f64<4>(T, segs, bases, psi, y, work, part, r16, q4);
+      else item_f64<2>(T, segs, bases, psi, y, work, part, r16, q4);
+    }
+  } while (wq.next(lane));
 }
 
 // Y tile += sum of its partial tiles, in part order
@@ -221,7 +222,8 @@ __global__ void reduce_kernel(const Reduce *__restrict__ red, int nred, const do
   }
 }
 
-__global__ void zero_kernel(double *y, int64_t n) {
+__global__ void zero_kernel(double *y, int64_t n, int32_t *counters) {
+  if (counters) clear_counters(counters);
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
     y[i] = 0.0;
@@ -268,26 +270,25 @@ void launch_dress(const DressItem *items, int nitems, const int64_t *src_off, co
                      nitems, src_off, alpha, bases, dst);
 }
 
-void launch_zero(double *y, int64_t n, void *stream) {
-  if (n <= 0) return;
-  int grid = (int)std::min<int64_t>((n + 255) / 256, 4096);
-  hipLaunchKernelGGL(zero_kernel, dim3(grid), dim3(256), 0, (hipStream_t)stream, y, n);
+void launch_zero(double *y, int64_t n, int32_t *counters, void *stream) {
+  if (n <= 0 && !counters) return;
+  int grid = (int)std::min<int64_t>((std::max<int64_t>(n, 1) + 255) / 256, 4096);
+  hipLaunchKernelGGL(zero_kernel, dim3(grid), dim3(256), 0, (hipStream_t)stream, y, n, counters);
 }
 
 void launch_tiles_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles, const XcdQueues &q,
-                      int32_t *counters, const double *const *bases, const double *psi, double *y, double *work,
+                      QueueSets &qs, const double *const *bases, const double *psi, double *y, double *work,
                       double *part, void *stream) {
   if (ntiles <= 0) return;
   hipStream_t s = (hipStream_t)stream;
-  launch_fill_int(counters, NXCD, 0, stream);
-  int grid = std::min((ntiles + WAVES - 1) / WAVES, 256 * 16);
-  grid = (grid + 7) / 8 * 8;
+  const int grid = wave_grid(ntiles, F64_GRID), chunk = wave_chunk(ntiles, F64_GRID);
   if (stage == 1)
-    hipLaunchKernelGGL(stage_f64_kernel<1>, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, q, counters, bases,
-                       psi, y, work, part);
+    hipLaunchKernelGGL(stage_f64_kernel<1>, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, q, qs.cur(), qs.other(),
+                       chunk, bases, psi, y, work, part);
   else
-    hipLaunchKernelGGL(stage_f64_kernel<2>, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, q, counters, bases,
-                       psi, y, work, part);
+    hipLaunchKernelGGL(stage_f64_kernel<2>, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, q, qs.cur(), qs.other(),
+                       chunk, bases, psi, y, work, part);
+  qs.launch++;
 }
 
 void launch_reduce(const Reduce *red, int nred, const double *part, double *y, void *stream) {

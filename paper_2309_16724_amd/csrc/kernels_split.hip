@@ -190,6 +190,7 @@ constexpr int WAIT_VM0 = 0x0F70, WAIT_LGKM0 = 0xC07F;
 
 // LDS stage of one wavefront: (MB + NB) * NS chunks of 64 lanes x 16 bytes
 constexpr int stage_bytes(int ns) { return 5 * ns * 1024; }
+constexpr int LDS_BYTES = 160 * 1024;   // per CU
 
 // FP32 sum of slice-product group d for s = NS (see slice_groups)
 template <int NS>
@@ -368,6 +369,7 @@ template <int NS>
 __device__ __forceinline__ void items_split(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,
                                             const SegS *__restrict__ ssegs, const XcdQueues &q,
                                             int32_t *__restrict__ counters,
+                                            int32_t *__restrict__ next_counters, int chunk,
                                             const double *const *__restrict__ bases, const double *__restrict__ psi,
                                             double *__restrict__ y, double *__restrict__ work,
                                             double *__restrict__ part, const SliceBufs &bufs) {
@@ -375,18 +377,17 @@ __device__ __forceinline__ void items_split(const Tile *__restrict__ tiles, cons
   const int r16 = lane & 15, q4 = lane >> 4;
   __shared__ __attribute__((aligned(1024))) char lds[WAVES * stage_bytes(NS)];
   char *stage = lds + wave * stage_bytes(NS);
-  const int x = xcc_id();
-  int qi = 0;
-  for (;;) {
-    int v = -1;
-    if (lane == 0) v = queue_next(q, counters, x, qi);
-    const int t = __builtin_amdgcn_readfirstlane(v);
-    if (t < 0) break;
-    const Tile T = tiles[t];
-    if (T.mb == 1) item_split<1, NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, stage, r16, q4);
-    else if (T.mb == 4) item_split<4, NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, stage, r16, q4);
-    else item_split<2, NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, stage, r16, q4);
-  }
+  clear_counters(next_counters);
+  WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD) * WAVES + wave, (int)(gridDim.x / NXCD) * WAVES, chunk);
+  do {
+    wq.request(lane == 0);
+    for (; wq.t < wq.tend; wq.t++) {
+      const Tile T = tiles[wq.t];
+      if (T.mb == 1) item_split<1, NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, stage, r16, q4);
+      else if (T.mb == 4) item_split<4, NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, stage, r16, q4);
+      else item_split<2, NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, stage, r16, q4);
+    }
+  } while (wq.next(lane));
 }
 
 // ------------------------------------------------------------ work-group tiles
@@ -592,6 +593,7 @@ template <int NS>
 __device__ __forceinline__ void macro_items(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,
                                             const SegS *__restrict__ ssegs, const XcdQueues &q,
                                             int32_t *__restrict__ counters,
+                                            int32_t *__restrict__ next_counters, int32_t *__restrict__ mailboxes,
                                             const double *const *__restrict__ bases, const double *__restrict__ psi,
                                             double *__restrict__ y, double *__restrict__ work,
                                             double *__restrict__ part, const SliceBufs &bufs) {
@@ -600,20 +602,29 @@ __device__ __forceinline__ void macro_items(const Tile *__restrict__ tiles, cons
   // tile index taken by thread 0 reaches the other wavefronts through this
   // work group's mailbox in global memory (atomics: coherent at the L2)
   __shared__ __attribute__((aligned(1024))) char lds[2 * mstage_bytes(NS)];
-  int32_t *mailbox = counters + NXCD + blockIdx.x;
-  const int x = xcc_id();   // this work group's XCD: its own range first
-  int qi = 0;               // thread 0's queue state
+  int32_t *mailbox = mailboxes + blockIdx.x;
+  clear_counters(next_counters);
+  WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD), (int)(gridDim.x / NXCD), 1);
+  int t = wq.t < wq.tend ? wq.t : -1;
+  bool fixed = true;   // t is this work group's fixed first tile (-1: none)
   for (;;) {
-    if (threadIdx.x == 0) atomicExch(mailbox, queue_next(q, counters, x, qi));
-    // every wave reads the mailbox before the barrier inside macro_split, the
-    // earliest point where thread 0 can write it again
+    if (t < 0 && !fixed) break;   // every range is used up: the whole work group leaves
+    if (wave == 0) wq.request(lane == 0);
+    if (t >= 0) {
+      const Tile T = tiles[t];
+      macro_split<NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, lds, wave, lane);
+    }
+    fixed = false;
+    if (wave == 0) {
+      const int v = wq.next(lane) ? wq.t : -1;
+      if (lane == 0) atomicExch(mailbox, v);
+    }
+    // every wave reads the mailbox before the barrier inside the tile, the
+    // earliest point after which wave 0 can write it again
     __syncthreads();
     int v = 0;
     if (lane == 0) v = atomicAdd(mailbox, 0);
-    const int t = __builtin_amdgcn_readfirstlane(v);
-    if (t < 0) break;   // every queue is empty: the whole work group leaves
-    const Tile T = tiles[t];
-    macro_split<NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, lds, wave, lane);
+    t = __builtin_amdgcn_readfirstlane(v);
   }
 }
 
@@ -621,18 +632,20 @@ __device__ __forceinline__ void macro_items(const Tile *__restrict__ tiles, cons
   __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))                 \
   stage1_msplit##NS##_kernel(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,                  \
                              const SegS *__restrict__ ssegs, XcdQueues q, int32_t *__restrict__ counters,   \
+                             int32_t *__restrict__ next_counters, int32_t *__restrict__ mailboxes,           \
                              const double *const *__restrict__ bases, const double *__restrict__ psi,       \
                              double *__restrict__ y, double *__restrict__ work, double *__restrict__ part,   \
                              SliceBufs bufs) {                                                              \
-    macro_items<NS>(tiles, segs, ssegs, q, counters, bases, psi, y, work, part, bufs);                      \
+    macro_items<NS>(tiles, segs, ssegs, q, counters, next_counters, mailboxes, bases, psi, y, work, part, bufs);                      \
   }                                                                                                         \
   __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))                 \
   stage2_msplit##NS##_kernel(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,                  \
                              const SegS *__restrict__ ssegs, XcdQueues q, int32_t *__restrict__ counters,   \
+                             int32_t *__restrict__ next_counters, int32_t *__restrict__ mailboxes,           \
                              const double *const *__restrict__ bases, const double *__restrict__ psi,       \
                              double *__restrict__ y, double *__restrict__ work, double *__restrict__ part,   \
                              SliceBufs bufs) {                                                              \
-    macro_items<NS>(tiles, segs, ssegs, q, counters, bases, psi, y, work, part, bufs);                      \
+    macro_items<NS>(tiles, segs, ssegs, q, counters, next_counters, mailboxes, bases, psi, y, work, part, bufs);                      \
   }
 
 MACRO_KERNELS(3)
@@ -863,6 +876,7 @@ template <int NS>
 __device__ __forceinline__ void wide_items(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,
                                            const SegS *__restrict__ ssegs, const XcdQueues &q,
                                            int32_t *__restrict__ counters,
+                                            int32_t *__restrict__ next_counters, int32_t *__restrict__ mailboxes,
                                            const double *const *__restrict__ bases, const double *__restrict__ psi,
                                            double *__restrict__ y, double *__restrict__ work,
                                            double *__restrict__ part, const SliceBufs &bufs) {
@@ -872,18 +886,29 @@ __device__ __forceinline__ void wide_items(const Tile *__restrict__ tiles, const
   // mailbox as in macro_items
   __shared__ __attribute__((aligned(1024))) char lds0[wstage_bytes(NS)];
   __shared__ __attribute__((aligned(1024))) char lds1[wstage_bytes(NS)];
-  int32_t *mailbox = counters + NXCD + blockIdx.x;
-  const int x = xcc_id();
-  int qi = 0;
+  int32_t *mailbox = mailboxes + blockIdx.x;
+  clear_counters(next_counters);
+  WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD), (int)(gridDim.x / NXCD), 1);
+  int t = wq.t < wq.tend ? wq.t : -1;
+  bool fixed = true;   // t is this work group's fixed first tile (-1: none)
   for (;;) {
-    if (threadIdx.x == 0) atomicExch(mailbox, queue_next(q, counters, x, qi));
+    if (t < 0 && !fixed) break;   // every range is used up: the whole work group leaves
+    if (wave == 0) wq.request(lane == 0);
+    if (t >= 0) {
+      const Tile T = tiles[t];
+      wide_split<NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, lds0, lds1, wave, lane);
+    }
+    fixed = false;
+    if (wave == 0) {
+      const int v = wq.next(lane) ? wq.t : -1;
+      if (lane == 0) atomicExch(mailbox, v);
+    }
+    // every wave reads the mailbox before the barrier inside the tile, the
+    // earliest point after which wave 0 can write it again
     __syncthreads();
     int v = 0;
     if (lane == 0) v = atomicAdd(mailbox, 0);
-    const int t = __builtin_amdgcn_readfirstlane(v);
-    if (t < 0) break;
-    const Tile T = tiles[t];
-    wide_split<NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, lds0, lds1, wave, lane);
+    t = __builtin_amdgcn_readfirstlane(v);
   }
 }
 
@@ -891,18 +916,20 @@ __device__ __forceinline__ void wide_items(const Tile *__restrict__ tiles, const
   __global__ void __launch_bounds__(64 * WIDE_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))           \
   stage1_wsplit##NS##_kernel(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,                  \
                              const SegS *__restrict__ ssegs, XcdQueues q, int32_t *__restrict__ counters,   \
+                             int32_t *__restrict__ next_counters, int32_t *__restrict__ mailboxes,           \
                              const double *const *__restrict__ bases, const double *__restrict__ psi,       \
                              double *__restrict__ y, double *__restrict__ work, double *__restrict__ part,   \
                              SliceBufs bufs) {                                                              \
-    wide_items<NS>(tiles, segs, ssegs, q, counters, bases, psi, y, work, part, bufs);                       \
+    wide_items<NS>(tiles, segs, ssegs, q, counters, next_counters, mailboxes, bases, psi, y, work, part, bufs);                       \
   }                                                                                                         \
   __global__ void __launch_bounds__(64 * WIDE_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))           \
   stage2_wsplit##NS##_kernel(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,                  \
                              const SegS *__restrict__ ssegs, XcdQueues q, int32_t *__restrict__ counters,   \
+                             int32_t *__restrict__ next_counters, int32_t *__restrict__ mailboxes,           \
                              const double *const *__restrict__ bases, const double *__restrict__ psi,       \
                              double *__restrict__ y, double *__restrict__ work, double *__restrict__ part,   \
                              SliceBufs bufs) {                                                              \
-    wide_items<NS>(tiles, segs, ssegs, q, counters, bases, psi, y, work, part, bufs);                       \
+    wide_items<NS>(tiles, segs, ssegs, q, counters, next_counters, mailboxes, bases, psi, y, work, part, bufs);                       \
   }
 
 WIDE_KERNELS(3)
@@ -912,17 +939,19 @@ WIDE_KERNELS(5)
 #define SPLIT_KERNELS(NS)                                                                                   \
   __global__ void __launch_bounds__(64 * WAVES) stage1_split##NS##_kernel(                                  \
       const Tile *__restrict__ tiles, const Seg *__restrict__ segs, const SegS *__restrict__ ssegs,         \
-      XcdQueues q, int32_t *__restrict__ counters, const double *const *__restrict__ bases,                 \
+      XcdQueues q, int32_t *__restrict__ counters, int32_t *__restrict__ next_counters, int chunk,               \
+      const double *const *__restrict__ bases,                 \
       const double *__restrict__ psi, double *__restrict__ y, double *__restrict__ work,                    \
       double *__restrict__ part, SliceBufs bufs) {                                                          \
-    items_split<NS>(tiles, segs, ssegs, q, counters, bases, psi, y, work, part, bufs);                      \
+    items_split<NS>(tiles, segs, ssegs, q, counters, next_counters, chunk, bases, psi, y, work, part, bufs);                      \
   }                                                                                                         \
   __global__ void __launch_bounds__(64 * WAVES) stage2_split##NS##_kernel(                                  \
       const Tile *__restrict__ tiles, const Seg *__restrict__ segs, const SegS *__restrict__ ssegs,         \
-      XcdQueues q, int32_t *__restrict__ counters, const double *const *__restrict__ bases,                 \
+      XcdQueues q, int32_t *__restrict__ counters, int32_t *__restrict__ next_counters, int chunk,               \
+      const double *const *__restrict__ bases,                 \
       const double *__restrict__ psi, double *__restrict__ y, double *__restrict__ work,                    \
       double *__restrict__ part, SliceBufs bufs) {                                                          \
-    items_split<NS>(tiles, segs, ssegs, q, counters, bases, psi, y, work, part, bufs);                      \
+    items_split<NS>(tiles, segs, ssegs, q, counters, next_counters, chunk, bases, psi, y, work, part, bufs);                      \
   }
 
 SPLIT_KERNELS(3)
@@ -932,11 +961,10 @@ SPLIT_KERNELS(6)
 SPLIT_KERNELS(7)
 
 void launch_macro_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles,
-                        const XcdQueues &q, int32_t *counters, int nslices, const double *const *bases,
+                        const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
                         const double *psi, double *y, double *work, double *part, SliceBufs bufs, void *stream) {
   if (ntiles <= 0) return;
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, s, counters, (int64_t)NXCD, 0);
   // two work groups resident per CU (80 KiB of LDS each at s = 5); every work
   // group takes tiles until all queues are empty
   const int grid = std::max(8, std::min((ntiles + 7) / 8 * 8, MACRO_GRID));
@@ -944,10 +972,11 @@ void launch_macro_split(int stage, const Tile *tiles, const Seg *segs, const Seg
   if (nslices == NS) {                                                                                      \
     if (stage == 1)                                                                                         \
       hipLaunchKernelGGL(stage1_msplit##NS##_kernel, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, ssegs,  \
-                         q, counters, bases, psi, y, work, part, bufs);                                     \
+                         q, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);           \
     else                                                                                                    \
       hipLaunchKernelGGL(stage2_msplit##NS##_kernel, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, ssegs,  \
-                         q, counters, bases, psi, y, work, part, bufs);                                     \
+                         q, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);           \
+    qs.launch++;                                                                                            \
     return;                                                                                                 \
   }
   MLAUNCH(3)
@@ -959,21 +988,21 @@ void launch_macro_split(int stage, const Tile *tiles, const Seg *segs, const Seg
 }
 
 void launch_wide_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles,
-                       const XcdQueues &q, int32_t *counters, int nslices, const double *const *bases,
+                       const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
                        const double *psi, double *y, double *work, double *part, SliceBufs bufs, void *stream) {
   if (ntiles <= 0) return;
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, s, counters, (int64_t)NXCD, 0);
   // one work group per CU (the two stages take all 160 KiB of LDS at s = 5)
   const int grid = std::max(8, std::min((ntiles + 7) / 8 * 8, WIDE_GRID));
 #define WLAUNCH(NS)                                                                                         \
   if (nslices == NS) {                                                                                      \
     if (stage == 1)                                                                                         \
       hipLaunchKernelGGL(stage1_wsplit##NS##_kernel, dim3(grid), dim3(64 * WIDE_WAVES), 0, s, tiles, segs,  \
-                         ssegs, q, counters, bases, psi, y, work, part, bufs);                              \
+                         ssegs, q, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);    \
     else                                                                                                    \
       hipLaunchKernelGGL(stage2_wsplit##NS##_kernel, dim3(grid), dim3(64 * WIDE_WAVES), 0, s, tiles, segs,  \
-                         ssegs, q, counters, bases, psi, y, work, part, bufs);                              \
+                         ssegs, q, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);    \
+    qs.launch++;                                                                                            \
     return;                                                                                                 \
   }
   WLAUNCH(3)
@@ -983,21 +1012,22 @@ void launch_wide_split(int stage, const Tile *tiles, const Seg *segs, const SegS
 }
 
 void launch_tiles_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles,
-                        const XcdQueues &q, int32_t *counters, int nslices, const double *const *bases,
+                        const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
                         const double *psi, double *y, double *work, double *part, SliceBufs bufs, void *stream) {
   if (ntiles <= 0) return;
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(fill_int_kernel, dim3(1), dim3(64), 0, s, counters, (int64_t)NXCD, 0);
-  int grid = std::min((ntiles + WAVES - 1) / WAVES, 256 * 16);
-  grid = (grid + 7) / 8 * 8;
+  // work groups that the LDS stages let run at once
+  const int resident = 256 * std::max(1, LDS_BYTES / (WAVES * stage_bytes(nslices)));
+  const int grid = wave_grid(ntiles, resident), chunk = wave_chunk(ntiles, resident);
 #define LAUNCH(NS)                                                                                          \
   if (nslices == NS) {                                                                                      \
     if (stage == 1)                                                                                         \
       hipLaunchKernelGGL(stage1_split##NS##_kernel, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, ssegs,   \
-                         q, counters, bases, psi, y, work, part, bufs);                                     \
+                         q, qs.cur(), qs.other(), chunk, bases, psi, y, work, part, bufs);           \
     else                                                                                                    \
       hipLaunchKernelGGL(stage2_split##NS##_kernel, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, ssegs,   \
-                         q, counters, bases, psi, y, work, part, bufs);                                     \
+                         q, qs.cur(), qs.other(), chunk, bases, psi, y, work, part, bufs);           \
+    qs.launch++;                                                                                            \
     return;                                                                                                 \
   }
   LAUNCH(3)

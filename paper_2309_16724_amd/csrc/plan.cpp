@@ -1050,13 +1050,11 @@ void release_plan(dmrg_plan *P) {
 // Kernel launches of one H.psi issued by enqueue (launchers skip empty lists).
 int count_launches(const dmrg_plan *P) {
   const bool split = P->precision == DMRG_SPLIT_BF16;
-  int n = P->psi_len > 0;
+  int n = 1;
   if (split) n += !P->jobs_psi.empty();
   for (const Chunk &ch : P->chunks) {
-    // every tile launch clears its queue counters first
-    n += 2 * (!ch.tile1.empty() + !ch.tile2.empty() + !ch.tile1m.empty() + !ch.tile2m.empty() +
-              !ch.tile1x.empty() + !ch.tile2x.empty()) +
-         !ch.red2.empty();
+    n += !ch.tile1.empty() + !ch.tile2.empty() + !ch.tile1m.empty() + !ch.tile2m.empty() + !ch.tile1x.empty() +
+         !ch.tile2x.empty() + !ch.red2.empty();
     if (split) n += (ch.t_exps > 0) + !ch.titems.empty();
   }
   return n;
@@ -1395,7 +1393,8 @@ struct RunBufs {
 };
 
 int enqueue_with(dmrg_plan *p, const double *psi, double *hpsi, void *stream, bool prof, const RunBufs &B) {
-  launch_zero(hpsi, p->psi_len, stream);
+  QueueSets qs{B.counters};
+  launch_zero(hpsi, p->psi_len, qs.cur(), stream);
   const bool split = p->precision == DMRG_SPLIT_BF16;
   if (split)
     launch_slices(p->d_jobs_psi, (int)p->jobs_psi.size(), p->n_slices, p->d_bases, psi, B.work, B.sb, stream);
@@ -1435,21 +1434,21 @@ int enqueue_with(dmrg_plan *p, const double *psi, double *hpsi, void *stream, bo
           rc = timed(30 + stage, s1 ? ch.flops1x : ch.flops2x, [&] {
             launch_wide_split(stage, s1 ? ch.d_tile1x : ch.d_tile2x, s1 ? ch.d_seg1 : ch.d_seg2,
                               s1 ? ch.d_sseg1 : ch.d_sseg2, (int)(s1 ? ch.tile1x : ch.tile2x).size(),
-                              s1 ? ch.q1x : ch.q2x, B.counters, p->n_slices, p->d_bases, psi, hpsi, B.work,
+                              s1 ? ch.q1x : ch.q2x, qs, p->n_slices, p->d_bases, psi, hpsi, B.work,
                               B.part, B.sb, stream);
           });
         if (!rc && !(s1 ? ch.tile1m : ch.tile2m).empty())
           rc = timed(10 + stage, s1 ? ch.flops1m : ch.flops2m, [&] {
             launch_macro_split(stage, s1 ? ch.d_tile1m : ch.d_tile2m, s1 ? ch.d_seg1 : ch.d_seg2,
                                s1 ? ch.d_sseg1 : ch.d_sseg2, (int)(s1 ? ch.tile1m : ch.tile2m).size(),
-                               s1 ? ch.q1m : ch.q2m, B.counters, p->n_slices, p->d_bases, psi, hpsi, B.work,
+                               s1 ? ch.q1m : ch.q2m, qs, p->n_slices, p->d_bases, psi, hpsi, B.work,
                                B.part, B.sb, stream);
           });
         if (!rc && !(s1 ? ch.tile1 : ch.tile2).empty())
           rc = timed(20 + stage, s1 ? ch.flops1w : ch.flops2w, [&] {
             launch_tiles_split(stage, s1 ? ch.d_tile1 : ch.d_tile2, s1 ? ch.d_seg1 : ch.d_seg2,
                                s1 ? ch.d_sseg1 : ch.d_sseg2, (int)(s1 ? ch.tile1 : ch.tile2).size(),
-                               s1 ? ch.q1 : ch.q2, B.counters, p->n_slices, p->d_bases, psi, hpsi, B.work,
+                               s1 ? ch.q1 : ch.q2, qs, p->n_slices, p->d_bases, psi, hpsi, B.work,
                                B.part, B.sb, stream);
           });
       } else {
@@ -1457,7 +1456,7 @@ int enqueue_with(dmrg_plan *p, const double *psi, double *hpsi, void *stream, bo
         if (!(s1 ? ch.tile1 : ch.tile2).empty())
           rc = timed(20 + stage, s1 ? ch.flops1w : ch.flops2w, [&] {
             launch_tiles_f64(stage, s1 ? ch.d_tile1 : ch.d_tile2, s1 ? ch.d_seg1 : ch.d_seg2,
-                             (int)(s1 ? ch.tile1 : ch.tile2).size(), s1 ? ch.q1 : ch.q2, B.counters, p->d_bases,
+                             (int)(s1 ? ch.tile1 : ch.tile2).size(), s1 ? ch.q1 : ch.q2, qs, p->d_bases,
                              psi, hpsi, B.work, B.part, stream);
           });
       }

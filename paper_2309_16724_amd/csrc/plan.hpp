@@ -42,18 +42,44 @@ constexpr int WIDE_MAX_SLICES = 5;
 constexpr int tile_rows(int mb) { return mb == WIDE_MB ? WIDE_EDGE : mb == MACRO_MB ? MACRO_EDGE : 16 * mb; }
 constexpr int tile_cols(int mb) { return mb == WIDE_MB ? WIDE_EDGE : mb == MACRO_MB ? MACRO_EDGE : 64 / mb; }
 
-// Per-XCD queues of a work-group tile list: the list (cost-sorted, operand
-// bands in patches) is cut into NXCD contiguous ranges of equal cost; the work
-// groups of XCD x take the tiles of range x in order through an atomic
-// counter and then help the other ranges, so the tiles that run side by side
-// on one XCD are neighbours in the list and share operand bands in its L2.
+// Per-XCD queues of a tile list: the list (cost-sorted, operand bands in
+// patches) is cut into NXCD contiguous ranges of equal cost; the workers of XCD
+// x take the tiles of range x in order (the first ones by their index, then
+// through an atomic counter) and then help the other ranges, so the tiles
+// that run side by side on one XCD are neighbours in the list and share
+// operand bands in its L2.
 constexpr int NXCD = 8;
 constexpr int MACRO_GRID = 512;          // work groups of a work-group tile launch (two per CU)
 constexpr int WIDE_GRID = 256;           // work groups of a wide tile launch (one per CU)
-constexpr int QUEUE_INTS = NXCD + MACRO_GRID;   // queue counters, then one mailbox per work group
+constexpr int QUEUE_STRIDE = 32;         // ints between counters: a 128-byte line each
+constexpr int QUEUE_SET = NXCD * QUEUE_STRIDE;
+constexpr int QUEUE_INTS = 2 * QUEUE_SET + MACRO_GRID;   // two counter sets, then one mailbox per work group
 struct XcdQueues {
   int32_t start[NXCD + 1];
 };
+// Counters of consecutive tile launches on one stream: a launch uses the
+// current set, which is zero when it starts, and clears the other one.  The
+// first set is cleared by the launch_zero that opens the sequence.
+struct QueueSets {
+  int32_t *base;
+  int launch = 0;
+  int32_t *cur() const { return base + (launch & 1) * QUEUE_SET; }
+  int32_t *other() const { return base + (1 - (launch & 1)) * QUEUE_SET; }
+  int32_t *mailbox() const { return base + 2 * QUEUE_SET; }
+};
+
+// Work groups of a wavefront-tile launch (a multiple of NXCD, no more than fit
+// on the chip at once: `resident`) and tiles per chunk: one tile while every
+// wavefront takes few of them, up to eight for long lists of short tiles, so
+// that each wavefront still asks for about sixteen chunks.
+inline int wave_grid(int ntiles, int resident) {
+  const int blocks = (ntiles + 3) / 4;
+  return blocks < resident ? (blocks + NXCD - 1) / NXCD * NXCD : resident;
+}
+inline int wave_chunk(int ntiles, int resident) {
+  const int c = ntiles / (resident * 4 * 16);
+  return c < 1 ? 1 : c > 8 ? 8 : c;
+}
 
 // One work item: a (16*mb) x (64/mb) tile of an m x n output block (rows
 // i0.., columns j0..) accumulated over segments seg0..seg0+nseg-1 and stored
@@ -217,13 +243,13 @@ constexpr int KPART = 2048;   // target summed K of one second-stage work item
 // default cap of the stripe workspace (288 GB of HBM hold the largest plans in one chunk)
 constexpr int64_t DEFAULT_WORKSPACE = (int64_t)64 << 30;
 
-void launch_zero(double *y, int64_t n, void *stream);
+// y := 0, and the counters of the first tile launch that follows (may be NULL)
+void launch_zero(double *y, int64_t n, int32_t *counters, void *stream);
 void launch_dress(const DressItem *items, int nitems, const int64_t *src_off, const double *alpha,
                   const double *const *bases, double *dst, void *stream);
-// tiles from per-XCD queues; counters: QUEUE_INTS ints of device memory, the
-// NXCD queue counters cleared by this call before the launch
+// tiles from per-XCD queues; qs: QUEUE_INTS ints of device memory (QueueSets)
 void launch_tiles_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles, const XcdQueues &q,
-                      int32_t *counters, const double *const *bases, const double *psi, double *y, double *work,
+                      QueueSets &qs, const double *const *bases, const double *psi, double *y, double *work,
                       double *part, void *stream);
 void launch_reduce(const Reduce *red, int nred, const double *part, double *y, void *stream);
 void launch_transpose(const TransJob *jobs, int njobs, const double *src, double *dst, void *stream);
@@ -249,16 +275,15 @@ int64_t plan_scratch_layout(const dmrg_plan_t *p, int64_t off[SCRATCH_REGIONS]);
 int enqueue_scratch(dmrg_plan_t *p, const double *psi, double *hpsi, void *stream, char *base);
 // wavefront tiles (one tile per wavefront) from per-XCD queues
 void launch_tiles_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles,
-                        const XcdQueues &q, int32_t *counters, int nslices, const double *const *bases,
+                        const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
                         const double *psi, double *y, double *work, double *part, SliceBufs bufs, void *stream);
-// work-group (MACRO_MB) tiles from per-XCD queues; counters: QUEUE_INTS ints
-// of device memory, the NXCD queue counters cleared by this call before the launch
+// work-group (MACRO_MB) tiles from per-XCD queues
 void launch_macro_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles,
-                        const XcdQueues &q, int32_t *counters, int nslices, const double *const *bases,
+                        const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
                         const double *psi, double *y, double *work, double *part, SliceBufs bufs, void *stream);
 // wide (WIDE_MB) tiles, s <= WIDE_MAX_SLICES, same queue protocol
 void launch_wide_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles,
-                       const XcdQueues &q, int32_t *counters, int nslices, const double *const *bases,
+                       const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
                        const double *psi, double *y, double *work, double *part, SliceBufs bufs, void *stream);
 
 }  // namespace dmrg

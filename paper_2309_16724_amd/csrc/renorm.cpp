@@ -1489,12 +1489,13 @@ extern "C" int dmrg_renorm_apply(dmrg_renorm_t *r, const double *u, double *out,
   }
   hipStream_t hs = (hipStream_t)stream;
   launch_transpose(r->d_uj, (int)r->b.ujobs.size(), u, r->d_ut, stream);
-  launch_zero(out, r->b.out_len, stream);
+  QueueSets qs{r->d_cnt};
+  launch_zero(out, r->b.out_len, qs.cur(), stream);
   if (r->prof) (void)hipEventRecord(ev[0], hs);
-  launch_tiles_f64(1, r->d_t1, r->d_s1, (int)r->b.t1.size(), r->b.q1, r->d_cnt, r->d_bases, r->d_ut, out,
+  launch_tiles_f64(1, r->d_t1, r->d_s1, (int)r->b.t1.size(), r->b.q1, qs, r->d_bases, r->d_ut, out,
                    r->d_work, nullptr, stream);
   if (r->prof) { (void)hipEventRecord(ev[1], hs); (void)hipEventRecord(ev[2], hs); }
-  launch_tiles_f64(2, r->d_t2, r->d_s2, (int)r->b.t2.size(), r->b.q2, r->d_cnt, r->d_bases, r->d_ut, out,
+  launch_tiles_f64(2, r->d_t2, r->d_s2, (int)r->b.t2.size(), r->b.q2, qs, r->d_bases, r->d_ut, out,
                    r->d_work, nullptr, stream);
   if (r->prof) {
     (void)hipEventRecord(ev[3], hs);

@@ -240,8 +240,9 @@ extern "C" int dmrg_truncate(const dmrg_problem_t *prob, int32_t flags, const do
   if (hipMemcpyAsync(d_t, st.data(), st.size() * sizeof(Tile), hipMemcpyHostToDevice, hs) != hipSuccess ||
       hipMemcpyAsync(d_s, segs.data(), segs.size() * sizeof(Seg), hipMemcpyHostToDevice, hs) != hipSuccess)
     return fail(DMRG_EHIP, "copying the density-matrix lists failed");
-  launch_zero(d_rho, roff.back(), stream);
-  launch_tiles_f64(1, d_t, d_s, (int)st.size(), q, d_cnt, d_bases, psi, d_rho, nullptr, nullptr, stream);
+  QueueSets qs{d_cnt};
+  launch_zero(d_rho, roff.back(), qs.cur(), stream);
+  launch_tiles_f64(1, d_t, d_s, (int)st.size(), q, qs, d_bases, psi, d_rho, nullptr, nullptr, stream);
   if (rocblas_create_handle(&h) != rocblas_status_success || rocblas_set_stream(h, hs) != rocblas_status_success)
     return fail(DMRG_EHIP, "rocBLAS handle");
   for (size_t si = 0; si < prod.size(); si++) {
