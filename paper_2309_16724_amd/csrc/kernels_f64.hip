@@ -28,6 +28,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // otherwise each wait drains every load in flight and the prefetch is lost.
 typedef const double __attribute__((address_space(1))) *gcptr;
 typedef double __attribute__((address_space(1))) *gptr;
+typedef const char __attribute__((address_space(1))) *gbptr;
 __device__ __forceinline__ double gld(const double *p) { return *(gcptr)p; }
 
 
@@ -201,6 +202,272 @@ __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu
   } while (wq.next(lane));
 }
 
+// ------------------------------------------------------------ work-group tiles
+// Output tiles of whole work groups: WM x WN wavefronts, each with MBW x NBW
+// MFMA blocks.  The 16 x 16 blocks of the tile go to the wavefronts in turn
+// (block row b to wavefront row b % WM, likewise the columns), so that a
+// ragged tile leaves every wavefront about the same share; blocks outside the
+// output are skipped.  Each 16-wide K step of both operands goes from global
+// memory through registers into one of two LDS stages (64 consecutive lines
+// of one K per wavefront and load: whole 128-byte lines, K wave-uniform)
+// while the step before is computed from the other; the row strides in LDS
+// are 16 modulo 32 doubles, which spreads the four K rows of an operand read
+// over all banks.
+template <int WM_, int WN_, int MBW_, int NBW_, int WAVES_PER_SIMD>
+struct WgTile {
+  static constexpr int WM = WM_, WN = WN_, MBW = MBW_, NBW = NBW_, EU = WAVES_PER_SIMD;
+  static constexpr int BM = 16 * WM * MBW, BN = 16 * WN * NBW, NT = 64 * WM * WN;
+  static constexpr int KS = 16, LDA = BM + 16, LDB = BN + 16;
+  static constexpr int RA = NT / BM, RB = NT / BN;       // K rows one load of all threads covers
+  static constexpr int NA = KS / RA, NB = KS / RB;       // loads per thread and step
+  static constexpr int STAGE = KS * (LDA + LDB);         // doubles
+  static_assert(BM % 64 == 0 && BN % 64 == 0, "a wavefront's loads have one K");
+};
+typedef WgTile<2, 4, 4, 2, 4> WideF64;    // 128 x 128
+typedef WgTile<2, 2, 2, 2, 4> MacroF64;   // 64 x 64
+static_assert(WideF64::BM == WIDE_EDGE && WideF64::BN == WIDE_EDGE, "F64_WIDE_MB tiles");
+static_assert(MacroF64::BM == MACRO_EDGE && MacroF64::BN == MACRO_EDGE, "MACRO_MB tiles");
+
+// segment descriptors do not change during a launch: scalar loads
+typedef const Seg __attribute__((address_space(4))) CSegF;
+
+template <typename G>
+__device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict__ segs, const double *const *bases,
+                                            const double *psi, double *y, double *work, double *part, double *lds,
+                                            int wave, int lane) {
+  const CSegF *cs = (const CSegF *)segs + T.seg0;
+  const int r16 = lane & 15, q4 = lane >> 4;
+  const int wr = wave / G::WN, wc = wave % G::WN;
+  const int mt = min(G::BM, T.m - T.i0), nt = min(G::BN, T.n - T.j0);
+  // blocks of this wavefront inside the output
+  const int nbi = max(0, ((mt + 15) / 16 - wr + G::WM - 1) / G::WM);
+  const int nbj = max(0, ((nt + 15) / 16 - wc + G::WN - 1) / G::WN);
+  v4d acc[G::MBW][G::NBW];
+#pragma unroll
+  for (int a = 0; a < G::MBW; a++)
+#pragma unroll
+    for (int b = 0; b < G::NBW; b++) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
+  int si = 0;
+  while (si < T.nseg && cs[si].a_base < 0) si++;
+  if (si < T.nseg) {
+    // this thread's line of each operand (lines past the output read the last
+    // one, never stored) and its wave-uniform first K row of a step; element e
+    // of a thread is row `kr + R e`.  Addresses are a uniform pointer plus the
+    // line's 32-bit byte offset (a tile's lines span at most BM a_i or a few
+    // positions' blocks of B).  The pointer walks along K by additions, over
+    // the position boundaries that both operands share: computing (position,
+    // offset) by division cost some 900 scalar instructions per step, as long
+    // as its products.
+    static_assert(G::BM == G::BN && G::RA * G::NA == G::KS, "both operands have the same rows per thread");
+    constexpr int R = G::RA, N = G::NA;
+    const int line = (wave * 64 + lane) % G::BM, kr = wave * 64 / G::BM;
+    const int il = min(line, mt - 1), jl = T.j0 + min(line, nt - 1);
+    double pa[N], pb[N];
+    // walk of the segment being loaded: row pointers, row within the position
+    const double *wa, *wb;
+    int64_t da, ea, db, eb;    // per R rows, extra at a position boundary
+    int wk, wkb, wK;
+    uint32_t ao, bo;
+    auto open = [&](int qi) {
+      CSegF &S = cs[qi];
+      wK = S.K;
+      wkb = S.a_kb;
+      int64_t ak = S.a_k, bk = S.b_k;
+      if (wkb == 1) {   // one row per position: the rows are the positions
+        wkb = wK;
+        ak = S.a_p;
+        bk = S.b_pk;
+      }
+      da = R * ak;
+      db = R * bk;
+      ea = S.a_p - wkb * ak;
+      eb = S.b_pk - wkb * bk;
+      const int p0 = T.j0 < S.b_nb ? 0 : T.j0 / S.b_nb;
+      const int row = min(kr, wK - 1);
+      wk = row;
+      wa = base_ptr(S.a_base, bases, psi, y, work, part) + S.a_off + (int64_t)T.i0 * S.a_i + row * ak;
+      wb = base_ptr(S.b_base, bases, psi, y, work, part) + S.b_off + (int64_t)p0 * S.b_pn + row * bk;
+      if (wk >= wkb) {   // kr < R <= 4, positions of at least two rows
+        wk -= wkb;
+        wa += ea;
+        wb += eb;
+        if (wk >= wkb) {
+          wk -= wkb;
+          wa += ea;
+          wb += eb;
+        }
+      }
+      ao = 8u * (uint32_t)il * (uint32_t)S.a_i;
+      int pn = 0, jn = jl - p0 * S.b_nb;
+      if (S.b_nb < T.n && jn >= S.b_nb) {
+        pn = jn / S.b_nb;
+        jn -= pn * S.b_nb;
+      }
+      bo = 8u * ((uint32_t)pn * (uint32_t)S.b_pn + (uint32_t)jn * (uint32_t)S.b_n);
+    };
+    // the step at k0; the walk ends at the first row of the next step, or
+    // stays on the segment's last rows (read again for the rows past K)
+    auto load = [&](int k0) {
+#pragma unroll
+      for (int e = 0; e < N; e++) {
+        pa[e] = *(gcptr)((gbptr)wa + ao);
+        pb[e] = *(gcptr)((gbptr)wb + bo);
+        if (k0 + kr + R * (e + 1) < wK) {
+          wa += da;
+          wb += db;
+          wk += R;
+          if (wk >= wkb) {
+            wk -= wkb;
+            wa += ea;
+            wb += eb;
+            if (R > 2 && wk >= wkb) {
+              wk -= wkb;
+              wa += ea;
+              wb += eb;
+            }
+          }
+        }
+      }
+    };
+    // ... into an LDS stage: A scaled by the segment's factor, K rows past the
+    // segment's end as zeros
+    auto store = [&](int qi, int k0, double *st) {
+      const int K = cs[qi].K;
+      const double s = cs[qi].s;
+      double *as = st + line, *bs = st + G::KS * G::LDA + line;
+#pragma unroll
+      for (int e = 0; e < N; e++) {
+        const int k = kr + R * e;
+        as[k * G::LDA] = k0 + k < K ? s * pa[e] : 0.0;
+        bs[k * G::LDB] = k0 + k < K ? pb[e] : 0.0;
+      }
+    };
+    // ksteps K steps of four from stage st, the operands of the next one read
+    // while this one's products run.  One path with a uniform branch per
+    // block: a separate path for whole tiles made the accumulators live twice.
+    auto compute = [&](const double *st, int ksteps) {
+      const double *as = st + q4 * G::LDA + 16 * wr + r16, *bs = st + G::KS * G::LDA + q4 * G::LDB + 16 * wc + r16;
+#pragma unroll
+      for (int kk = 0; kk < G::KS / 4; kk++) {
+        if (kk < ksteps) {
+          double a[G::MBW], b[G::NBW];
+#pragma unroll
+          for (int bi = 0; bi < G::MBW; bi++) a[bi] = as[4 * kk * G::LDA + 16 * G::WM * bi];
+#pragma unroll
+          for (int bj = 0; bj < G::NBW; bj++) b[bj] = bs[4 * kk * G::LDB + 16 * G::WN * bj];
+#pragma unroll
+          for (int bi = 0; bi < G::MBW; bi++)
+#pragma unroll
+            for (int bj = 0; bj < G::NBW; bj++)
+              if (bi < nbi && bj < nbj)
+                acc[bi][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[bi], b[bj], acc[bi][bj], 0, 0, 0);
+        }
+      }
+    };
+    int k0 = 0, cur = 0;
+    open(si);
+    load(0);
+    store(si, 0, lds);
+    for (;;) {
+      __syncthreads();   // this step is in stage cur, the other stage is free
+      const int K = cs[si].K;
+      int nsi = si, nk0 = k0 + G::KS;
+      if (nk0 >= K) {
+        nk0 = 0;
+        nsi++;
+        while (nsi < T.nseg && cs[nsi].a_base < 0) nsi++;
+      }
+      const bool more = nsi < T.nseg;
+      if (more) {
+        if (nsi != si) open(nsi);
+        load(nk0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      compute(lds + cur * G::STAGE, (min(G::KS, K - k0) + 3) / 4);
+      __builtin_amdgcn_sched_barrier(0);
+      if (!more) break;
+      cur ^= 1;
+      store(nsi, nk0, lds + cur * G::STAGE);
+      si = nsi;
+      k0 = nk0;
+    }
+  }
+  // identity left operators: tile += s * B restricted to the tile (one
+  // position, K == rows).  Lanes outside the output read its last row or
+  // column, so that no load waits for another.
+  // (the lane index passes through an empty asm, here and below, so that the
+  // offsets derived from it are not kept in registers during the K loop)
+  asm volatile("" : "+v"(lane));
+  for (si = 0; si < T.nseg; si++) {
+    CSegF &S = cs[si];
+    if (S.a_base >= 0) continue;
+    const double *B = base_ptr(S.b_base, bases, psi, y, work, part) + S.b_off;
+    const double s = S.s;
+#pragma unroll
+    for (int bi = 0; bi < G::MBW; bi++) {
+      double v[G::NBW][4];
+#pragma unroll
+      for (int bj = 0; bj < G::NBW; bj++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const int i = T.i0 + min(16 * (wr + G::WM * bi) + (lane >> 4) + 4 * r, mt - 1);
+          const int j = T.j0 + min(16 * (wc + G::WN * bj) + (lane & 15), nt - 1);
+          v[bj][r] = gld(B + i * S.b_k + j * S.b_n);
+        }
+#pragma unroll
+      for (int bj = 0; bj < G::NBW; bj++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) acc[bi][bj][r] += s * v[bj][r];
+    }
+  }
+  asm volatile("" : "+v"(lane));
+  double *C = const_cast<double *>(base_ptr(T.c_base, bases, psi, y, work, part)) + T.c_off;
+#pragma unroll
+  for (int bi = 0; bi < G::MBW; bi++)
+#pragma unroll
+    for (int bj = 0; bj < G::NBW; bj++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const int i = 16 * (wr + G::WM * bi) + (lane >> 4) + 4 * r, j = 16 * (wc + G::WN * bj) + (lane & 15);
+        if (i < mt && j < nt) {
+          gptr c = (gptr)(T.rowmajor ? C + (int64_t)(T.ci0 + i) * T.ldc + (T.cj0 + j)
+                                     : C + (int64_t)(T.ci0 + i) + (int64_t)(T.cj0 + j) * T.ldc);
+          *c = T.accumulate ? *c + acc[bi][bj][r] : acc[bi][bj][r];
+        }
+      }
+}
+
+template <typename G, int STAGE>
+__global__ void __launch_bounds__(G::NT) __attribute__((amdgpu_waves_per_eu(G::EU, G::EU))) wg_f64_kernel(
+    const Tile *__restrict__ tiles, const Seg *__restrict__ segs, XcdQueues q, int32_t *__restrict__ counters,
+    int32_t *__restrict__ next_counters, const double *const *__restrict__ bases, const double *__restrict__ psi,
+    double *__restrict__ y, double *__restrict__ work, double *__restrict__ part) {
+  __shared__ double lds[2 * G::STAGE];
+  // the next tile's index, in the padding of the first LDS row (with an int of
+  // its own the 64 x 64 tiles would exceed a quarter of the LDS)
+  int *taken = (int *)(lds + G::BM);
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  clear_counters(next_counters);
+  WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD), (int)(gridDim.x / NXCD), 1);
+  int t = wq.t < wq.tend ? wq.t : -1;
+  bool fixed = true;   // t is this work group's fixed first tile (-1: none)
+  while (t >= 0 || fixed) {
+    if (wave == 0) wq.request(lane == 0);
+    if (t >= 0) {
+      const Tile T = tiles[t];
+      wg_tile_f64<G>(T, segs, bases, psi, y, work, part, lds, wave, lane);
+    }
+    fixed = false;
+    if (wave == 0) {
+      const int v = wq.next(lane) ? wq.t : -1;
+      if (lane == 0) *taken = v;
+    }
+    __syncthreads();
+    t = __builtin_amdgcn_readfirstlane(*taken);
+    __syncthreads();   // everyone has read `taken` and the last LDS stage
+  }
+}
+
 // Y tile += sum of its partial tiles, in part order
 // one output tile per blockIdx.x (grid-stride), its elements shared by the
 // REDUCE_SPLIT blocks along y: the 128 x 128 tiles of wide plans have 16384
@@ -276,12 +543,12 @@ void launch_zero(double *y, int64_t n, int32_t *counters, void *stream) {
   hipLaunchKernelGGL(zero_kernel, dim3(grid), dim3(256), 0, (hipStream_t)stream, y, n, counters);
 }
 
-void launch_tiles_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles, const XcdQueues &q,
+void launch_tiles_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles, double flops, const XcdQueues &q,
                       QueueSets &qs, const double *const *bases, const double *psi, double *y, double *work,
                       double *part, void *stream) {
   if (ntiles <= 0) return;
   hipStream_t s = (hipStream_t)stream;
-  const int grid = wave_grid(ntiles, F64_GRID), chunk = wave_chunk(ntiles, F64_GRID);
+  const int grid = wave_grid(ntiles, F64_GRID), chunk = wave_chunk(ntiles, F64_GRID, flops);
   if (stage == 1)
     hipLaunchKernelGGL(stage_f64_kernel<1>, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, q, qs.cur(), qs.other(),
                        chunk, bases, psi, y, work, part);
@@ -289,6 +556,32 @@ void launch_tiles_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles,
     hipLaunchKernelGGL(stage_f64_kernel<2>, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, q, qs.cur(), qs.other(),
                        chunk, bases, psi, y, work, part);
   qs.launch++;
+}
+
+template <typename G>
+static void launch_wg_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles, const XcdQueues &q, QueueSets &qs,
+                          const double *const *bases, const double *psi, double *y, double *work, double *part,
+                          hipStream_t s) {
+  // as many work groups as are resident at once: G::EU wavefronts per SIMD
+  const int resident = 256 * (G::EU * 4 * 64 / G::NT);
+  const int grid = std::min((ntiles + NXCD - 1) / NXCD * NXCD, resident);
+  if (stage == 1)
+    hipLaunchKernelGGL((wg_f64_kernel<G, 1>), dim3(grid), dim3(G::NT), 0, s, tiles, segs, q, qs.cur(), qs.other(), bases,
+                       psi, y, work, part);
+  else
+    hipLaunchKernelGGL((wg_f64_kernel<G, 2>), dim3(grid), dim3(G::NT), 0, s, tiles, segs, q, qs.cur(), qs.other(), bases,
+                       psi, y, work, part);
+  qs.launch++;
+}
+
+void launch_wg_tiles_f64(int stage, int mb, const Tile *tiles, const Seg *segs, int ntiles, const XcdQueues &q,
+                         QueueSets &qs, const double *const *bases, const double *psi, double *y, double *work,
+                         double *part, void *stream) {
+  if (ntiles <= 0) return;
+  if (mb == F64_WIDE_MB)
+    launch_wg_f64<WideF64>(stage, tiles, segs, ntiles, q, qs, bases, psi, y, work, part, (hipStream_t)stream);
+  else
+    launch_wg_f64<MacroF64>(stage, tiles, segs, ntiles, q, qs, bases, psi, y, work, part, (hipStream_t)stream);
 }
 
 void launch_reduce(const Reduce *red, int nred, const double *part, double *y, void *stream) {

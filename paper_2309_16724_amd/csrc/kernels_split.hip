@@ -1012,13 +1012,13 @@ void launch_wide_split(int stage, const Tile *tiles, const Seg *segs, const SegS
 }
 
 void launch_tiles_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles,
-                        const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
+                        double flops, const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
                         const double *psi, double *y, double *work, double *part, SliceBufs bufs, void *stream) {
   if (ntiles <= 0) return;
   hipStream_t s = (hipStream_t)stream;
   // work groups that the LDS stages let run at once
   const int resident = 256 * std::max(1, LDS_BYTES / (WAVES * stage_bytes(nslices)));
-  const int grid = wave_grid(ntiles, resident), chunk = wave_chunk(ntiles, resident);
+  const int grid = wave_grid(ntiles, resident), chunk = wave_chunk(ntiles, resident, flops);
 #define LAUNCH(NS)                                                                                          \
   if (nslices == NS) {                                                                                      \
     if (stage == 1)                                                                                         \

@@ -115,6 +115,7 @@ struct dmrg_plan {
   int kpart = KPART, tile_policy = 0, xcd = 0, flags = 0;
   int macro_min = MACRO_MIN;          // split plans: work-group tiles for outputs >= this (0: none)
   int wide_min = WIDE_MIN;            // split plans, s <= 5: wide tiles for outputs >= this (0: none)
+  bool wg_tiles = true;               // FP64 plans: work-group tiles (set by build_plan)
   int64_t budget = DEFAULT_WORKSPACE;
   int tuned = 0;
   double tune_ms = 0.0;
@@ -203,29 +204,6 @@ struct Stripe {
 
 struct TaskRef { int prob; int task; };
 
-// MFMA row blocks of the tiles of an m x n output: skinny outputs get 16x64 or
-// 64x16 tiles, the rest 32x32
-int tile_mb(int m, int n, int policy) {
-  if (m <= 16) return 1;
-  if (policy == 0 && n <= 16) return 4;
-  return 2;
-}
-
-// Grid cells (row tile, column tile) of an nr x nc tile grid in patches of
-// PATCH x PATCH, patch-major, row-major inside a patch.  Work groups take
-// consecutive list entries (on one XCD with DMRG_PLAN_XCD), so the tiles that
-// run side by side share PATCH operand row bands and PATCH column bands in
-// that XCD's L2 instead of each fetching its own.
-constexpr int PATCH = 8;
-std::vector<std::pair<int, int>> patch_order(int nr, int nc) {
-  std::vector<std::pair<int, int>> v;
-  for (int pr = 0; pr < nr; pr += PATCH)
-    for (int pc = 0; pc < nc; pc += PATCH)
-      for (int r = pr; r < std::min(nr, pr + PATCH); r++)
-        for (int c = pc; c < std::min(nc, pc + PATCH); c++) v.push_back({r, c});
-  return v;
-}
-
 // algorithmic flops of a tile list: 2 (tile rows) (tile columns) K over its
 // segments with a left operator (identity segments are additions)
 double list_flops(const std::vector<Tile> &tiles, const std::vector<Seg> &segs) {
@@ -238,23 +216,6 @@ double list_flops(const std::vector<Tile> &tiles, const std::vector<Seg> &segs) 
   return f;
 }
 
-// NXCD contiguous ranges of a tile list with about equal summed cost
-XcdQueues xcd_queues(const std::vector<double> &cost) {
-  XcdQueues q{};
-  double tot = 0.0;
-  for (double c : cost) tot += c;
-  const int n = (int)cost.size();
-  double acc = 0.0;
-  int i = 0;
-  q.start[0] = 0;
-  for (int x = 1; x < NXCD; x++) {
-    while (i < n && acc + 0.5 * cost[i] < tot * x / NXCD) acc += cost[i++];
-    q.start[x] = i;
-  }
-  q.start[NXCD] = n;
-  return q;
-}
-
 // work-group tiles for split plans whose output is at least macro_min on both sides
 bool use_macro(const dmrg_plan *P, int m, int n) {
   return P->precision == DMRG_SPLIT_BF16 && P->macro_min > 0 && m >= P->macro_min && n >= P->macro_min;
@@ -265,34 +226,13 @@ bool use_wide(const dmrg_plan *P, int m, int n) {
          m >= P->wide_min && n >= P->wide_min;
 }
 
-// Tiles of an m x n output (top-left corner and kind mb).  Outputs that take
-// wide tiles are cut into 128-wide row and column bands (a last band of at
-// least wide_min lines is wide too): the wide x wide cells in patch order,
-// then the rest of the output -- the columns beyond the wide bands next to
-// them, then the rows below -- in tiles chosen for those strips.  Other
-// outputs get one kind of tile in patch order.
-struct Cell { int i0, j0, mb; };
+// Tiles of an m x n output (see cut_output); split plans take wide and 64 x 64
+// tiles by their own thresholds.
 std::vector<Cell> output_cells(const dmrg_plan *P, int m, int n) {
-  std::vector<Cell> v;
-  auto grid = [&](int r0, int c0, int rows, int cols) {
-    if (rows <= 0 || cols <= 0) return;
-    const int mb = use_macro(P, rows, cols) ? MACRO_MB : tile_mb(rows, cols, P->tile_policy);
-    const int tr = tile_rows(mb), tc = tile_cols(mb);
-    for (const auto &c : patch_order((rows + tr - 1) / tr, (cols + tc - 1) / tc))
-      v.push_back({r0 + c.first * tr, c0 + c.second * tc, mb});
-  };
-  if (!use_wide(P, m, n)) {
-    grid(0, 0, m, n);
-    return v;
-  }
-  const int tail = std::min(P->wide_min, WIDE_EDGE);
-  auto bands = [&](int len) { return len / WIDE_EDGE + (len % WIDE_EDGE >= tail ? 1 : 0); };
-  const int nr = bands(m), nc = bands(n);
-  const int mw = std::min(m, nr * WIDE_EDGE), nw = std::min(n, nc * WIDE_EDGE);
-  for (const auto &c : patch_order(nr, nc)) v.push_back({c.first * WIDE_EDGE, c.second * WIDE_EDGE, WIDE_MB});
-  grid(0, nw, mw, n - nw);
-  grid(mw, 0, m - mw, n);
-  return v;
+  if (P->precision == DMRG_FP64) return f64_cells(m, n, P->tile_policy, P->wg_tiles);
+  return cut_output(m, n, use_wide(P, m, n) ? WIDE_MB : 0, std::min(P->wide_min, WIDE_EDGE), [&](int rows, int cols) {
+    return use_macro(P, rows, cols) ? MACRO_MB : wave_mb(rows, cols, P->tile_policy);
+  });
 }
 
 int prepare_device(dmrg_plan *P);
@@ -301,6 +241,10 @@ int replan(dmrg_plan *P);
 
 int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
   const bool trow = P->precision != DMRG_SPLIT_BF16;   // stripe layout, see the first stage
+  P->wg_tiles = true;
+  for (const auto &pp : P->probs)
+    for (const auto *sec : {&pp->L.sec, &pp->R.sec})
+      for (const dmrg_sector_t &s : *sec) P->wg_tiles = P->wg_tiles && s.dim < WG_MAX_DIM;
   // ---- split tasks into chunks whose stripes fit the workspace budget
   std::vector<std::vector<TaskRef>> chunk_tasks(1);
   std::map<StripeKey, std::set<int>> cur;
@@ -414,7 +358,7 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
             t.m = s.dL; t.n = N; t.i0 = i0; t.j0 = j0; t.ci0 = i0; t.cj0 = j0;
             t.mb = mb;
             t.seg0 = sidx; t.nseg = 1; t.accumulate = 0;
-            if (mb == WIDE_MB) {
+            if (mb == WIDE_MB || mb == F64_WIDE_MB) {
               ch.tile1x.push_back(t);
               cost1x.push_back(s.dRin);
             } else if (mb == MACRO_MB) {
@@ -557,16 +501,23 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
       const auto cells = output_cells(P, F.dL, F.dR);
       const int np = (int)parts.size();
       // partial tiles of cell c, part p at npart + coff[c] + p tm tn (tm x tn
-      // the cell's tile shape); the list runs over parts (outer) and cells in
+      // the cell's tile shape, for FP64 work-group tiles its part inside the
+      // output); the list runs over parts (outer) and cells in
       // patch order (inner), so the tiles that run together share their K range
+      auto cell_rows = [&](const Cell &c) {
+        return trow && c.mb >= MACRO_MB ? std::min(tile_rows(c.mb), F.dL - c.i0) : tile_rows(c.mb);
+      };
+      auto cell_cols = [&](const Cell &c) {
+        return trow && c.mb >= MACRO_MB ? std::min(tile_cols(c.mb), F.dR - c.j0) : tile_cols(c.mb);
+      };
       std::vector<int64_t> coff(cells.size() + 1, 0);
       for (size_t c = 0; c < cells.size(); c++)
-        coff[c + 1] = coff[c] + (int64_t)np * tile_rows(cells[c].mb) * tile_cols(cells[c].mb);
+        coff[c + 1] = coff[c] + (int64_t)np * cell_rows(cells[c]) * cell_cols(cells[c]);
       for (int pi = 0; pi < np; pi++)
         for (size_t c = 0; c < cells.size(); c++) {
           const int i0 = cells[c].i0, j0 = cells[c].j0, mb = cells[c].mb;
-          const int tm = tile_rows(mb), tn = tile_cols(mb);
-          auto &dst = mb == WIDE_MB ? tiles2x : mb == MACRO_MB ? tiles2m : tiles2;
+          const int tm = cell_rows(cells[c]), tn = cell_cols(cells[c]);
+          auto &dst = mb == WIDE_MB || mb == F64_WIDE_MB ? tiles2x : mb == MACRO_MB ? tiles2m : tiles2;
           Tile t{};
           t.m = F.dL; t.n = F.dR; t.i0 = i0; t.j0 = j0; t.mb = mb;
           t.seg0 = seg0 + parts[pi].first;
@@ -618,18 +569,18 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
       ch.tile2x.push_back(x.second);
       cost2x.push_back(x.first);
     }
-    ch.q1 = xcd_queues(cost1);
-    ch.q2 = xcd_queues(cost2);
+    ch.q1 = xcd_queues(cost1.data(), (int)cost1.size());
+    ch.q2 = xcd_queues(cost2.data(), (int)cost2.size());
     ch.flops1m = list_flops(ch.tile1m, ch.seg1);
     ch.flops1w = list_flops(ch.tile1, ch.seg1);
     ch.flops2m = list_flops(ch.tile2m, ch.seg2);
     ch.flops2w = list_flops(ch.tile2, ch.seg2);
-    ch.q1m = xcd_queues(cost1m);
-    ch.q2m = xcd_queues(cost2m);
+    ch.q1m = xcd_queues(cost1m.data(), (int)cost1m.size());
+    ch.q2m = xcd_queues(cost2m.data(), (int)cost2m.size());
     ch.flops1x = list_flops(ch.tile1x, ch.seg1);
     ch.flops2x = list_flops(ch.tile2x, ch.seg2);
-    ch.q1x = xcd_queues(cost1x);
-    ch.q2x = xcd_queues(cost2x);
+    ch.q1x = xcd_queues(cost1x.data(), (int)cost1x.size());
+    ch.q2x = xcd_queues(cost2x.data(), (int)cost2x.size());
     P->chunks.push_back(std::move(ch));
   }
   P->stats.flops = P->stats.stage1_flops + P->stats.stage2_flops;
@@ -1448,15 +1399,28 @@ int enqueue_with(dmrg_plan *p, const double *psi, double *hpsi, void *stream, bo
           rc = timed(20 + stage, s1 ? ch.flops1w : ch.flops2w, [&] {
             launch_tiles_split(stage, s1 ? ch.d_tile1 : ch.d_tile2, s1 ? ch.d_seg1 : ch.d_seg2,
                                s1 ? ch.d_sseg1 : ch.d_sseg2, (int)(s1 ? ch.tile1 : ch.tile2).size(),
-                               s1 ? ch.q1 : ch.q2, qs, p->n_slices, p->d_bases, psi, hpsi, B.work,
+                               s1 ? ch.flops1w : ch.flops2w, s1 ? ch.q1 : ch.q2, qs, p->n_slices, p->d_bases, psi, hpsi, B.work,
                                B.part, B.sb, stream);
           });
       } else {
         const bool s1 = stage == 1;
-        if (!(s1 ? ch.tile1 : ch.tile2).empty())
+        if (!(s1 ? ch.tile1x : ch.tile2x).empty())
+          rc = timed(30 + stage, s1 ? ch.flops1x : ch.flops2x, [&] {
+            launch_wg_tiles_f64(stage, F64_WIDE_MB, s1 ? ch.d_tile1x : ch.d_tile2x, s1 ? ch.d_seg1 : ch.d_seg2,
+                                (int)(s1 ? ch.tile1x : ch.tile2x).size(), s1 ? ch.q1x : ch.q2x, qs, p->d_bases, psi,
+                                hpsi, B.work, B.part, stream);
+          });
+        if (!rc && !(s1 ? ch.tile1m : ch.tile2m).empty())
+          rc = timed(10 + stage, s1 ? ch.flops1m : ch.flops2m, [&] {
+            launch_wg_tiles_f64(stage, MACRO_MB, s1 ? ch.d_tile1m : ch.d_tile2m, s1 ? ch.d_seg1 : ch.d_seg2,
+                                (int)(s1 ? ch.tile1m : ch.tile2m).size(), s1 ? ch.q1m : ch.q2m, qs, p->d_bases, psi,
+                                hpsi, B.work, B.part, stream);
+          });
+        if (!rc && !(s1 ? ch.tile1 : ch.tile2).empty())
           rc = timed(20 + stage, s1 ? ch.flops1w : ch.flops2w, [&] {
             launch_tiles_f64(stage, s1 ? ch.d_tile1 : ch.d_tile2, s1 ? ch.d_seg1 : ch.d_seg2,
-                             (int)(s1 ? ch.tile1 : ch.tile2).size(), s1 ? ch.q1 : ch.q2, qs, p->d_bases,
+                             (int)(s1 ? ch.tile1 : ch.tile2).size(), s1 ? ch.flops1w : ch.flops2w, s1 ? ch.q1 : ch.q2, qs,
+                             p->d_bases,
                              psi, hpsi, B.work, B.part, stream);
           });
       }
@@ -1860,8 +1824,10 @@ extern "C" int dmrg_debug_plan_host_apply(const dmrg_problem_t *prob, const doub
     return DMRG_OK;
   }
   for (auto &ch : P->chunks) {
-    host_tiles(ch.tile1, ch.seg1, P->bases_h, psi, y, work.data(), part.data());
-    host_tiles(ch.tile2, ch.seg2, P->bases_h, psi, y, work.data(), part.data());
+    for (const auto *l : {&ch.tile1x, &ch.tile1m, &ch.tile1})
+      host_tiles(*l, ch.seg1, P->bases_h, psi, y, work.data(), part.data());
+    for (const auto *l : {&ch.tile2x, &ch.tile2m, &ch.tile2})
+      host_tiles(*l, ch.seg2, P->bases_h, psi, y, work.data(), part.data());
     host_reduce(ch.red2, part.data(), y);
   }
   delete P;

@@ -1,5 +1,7 @@
 // Device plan: stripe products (Sec. III A) as grouped GEMM tiles.
 #pragma once
+#include <algorithm>
+#include <vector>
 #include "common.hpp"
 
 namespace dmrg {
@@ -22,9 +24,8 @@ struct Seg {
 };
 
 // Work-group tiles: a tile with mb == MACRO_MB is a 64 x 64 tile computed by
-// the four wavefronts of a work group together (each a 32 x 32 quarter) from
-// operand tiles they stage in LDS once; the other tiles belong to one
-// wavefront each.
+// the four wavefronts of a work group together from operand tiles they stage
+// in LDS once; the other tiles belong to one wavefront each.
 constexpr int MACRO_MB = 8;
 constexpr int MACRO_EDGE = 64;
 constexpr int MACRO_MIN = 48;   // default: outputs with both dims >= 48 get work-group tiles
@@ -39,8 +40,9 @@ constexpr int WIDE_EDGE = 128;
 constexpr int WIDE_MIN = 48;
 constexpr int WIDE_WAVES = 8;
 constexpr int WIDE_MAX_SLICES = 5;
-constexpr int tile_rows(int mb) { return mb == WIDE_MB ? WIDE_EDGE : mb == MACRO_MB ? MACRO_EDGE : 16 * mb; }
-constexpr int tile_cols(int mb) { return mb == WIDE_MB ? WIDE_EDGE : mb == MACRO_MB ? MACRO_EDGE : 64 / mb; }
+constexpr int F64_WIDE_MB = 32;   // 128 x 128 FP64 tiles of whole work groups (a kernel of their own)
+constexpr int tile_rows(int mb) { return mb == WIDE_MB || mb == F64_WIDE_MB ? WIDE_EDGE : mb == MACRO_MB ? MACRO_EDGE : 16 * mb; }
+constexpr int tile_cols(int mb) { return mb == WIDE_MB || mb == F64_WIDE_MB ? WIDE_EDGE : mb == MACRO_MB ? MACRO_EDGE : 64 / mb; }
 
 // Per-XCD queues of a tile list: the list (cost-sorted, operand bands in
 // patches) is cut into NXCD contiguous ranges of equal cost; the workers of XCD
@@ -69,16 +71,91 @@ struct QueueSets {
 };
 
 // Work groups of a wavefront-tile launch (a multiple of NXCD, no more than fit
-// on the chip at once: `resident`) and tiles per chunk: one tile while every
-// wavefront takes few of them, up to eight for long lists of short tiles, so
-// that each wavefront still asks for about sixteen chunks.
+// on the chip at once: `resident`) and tiles per chunk.  Chunks of more than
+// one tile spare atomics where the tiles are short (flops: of the whole list;
+// a chunk is at most about 2^18, four 32 x 32 tiles of K = 32), but the
+// wavefronts then work a chunk apart in the list and share fewer operand bands
+// in L2: at L=54, D=1024 (K about 200) chunks of eight cost 7 %.  Every
+// wavefront still asks for about sixteen chunks.
 inline int wave_grid(int ntiles, int resident) {
   const int blocks = (ntiles + 3) / 4;
   return blocks < resident ? (blocks + NXCD - 1) / NXCD * NXCD : resident;
 }
-inline int wave_chunk(int ntiles, int resident) {
-  const int c = ntiles / (resident * 4 * 16);
-  return c < 1 ? 1 : c > 8 ? 8 : c;
+inline int wave_chunk(int ntiles, int resident, double flops) {
+  const double by_count = ntiles / (resident * 4.0 * 16.0), by_size = 262144.0 * ntiles / (flops > 1.0 ? flops : 1.0);
+  const double c = by_count < by_size ? by_count : by_size;
+  return c < 1.0 ? 1 : c > 8.0 ? 8 : (int)c;
+}
+
+// FP64 outputs with both sides >= F64_WIDE_MIN, one of them at least a whole
+// band, take 128 x 128 work-group tiles; other outputs (and the strips beyond
+// the bands) with both sides >= F64_MACRO_MIN 64 x 64 ones.  A 32 x 32
+// wavefront tile fetches 0.125 B per flop, 4.5 TB/s at the 36 TF/s it reached
+// on large outputs; a 128 x 128 one a quarter of that.  L=54, D=1024: 138.8 ms
+// with wavefront tiles alone, 87.6 ms with 64/48, 89.7 ms with 48/33, 92 ms
+// with 96/48 or 64 x 64 tiles alone.  L=24, D=512 (sectors up to 83): 128-wide
+// tiles of which one side is half empty cost 0.87 ms where 64 x 64 ones take
+// 0.63, so a whole band is asked for.  Sectors of WG_MAX_DIM states and more stay with wavefront tiles (the
+// work-group tiles address an operand's lines by 32-bit byte offsets).
+constexpr int F64_WIDE_MIN = 64, F64_MACRO_MIN = 48, WG_MAX_DIM = 1 << 14;
+
+// A cell of an output's tiling: top-left corner and tile kind.
+struct Cell { int i0, j0, mb; };
+
+// MFMA row blocks of the wavefront tiles of an m x n output: skinny outputs get
+// 16x64 or 64x16 tiles, the rest 32x32 (policy 1: narrow ones too)
+inline int wave_mb(int m, int n, int policy) { return m <= 16 ? 1 : policy == 0 && n <= 16 ? 4 : 2; }
+
+// Grid cells (row tile, column tile) of an nr x nc tile grid in patches of
+// PATCH x PATCH, patch-major, row-major inside a patch.  The workers of an XCD
+// take consecutive list entries, so the tiles that run side by side share
+// PATCH operand row bands and PATCH column bands in that XCD's L2 instead of
+// each fetching its own.
+constexpr int PATCH = 8;
+inline std::vector<std::pair<int, int>> patch_order(int nr, int nc) {
+  std::vector<std::pair<int, int>> v;
+  for (int pr = 0; pr < nr; pr += PATCH)
+    for (int pc = 0; pc < nc; pc += PATCH)
+      for (int r = pr; r < std::min(nr, pr + PATCH); r++)
+        for (int c = pc; c < std::min(nc, pc + PATCH); c++) v.push_back({r, c});
+  return v;
+}
+
+// Tiles of an m x n output.  With `wide` it is cut into 128-wide row and
+// column bands (a last band of at least `tail` lines is wide too): the wide x
+// wide cells in patch order, then the columns beyond the bands, then the rows
+// below them, in tiles that small(rows, columns) chooses for those strips;
+// without, the whole output gets one kind of tile.
+// (wide: the kind of the 128 x 128 tiles, 0 for none.)
+template <typename F>
+std::vector<Cell> cut_output(int m, int n, int wide, int tail, F &&small) {
+  std::vector<Cell> v;
+  auto grid = [&](int r0, int c0, int rows, int cols) {
+    if (rows <= 0 || cols <= 0) return;
+    const int mb = small(rows, cols), tr = tile_rows(mb), tc = tile_cols(mb);
+    for (const auto &c : patch_order((rows + tr - 1) / tr, (cols + tc - 1) / tc))
+      v.push_back({r0 + c.first * tr, c0 + c.second * tc, mb});
+  };
+  if (!wide) {
+    grid(0, 0, m, n);
+    return v;
+  }
+  auto bands = [&](int len) { return len / WIDE_EDGE + (len % WIDE_EDGE >= tail ? 1 : 0); };
+  const int nr = bands(m), nc = bands(n);
+  const int mw = std::min(m, nr * WIDE_EDGE), nw = std::min(n, nc * WIDE_EDGE);
+  for (const auto &c : patch_order(nr, nc)) v.push_back({c.first * WIDE_EDGE, c.second * WIDE_EDGE, wide});
+  grid(0, nw, mw, n - nw);
+  grid(mw, 0, m - mw, n);
+  return v;
+}
+
+// ... of an FP64 output; wg: work-group tiles allowed
+inline std::vector<Cell> f64_cells(int m, int n, int policy, bool wg) {
+  const bool wide = wg && std::min(m, n) >= F64_WIDE_MIN && std::max(m, n) >= WIDE_EDGE;
+  return cut_output(m, n, wide ? F64_WIDE_MB : 0, F64_WIDE_MIN,
+                    [&](int rows, int cols) {
+                      return wg && std::min(rows, cols) >= F64_MACRO_MIN ? MACRO_MB : wave_mb(rows, cols, policy);
+                    });
 }
 
 // One work item: a (16*mb) x (64/mb) tile of an m x n output block (rows
@@ -247,10 +324,71 @@ constexpr int64_t DEFAULT_WORKSPACE = (int64_t)64 << 30;
 void launch_zero(double *y, int64_t n, int32_t *counters, void *stream);
 void launch_dress(const DressItem *items, int nitems, const int64_t *src_off, const double *alpha,
                   const double *const *bases, double *dst, void *stream);
-// tiles from per-XCD queues; qs: QUEUE_INTS ints of device memory (QueueSets)
-void launch_tiles_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles, const XcdQueues &q,
+// tiles from per-XCD queues; flops: of the list; qs: QUEUE_INTS ints of device
+// memory (QueueSets)
+void launch_tiles_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles, double flops, const XcdQueues &q,
                       QueueSets &qs, const double *const *bases, const double *psi, double *y, double *work,
                       double *part, void *stream);
+// 128 x 128 (mb == F64_WIDE_MB) or 64 x 64 (MACRO_MB) FP64 tiles of whole work groups
+void launch_wg_tiles_f64(int stage, int mb, const Tile *tiles, const Seg *segs, int ntiles, const XcdQueues &q,
+                         QueueSets &qs, const double *const *bases, const double *psi, double *y, double *work,
+                         double *part, void *stream);
+
+// NXCD contiguous ranges of a tile list with about equal summed cost
+inline XcdQueues xcd_queues(const double *cost, int n) {
+  XcdQueues q{};
+  double tot = 0.0, acc = 0.0;
+  for (int i = 0; i < n; i++) tot += cost[i];
+  int i = 0;
+  for (int x = 1; x < NXCD; x++) {
+    while (i < n && acc + 0.5 * cost[i] < tot * x / NXCD) acc += cost[i++];
+    q.start[x] = i;
+  }
+  q.start[NXCD] = n;
+  return q;
+}
+
+// An FP64 tile list sorted by kind (wide, 64 x 64, wavefront tiles), each kind
+// by falling cost (tile area times K), with its queues.
+struct KindLists {
+  int first[4] = {0, 0, 0, 0};   // of each kind; first[3]: length
+  double flops[3] = {0.0, 0.0, 0.0};
+  XcdQueues q[3];
+};
+inline KindLists sort_by_kind(std::vector<Tile> &tiles, const std::vector<double> &cost) {
+  auto kind = [&](int i) { return tiles[i].mb == F64_WIDE_MB ? 0 : tiles[i].mb == MACRO_MB ? 1 : 2; };
+  std::vector<int> ord(tiles.size());
+  for (size_t i = 0; i < ord.size(); i++) ord[i] = (int)i;
+  std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) {
+    return kind(a) != kind(b) ? kind(a) < kind(b) : cost[a] > cost[b];
+  });
+  KindLists L;
+  std::vector<Tile> t(tiles.size());
+  std::vector<double> c(tiles.size());
+  for (size_t i = 0; i < ord.size(); i++) {
+    const int k = kind(ord[i]);
+    t[i] = tiles[ord[i]];
+    c[i] = cost[ord[i]];
+    L.first[k + 1] = (int)i + 1;
+    L.flops[k] += 2.0 * c[i];
+  }
+  for (int k = 0; k < 3; k++) {
+    L.first[k + 1] = std::max(L.first[k], L.first[k + 1]);
+    L.q[k] = xcd_queues(c.data() + L.first[k], L.first[k + 1] - L.first[k]);
+  }
+  tiles.swap(t);
+  return L;
+}
+// the launches of such a list
+inline void launch_lists_f64(int stage, const Tile *tiles, const Seg *segs, const KindLists &L, QueueSets &qs,
+                             const double *const *bases, const double *psi, double *y, double *work, double *part,
+                             void *stream) {
+  for (int k = 0; k < 2; k++)
+    launch_wg_tiles_f64(stage, k == 0 ? F64_WIDE_MB : MACRO_MB, tiles + L.first[k], segs, L.first[k + 1] - L.first[k],
+                        L.q[k], qs, bases, psi, y, work, part, stream);
+  launch_tiles_f64(stage, tiles + L.first[2], segs, L.first[3] - L.first[2], L.flops[2], L.q[2], qs, bases, psi, y, work,
+                   part, stream);
+}
 void launch_reduce(const Reduce *red, int nred, const double *part, double *y, void *stream);
 void launch_transpose(const TransJob *jobs, int njobs, const double *src, double *dst, void *stream);
 void launch_diag(const DiagBlock *blocks, const DiagTerm *terms, int nblocks,
@@ -275,7 +413,7 @@ int64_t plan_scratch_layout(const dmrg_plan_t *p, int64_t off[SCRATCH_REGIONS]);
 int enqueue_scratch(dmrg_plan_t *p, const double *psi, double *hpsi, void *stream, char *base);
 // wavefront tiles (one tile per wavefront) from per-XCD queues
 void launch_tiles_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles,
-                        const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
+                        double flops, const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
                         const double *psi, double *y, double *work, double *part, SliceBufs bufs, void *stream);
 // work-group (MACRO_MB) tiles from per-XCD queues
 void launch_macro_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles,

@@ -43,27 +43,6 @@ using namespace dmrg;
 
 namespace {
 
-// wavefront tile shape for an m x n output: 16 x 64 for short outputs,
-// 64 x 16 for narrow ones, else 32 x 32
-int tile_mb(int m, int n) { return m <= 16 ? 1 : n <= 16 ? 4 : 2; }
-
-// NXCD contiguous ranges of a cost-sorted tile list with about equal cost
-XcdQueues equal_cost_ranges(const std::vector<double> &cost) {
-  XcdQueues q{};
-  double tot = 0.0;
-  for (double c : cost) tot += c;
-  const int n = (int)cost.size();
-  double acc = 0.0;
-  int i = 0;
-  for (int x = 1; x < NXCD; x++) {
-    while (i < n && acc + 0.5 * cost[i] < tot * x / NXCD) acc += cost[i++];
-    q.start[x] = i;
-  }
-  q.start[0] = 0;
-  q.start[NXCD] = n;
-  return q;
-}
-
 const int RSITE_N[3] = {0, 1, 2};
 const int RSITE_S[3] = {0, 1, 0};
 constexpr int RENORM_DEFAULT_MASK =
@@ -883,7 +862,7 @@ struct Built {
   int64_t out_len = 0;
   std::vector<Tile> t1, t2;
   std::vector<Seg> s1, s2;
-  XcdQueues q1{}, q2{};
+  KindLists l1, l2;              // their kinds, sorted
   int64_t work_len = 0;
   std::vector<TransJob> ujobs;   // U -> U^T per kept sector (every apply)
   std::vector<TransJob> ljobs;   // left records used as adjoints -> transposed copy (once)
@@ -1142,18 +1121,19 @@ int build_renorm(const dmrg_problem_t *prob, const dmrg_rkeep_t *keep, int n_kee
   std::vector<double> cost1, cost2;
   B.work_len = 0;
   B.flops1 = B.flops2 = 0.0;
+  bool wg = true;   // every segment has one position, so work-group tiles can walk it
+  for (const dmrg_sector_t &x : L.sec) wg = wg && x.dim < WG_MAX_DIM;
+  for (int k = 0; k < n_keep; k++) wg = wg && kept(k) < WG_MAX_DIM;
   auto add_tiles = [&](std::vector<Tile> &tiles, std::vector<double> &cost, int m, int n, int c_base,
                        int64_t c_off, int64_t ldc, int seg0, int nseg, double ksum, int rowmajor) {
-    const int mb = tile_mb(m, n), tr = tile_rows(mb), tc = tile_cols(mb);
-    for (int i0 = 0; i0 < m; i0 += tr)
-      for (int j0 = 0; j0 < n; j0 += tc) {
-        Tile T{};
-        T.c_off = c_off; T.ldc = ldc; T.c_base = c_base;
-        T.m = m; T.n = n; T.i0 = i0; T.j0 = j0; T.ci0 = i0; T.cj0 = j0;
-        T.mb = mb; T.seg0 = seg0; T.nseg = nseg; T.accumulate = 0; T.rowmajor = rowmajor;
-        tiles.push_back(T);
-        cost.push_back((double)std::min(tr, m - i0) * std::min(tc, n - j0) * ksum);
-      }
+    for (const Cell &c : f64_cells(m, n, 0, wg)) {
+      Tile T{};
+      T.c_off = c_off; T.ldc = ldc; T.c_base = c_base;
+      T.m = m; T.n = n; T.i0 = c.i0; T.j0 = c.j0; T.ci0 = c.i0; T.cj0 = c.j0;
+      T.mb = c.mb; T.seg0 = seg0; T.nseg = nseg; T.accumulate = 0; T.rowmajor = rowmajor;
+      tiles.push_back(T);
+      cost.push_back((double)std::min(tile_rows(c.mb), m - c.i0) * std::min(tile_cols(c.mb), n - c.j0) * ksum);
+    }
   };
   // Operand layouts that let every wavefront load whole lines (lanes run
   // along output rows of A and along output columns of B): U is read from
@@ -1290,21 +1270,8 @@ int build_renorm(const dmrg_problem_t *prob, const dmrg_rkeep_t *keep, int n_kee
     err = {DMRG_ERANGE, "internal: a product reaches beyond its array"};
     return err.code;
   }
-  // cost-sorted lists, cut into per-XCD ranges
-  auto sort_list = [](std::vector<Tile> &tiles, std::vector<double> &cost) {
-    std::vector<int> ord(tiles.size());
-    for (size_t i = 0; i < ord.size(); i++) ord[i] = (int)i;
-    std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return cost[a] > cost[b]; });
-    std::vector<Tile> t2(tiles.size());
-    std::vector<double> c2(tiles.size());
-    for (size_t i = 0; i < ord.size(); i++) { t2[i] = tiles[ord[i]]; c2[i] = cost[ord[i]]; }
-    tiles.swap(t2);
-    cost.swap(c2);
-  };
-  sort_list(B.t1, cost1);
-  sort_list(B.t2, cost2);
-  B.q1 = equal_cost_ranges(cost1);
-  B.q2 = equal_cost_ranges(cost2);
+  B.l1 = sort_by_kind(B.t1, cost1);
+  B.l2 = sort_by_kind(B.t2, cost2);
   B.build_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   return DMRG_OK;
 }
@@ -1492,11 +1459,9 @@ extern "C" int dmrg_renorm_apply(dmrg_renorm_t *r, const double *u, double *out,
   QueueSets qs{r->d_cnt};
   launch_zero(out, r->b.out_len, qs.cur(), stream);
   if (r->prof) (void)hipEventRecord(ev[0], hs);
-  launch_tiles_f64(1, r->d_t1, r->d_s1, (int)r->b.t1.size(), r->b.q1, qs, r->d_bases, r->d_ut, out,
-                   r->d_work, nullptr, stream);
+  launch_lists_f64(1, r->d_t1, r->d_s1, r->b.l1, qs, r->d_bases, r->d_ut, out, r->d_work, nullptr, stream);
   if (r->prof) { (void)hipEventRecord(ev[1], hs); (void)hipEventRecord(ev[2], hs); }
-  launch_tiles_f64(2, r->d_t2, r->d_s2, (int)r->b.t2.size(), r->b.q2, qs, r->d_bases, r->d_ut, out,
-                   r->d_work, nullptr, stream);
+  launch_lists_f64(2, r->d_t2, r->d_s2, r->b.l2, qs, r->d_bases, r->d_ut, out, r->d_work, nullptr, stream);
   if (r->prof) {
     (void)hipEventRecord(ev[3], hs);
     for (auto &x : ev) r->ev.push_back(x);

@@ -73,8 +73,6 @@ std::vector<TSec> left_product(const std::vector<dmrg_sector_t> &lsec) {
   return out;
 }
 
-int tile_shape(int m, int n) { return m <= 16 ? 1 : n <= 16 ? 4 : 2; }
-
 // The density-matrix products of one truncation: rho of every product
 // sector (offsets roff, column-major rows x rows) as tiles over psi.
 struct RhoLists {
@@ -114,6 +112,9 @@ int build_rho(const dmrg_problem_t *prob, int32_t flags, RhoLists &RL) {
         ci = c;
     parts[si][ci][right ? std::make_tuple(b.iL, b.l, b.SLl) : std::make_tuple(b.r, b.iR, b.SrR)] = bi;
   }
+  bool wg = true;   // every segment has one position, so work-group tiles can walk it
+  for (const auto *sec : {&L.sec, &R.sec})
+    for (const dmrg_sector_t &x : *sec) wg = wg && x.dim < WG_MAX_DIM;
   // rho blocks as tiles: rho(a, a') += X_{a,c} X_{a',c}^T over common right parts c
   roff.assign(prod.size() + 1, 0);
   for (size_t i = 0; i < prod.size(); i++) roff[i + 1] = roff[i] + (int64_t)prod[i].rows * prod[i].rows;
@@ -145,17 +146,16 @@ int build_rho(const dmrg_problem_t *prob, int32_t flags, RhoLists &RL) {
         }
         const int nseg = (int)segs.size() - seg0;
         if (nseg == 0) continue;
-        const int m = ca.dim, n = cb.dim, mb = tile_shape(m, n), tr = tile_rows(mb), tc = tile_cols(mb);
-        for (int i0 = 0; i0 < m; i0 += tr)
-          for (int j0 = 0; j0 < n; j0 += tc) {
-            Tile T{};
-            T.c_off = roff[si] + ca.row0 + (int64_t)cb.row0 * P.rows;
-            T.ldc = P.rows; T.c_base = BASE_Y;
-            T.m = m; T.n = n; T.i0 = i0; T.j0 = j0; T.ci0 = i0; T.cj0 = j0;
-            T.mb = mb; T.seg0 = seg0; T.nseg = nseg; T.accumulate = 0; T.rowmajor = 0;
-            tiles.push_back(T);
-            cost.push_back((double)std::min(tr, m - i0) * std::min(tc, n - j0) * ksum);
-          }
+        const int m = ca.dim, n = cb.dim;
+        for (const Cell &c : f64_cells(m, n, 0, wg)) {
+          Tile T{};
+          T.c_off = roff[si] + ca.row0 + (int64_t)cb.row0 * P.rows;
+          T.ldc = P.rows; T.c_base = BASE_Y;
+          T.m = m; T.n = n; T.i0 = c.i0; T.j0 = c.j0; T.ci0 = c.i0; T.cj0 = c.j0;
+          T.mb = c.mb; T.seg0 = seg0; T.nseg = nseg; T.accumulate = 0; T.rowmajor = 0;
+          tiles.push_back(T);
+          cost.push_back((double)std::min(tile_rows(c.mb), m - c.i0) * std::min(tile_cols(c.mb), n - c.j0) * ksum);
+        }
       }
   }
   // every lane's reads stay inside psi (lanes past the tile or K read row 0,
@@ -187,26 +187,7 @@ extern "C" int dmrg_truncate(const dmrg_problem_t *prob, int32_t flags, const do
   std::vector<int64_t> &roff = RL.roff;
   std::vector<Tile> &tiles = RL.tiles;
   std::vector<Seg> &segs = RL.segs;
-  std::vector<double> &cost = RL.cost;
-  std::vector<int> ord(tiles.size());
-  for (size_t i = 0; i < ord.size(); i++) ord[i] = (int)i;
-  std::stable_sort(ord.begin(), ord.end(), [&](int a, int b) { return cost[a] > cost[b]; });
-  std::vector<Tile> st(tiles.size());
-  std::vector<double> sc(tiles.size());
-  for (size_t i = 0; i < ord.size(); i++) { st[i] = tiles[ord[i]]; sc[i] = cost[ord[i]]; }
-  XcdQueues q{};
-  {
-    double tot = 0.0, acc = 0.0;
-    for (double c : sc) tot += c;
-    int i = 0;
-    const int n = (int)sc.size();
-    for (int x = 1; x < NXCD; x++) {
-      while (i < n && acc + 0.5 * sc[i] < tot * x / NXCD) acc += sc[i++];
-      q.start[x] = i;
-    }
-    q.start[0] = 0;
-    q.start[NXCD] = n;
-  }
+  const KindLists kinds = sort_by_kind(tiles, RL.cost);
   int maxn = 1;
   for (const TSec &P : prod) maxn = std::max(maxn, P.rows);
   hipStream_t hs = (hipStream_t)stream;
@@ -228,7 +209,7 @@ extern "C" int dmrg_truncate(const dmrg_problem_t *prob, int32_t flags, const do
     set_error(msg);
     return code;
   };
-  bool ok = hipMalloc((void **)&d_t, std::max<size_t>(16, st.size() * sizeof(Tile))) == hipSuccess &&
+  bool ok = hipMalloc((void **)&d_t, std::max<size_t>(16, tiles.size() * sizeof(Tile))) == hipSuccess &&
             hipMalloc((void **)&d_s, std::max<size_t>(16, segs.size() * sizeof(Seg))) == hipSuccess &&
             hipMalloc((void **)&d_cnt, QUEUE_INTS * sizeof(int32_t)) == hipSuccess &&
             hipMalloc((void **)&d_info, prod.size() * sizeof(int32_t)) == hipSuccess &&
@@ -237,12 +218,12 @@ extern "C" int dmrg_truncate(const dmrg_problem_t *prob, int32_t flags, const do
             hipMalloc((void **)&d_e, (size_t)maxn * sizeof(double)) == hipSuccess &&
             hipMalloc((void **)&d_bases, 16) == hipSuccess;
   if (!ok) return fail(DMRG_ENOMEM, "device allocation failed");
-  if (hipMemcpyAsync(d_t, st.data(), st.size() * sizeof(Tile), hipMemcpyHostToDevice, hs) != hipSuccess ||
+  if (hipMemcpyAsync(d_t, tiles.data(), tiles.size() * sizeof(Tile), hipMemcpyHostToDevice, hs) != hipSuccess ||
       hipMemcpyAsync(d_s, segs.data(), segs.size() * sizeof(Seg), hipMemcpyHostToDevice, hs) != hipSuccess)
     return fail(DMRG_EHIP, "copying the density-matrix lists failed");
   QueueSets qs{d_cnt};
   launch_zero(d_rho, roff.back(), qs.cur(), stream);
-  launch_tiles_f64(1, d_t, d_s, (int)st.size(), q, qs, d_bases, psi, d_rho, nullptr, nullptr, stream);
+  launch_lists_f64(1, d_t, d_s, kinds, qs, d_bases, psi, d_rho, nullptr, nullptr, stream);
   if (rocblas_create_handle(&h) != rocblas_status_success || rocblas_set_stream(h, hs) != rocblas_status_success)
     return fail(DMRG_EHIP, "rocBLAS handle");
   for (size_t si = 0; si < prod.size(); si++) {
