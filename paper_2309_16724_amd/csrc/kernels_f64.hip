@@ -32,157 +32,281 @@ typedef const char __attribute__((address_space(1))) *gbptr;
 __device__ __forceinline__ double gld(const double *p) { return *(gcptr)p; }
 
 
-__device__ __forceinline__ const double *base_ptr(int id, const double *const *bases, const double *psi,
-                                                  const double *y, const double *work, const double *part) {
-  return id == BASE_PSI ? psi : id == BASE_Y ? y : id == BASE_WORK ? work : id == BASE_PART ? part
-                                                                                             : bases[id - BASE_OPS];
+// Operands lie in psi, in the stripe workspace or in operator arrays, which are
+// addressed absolutely (resolve_bases).  First-stage tiles are stored in the
+// workspace, second-stage ones in the output or among the partial tiles.
+__device__ __forceinline__ const double *seg_ptr(int id, const double *psi, const double *work) {
+  return id == BASE_PSI ? psi : id == BASE_WORK ? work : nullptr;
+}
+template <int STAGE>
+__device__ __forceinline__ double *out_ptr(int id, double *y, double *work, double *part) {
+  return STAGE == 1 ? work : id == BASE_Y ? y : part;
 }
 
-// One work item: tile of MB x NB MFMA blocks (MB * NB == 4).
-template <int MB>
-__device__ __forceinline__ void item_f64(const Tile &T, const Seg *__restrict__ segs, const double *const *bases,
-                                         const double *psi, double *y, double *work, double *part, int r16,
-                                         int q4) {
-  constexpr int NB = 4 / MB;
+// descriptors do not change during a launch: scalar loads
+typedef const Seg __attribute__((address_space(4))) CSegF;
+
+// Wavefront tiles.  The stages have kernels of their own, each holding only
+// what its segments need: a first-stage tile has one segment, one position
+// along K and column positions of B, and is stored row-major; a second-stage
+// (or density-matrix) tile sums many segments with positions along K and is
+// stored column-major.  With both in one kernel and the walk over segments
+// inlined for every buffer the code took 61 KB, as much as the instruction
+// cache, and wavefronts of short tiles spent half their time waiting for
+// instructions.  MB x NB are the MFMA blocks inside the output (a 16 x 64
+// tile of a 3 x 7 output is one block, not four).
+//
+// Each operand's K steps (four rows) are DEPTH deep in flight in registers:
+// while the matrix core works on one, the loads of the step DEPTH later fill
+// its buffer.  A lane whose next row lies past the end of K stays on its last
+// row; such rows are scaled by zero instead of s (the operands are finite).
+// Lanes outside the output read its last line (never stored), so no load
+// depends on a condition.  Scheduling barriers keep each buffer's refill in
+// program order: the oldest buffer's loads are always the ones waited for.
+template <int MB, int NB>
+struct StepF64 {
+  double a[MB], b[NB];
+};
+
+template <int MB, int NB>
+__device__ __forceinline__ void mma_f64(v4d (&acc)[MB][NB], const StepF64<MB, NB> &x, double sk) {
+  double a[MB], b[NB];
+#pragma unroll
+  for (int bi = 0; bi < MB; bi++) a[bi] = sk * x.a[bi];
+#pragma unroll
+  for (int bj = 0; bj < NB; bj++) b[bj] = x.b[bj];
+#pragma unroll
+  for (int bi = 0; bi < MB; bi++)
+#pragma unroll
+    for (int bj = 0; bj < NB; bj++)
+      acc[bi][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[bi], b[bj], acc[bi][bj], 0, 0, 0);
+}
+
+// offsets of up to 2^32 elements: one multiply-add each
+__device__ __forceinline__ const double *mad(const double *p, unsigned n, int64_t stride) {
+  return p + (uint64_t)n * (uint32_t)stride;
+}
+
+// first stage: T = X op(D), one segment
+template <int MB, int NB>
+__device__ __forceinline__ void item1_f64(const Tile &T, const Seg *__restrict__ segs, const double *psi, double *y,
+                                          double *work, double *part, int r16, int q4) {
+  constexpr int DEPTH = 4;
   v4d acc[MB][NB];
+#pragma unroll
   for (int a = 0; a < MB; a++)
+#pragma unroll
     for (int b = 0; b < NB; b++) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
   const int mrem = T.m - T.i0, nrem = T.n - T.j0;
-  for (int si = 0; si < T.nseg; si++) {
-    const Seg S = segs[T.seg0 + si];
-    const double *B = base_ptr(S.b_base, bases, psi, y, work, part) + S.b_off;
-    int64_t boff[NB];
-    bool bok[NB];
-    for (int bj = 0; bj < NB; bj++) {
-      int n = T.j0 + 16 * bj + r16;
-      bok[bj] = (16 * bj + r16) < nrem;
-      int pn = bok[bj] ? n / S.b_nb : 0;
-      boff[bj] = bok[bj] ? (int64_t)pn * S.b_pn + (int64_t)(n - pn * S.b_nb) * S.b_n : 0;
+  CSegF &S = ((const CSegF *)segs)[T.seg0];
+  const int K = S.K;
+  const double s = S.s;
+  int k = min(q4, K - 1);
+  const double *pa[MB], *pb[NB];
+  const double *A = mad(seg_ptr(S.a_base, psi, work) + S.a_off, k, S.a_k);
+  const double *B = mad(seg_ptr(S.b_base, psi, work) + S.b_off, k, S.b_k);
+#pragma unroll
+  for (int bi = 0; bi < MB; bi++) pa[bi] = mad(A, T.i0 + min(16 * bi + r16, mrem - 1), S.a_i);
+#pragma unroll
+  for (int bj = 0; bj < NB; bj++) {
+    const unsigned n = T.j0 + min(16 * bj + r16, nrem - 1);
+    unsigned pn = 0;
+    if (S.b_nb < T.n) pn = n / (unsigned)S.b_nb;
+    pb[bj] = mad(mad(B, pn, S.b_pn), n - pn * S.b_nb, S.b_n);
+  }
+  k = q4;
+  const int64_t da = 4 * S.a_k, db = 4 * S.b_k;
+  StepF64<MB, NB> st[DEPTH];
+  auto refill = [&](StepF64<MB, NB> &x) {
+#pragma unroll
+    for (int bi = 0; bi < MB; bi++) x.a[bi] = gld(pa[bi]);
+#pragma unroll
+    for (int bj = 0; bj < NB; bj++) x.b[bj] = gld(pb[bj]);
+    k += 4;
+    if (k < K) {
+#pragma unroll
+      for (int bi = 0; bi < MB; bi++) pa[bi] += da;
+#pragma unroll
+      for (int bj = 0; bj < NB; bj++) pb[bj] += db;
     }
-    if (S.a_base < 0) {
-      // identity left operator: tile += s * B restricted to the tile (K == rows)
-      for (int bi = 0; bi < MB; bi++)
-        for (int bj = 0; bj < NB; bj++)
-          for (int r = 0; r < 4; r++) {
-            int i = 16 * bi + q4 + 4 * r;
-            if (i < mrem && bok[bj]) {
-              int k = T.i0 + i;
-              int pk = k / S.b_kb;
-              acc[bi][bj][r] += S.s * gld(B + (int64_t)pk * S.b_pk + (int64_t)(k - pk * S.b_kb) * S.b_k + boff[bj]);
-            }
-          }
-      continue;
-    }
-    const double *A = base_ptr(S.a_base, bases, psi, y, work, part) + S.a_off;
-    int64_t aoff[MB];
-    bool aok[MB];
-    for (int bi = 0; bi < MB; bi++) {
-      aok[bi] = (16 * bi + r16) < mrem;
-      aoff[bi] = aok[bi] ? (int64_t)(T.i0 + 16 * bi + r16) * S.a_i : 0;
-    }
-    const double s = S.s;
-    // Two operand buffers of one K step each, used alternately: while the
-    // matrix core works on one, the loads of the next-but-one step fill the
-    // other.  The loop is unrolled by two so the buffers are never copied (a
-    // copy would wait for the loads just issued), and no load depends on a
-    // condition: lanes outside the tile read an element inside the operand
-    // (their outputs are never stored), and lanes past the end of K read
-    // element K-1 and scale it by zero instead of s (operands are finite).
-    const unsigned akb = (unsigned)S.a_kb, bkb = (unsigned)S.b_kb;
-    auto step = [&](int k0, const double *an, const double *bn) {
-      const double sk = k0 + q4 < S.K ? s : 0.0;
-      double ac[MB];
-      for (int bi = 0; bi < MB; bi++) ac[bi] = sk * an[bi];
-      for (int bi = 0; bi < MB; bi++)
-        for (int bj = 0; bj < NB; bj++)
-          acc[bi][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64(ac[bi], bn[bj], acc[bi][bj], 0, 0, 0);
-    };
-    // scheduling barriers keep each buffer's refill in program order, so the
-    // older buffer's loads are always the ones waited for; one exit: a second
-    // half past K contributes zero (its scale is zero)
-    auto kloop = [&](auto &&fetch) {
-      double a0[MB], b0[NB], a1[MB], b1[NB];
-      fetch(0, a0, b0);
-      __builtin_amdgcn_sched_barrier(0);
-      fetch(4, a1, b1);
-      __builtin_amdgcn_sched_barrier(0);
-      for (int k0 = 0; k0 < S.K; k0 += 8) {
-        step(k0, a0, b0);
-        fetch(k0 + 8, a0, b0);
-        __builtin_amdgcn_sched_barrier(0);
-        step(k0 + 4, a1, b1);
-        fetch(k0 + 12, a1, b1);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    if (akb >= 4 && bkb >= 4) {
-      // A lane's K index k0 + q4 moves by 4 per step and crosses at most one
-      // position boundary, so its (position, offset) pairs are carried along
-      // with adds and selects; lanes at or past K read element K - 1, whose
-      // offsets are wave-uniform.
-      const unsigned kl = (unsigned)S.K - 1, pla = kl / akb, plb = kl / bkb;
-      const int64_t al = (int64_t)pla * S.a_p + (int64_t)(kl - pla * akb) * S.a_k;
-      const int64_t bl = (int64_t)plb * S.b_pk + (int64_t)(kl - plb * bkb) * S.b_k;
-      const int64_t ad = 4 * S.a_k, aw = S.a_p - (int64_t)akb * S.a_k;
-      const int64_t bd = 4 * S.b_k, bw = S.b_pk - (int64_t)bkb * S.b_k;
-      unsigned ka = q4, kb = q4;
-      int64_t ao = (int64_t)q4 * S.a_k, bo = (int64_t)q4 * S.b_k;
-      kloop([&](int k0, double *an, double *bn) {
-        int64_t ua = ao, ub = bo;
-        if (k0 + 4 > S.K && k0 + q4 >= S.K) {
-          ua = al;
-          ub = bl;
-        }
-        for (int bi = 0; bi < MB; bi++) an[bi] = gld(A + ua + aoff[bi]);
-        for (int bj = 0; bj < NB; bj++) bn[bj] = gld(B + ub + boff[bj]);
-        ka += 4;
-        ao += ad;
-        if (ka >= akb) {
-          ka -= akb;
-          ao += aw;
-        }
-        kb += 4;
-        bo += bd;
-        if (kb >= bkb) {
-          kb -= bkb;
-          bo += bw;
-        }
-      });
-    } else {
-      kloop([&](int k0, double *an, double *bn) {
-        const int k = min(k0 + q4, S.K - 1);
-        const unsigned pa = (unsigned)k / akb, ka = (unsigned)k - pa * akb;
-        const unsigned pb = (unsigned)k / bkb, kb = (unsigned)k - pb * bkb;
-        const int64_t ak = (int64_t)pa * S.a_p + (int64_t)ka * S.a_k;
-        const int64_t bk = (int64_t)pb * S.b_pk + (int64_t)kb * S.b_k;
-        for (int bi = 0; bi < MB; bi++) an[bi] = gld(A + ak + aoff[bi]);
-        for (int bj = 0; bj < NB; bj++) bn[bj] = gld(B + bk + boff[bj]);
-      });
+    __builtin_amdgcn_sched_barrier(0);
+  };
+#pragma unroll
+  for (int u = 0; u < DEPTH; u++) refill(st[u]);
+  for (int k0 = 0; k0 < K; k0 += 4 * DEPTH) {
+#pragma unroll
+    for (int u = 0; u < DEPTH; u++) {
+      if (k0 + 4 * u < K) mma_f64<MB, NB>(acc, st[u], k0 + 4 * u + q4 < K ? s : 0.0);
+      refill(st[u]);
     }
   }
-  double *C = const_cast<double *>(base_ptr(T.c_base, bases, psi, y, work, part)) + T.c_off;
+  double *C = out_ptr<1>(T.c_base, y, work, part) + T.c_off;
+#pragma unroll
   for (int bi = 0; bi < MB; bi++)
-    for (int bj = 0; bj < NB; bj++)
-      for (int r = 0; r < 4; r++) {
-        int i = 16 * bi + q4 + 4 * r, j = 16 * bj + r16;
-        if (i < mrem && j < nrem) {
-          gptr c = (gptr)(T.rowmajor ? C + (int64_t)(T.ci0 + i) * T.ldc + (T.cj0 + j)
-                                     : C + (int64_t)(T.ci0 + i) + (int64_t)(T.cj0 + j) * T.ldc);
-          *c = T.accumulate ? *c + acc[bi][bj][r] : acc[bi][bj][r];
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int i = 16 * bi + q4 + 4 * r;
+      gptr c = (gptr)(C + (int64_t)(T.ci0 + i) * T.ldc + (T.cj0 + r16));
+#pragma unroll
+      for (int bj = 0; bj < NB; bj++)
+        if (i < mrem && 16 * bj + r16 < nrem) c[16 * bj] = acc[bi][bj][r];
+    }
+}
+
+// second stage: the K steps of all segments form one sequence, loaded ahead
+// across segment boundaries.  Tiles of small sectors sum hundreds of segments
+// of a few rows (L=8: 138 of 8 rows); with the loads started anew at every
+// segment each one cost its descriptor's and its operands' latency, 3.3 us.
+// The next segment's descriptor is read while the current one is walked.
+// Every lane walks its own row: `k`, its row `kk` in the position and its two
+// operand pointers move by the same uniform strides, with one more at a
+// position boundary (both operands have the same positions).
+template <int MB, int NB, int DEPTH>
+__device__ __forceinline__ void item2_f64(const Tile &T, const Seg *__restrict__ segs, const double *psi, double *y,
+                                          double *work, double *part, int r16, int q4) {
+  v4d acc[MB][NB];
+#pragma unroll
+  for (int a = 0; a < MB; a++)
+#pragma unroll
+    for (int b = 0; b < NB; b++) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
+  const int mrem = T.m - T.i0, nrem = T.n - T.j0;
+  const CSegF *cs = (const CSegF *)segs + T.seg0;
+  if (T.nid < T.nseg) {
+    // uniform state of the walk ...
+    int si = T.nid, K = 0, kb = 1, dk = 0, k0 = 0;
+    double s = 0.0;
+    int64_t da = 0, ea = 0, db = 0, eb = 0;   // per step, extra at a position boundary
+    // ... and this lane's
+    int k = 0, kk = 0;
+    const double *pa = nullptr, *pb = nullptr;
+    uint32_t ao[MB], bo[NB];   // lines of the further blocks, elements past the first one's
+    const unsigned i0 = min(r16, mrem - 1), j0 = min(r16, nrem - 1);
+    struct {
+      int64_t a_off, b_off, da, ea, db, eb;
+      double s;
+      uint32_t a_p, a_i, a_k, b_pk, b_k, b_n;   // strides below 2^32 (see mad)
+      int a_base, b_base, K, kb;
+    } nx;   // descriptor of segment si
+    auto fetch_desc = [&]() {
+      CSegF &S = cs[si];
+      nx.a_off = S.a_off; nx.b_off = S.b_off;
+      nx.a_p = (uint32_t)S.a_p; nx.a_i = (uint32_t)S.a_i; nx.a_k = (uint32_t)S.a_k;
+      nx.b_pk = (uint32_t)S.b_pk; nx.b_k = (uint32_t)S.b_k; nx.b_n = (uint32_t)S.b_n;
+      nx.da = S.da; nx.ea = S.ea; nx.db = S.db; nx.eb = S.eb;
+      nx.s = S.s;
+      nx.a_base = S.a_base; nx.b_base = S.b_base;
+      nx.K = S.K; nx.kb = S.a_kb;
+    };
+    auto open = [&]() {
+      K = nx.K;
+      kb = nx.kb;
+      s = nx.s;
+      k0 = 0;
+      dk = kb > 4 ? 4 : kb == 3 ? 1 : 0;   // 4 mod kb
+      da = nx.da;
+      ea = nx.ea;
+      db = nx.db;
+      eb = nx.eb;
+      k = min(q4, K - 1);
+      const unsigned p = kb >= 4 ? 0 : kb == 3 ? (k == 3) : kb == 2 ? k >> 1 : k;
+      kk = k - p * kb;
+      pa = seg_ptr(nx.a_base, psi, work) + nx.a_off;
+      pb = seg_ptr(nx.b_base, psi, work) + nx.b_off;
+      pa = mad(mad(mad(pa, p, nx.a_p), kk, nx.a_k), T.i0 + i0, nx.a_i);
+      pb = mad(mad(mad(pb, p, nx.b_pk), kk, nx.b_k), T.j0 + j0, nx.b_n);
+      k = q4;
+#pragma unroll
+      for (int bi = 1; bi < MB; bi++) ao[bi] = (uint32_t)(min(16 * bi + r16, mrem - 1) - i0) * nx.a_i;
+#pragma unroll
+      for (int bj = 1; bj < NB; bj++) bo[bj] = (uint32_t)(min(16 * bj + r16, nrem - 1) - j0) * nx.b_n;
+      si++;
+      if (si < T.nseg) fetch_desc();
+    };
+    StepF64<MB, NB> st[DEPTH];
+    double ss[DEPTH];   // scale and rows left of each buffered step (rows <= 0: none)
+    int rem[DEPTH];
+    fetch_desc();
+    open();
+#pragma unroll
+    for (int u = 0; u < DEPTH; u++) rem[u] = 0;
+    // rounds of DEPTH steps: the first one only fills the buffers, the last one
+    // is the one whose first refill found no step
+    do {
+#pragma unroll
+      for (int u = 0; u < DEPTH; u++) {
+        if (rem[u] > 0) mma_f64<MB, NB>(acc, st[u], q4 < rem[u] ? ss[u] : 0.0);
+        if (k0 >= K && si < T.nseg) open();
+        ss[u] = s;
+        rem[u] = K - k0;
+        st[u].a[0] = gld(pa);
+#pragma unroll
+        for (int bi = 1; bi < MB; bi++) st[u].a[bi] = gld(pa + ao[bi]);
+        st[u].b[0] = gld(pb);
+#pragma unroll
+        for (int bj = 1; bj < NB; bj++) st[u].b[bj] = gld(pb + bo[bj]);
+        k0 += 4;
+        k += 4;
+        if (k < K) {
+          pa += da;
+          pb += db;
+          kk += dk;
+          if (kk >= kb) {
+            kk -= kb;
+            pa += ea;
+            pb += eb;
+          }
         }
+        __builtin_amdgcn_sched_barrier(0);
       }
+    } while (rem[0] > 0);
+  }
+  // identity left operators (the first segments): tile += s * B restricted to
+  // the tile (one position, K == rows).  (The lane's coordinates pass through
+  // an empty asm so that offsets derived from them are computed here, not kept
+  // in registers during the loop above.)
+  asm volatile("" : "+v"(r16), "+v"(q4));
+  for (int si = 0; si < T.nid; si++) {
+    CSegF &S = cs[si];
+    const double *B = seg_ptr(S.b_base, psi, work) + S.b_off + T.i0 * S.b_k + T.j0 * S.b_n;
+    const double s = S.s;
+    double v[MB][NB][4];
+#pragma unroll
+    for (int bi = 0; bi < MB; bi++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const double *row = mad(B, min(16 * bi + q4 + 4 * r, mrem - 1), S.b_k);
+#pragma unroll
+        for (int bj = 0; bj < NB; bj++) v[bi][bj][r] = gld(mad(row, min(16 * bj + r16, nrem - 1), S.b_n));
+      }
+#pragma unroll
+    for (int bi = 0; bi < MB; bi++)
+#pragma unroll
+      for (int bj = 0; bj < NB; bj++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) acc[bi][bj][r] += s * v[bi][bj][r];
+  }
+  double *C = out_ptr<2>(T.c_base, y, work, part) + T.c_off;
+#pragma unroll
+  for (int bj = 0; bj < NB; bj++) {
+    const int j = 16 * bj + r16;
+    gptr c = (gptr)(C + (int64_t)(T.cj0 + j) * T.ldc + (T.ci0 + q4));
+#pragma unroll
+    for (int bi = 0; bi < MB; bi++)
+#pragma unroll
+      for (int r = 0; r < 4; r++)
+        if (16 * bi + 4 * r + q4 < mrem && j < nrem)
+          c[16 * bi + 4 * r] = T.accumulate ? c[16 * bi + 4 * r] + acc[bi][bj][r] : acc[bi][bj][r];
+  }
 }
 
 // One launch per stage: every wavefront takes tiles from the per-XCD queues
 // of the stage's cost-sorted list and runs the work item of the tile's shape.
-// Three wavefronts per SIMD (at most 168 registers, no spills): more loads in
-// flight per SIMD than the two that the register use of an unbounded build
-// allows; four spill.
-constexpr int F64_GRID = 256 * 3;   // resident work groups (three wavefronts per SIMD)
+// Four wavefronts per SIMD (at most 128 registers, no spills).
+constexpr int F64_GRID = 256 * 4;   // resident work groups
 template <int STAGE>
-__global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(3, 3))) stage_f64_kernel(
+__global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4, 4))) stage_f64_kernel(
     const Tile *__restrict__ tiles, const Seg *__restrict__ segs, XcdQueues q, int32_t *__restrict__ counters,
-    int32_t *__restrict__ next_counters, int chunk, const double *const *__restrict__ bases, const double *__restrict__ psi, double *__restrict__ y,
+    int32_t *__restrict__ next_counters, int chunk, const double *__restrict__ psi, double *__restrict__ y,
     double *__restrict__ work, double *__restrict__ part) {
   const int lane = threadIdx.x & 63;
   const int r16 = lane & 15, q4 = lane >> 4;
@@ -192,12 +316,26 @@ __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD) * WAVES + wave, (int)(gridDim.x / NXCD) * WAVES, chunk);
   do {
-    wq.request(lane == 0);
-    for (; wq.t < wq.tend; wq.t++) {
-      const Tile T = tiles[wq.t];
-      if (T.mb == 1) item_f64<1>(T, segs, bases, psi, y, work, part, r16, q4);
-      else if (T.mb == 4) item_f64<4>(T, segs, bases, psi, y, work, part, r16, q4);
-      else item_f64<2>(T, segs, bases, psi, y, work, part, r16, q4);
+    const int tend = __builtin_amdgcn_readfirstlane(wq.tend), step = __builtin_amdgcn_readfirstlane(wq.step);
+    for (int t = __builtin_amdgcn_readfirstlane(wq.t); t < tend; t += step) {
+      if (t + step >= tend) wq.request(lane == 0);
+      const Tile T = tiles[t];
+      const int nbi = min((T.m - T.i0 + 15) / 16, T.mb), nbj = min((T.n - T.j0 + 15) / 16, 4 / T.mb);
+#define ITEM(M, N, D)                                                          \
+  if (STAGE == 1) item1_f64<M, N>(T, segs, psi, y, work, part, r16, q4);       \
+  else item2_f64<M, N, D>(T, segs, psi, y, work, part, r16, q4);
+      if (nbi == 1 && nbj == 1) {
+        ITEM(1, 1, 6)
+      } else if (nbi == 1 && nbj == 2) {
+        ITEM(1, 2, 4)
+      } else if (nbi == 1) {
+        ITEM(1, 4, 4)
+      } else if (T.mb == 2) {
+        ITEM(2, 2, 4)
+      } else {
+        ITEM(4, 1, 4)
+      }
+#undef ITEM
     }
   } while (wq.next(lane));
 }
@@ -228,13 +366,9 @@ typedef WgTile<2, 2, 2, 2, 4> MacroF64;   // 64 x 64
 static_assert(WideF64::BM == WIDE_EDGE && WideF64::BN == WIDE_EDGE, "F64_WIDE_MB tiles");
 static_assert(MacroF64::BM == MACRO_EDGE && MacroF64::BN == MACRO_EDGE, "MACRO_MB tiles");
 
-// segment descriptors do not change during a launch: scalar loads
-typedef const Seg __attribute__((address_space(4))) CSegF;
-
-template <typename G>
-__device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict__ segs, const double *const *bases,
-                                            const double *psi, double *y, double *work, double *part, double *lds,
-                                            int wave, int lane) {
+template <typename G, int STAGE>
+__device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict__ segs, const double *psi, double *y,
+                                            double *work, double *part, double *lds, int wave, int lane) {
   const CSegF *cs = (const CSegF *)segs + T.seg0;
   const int r16 = lane & 15, q4 = lane >> 4;
   const int wr = wave / G::WN, wc = wave % G::WN;
@@ -247,8 +381,7 @@ __device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict
   for (int a = 0; a < G::MBW; a++)
 #pragma unroll
     for (int b = 0; b < G::NBW; b++) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
-  int si = 0;
-  while (si < T.nseg && cs[si].a_base < 0) si++;
+  int si = T.nid;   // identity segments come first
   if (si < T.nseg) {
     // this thread's line of each operand (lines past the output read the last
     // one, never stored) and its wave-uniform first K row of a step; element e
@@ -282,11 +415,11 @@ __device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict
       db = R * bk;
       ea = S.a_p - wkb * ak;
       eb = S.b_pk - wkb * bk;
-      const int p0 = T.j0 < S.b_nb ? 0 : T.j0 / S.b_nb;
+      const int p0 = STAGE == 2 || T.j0 < S.b_nb ? 0 : T.j0 / S.b_nb;
       const int row = min(kr, wK - 1);
       wk = row;
-      wa = base_ptr(S.a_base, bases, psi, y, work, part) + S.a_off + (int64_t)T.i0 * S.a_i + row * ak;
-      wb = base_ptr(S.b_base, bases, psi, y, work, part) + S.b_off + (int64_t)p0 * S.b_pn + row * bk;
+      wa = seg_ptr(S.a_base, psi, work) + S.a_off + (int64_t)T.i0 * S.a_i + row * ak;
+      wb = seg_ptr(S.b_base, psi, work) + S.b_off + (int64_t)p0 * S.b_pn + row * bk;
       if (wk >= wkb) {   // kr < R <= 4, positions of at least two rows
         wk -= wkb;
         wa += ea;
@@ -299,7 +432,7 @@ __device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict
       }
       ao = 8u * (uint32_t)il * (uint32_t)S.a_i;
       int pn = 0, jn = jl - p0 * S.b_nb;
-      if (S.b_nb < T.n && jn >= S.b_nb) {
+      if (STAGE == 1 && S.b_nb < T.n && jn >= S.b_nb) {
         pn = jn / S.b_nb;
         jn -= pn * S.b_nb;
       }
@@ -316,7 +449,7 @@ __device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict
           wa += da;
           wb += db;
           wk += R;
-          if (wk >= wkb) {
+          if (STAGE == 2 && wk >= wkb) {
             wk -= wkb;
             wa += ea;
             wb += eb;
@@ -375,7 +508,6 @@ __device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict
       if (nk0 >= K) {
         nk0 = 0;
         nsi++;
-        while (nsi < T.nseg && cs[nsi].a_base < 0) nsi++;
       }
       const bool more = nsi < T.nseg;
       if (more) {
@@ -398,10 +530,9 @@ __device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict
   // (the lane index passes through an empty asm, here and below, so that the
   // offsets derived from it are not kept in registers during the K loop)
   asm volatile("" : "+v"(lane));
-  for (si = 0; si < T.nseg; si++) {
+  for (si = 0; STAGE == 2 && si < T.nid; si++) {
     CSegF &S = cs[si];
-    if (S.a_base >= 0) continue;
-    const double *B = base_ptr(S.b_base, bases, psi, y, work, part) + S.b_off;
+    const double *B = seg_ptr(S.b_base, psi, work) + S.b_off;
     const double s = S.s;
 #pragma unroll
     for (int bi = 0; bi < G::MBW; bi++) {
@@ -421,7 +552,7 @@ __device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict
     }
   }
   asm volatile("" : "+v"(lane));
-  double *C = const_cast<double *>(base_ptr(T.c_base, bases, psi, y, work, part)) + T.c_off;
+  double *C = out_ptr<STAGE>(T.c_base, y, work, part) + T.c_off;
 #pragma unroll
   for (int bi = 0; bi < G::MBW; bi++)
 #pragma unroll
@@ -430,9 +561,9 @@ __device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict
       for (int r = 0; r < 4; r++) {
         const int i = 16 * (wr + G::WM * bi) + (lane >> 4) + 4 * r, j = 16 * (wc + G::WN * bj) + (lane & 15);
         if (i < mt && j < nt) {
-          gptr c = (gptr)(T.rowmajor ? C + (int64_t)(T.ci0 + i) * T.ldc + (T.cj0 + j)
+          gptr c = (gptr)(STAGE == 1 ? C + (int64_t)(T.ci0 + i) * T.ldc + (T.cj0 + j)
                                      : C + (int64_t)(T.ci0 + i) + (int64_t)(T.cj0 + j) * T.ldc);
-          *c = T.accumulate ? *c + acc[bi][bj][r] : acc[bi][bj][r];
+          *c = STAGE == 2 && T.accumulate ? *c + acc[bi][bj][r] : acc[bi][bj][r];
         }
       }
 }
@@ -440,31 +571,35 @@ __device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict
 template <typename G, int STAGE>
 __global__ void __launch_bounds__(G::NT) __attribute__((amdgpu_waves_per_eu(G::EU, G::EU))) wg_f64_kernel(
     const Tile *__restrict__ tiles, const Seg *__restrict__ segs, XcdQueues q, int32_t *__restrict__ counters,
-    int32_t *__restrict__ next_counters, const double *const *__restrict__ bases, const double *__restrict__ psi,
+    int32_t *__restrict__ next_counters, const double *__restrict__ psi,
     double *__restrict__ y, double *__restrict__ work, double *__restrict__ part) {
   __shared__ double lds[2 * G::STAGE];
-  // the next tile's index, in the padding of the first LDS row (with an int of
-  // its own the 64 x 64 tiles would exceed a quarter of the LDS)
+  // the next tiles, in the padding of the first LDS row (with ints of their own
+  // the 64 x 64 tiles would exceed a quarter of the LDS)
   int *taken = (int *)(lds + G::BM);
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   clear_counters(next_counters);
   WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD), (int)(gridDim.x / NXCD), 1);
-  int t = wq.t < wq.tend ? wq.t : -1;
-  bool fixed = true;   // t is this work group's fixed first tile (-1: none)
-  while (t >= 0 || fixed) {
-    if (wave == 0) wq.request(lane == 0);
-    if (t >= 0) {
-      const Tile T = tiles[t];
-      wg_tile_f64<G>(T, segs, bases, psi, y, work, part, lds, wave, lane);
+  for (bool more = true; more;) {
+    for (; wq.t < wq.tend; wq.t += wq.step) {
+      if (wave == 0 && wq.last()) wq.request(lane == 0);
+      const Tile T = tiles[__builtin_amdgcn_readfirstlane(wq.t)];
+      wg_tile_f64<G, STAGE>(T, segs, psi, y, work, part, lds, wave, lane);
+      __syncthreads();   // everyone has read the last LDS stage
     }
-    fixed = false;
     if (wave == 0) {
-      const int v = wq.next(lane) ? wq.t : -1;
-      if (lane == 0) *taken = v;
+      more = wq.next(lane);
+      if (lane == 0) {
+        taken[0] = more ? wq.t : 0;
+        taken[1] = more ? wq.tend : -1;
+      }
     }
     __syncthreads();
-    t = __builtin_amdgcn_readfirstlane(*taken);
-    __syncthreads();   // everyone has read `taken` and the last LDS stage
+    wq.t = __builtin_amdgcn_readfirstlane(taken[0]);
+    wq.tend = __builtin_amdgcn_readfirstlane(taken[1]);
+    wq.step = 1;
+    more = wq.t < wq.tend;
+    __syncthreads();   // everyone has read `taken`
   }
 }
 
@@ -544,44 +679,46 @@ void launch_zero(double *y, int64_t n, int32_t *counters, void *stream) {
 }
 
 void launch_tiles_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles, double flops, const XcdQueues &q,
-                      QueueSets &qs, const double *const *bases, const double *psi, double *y, double *work,
+                      QueueSets &qs, const double *psi, double *y, double *work,
                       double *part, void *stream) {
   if (ntiles <= 0) return;
   hipStream_t s = (hipStream_t)stream;
-  const int grid = wave_grid(ntiles, F64_GRID), chunk = wave_chunk(ntiles, F64_GRID, flops);
+  const int grid = wave_grid(ntiles, F64_GRID), chunk = wave_chunk(ntiles, flops);
+  const XcdQueues dq = deal(q, grid / NXCD * WAVES);
   if (stage == 1)
-    hipLaunchKernelGGL(stage_f64_kernel<1>, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, q, qs.cur(), qs.other(),
-                       chunk, bases, psi, y, work, part);
+    hipLaunchKernelGGL(stage_f64_kernel<1>, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, dq, qs.cur(), qs.other(),
+                       chunk, psi, y, work, part);
   else
-    hipLaunchKernelGGL(stage_f64_kernel<2>, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, q, qs.cur(), qs.other(),
-                       chunk, bases, psi, y, work, part);
+    hipLaunchKernelGGL(stage_f64_kernel<2>, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, dq, qs.cur(), qs.other(),
+                       chunk, psi, y, work, part);
   qs.launch++;
 }
 
 template <typename G>
 static void launch_wg_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles, const XcdQueues &q, QueueSets &qs,
-                          const double *const *bases, const double *psi, double *y, double *work, double *part,
+                          const double *psi, double *y, double *work, double *part,
                           hipStream_t s) {
   // as many work groups as are resident at once: G::EU wavefronts per SIMD
   const int resident = 256 * (G::EU * 4 * 64 / G::NT);
   const int grid = std::min((ntiles + NXCD - 1) / NXCD * NXCD, resident);
+  const XcdQueues dq = deal(q, grid / NXCD);
   if (stage == 1)
-    hipLaunchKernelGGL((wg_f64_kernel<G, 1>), dim3(grid), dim3(G::NT), 0, s, tiles, segs, q, qs.cur(), qs.other(), bases,
+    hipLaunchKernelGGL((wg_f64_kernel<G, 1>), dim3(grid), dim3(G::NT), 0, s, tiles, segs, dq, qs.cur(), qs.other(),
                        psi, y, work, part);
   else
-    hipLaunchKernelGGL((wg_f64_kernel<G, 2>), dim3(grid), dim3(G::NT), 0, s, tiles, segs, q, qs.cur(), qs.other(), bases,
+    hipLaunchKernelGGL((wg_f64_kernel<G, 2>), dim3(grid), dim3(G::NT), 0, s, tiles, segs, dq, qs.cur(), qs.other(),
                        psi, y, work, part);
   qs.launch++;
 }
 
 void launch_wg_tiles_f64(int stage, int mb, const Tile *tiles, const Seg *segs, int ntiles, const XcdQueues &q,
-                         QueueSets &qs, const double *const *bases, const double *psi, double *y, double *work,
+                         QueueSets &qs, const double *psi, double *y, double *work,
                          double *part, void *stream) {
   if (ntiles <= 0) return;
   if (mb == F64_WIDE_MB)
-    launch_wg_f64<WideF64>(stage, tiles, segs, ntiles, q, qs, bases, psi, y, work, part, (hipStream_t)stream);
+    launch_wg_f64<WideF64>(stage, tiles, segs, ntiles, q, qs, psi, y, work, part, (hipStream_t)stream);
   else
-    launch_wg_f64<MacroF64>(stage, tiles, segs, ntiles, q, qs, bases, psi, y, work, part, (hipStream_t)stream);
+    launch_wg_f64<MacroF64>(stage, tiles, segs, ntiles, q, qs, psi, y, work, part, (hipStream_t)stream);
 }
 
 void launch_reduce(const Reduce *red, int nred, const double *part, double *y, void *stream) {

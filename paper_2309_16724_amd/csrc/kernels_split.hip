@@ -380,9 +380,9 @@ __device__ __forceinline__ void items_split(const Tile *__restrict__ tiles, cons
   clear_counters(next_counters);
   WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD) * WAVES + wave, (int)(gridDim.x / NXCD) * WAVES, chunk);
   do {
-    wq.request(lane == 0);
-    for (; wq.t < wq.tend; wq.t++) {
-      const Tile T = tiles[wq.t];
+    for (; wq.t < wq.tend; wq.t += wq.step) {
+      if (wq.last()) wq.request(lane == 0);
+      const Tile T = tiles[__builtin_amdgcn_readfirstlane(wq.t)];
       if (T.mb == 1) item_split<1, NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, stage, r16, q4);
       else if (T.mb == 4) item_split<4, NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, stage, r16, q4);
       else item_split<2, NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, stage, r16, q4);
@@ -605,16 +605,14 @@ __device__ __forceinline__ void macro_items(const Tile *__restrict__ tiles, cons
   int32_t *mailbox = mailboxes + blockIdx.x;
   clear_counters(next_counters);
   WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD), (int)(gridDim.x / NXCD), 1);
-  int t = wq.t < wq.tend ? wq.t : -1;
-  bool fixed = true;   // t is this work group's fixed first tile (-1: none)
-  for (;;) {
-    if (t < 0 && !fixed) break;   // every range is used up: the whole work group leaves
-    if (wave == 0) wq.request(lane == 0);
-    if (t >= 0) {
-      const Tile T = tiles[t];
+  for (bool more = true; more;) {
+    for (; wq.t < wq.tend; wq.t += wq.step) {
+      if (wave == 0 && wq.last()) wq.request(lane == 0);
+      const Tile T = tiles[__builtin_amdgcn_readfirstlane(wq.t)];
       macro_split<NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, lds, wave, lane);
     }
-    fixed = false;
+    // the next tiles reach the wavefronts through this work group's mailbox
+    // (chunks of one tile; atomics: coherent at the L2)
     if (wave == 0) {
       const int v = wq.next(lane) ? wq.t : -1;
       if (lane == 0) atomicExch(mailbox, v);
@@ -624,7 +622,10 @@ __device__ __forceinline__ void macro_items(const Tile *__restrict__ tiles, cons
     __syncthreads();
     int v = 0;
     if (lane == 0) v = atomicAdd(mailbox, 0);
-    t = __builtin_amdgcn_readfirstlane(v);
+    wq.t = __builtin_amdgcn_readfirstlane(v);
+    more = wq.t >= 0;
+    wq.tend = wq.t + 1;
+    wq.step = 1;
   }
 }
 
@@ -889,16 +890,14 @@ __device__ __forceinline__ void wide_items(const Tile *__restrict__ tiles, const
   int32_t *mailbox = mailboxes + blockIdx.x;
   clear_counters(next_counters);
   WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD), (int)(gridDim.x / NXCD), 1);
-  int t = wq.t < wq.tend ? wq.t : -1;
-  bool fixed = true;   // t is this work group's fixed first tile (-1: none)
-  for (;;) {
-    if (t < 0 && !fixed) break;   // every range is used up: the whole work group leaves
-    if (wave == 0) wq.request(lane == 0);
-    if (t >= 0) {
-      const Tile T = tiles[t];
+  for (bool more = true; more;) {
+    for (; wq.t < wq.tend; wq.t += wq.step) {
+      if (wave == 0 && wq.last()) wq.request(lane == 0);
+      const Tile T = tiles[__builtin_amdgcn_readfirstlane(wq.t)];
       wide_split<NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, lds0, lds1, wave, lane);
     }
-    fixed = false;
+    // the next tiles reach the wavefronts through this work group's mailbox
+    // (chunks of one tile; atomics: coherent at the L2)
     if (wave == 0) {
       const int v = wq.next(lane) ? wq.t : -1;
       if (lane == 0) atomicExch(mailbox, v);
@@ -908,7 +907,10 @@ __device__ __forceinline__ void wide_items(const Tile *__restrict__ tiles, const
     __syncthreads();
     int v = 0;
     if (lane == 0) v = atomicAdd(mailbox, 0);
-    t = __builtin_amdgcn_readfirstlane(v);
+    wq.t = __builtin_amdgcn_readfirstlane(v);
+    more = wq.t >= 0;
+    wq.tend = wq.t + 1;
+    wq.step = 1;
   }
 }
 
@@ -968,14 +970,15 @@ void launch_macro_split(int stage, const Tile *tiles, const Seg *segs, const Seg
   // two work groups resident per CU (80 KiB of LDS each at s = 5); every work
   // group takes tiles until all queues are empty
   const int grid = std::max(8, std::min((ntiles + 7) / 8 * 8, MACRO_GRID));
+  const XcdQueues dq = deal(q, grid / NXCD);
 #define MLAUNCH(NS)                                                                                         \
   if (nslices == NS) {                                                                                      \
     if (stage == 1)                                                                                         \
       hipLaunchKernelGGL(stage1_msplit##NS##_kernel, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, ssegs,  \
-                         q, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);           \
+                         dq, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);           \
     else                                                                                                    \
       hipLaunchKernelGGL(stage2_msplit##NS##_kernel, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, ssegs,  \
-                         q, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);           \
+                         dq, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);           \
     qs.launch++;                                                                                            \
     return;                                                                                                 \
   }
@@ -994,14 +997,15 @@ void launch_wide_split(int stage, const Tile *tiles, const Seg *segs, const SegS
   hipStream_t s = (hipStream_t)stream;
   // one work group per CU (the two stages take all 160 KiB of LDS at s = 5)
   const int grid = std::max(8, std::min((ntiles + 7) / 8 * 8, WIDE_GRID));
+  const XcdQueues dq = deal(q, grid / NXCD);
 #define WLAUNCH(NS)                                                                                         \
   if (nslices == NS) {                                                                                      \
     if (stage == 1)                                                                                         \
       hipLaunchKernelGGL(stage1_wsplit##NS##_kernel, dim3(grid), dim3(64 * WIDE_WAVES), 0, s, tiles, segs,  \
-                         ssegs, q, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);    \
+                         ssegs, dq, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);    \
     else                                                                                                    \
       hipLaunchKernelGGL(stage2_wsplit##NS##_kernel, dim3(grid), dim3(64 * WIDE_WAVES), 0, s, tiles, segs,  \
-                         ssegs, q, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);    \
+                         ssegs, dq, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);    \
     qs.launch++;                                                                                            \
     return;                                                                                                 \
   }
@@ -1018,15 +1022,16 @@ void launch_tiles_split(int stage, const Tile *tiles, const Seg *segs, const Seg
   hipStream_t s = (hipStream_t)stream;
   // work groups that the LDS stages let run at once
   const int resident = 256 * std::max(1, LDS_BYTES / (WAVES * stage_bytes(nslices)));
-  const int grid = wave_grid(ntiles, resident), chunk = wave_chunk(ntiles, resident, flops);
+  const int grid = wave_grid(ntiles, resident), chunk = wave_chunk(ntiles, flops);
+  const XcdQueues dq = deal(q, grid / NXCD * WAVES);
 #define LAUNCH(NS)                                                                                          \
   if (nslices == NS) {                                                                                      \
     if (stage == 1)                                                                                         \
       hipLaunchKernelGGL(stage1_split##NS##_kernel, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, ssegs,   \
-                         q, qs.cur(), qs.other(), chunk, bases, psi, y, work, part, bufs);           \
+                         dq, qs.cur(), qs.other(), chunk, bases, psi, y, work, part, bufs);           \
     else                                                                                                    \
       hipLaunchKernelGGL(stage2_split##NS##_kernel, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, ssegs,   \
-                         q, qs.cur(), qs.other(), chunk, bases, psi, y, work, part, bufs);           \
+                         dq, qs.cur(), qs.other(), chunk, bases, psi, y, work, part, bufs);           \
     qs.launch++;                                                                                            \
     return;                                                                                                 \
   }

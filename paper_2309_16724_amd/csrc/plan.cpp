@@ -2,6 +2,7 @@
 #include "plan.hpp"
 #include <hip/hip_runtime_api.h>
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -190,8 +191,10 @@ int upload(dmrg_plan *p, const std::vector<T> &v, T **out, bool plan_level = tru
 
 struct StripeKey {
   int prob, E, rec, adj, dress;
+  // by operator record first: the stripes of one record over all wavefunction
+  // blocks follow each other, so the first stage reads it once into L2
   bool operator<(const StripeKey &o) const {
-    return std::tie(prob, E, rec, adj, dress) < std::tie(o.prob, o.E, o.rec, o.adj, o.dress);
+    return std::tie(prob, rec, adj, dress, E) < std::tie(o.prob, o.rec, o.adj, o.dress, o.E);
   }
 };
 
@@ -358,15 +361,16 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
             t.m = s.dL; t.n = N; t.i0 = i0; t.j0 = j0; t.ci0 = i0; t.cj0 = j0;
             t.mb = mb;
             t.seg0 = sidx; t.nseg = 1; t.accumulate = 0;
+            const double c1 = tile_cost(mb, std::min(tile_rows(mb), s.dL - i0), std::min(tile_cols(mb), N - j0), 1, s.dRin);
             if (mb == WIDE_MB || mb == F64_WIDE_MB) {
               ch.tile1x.push_back(t);
-              cost1x.push_back(s.dRin);
+              cost1x.push_back(c1);
             } else if (mb == MACRO_MB) {
               ch.tile1m.push_back(t);
-              cost1m.push_back(s.dRin);
+              cost1m.push_back(c1);
             } else {
               ch.tile1.push_back(t);
-              cost1.push_back(s.dRin);
+              cost1.push_back(c1);
             }
           }
         s0 = s1;
@@ -374,7 +378,9 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
     }
     max_work = std::max(max_work, woff);
     // second stage: segments grouped by output block
-    std::map<std::pair<int, int>, std::vector<std::pair<Seg, Seg2Info>>> byF;
+    // (problem, right sector, block): the blocks of one right sector read the
+    // same stripes, so their tiles run next to each other
+    std::map<std::array<int, 3>, std::vector<std::pair<Seg, Seg2Info>>> byF;
     for (auto &r : ct) {
       const ProbPlan &pp = *P->probs[r.prob];
       const Tasks &T = pp.T;
@@ -393,7 +399,7 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
         rowsA = pp.L.sec[ra.row_sec].dim; colsA = pp.L.sec[ra.col_sec].dim;
         recoffA = ra.off;
       }
-      auto &segs = byF[{r.prob, tk.F}];
+      auto &segs = byF[{r.prob, F.iR, tk.F}];
       size_t q = 0;
       while (q < row.pos.size()) {
         size_t q1 = q + 1;
@@ -454,8 +460,8 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
     std::vector<std::pair<double, Tile>> tiles2, tiles2m, tiles2x;
     int64_t npart = 0;   // partial-tile elements
     for (auto &kv : byF) {
-      const ProbPlan &pp = *P->probs[kv.first.first];
-      const PsiBlock &F = pp.T.blocks[kv.first.second];
+      const ProbPlan &pp = *P->probs[kv.first[0]];
+      const PsiBlock &F = pp.T.blocks[kv.first[2]];
       // pieces of at most KPART along K, cut at position boundaries
       std::vector<Seg> pieces;
       std::vector<Seg2Info> pinfo;
@@ -495,20 +501,34 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
       }
       parts.push_back({b0, (int)pieces.size()});
       pcost.push_back(cost);
+      // identity pieces first within a part
+      std::vector<int> pnid;
+      for (const auto &pt : parts) {
+        std::vector<Seg> g(pieces.begin() + pt.first, pieces.begin() + pt.second);
+        std::vector<Seg2Info> gi(pinfo.begin() + pt.first, pinfo.begin() + pt.second);
+        int o = pt.first;
+        for (int pass = 0; pass < 2; pass++) {
+          for (size_t i = 0; i < g.size(); i++)
+            if ((g[i].a_base < 0) == (pass == 0)) {
+              pieces[o] = g[i];
+              pinfo[o++] = gi[i];
+            }
+          if (pass == 0) pnid.push_back(o - pt.first);
+        }
+      }
       int seg0 = (int)ch.seg2.size();
       for (auto &g : pieces) ch.seg2.push_back(g);
       for (auto &gi : pinfo) ch.s2info.push_back(gi);
       const auto cells = output_cells(P, F.dL, F.dR);
       const int np = (int)parts.size();
       // partial tiles of cell c, part p at npart + coff[c] + p tm tn (tm x tn
-      // the cell's tile shape, for FP64 work-group tiles its part inside the
-      // output); the list runs over parts (outer) and cells in
+      // the tile's part inside the output); the list runs over parts (outer) and cells in
       // patch order (inner), so the tiles that run together share their K range
       auto cell_rows = [&](const Cell &c) {
-        return trow && c.mb >= MACRO_MB ? std::min(tile_rows(c.mb), F.dL - c.i0) : tile_rows(c.mb);
+        return std::min(tile_rows(c.mb), F.dL - c.i0);
       };
       auto cell_cols = [&](const Cell &c) {
-        return trow && c.mb >= MACRO_MB ? std::min(tile_cols(c.mb), F.dR - c.j0) : tile_cols(c.mb);
+        return std::min(tile_cols(c.mb), F.dR - c.j0);
       };
       std::vector<int64_t> coff(cells.size() + 1, 0);
       for (size_t c = 0; c < cells.size(); c++)
@@ -522,6 +542,7 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
           t.m = F.dL; t.n = F.dR; t.i0 = i0; t.j0 = j0; t.mb = mb;
           t.seg0 = seg0 + parts[pi].first;
           t.nseg = parts[pi].second - parts[pi].first;
+          t.nid = pnid[pi];
           if (np == 1) {
             t.c_base = BASE_Y;
             t.c_off = pp.psi_off + F.off;
@@ -544,14 +565,16 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
             t.ci0 = 0; t.cj0 = 0;
             t.accumulate = 0;
           }
-          dst.push_back({pcost[pi], t});
+          dst.push_back({tile_cost(mb, tm, tn, t.nseg, pcost[pi]), t});
         }
       if (np > 1) npart += coff[cells.size()];
     }
     ch.part_elems = npart;
     P->part_elems = std::max(P->part_elems, ch.part_elems);
+    // by falling cost within a factor of two: a full sort would take the tiles
+    // that share stripes apart
     auto by_cost = [](const std::pair<double, Tile> &a, const std::pair<double, Tile> &b) {
-      return a.first > b.first;
+      return std::ilogb(a.first) > std::ilogb(b.first);
     };
     std::stable_sort(tiles2.begin(), tiles2.end(), by_cost);
     std::stable_sort(tiles2m.begin(), tiles2m.end(), by_cost);
@@ -633,7 +656,9 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
   // ---- upload
   int rc;
   for (auto &ch : P->chunks) {
-    if ((rc = upload(P, ch.seg1, &ch.d_seg1)) || (rc = upload(P, ch.seg2, &ch.d_seg2)) ||
+    const bool f64 = P->precision == DMRG_FP64;
+    if ((rc = upload(P, f64 ? resolve_bases(ch.seg1, P->bases_h.data()) : ch.seg1, &ch.d_seg1)) ||
+        (rc = upload(P, f64 ? resolve_bases(ch.seg2, P->bases_h.data()) : ch.seg2, &ch.d_seg2)) ||
         (rc = upload(P, ch.tile1, &ch.d_tile1)) || (rc = upload(P, ch.tile2, &ch.d_tile2)) ||
         (rc = upload(P, ch.tile1m, &ch.d_tile1m)) || (rc = upload(P, ch.tile2m, &ch.d_tile2m)) ||
         (rc = upload(P, ch.tile1x, &ch.d_tile1x)) || (rc = upload(P, ch.tile2x, &ch.d_tile2x)) ||
@@ -1407,20 +1432,19 @@ int enqueue_with(dmrg_plan *p, const double *psi, double *hpsi, void *stream, bo
         if (!(s1 ? ch.tile1x : ch.tile2x).empty())
           rc = timed(30 + stage, s1 ? ch.flops1x : ch.flops2x, [&] {
             launch_wg_tiles_f64(stage, F64_WIDE_MB, s1 ? ch.d_tile1x : ch.d_tile2x, s1 ? ch.d_seg1 : ch.d_seg2,
-                                (int)(s1 ? ch.tile1x : ch.tile2x).size(), s1 ? ch.q1x : ch.q2x, qs, p->d_bases, psi,
-                                hpsi, B.work, B.part, stream);
+                                (int)(s1 ? ch.tile1x : ch.tile2x).size(), s1 ? ch.q1x : ch.q2x, qs, psi, hpsi, B.work, B.part,
+                                stream);
           });
         if (!rc && !(s1 ? ch.tile1m : ch.tile2m).empty())
           rc = timed(10 + stage, s1 ? ch.flops1m : ch.flops2m, [&] {
             launch_wg_tiles_f64(stage, MACRO_MB, s1 ? ch.d_tile1m : ch.d_tile2m, s1 ? ch.d_seg1 : ch.d_seg2,
-                                (int)(s1 ? ch.tile1m : ch.tile2m).size(), s1 ? ch.q1m : ch.q2m, qs, p->d_bases, psi,
-                                hpsi, B.work, B.part, stream);
+                                (int)(s1 ? ch.tile1m : ch.tile2m).size(), s1 ? ch.q1m : ch.q2m, qs, psi, hpsi, B.work, B.part,
+                                stream);
           });
         if (!rc && !(s1 ? ch.tile1 : ch.tile2).empty())
           rc = timed(20 + stage, s1 ? ch.flops1w : ch.flops2w, [&] {
             launch_tiles_f64(stage, s1 ? ch.d_tile1 : ch.d_tile2, s1 ? ch.d_seg1 : ch.d_seg2,
                              (int)(s1 ? ch.tile1 : ch.tile2).size(), s1 ? ch.flops1w : ch.flops2w, s1 ? ch.q1 : ch.q2, qs,
-                             p->d_bases,
                              psi, hpsi, B.work, B.part, stream);
           });
       }

@@ -21,6 +21,9 @@ struct Seg {
   double s;
   int32_t a_base, b_base;
   int32_t K, a_kb, b_kb, b_nb;
+  // FP64 device copies (resolve_bases): the operands' strides over four K rows,
+  // and the extra one when that crosses a position boundary (a_kb == b_kb)
+  int64_t da, ea, db, eb;
 };
 
 // Work-group tiles: a tile with mb == MACRO_MB is a 64 x 64 tile computed by
@@ -58,7 +61,17 @@ constexpr int QUEUE_SET = NXCD * QUEUE_STRIDE;
 constexpr int QUEUE_INTS = 2 * QUEUE_SET + MACRO_GRID;   // two counter sets, then one mailbox per work group
 struct XcdQueues {
   int32_t start[NXCD + 1];
+  int32_t dyn[NXCD];   // first tile of range r that its counter hands out (set per launch)
 };
+// Eleven twelfths of every range go round the workers in turn (at least one
+// tile each), the rest goes to whoever is free first.
+inline XcdQueues deal(XcdQueues q, int workers) {
+  for (int r = 0; r < NXCD; r++) {
+    const int len = q.start[r + 1] - q.start[r], rounds = (len - len / 12) / workers;
+    q.dyn[r] = q.start[r] + (int)std::min<int64_t>(len, (int64_t)workers * std::max(1, rounds));
+  }
+  return q;
+}
 // Counters of consecutive tile launches on one stream: a launch uses the
 // current set, which is zero when it starts, and clears the other one.  The
 // first set is cleared by the launch_zero that opens the sequence.
@@ -71,19 +84,14 @@ struct QueueSets {
 };
 
 // Work groups of a wavefront-tile launch (a multiple of NXCD, no more than fit
-// on the chip at once: `resident`) and tiles per chunk.  Chunks of more than
-// one tile spare atomics where the tiles are short (flops: of the whole list;
-// a chunk is at most about 2^18, four 32 x 32 tiles of K = 32), but the
-// wavefronts then work a chunk apart in the list and share fewer operand bands
-// in L2: at L=54, D=1024 (K about 200) chunks of eight cost 7 %.  Every
-// wavefront still asks for about sixteen chunks.
+// on the chip at once: `resident`) and tiles per dynamic chunk: at most about
+// 2^18 flops of the list's average (eight 16 x 16 tiles of K = 64), at most 8.
 inline int wave_grid(int ntiles, int resident) {
   const int blocks = (ntiles + 3) / 4;
   return blocks < resident ? (blocks + NXCD - 1) / NXCD * NXCD : resident;
 }
-inline int wave_chunk(int ntiles, int resident, double flops) {
-  const double by_count = ntiles / (resident * 4.0 * 16.0), by_size = 262144.0 * ntiles / (flops > 1.0 ? flops : 1.0);
-  const double c = by_count < by_size ? by_count : by_size;
+inline int wave_chunk(int ntiles, double flops) {
+  const double c = 262144.0 * ntiles / (flops > 1.0 ? flops : 1.0);
   return c < 1.0 ? 1 : c > 8.0 ? 8 : (int)c;
 }
 
@@ -97,10 +105,21 @@ inline int wave_chunk(int ntiles, int resident, double flops) {
 // tiles of which one side is half empty cost 0.87 ms where 64 x 64 ones take
 // 0.63, so a whole band is asked for.  Sectors of WG_MAX_DIM states and more stay with wavefront tiles (the
 // work-group tiles address an operand's lines by 32-bit byte offsets).
-constexpr int F64_WIDE_MIN = 64, F64_MACRO_MIN = 48, WG_MAX_DIM = 1 << 14;
+constexpr int F64_WIDE_MIN = 64, F64_WIDE_MAX = 96, F64_MACRO_MIN = 48, WG_MAX_DIM = 1 << 14;
 
 // A cell of an output's tiling: top-left corner and tile kind.
 struct Cell { int i0, j0, mb; };
+
+// Time of a tile, in units of a K row of a whole tile: MFMA blocks inside the
+// output (half a tile's time is not the products), and a constant for the
+// descriptors, the first loads and the store -- without it the range of a list
+// that holds its thousands of small tiles ran three times as long as the
+// others (L=54, D=512 renormalization).
+inline double tile_cost(int mb, int rows, int cols, int nseg, double ksum) {
+  const double blocks = (double)((rows + 15) / 16) * ((cols + 15) / 16) /
+                        ((double)tile_rows(mb) * tile_cols(mb) / 256.0);
+  return 32.0 + 4.0 * nseg + ksum * (0.5 + 0.5 * blocks);
+}
 
 // MFMA row blocks of the wavefront tiles of an m x n output: skinny outputs get
 // 16x64 or 64x16 tiles, the rest 32x32 (policy 1: narrow ones too)
@@ -151,11 +170,28 @@ std::vector<Cell> cut_output(int m, int n, int wide, int tail, F &&small) {
 
 // ... of an FP64 output; wg: work-group tiles allowed
 inline std::vector<Cell> f64_cells(int m, int n, int policy, bool wg) {
-  const bool wide = wg && std::min(m, n) >= F64_WIDE_MIN && std::max(m, n) >= WIDE_EDGE;
+  const bool wide = wg && std::min(m, n) >= F64_WIDE_MIN && std::max(m, n) >= F64_WIDE_MAX;
   return cut_output(m, n, wide ? F64_WIDE_MB : 0, F64_WIDE_MIN,
                     [&](int rows, int cols) {
                       return wg && std::min(rows, cols) >= F64_MACRO_MIN ? MACRO_MB : wave_mb(rows, cols, policy);
                     });
+}
+
+// Device copy of FP64 segments: operands in operator arrays (base BASE_OPS + k
+// at bases[k]) get the absolute element address as their offset, so that the
+// kernels need no look-up between a descriptor and its loads, and the strides
+// of the walk along K are filled in.
+inline std::vector<Seg> resolve_bases(std::vector<Seg> segs, const double *const *bases) {
+  for (Seg &S : segs) {
+    if (S.a_base >= BASE_OPS) S.a_off += (int64_t)((uintptr_t)bases[S.a_base - BASE_OPS] / sizeof(double));
+    const int64_t dp = 4 / S.a_kb, dk = 4 % S.a_kb;
+    S.da = dp * S.a_p + dk * S.a_k;
+    S.ea = S.a_p - S.a_kb * S.a_k;
+    S.db = dp * S.b_pk + dk * S.b_k;
+    S.eb = S.b_pk - S.b_kb * S.b_k;
+    if (S.b_base >= BASE_OPS) S.b_off += (int64_t)((uintptr_t)bases[S.b_base - BASE_OPS] / sizeof(double));
+  }
+  return segs;
 }
 
 // One work item: a (16*mb) x (64/mb) tile of an m x n output block (rows
@@ -170,8 +206,9 @@ struct Tile {
   int32_t ci0, cj0;
   int32_t mb;           // MFMA row blocks: 1, 2 or 4 (column blocks 4 / mb)
   int32_t seg0, nseg;
-  int32_t accumulate;   // 1: C += acc, 0: C = acc
-  int32_t rowmajor;     // output layout, see above
+  int32_t nid;          // identity segments, the first ones of the tile
+  int16_t accumulate;   // 1: C += acc, 0: C = acc
+  int16_t rowmajor;     // output layout, see above
 };
 
 // Transposed copy of one operator record: npos column-major rows x cols
@@ -327,12 +364,10 @@ void launch_dress(const DressItem *items, int nitems, const int64_t *src_off, co
 // tiles from per-XCD queues; flops: of the list; qs: QUEUE_INTS ints of device
 // memory (QueueSets)
 void launch_tiles_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles, double flops, const XcdQueues &q,
-                      QueueSets &qs, const double *const *bases, const double *psi, double *y, double *work,
-                      double *part, void *stream);
+                      QueueSets &qs, const double *psi, double *y, double *work, double *part, void *stream);
 // 128 x 128 (mb == F64_WIDE_MB) or 64 x 64 (MACRO_MB) FP64 tiles of whole work groups
 void launch_wg_tiles_f64(int stage, int mb, const Tile *tiles, const Seg *segs, int ntiles, const XcdQueues &q,
-                         QueueSets &qs, const double *const *bases, const double *psi, double *y, double *work,
-                         double *part, void *stream);
+                         QueueSets &qs, const double *psi, double *y, double *work, double *part, void *stream);
 
 // NXCD contiguous ranges of a tile list with about equal summed cost
 inline XcdQueues xcd_queues(const double *cost, int n) {
@@ -349,13 +384,13 @@ inline XcdQueues xcd_queues(const double *cost, int n) {
 }
 
 // An FP64 tile list sorted by kind (wide, 64 x 64, wavefront tiles), each kind
-// by falling cost (tile area times K), with its queues.
+// by falling cost, with its queues; flops: 2 (rows) (columns) K of its tiles.
 struct KindLists {
   int first[4] = {0, 0, 0, 0};   // of each kind; first[3]: length
   double flops[3] = {0.0, 0.0, 0.0};
   XcdQueues q[3];
 };
-inline KindLists sort_by_kind(std::vector<Tile> &tiles, const std::vector<double> &cost) {
+inline KindLists sort_by_kind(std::vector<Tile> &tiles, const std::vector<double> &cost, const std::vector<Seg> &segs) {
   auto kind = [&](int i) { return tiles[i].mb == F64_WIDE_MB ? 0 : tiles[i].mb == MACRO_MB ? 1 : 2; };
   std::vector<int> ord(tiles.size());
   for (size_t i = 0; i < ord.size(); i++) ord[i] = (int)i;
@@ -370,7 +405,8 @@ inline KindLists sort_by_kind(std::vector<Tile> &tiles, const std::vector<double
     t[i] = tiles[ord[i]];
     c[i] = cost[ord[i]];
     L.first[k + 1] = (int)i + 1;
-    L.flops[k] += 2.0 * c[i];
+    const double area = (double)std::min(tile_rows(t[i].mb), t[i].m - t[i].i0) * std::min(tile_cols(t[i].mb), t[i].n - t[i].j0);
+    for (int e = 0; e < t[i].nseg; e++) L.flops[k] += 2.0 * area * segs[t[i].seg0 + e].K;
   }
   for (int k = 0; k < 3; k++) {
     L.first[k + 1] = std::max(L.first[k], L.first[k + 1]);
@@ -381,13 +417,12 @@ inline KindLists sort_by_kind(std::vector<Tile> &tiles, const std::vector<double
 }
 // the launches of such a list
 inline void launch_lists_f64(int stage, const Tile *tiles, const Seg *segs, const KindLists &L, QueueSets &qs,
-                             const double *const *bases, const double *psi, double *y, double *work, double *part,
-                             void *stream) {
+                             const double *psi, double *y, double *work, double *part, void *stream) {
   for (int k = 0; k < 2; k++)
     launch_wg_tiles_f64(stage, k == 0 ? F64_WIDE_MB : MACRO_MB, tiles + L.first[k], segs, L.first[k + 1] - L.first[k],
-                        L.q[k], qs, bases, psi, y, work, part, stream);
-  launch_tiles_f64(stage, tiles + L.first[2], segs, L.first[3] - L.first[2], L.flops[2], L.q[2], qs, bases, psi, y, work,
-                   part, stream);
+                        L.q[k], qs, psi, y, work, part, stream);
+  launch_tiles_f64(stage, tiles + L.first[2], segs, L.first[3] - L.first[2], L.flops[2], L.q[2], qs, psi, y, work, part,
+                   stream);
 }
 void launch_reduce(const Reduce *red, int nred, const double *part, double *y, void *stream);
 void launch_transpose(const TransJob *jobs, int njobs, const double *src, double *dst, void *stream);

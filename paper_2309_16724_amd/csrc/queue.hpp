@@ -8,43 +8,44 @@ namespace dmrg {
 // Work list of one worker (a wavefront or a work group) of a tile launch.
 //
 // Range r = blockIdx % NXCD of the list belongs to the workers of the blocks
-// with that remainder, which the dispatcher places on one XCD.  A worker's
-// first chunk (`chunk` consecutive tiles) is fixed by its index; the rest of
-// the range is handed out through the range's atomic counter, and a worker
-// whose range is used up helps the others.  Atomics on one address run one
-// after the other (measured: about 60 per microsecond over eight counters in
-// one 64-byte line, where every take and every failing probe of 16384
-// wavefronts made the L=24, D=512 first stage take 4.9 ms for 292,000
-// tiles).  So the counters lie QUEUE_STRIDE ints apart, ranges that the fixed
-// chunks cover are never asked, the next chunk is requested before the
-// current one is computed, and a worker without work reads all counters
-// with one load before it takes from another range.
+// with that remainder, which the dispatcher places on one XCD.  Atomics on one
+// address run one after the other, about 100 ns each (measured: 60 to 80 per
+// microsecond over all counters, in one line or in a line each), and short
+// tiles end faster than that: one atomic per tile made the L=24, D=512 first
+// stage take 4.9 ms for 292,000 tiles.  So most of a range is dealt out in
+// turn, worker w taking tiles w, w + workers, ... of it (side by side, so that
+// the workers of an XCD share operand bands in its L2), and only its rest
+// [dyn, end) through the range's counter, `chunk` tiles at a time, requested
+// one tile ahead.  A worker without work reads all counters with one load
+// before it takes from another range.
 struct WorkQueue {
   const XcdQueues &q;
   int32_t *counters;
-  int range, workers, chunk;   // current range, workers per range, tiles per chunk
-  int t, tend;                 // current chunk [t, tend)
-  int pend = 0;                // lane 0: chunk index the pending request returned
+  int range, chunk;   // current range, tiles per dynamic chunk
+  int t, tend, step;  // current tiles t, t + step, ... < tend
+  int pend = 0;       // lane 0: chunk index the pending request returned
   bool asked = false;
 
-  // tiles of range r that the counters hand out
-  __device__ __forceinline__ int dynamic(int r) const {
-    return max(0, q.start[r + 1] - q.start[r] - workers * chunk);
+  // tiles of range r that its counter hands out
+  __device__ __forceinline__ int dynamic(int r) const { return q.start[r + 1] - q.dyn[r]; }
+  __device__ __forceinline__ WorkQueue(const XcdQueues &q_, int32_t *c, int w, int workers, int chunk_)
+      : q(q_), counters(c), range(blockIdx.x & (NXCD - 1)), chunk(chunk_) {
+    t = q.start[range] + w;
+    tend = q.dyn[range];
+    step = workers;
   }
-  __device__ __forceinline__ WorkQueue(const XcdQueues &q_, int32_t *c, int w, int workers_, int chunk_)
-      : q(q_), counters(c), range(blockIdx.x & (NXCD - 1)), workers(workers_), chunk(chunk_) {
-    t = q.start[range] + w * chunk;
-    tend = min(q.start[range + 1], t + chunk);
-  }
+  __device__ __forceinline__ bool last() const { return t + step >= tend; }
   // request the next chunk of the current range (result used by next())
   __device__ __forceinline__ void request(bool leader) {
     asked = dynamic(range) > 0;
     if (asked && leader) pend = atomicAdd(counters + range * QUEUE_STRIDE, 1);
   }
-  // called by a whole wavefront after its chunk: the next chunk, false at the
-  // end.  Every index is handed out exactly once.
+  // called by a whole wavefront after its last tile: the next chunk, false at
+  // the end.  Every index is handed out exactly once.
   __device__ __forceinline__ bool next(int lane) {
-    if (asked && take(range, __builtin_amdgcn_readfirstlane(pend))) return true;
+    const bool a = asked;
+    asked = false;
+    if (a && take(range, __builtin_amdgcn_readfirstlane(pend))) return true;
     for (;;) {
       // ranges with tiles left: lane r looks at range r
       bool left = false;
@@ -56,7 +57,7 @@ struct WorkQueue {
       if (!m) return false;
       // the first one at or after the current range, cyclically
       const unsigned rot = ((m >> range) | (m << (NXCD - range))) & ((1u << NXCD) - 1);
-      range = (range + __ffs(rot) - 1) & (NXCD - 1);
+      range = __builtin_amdgcn_readfirstlane((range + __ffs(rot) - 1) & (NXCD - 1));
       int k = 0;
       if (lane == 0) k = atomicAdd(counters + range * QUEUE_STRIDE, 1);
       if (take(range, __builtin_amdgcn_readfirstlane(k))) return true;
@@ -65,10 +66,12 @@ struct WorkQueue {
 
  private:
   __device__ __forceinline__ bool take(int r, int k) {
-    const int64_t d = dynamic(r), o = (int64_t)k * chunk;
-    if (o >= d) return false;
-    t = q.start[r] + workers * chunk + (int)o;
-    tend = min(q.start[r + 1], t + chunk);
+    const int64_t o = (int64_t)k * chunk;
+    if (o >= dynamic(r)) return false;
+    // (wave-uniform, and said to be: the descriptors of a tile are scalar loads)
+    t = __builtin_amdgcn_readfirstlane(q.dyn[r] + (int)o);
+    tend = __builtin_amdgcn_readfirstlane(min(q.start[r + 1], t + chunk));
+    step = 1;
     return true;
   }
 };

@@ -1132,7 +1132,7 @@ int build_renorm(const dmrg_problem_t *prob, const dmrg_rkeep_t *keep, int n_kee
       T.m = m; T.n = n; T.i0 = c.i0; T.j0 = c.j0; T.ci0 = c.i0; T.cj0 = c.j0;
       T.mb = c.mb; T.seg0 = seg0; T.nseg = nseg; T.accumulate = 0; T.rowmajor = rowmajor;
       tiles.push_back(T);
-      cost.push_back((double)std::min(tile_rows(c.mb), m - c.i0) * std::min(tile_cols(c.mb), n - c.j0) * ksum);
+      cost.push_back(tile_cost(c.mb, std::min(tile_rows(c.mb), m - c.i0), std::min(tile_cols(c.mb), n - c.j0), nseg, ksum));
     }
   };
   // Operand layouts that let every wavefront load whole lines (lanes run
@@ -1270,8 +1270,8 @@ int build_renorm(const dmrg_problem_t *prob, const dmrg_rkeep_t *keep, int n_kee
     err = {DMRG_ERANGE, "internal: a product reaches beyond its array"};
     return err.code;
   }
-  B.l1 = sort_by_kind(B.t1, cost1);
-  B.l2 = sort_by_kind(B.t2, cost2);
+  B.l1 = sort_by_kind(B.t1, cost1, B.s1);
+  B.l2 = sort_by_kind(B.t2, cost2, B.s2);
   B.build_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
   return DMRG_OK;
 }
@@ -1403,8 +1403,8 @@ extern "C" int dmrg_renorm_create(const dmrg_problem_t *prob, const dmrg_rkeep_t
     const double *bases[3] = {bdata, r->d_lt, r->d_dress};
     ok = ok && up((void **)&r->d_t1, r->b.t1.data(), r->b.t1.size() * sizeof(Tile)) &&
               up((void **)&r->d_t2, r->b.t2.data(), r->b.t2.size() * sizeof(Tile)) &&
-              up((void **)&r->d_s1, r->b.s1.data(), r->b.s1.size() * sizeof(Seg)) &&
-              up((void **)&r->d_s2, r->b.s2.data(), r->b.s2.size() * sizeof(Seg)) &&
+              up((void **)&r->d_s1, resolve_bases(r->b.s1, bases).data(), r->b.s1.size() * sizeof(Seg)) &&
+              up((void **)&r->d_s2, resolve_bases(r->b.s2, bases).data(), r->b.s2.size() * sizeof(Seg)) &&
               up((void **)&r->d_bases, bases, sizeof(bases)) &&
               up((void **)&r->d_cnt, nullptr, QUEUE_INTS * sizeof(int32_t)) &&
               up((void **)&r->d_work, nullptr, (size_t)r->b.work_len * sizeof(double));
@@ -1459,9 +1459,9 @@ extern "C" int dmrg_renorm_apply(dmrg_renorm_t *r, const double *u, double *out,
   QueueSets qs{r->d_cnt};
   launch_zero(out, r->b.out_len, qs.cur(), stream);
   if (r->prof) (void)hipEventRecord(ev[0], hs);
-  launch_lists_f64(1, r->d_t1, r->d_s1, r->b.l1, qs, r->d_bases, r->d_ut, out, r->d_work, nullptr, stream);
+  launch_lists_f64(1, r->d_t1, r->d_s1, r->b.l1, qs, r->d_ut, out, r->d_work, nullptr, stream);
   if (r->prof) { (void)hipEventRecord(ev[1], hs); (void)hipEventRecord(ev[2], hs); }
-  launch_lists_f64(2, r->d_t2, r->d_s2, r->b.l2, qs, r->d_bases, r->d_ut, out, r->d_work, nullptr, stream);
+  launch_lists_f64(2, r->d_t2, r->d_s2, r->b.l2, qs, r->d_ut, out, r->d_work, nullptr, stream);
   if (r->prof) {
     (void)hipEventRecord(ev[3], hs);
     for (auto &x : ev) r->ev.push_back(x);

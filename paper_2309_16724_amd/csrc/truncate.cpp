@@ -154,7 +154,7 @@ int build_rho(const dmrg_problem_t *prob, int32_t flags, RhoLists &RL) {
           T.m = m; T.n = n; T.i0 = c.i0; T.j0 = c.j0; T.ci0 = c.i0; T.cj0 = c.j0;
           T.mb = c.mb; T.seg0 = seg0; T.nseg = nseg; T.accumulate = 0; T.rowmajor = 0;
           tiles.push_back(T);
-          cost.push_back((double)std::min(tile_rows(c.mb), m - c.i0) * std::min(tile_cols(c.mb), n - c.j0) * ksum);
+          cost.push_back(tile_cost(c.mb, std::min(tile_rows(c.mb), m - c.i0), std::min(tile_cols(c.mb), n - c.j0), nseg, ksum));
         }
       }
   }
@@ -187,19 +187,19 @@ extern "C" int dmrg_truncate(const dmrg_problem_t *prob, int32_t flags, const do
   std::vector<int64_t> &roff = RL.roff;
   std::vector<Tile> &tiles = RL.tiles;
   std::vector<Seg> &segs = RL.segs;
-  const KindLists kinds = sort_by_kind(tiles, RL.cost);
+  const KindLists kinds = sort_by_kind(tiles, RL.cost, segs);
   int maxn = 1;
   for (const TSec &P : prod) maxn = std::max(maxn, P.rows);
   hipStream_t hs = (hipStream_t)stream;
+  const std::vector<Seg> dsegs = resolve_bases(segs, nullptr);   // operands in psi only
   Tile *d_t = nullptr;
   Seg *d_s = nullptr;
   int32_t *d_cnt = nullptr, *d_info = nullptr;
   double *d_rho = nullptr, *d_w = nullptr, *d_e = nullptr;
-  const double **d_bases = nullptr;
   rocblas_handle h = nullptr;
   auto cleanup = [&]() {
     if (h) rocblas_destroy_handle(h);
-    void *ptrs[] = {d_t, d_s, d_cnt, d_info, d_rho, d_w, d_e, (void *)d_bases};
+    void *ptrs[] = {d_t, d_s, d_cnt, d_info, d_rho, d_w, d_e};
     for (void *p : ptrs)
       if (p) (void)hipFree(p);
   };
@@ -215,15 +215,14 @@ extern "C" int dmrg_truncate(const dmrg_problem_t *prob, int32_t flags, const do
             hipMalloc((void **)&d_info, prod.size() * sizeof(int32_t)) == hipSuccess &&
             hipMalloc((void **)&d_rho, std::max<int64_t>(1, roff.back()) * sizeof(double)) == hipSuccess &&
             hipMalloc((void **)&d_w, std::max<int64_t>(1, prod.empty() ? 1 : (int64_t)prod.size() * maxn) * sizeof(double)) == hipSuccess &&
-            hipMalloc((void **)&d_e, (size_t)maxn * sizeof(double)) == hipSuccess &&
-            hipMalloc((void **)&d_bases, 16) == hipSuccess;
+            hipMalloc((void **)&d_e, (size_t)maxn * sizeof(double)) == hipSuccess;
   if (!ok) return fail(DMRG_ENOMEM, "device allocation failed");
   if (hipMemcpyAsync(d_t, tiles.data(), tiles.size() * sizeof(Tile), hipMemcpyHostToDevice, hs) != hipSuccess ||
-      hipMemcpyAsync(d_s, segs.data(), segs.size() * sizeof(Seg), hipMemcpyHostToDevice, hs) != hipSuccess)
+      hipMemcpyAsync(d_s, dsegs.data(), dsegs.size() * sizeof(Seg), hipMemcpyHostToDevice, hs) != hipSuccess)
     return fail(DMRG_EHIP, "copying the density-matrix lists failed");
   QueueSets qs{d_cnt};
   launch_zero(d_rho, roff.back(), qs.cur(), stream);
-  launch_lists_f64(1, d_t, d_s, kinds, qs, d_bases, psi, d_rho, nullptr, nullptr, stream);
+  launch_lists_f64(2, d_t, d_s, kinds, qs, psi, d_rho, nullptr, nullptr, stream);
   if (rocblas_create_handle(&h) != rocblas_status_success || rocblas_set_stream(h, hs) != rocblas_status_success)
     return fail(DMRG_EHIP, "rocBLAS handle");
   for (size_t si = 0; si < prod.size(); si++) {
