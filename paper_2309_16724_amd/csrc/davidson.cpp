@@ -428,7 +428,7 @@ static int solve(dmrg_plan_t *p, double *psi, double *evals, const dmrg_dav_opts
       A.nseg = np;
       A.floor_ = dfloor;
       A.t = tm;
-      launch_mlp_forward(opt.mlp->width, 1, A, stream);
+      launch_mlp_forward(opt.mlp->width, 1, A, FwdSegs{}, stream);
       HIPCHK(hipGetLastError());
       if ((rc = dots_host(tm, 1, tm))) return rc;
       std::vector<double> mm(hout, hout + np);

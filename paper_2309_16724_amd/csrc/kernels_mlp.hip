@@ -3,6 +3,7 @@
 // storage; reductions of the backward pass accumulate in FP64 in a fixed
 // order, so every result is reproducible bit for bit).
 #include <hip/hip_runtime.h>
+#include <algorithm>
 #include <cmath>
 #include "mlp.hpp"
 
@@ -10,7 +11,6 @@ namespace dmrg {
 
 namespace {
 
-constexpr int MR = 64;      // rows per forward block
 constexpr int NT = 256;     // threads per block
 
 struct POff {
@@ -49,7 +49,7 @@ __device__ constexpr int mfma_row(int q, int r) { return 4 * q + r; }
 
 // Features (x0, x1) and, in MODE 1, the diagonal step td of row i.
 template <int MODE>
-__device__ inline void row_inputs(const FwdArgs &A, int64_t i, float &f0, float &f1, double &td) {
+__device__ inline void row_inputs(const FwdArgs &A, const FwdSegs &S, int64_t i, float &f0, float &f1, double &td) {
   f0 = f1 = 0.0f;
   td = 0.0;
   if (i >= A.n) return;
@@ -57,65 +57,112 @@ __device__ inline void row_inputs(const FwdArgs &A, int64_t i, float &f0, float 
     f0 = A.x[i * MLP_IN];
     f1 = A.x[i * MLP_IN + 1];
   } else {
-    const int s = seg_of(A.seg_off, A.nseg, i);
-    const double den = A.d[i] - A.theta[s];
-    td = -A.r[i] / floored(den, A.floor_[s]);
-    f0 = (float)asinh(den / A.sigma[s]);
-    f1 = (float)A.f1[s];
+    double theta, sigma, floor_, feature;
+    if (A.theta) {
+      const int s = seg_of(A.seg_off, A.nseg, i);
+      theta = A.theta[s];
+      sigma = A.sigma[s];
+      floor_ = A.floor_[s];
+      feature = A.f1[s];
+    } else {
+      int s = 0;
+      for (int k = 1; k < A.nseg; k++) s += i >= S.off[k];
+      theta = S.theta[s];
+      sigma = S.sigma[s];
+      floor_ = S.floor_[s];
+      feature = S.f1[s];
+    }
+    const double den = A.d[i] - theta;
+    td = -A.r[i] / floored(den, floor_);
+    f0 = (float)asinh(den / sigma);
+    f1 = (float)feature;
   }
 }
 
-// MODE 0: rows from x[n][2], g out, optional activations z1, z2 (training).
+// pre-activation of layer 1 (the backward pass computes it again)
+__device__ __forceinline__ float layer1(float b1, float w10, float w11, float f0, float f1) {
+  return fmaf(f1, w11, fmaf(f0, w10, b1));
+}
+
+// MODE 0: rows from x[n][2], g out, optional activations z2 (training).
 // MODE 1: rows from Davidson vectors; t[i] = td_i (1 + g_i), td = -r/(d - theta).
-// Each wavefront takes 16 rows.  Layer 1 goes straight into registers: lane
-// l holds relu(z1) of row l % 16 at k = 4j + l / 16, j < W/4 -- exactly the A
-// operand of the K steps of layer 2, which runs on v_mfma_f32_16x16x4f32 over
-// W/16 column blocks with W2 staged through LDS in chunks of 32 rows shared
-// by the work group's four wavefronts.  Layer 3 reduces over the 16 lanes of
-// each output row.
-template <int W, int MODE>
-__global__ void __launch_bounds__(NT) mlp_fwd_kernel(const FwdArgs A) {
-  static_assert(W % 32 == 0 && MR == 64 && NT == 256, "64 rows of 4 wavefronts, W2 chunks of 32 rows");
-  constexpr int NB = W / 16, KS = W / 4, KC = 32;
-  __shared__ float w2c[KC][W];
+//
+// Four wavefronts as 4 / CS row groups of 16 rows and CS column groups of
+// W / CS columns.  Lane l computes layer 1 of row l % 16 at k = 4j + l / 16, the
+// A operand of step j of layer 2, when that step comes (two multiply-adds from
+// W1 and b1 in LDS: kept for all k they took W / 4 registers and three global
+// loads each); layer 2 runs on v_mfma_f32_16x16x4f32 with W2 going through
+// registers into one of two LDS chunks of 16 rows while the chunk before is
+// used (row stride W + 16: the four rows an operand read touches lie in
+// different banks).  Layer 3 reduces over the 16 lanes of each output row, then
+// over the column groups.  Bound: the FP32 matrix rate.  CS = 4 is for few
+// rows: at 4096 rows CS = 1 is 64 work groups on 256 CUs, 110 us; CS = 4 256.
+template <int W, int MODE, int CS>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) mlp_fwd_kernel(const FwdArgs A, const FwdSegs S) {
+  constexpr int NB = W / 16 / CS, KC = 16, LD = W + 16, RG = 4 / CS, ROWS = 16 * RG;
+  static_assert(W % (16 * CS) == 0 && (KC * W / 4) % NT == 0 || W < 64, "whole chunks");
+  __shared__ float w2c[2][KC][LD];
+  __shared__ float l1[3][W];
+  __shared__ float red[4][16];
   const POff o = poff(W);
   const float *__restrict__ p = A.params;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, q = lane >> 4;
-  const int64_t base = (int64_t)blockIdx.x * MR + wave * 16;
-  const int64_t arow = base + l16;
-  float f0, f1;
-  double td_unused;
-  row_inputs<MODE>(A, arow, f0, f1, td_unused);
-  float h[KS];
+  const int rg = wave / CS, cg = wave % CS;
+  const int64_t base = (int64_t)blockIdx.x * ROWS + rg * 16;
+  const int c0 = cg * (W / CS);
+  constexpr int V = KC * W / 4;                    // float4 per chunk
+  constexpr int PER = (V + NT - 1) / NT;
+  v4f pre[PER];
+  auto load = [&](int k0) {
 #pragma unroll
-  for (int j = 0; j < KS; j++) {
-    const int k = 4 * j + q;
-    const float z = p[o.b1 + k] + f0 * p[o.W1 + k] + f1 * p[o.W1 + W + k];
-    if (MODE == 0 && A.z1 && arow < A.n) A.z1[arow * W + k] = z;
-    h[j] = fmaxf(z, 0.0f);
+    for (int e = 0; e < PER; e++) {
+      const int v = tid + e * NT;
+      if (V % NT == 0 || v < V) {
+        const float *s = p + o.W2 + (int64_t)k0 * W + 4 * v;   // W2 starts at a multiple of 4 floats only for
+        pre[e] = (v4f){s[0], s[1], s[2], s[3]};                // 3 W % 4 == 0: four loads, merged when aligned
+      }
+    }
+  };
+  auto store = [&](int b) {
+#pragma unroll
+    for (int e = 0; e < PER; e++) {
+      const int v = tid + e * NT;
+      if (V % NT == 0 || v < V) *(v4f *)&w2c[b][4 * v / W][4 * v % W] = pre[e];
+    }
+  };
+  load(0);
+  for (int e = tid; e < W; e += NT) {
+    l1[0][e] = p[o.b1 + e];
+    l1[1][e] = p[o.W1 + e];
+    l1[2][e] = p[o.W1 + W + e];
   }
+  float f0, f1;
+  double td;
+  row_inputs<MODE>(A, S, base + l16, f0, f1, td);
+  store(0);
   v4f acc[NB];
 #pragma unroll
   for (int bj = 0; bj < NB; bj++) acc[bj] = (v4f){0.f, 0.f, 0.f, 0.f};
-#pragma unroll
   for (int k0 = 0; k0 < W; k0 += KC) {
-    __syncthreads();
-    for (int e = tid; e < KC * W; e += NT) w2c[e / W][e % W] = p[o.W2 + (int64_t)(k0 + e / W) * W + e % W];
-    __syncthreads();
+    const int b = (k0 / KC) & 1;
+    __syncthreads();   // chunk b is in LDS, the other one is free
+    if (k0 + KC < W) load(k0 + KC);
 #pragma unroll
     for (int kk = 0; kk < KC; kk += 4) {
-      const float a = h[(k0 + kk) / 4];
+      const int k = k0 + kk + q;
+      const float a = fmaxf(layer1(l1[0][k], l1[1][k], l1[2][k], f0, f1), 0.0f);
 #pragma unroll
       for (int bj = 0; bj < NB; bj++)
-        acc[bj] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w2c[kk + q][16 * bj + l16], acc[bj], 0, 0, 0);
+        acc[bj] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, w2c[b][kk + q][c0 + 16 * bj + l16], acc[bj], 0, 0, 0);
     }
+    if (k0 + KC < W) store(1 - b);
   }
   // layer 3
   float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int bj = 0; bj < NB; bj++) {
-    const int c = 16 * bj + l16;
+    const int c = c0 + 16 * bj + l16;
     const float bb = p[o.b2 + c], w3 = p[o.w3 + c];
 #pragma unroll
     for (int r = 0; r < 4; r++) {
@@ -128,22 +175,27 @@ __global__ void __launch_bounds__(NT) mlp_fwd_kernel(const FwdArgs A) {
 #pragma unroll
   for (int r = 0; r < 4; r++)
     for (int m = 8; m > 0; m >>= 1) part[r] += __shfl_xor(part[r], m, 16);
-  if (l16 == 0) {
-    const float b3 = p[o.b3];
+  if (CS > 1) {
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+      if (l16 == 0) red[wave][mfma_row(q, r)] = part[r];
+    __syncthreads();
+    if (cg != 0) return;
 #pragma unroll
     for (int r = 0; r < 4; r++) {
-      const int64_t orow = base + mfma_row(q, r);
-      if (orow >= A.n) continue;
-      const float g = part[r] + b3;
-      if (MODE == 0) {
-        A.g[orow] = g;
-      } else {
-        float x0, x1;
-        double td;
-        row_inputs<1>(A, orow, x0, x1, td);
-        A.t[orow] = td * (1.0 + (double)g);
-      }
+      part[r] = 0.0f;
+      for (int c = 0; c < CS; c++) part[r] += red[rg * CS + c][mfma_row(q, r)];
     }
+  }
+  const float b3 = p[o.b3];
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const int64_t orow = base + mfma_row(q, r);
+    const double tdr = MODE == 1 ? __shfl(td, mfma_row(q, r)) : 0.0;   // held by the lane of that row
+    if (l16 != 0 || orow >= A.n) continue;
+    const float g = part[r] + b3;
+    if (MODE == 0) A.g[orow] = g;
+    else A.t[orow] = tdr * (1.0 + (double)g);
   }
 }
 
@@ -168,88 +220,205 @@ __global__ void __launch_bounds__(NT) out_grad_kernel(const float *__restrict__ 
   if (threadIdx.x == 0) lpart[blockIdx.x] = red[0];
 }
 
-// dz2[i][c] = dg_i w3[c] [z2[i][c] > 0]
-__global__ void __launch_bounds__(NT) dz2_kernel(const float *__restrict__ dg, const float *__restrict__ z2,
-                                                 const float *__restrict__ w3, int64_t n, int W,
-                                                 float *__restrict__ dz2) {
-  const int64_t e = (int64_t)blockIdx.x * NT + threadIdx.x;
-  if (e >= n * W) return;
-  const int64_t i = e / W;
-  const int c = (int)(e % W);
-  dz2[e] = z2[e] > 0.0f ? dg[i] * w3[c] : 0.0f;
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// gradient of the layer-2 pre-activation
+__device__ __forceinline__ float dz2_of(float z2, float dg, float w3) { return z2 > 0.0f ? dg * w3 : 0.0f; }
+
+// dz1[i][k] = (sum_j dz2[i][j] W2[k][j]) [z1[i][k] > 0], products and sums in
+// FP64 on the matrix cores (v_mfma_f64_16x16x4: A[l%16][l/16], B[l/16][l%16],
+// D[l/16 + 4r][l%16]).  A wavefront computes 16 rows x CB blocks of 16 columns;
+// lane group l / 16 takes j = 16 s + 4 (l / 16) + e in step e, so that every
+// lane reads four consecutive j of both operands at once.
+template <int W>
+__global__ void __launch_bounds__(NT) dz1_kernel(const float *__restrict__ params, const float *__restrict__ x,
+                                                 const float *__restrict__ dg, const float *__restrict__ z2,
+                                                 int64_t n, float *__restrict__ dz1) {
+  constexpr int CB = W >= 64 ? 4 : W / 16, CG = W / (16 * CB);   // column groups
+  const POff o = poff(W);
+  const float *W2 = params + o.W2, *w3 = params + o.w3;
+  const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
+  const int64_t w = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t i0 = w / CG * 16;
+  const int c0 = (int)(w % CG) * 16 * CB;
+  if (i0 >= n) return;
+  const int64_t row = min(i0 + l16, n - 1);
+  const float dgi = dg[row];
+  v4d acc[CB];
+#pragma unroll
+  for (int b = 0; b < CB; b++) acc[b] = (v4d){0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+  for (int s = 0; s < W; s += 16) {
+    const int j = s + 4 * q;
+    float a[4], bw[CB][4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) a[e] = dz2_of(z2[row * W + j + e], dgi, w3[j + e]);
+#pragma unroll
+    for (int b = 0; b < CB; b++)
+#pragma unroll
+      for (int e = 0; e < 4; e++) bw[b][e] = W2[(int64_t)(c0 + 16 * b + l16) * W + j + e];
+#pragma unroll
+    for (int e = 0; e < 4; e++)
+#pragma unroll
+      for (int b = 0; b < CB; b++)
+        acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64((double)a[e], (double)bw[b][e], acc[b], 0, 0, 0);
+  }
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const int64_t i = i0 + q + 4 * r;
+    if (i >= n) continue;
+    const float f0 = x[i * MLP_IN], f1 = x[i * MLP_IN + 1];
+#pragma unroll
+    for (int b = 0; b < CB; b++) {
+      const int k = c0 + 16 * b + l16;
+      const float z1 = layer1(params[o.b1 + k], params[o.W1 + k], params[o.W1 + W + k], f0, f1);
+      dz1[i * W + k] = z1 > 0.0f ? (float)acc[b][r] : 0.0f;
+    }
+  }
 }
 
-// out[m][j] = sum_i Aop(i, m) Bop(i, j), FP64 accumulation in row order.
-// A == nullptr: Aop = 1.  reluA/reluB: operand taken through relu.
-__global__ void __launch_bounds__(NT) tn_kernel(const float *__restrict__ A, int64_t lda, int reluA,
-                                                const float *__restrict__ B, int64_t ldb, int reluB, int64_t n,
-                                                int M, int N, float *__restrict__ out) {
-  __shared__ float As[32][33], Bs[32][33];
-  const int tid = threadIdx.x, tj = tid & 31, tm = tid >> 5;   // 8 row groups x 32 columns
-  const int m0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int64_t i0 = 0; i0 < n; i0 += 32) {
-    __syncthreads();
-    for (int e = tid; e < 32 * 32; e += NT) {
-      const int ii = e >> 5, cc = e & 31;
-      const int64_t i = i0 + ii;
-      float av = 0.0f, bv = 0.0f;
-      if (i < n) {
-        if (m0 + cc < M) {
-          av = A ? A[i * lda + m0 + cc] : 1.0f;
-          if (reluA) av = fmaxf(av, 0.0f);
-        }
-        if (j0 + cc < N) {
-          bv = B[i * ldb + j0 + cc];
-          if (reluB) bv = fmaxf(bv, 0.0f);
-        }
+// Row splits of the gradient's sums over rows: at most 64 of dW2 (a multiple of
+// 16 rows, at least 256) and 256 of the column sums (at least 64 rows).
+struct Splits {
+  int64_t rows2;
+  int n2;
+  int64_t rowsv;
+  int nv;
+};
+__host__ __device__ inline Splits splits_of(int64_t n) {
+  Splits s;
+  s.rows2 = (n + 63) / 64;
+  s.rows2 = s.rows2 < 256 ? 256 : (s.rows2 + 15) / 16 * 16;
+  s.n2 = (int)((n + s.rows2 - 1) / s.rows2);
+  s.rowsv = (n + 255) / 256;
+  s.rowsv = s.rowsv < 64 ? 64 : s.rowsv;
+  s.nv = (int)((n + s.rowsv - 1) / s.rowsv);
+  return s;
+}
+// partial sums: [n2][W][W] of dW2, then [nv][5 W + 1]: dW1 (2 W), db1, db2, dw3, db3
+
+// Partial sums over row splits, FP64 throughout.  Blocks [0, nb2): dW2 =
+// relu(z1)^T dz2, a 32 x 32 tile of one split per wavefront on the FP64 matrix
+// cores, four K steps (16 rows) loaded at a time; the other blocks: column
+// sums, one thread per column.  With one work group per 32 x 32 tile walking
+// all rows in FP64 vector code this took 6 x 353 us at 4096 rows.
+template <int W>
+__global__ void __launch_bounds__(NT) grad_part_kernel(const float *__restrict__ params, const float *__restrict__ x,
+                                                       const float *__restrict__ dg, const float *__restrict__ z2,
+                                                       const float *__restrict__ dz1, int64_t n, int nb2,
+                                                       double *__restrict__ part) {
+  const POff o = poff(W);
+  const Splits sp = splits_of(n);
+  if ((int)blockIdx.x < nb2) {
+    constexpr int T = W / 32;
+    const int lane = threadIdx.x & 63, l16 = lane & 15, q = lane >> 4;
+    const int w = (int)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (w >= sp.n2 * T * T) return;
+    const int split = w / (T * T), m0 = w / T % T * 32, j0 = w % T * 32;
+    const int64_t r0 = split * sp.rows2, r1 = min(n, r0 + sp.rows2);
+    float b1[2], w10[2], w11[2], w3[2];
+#pragma unroll
+    for (int b = 0; b < 2; b++) {
+      const int m = m0 + 16 * b + l16;
+      b1[b] = params[o.b1 + m];
+      w10[b] = params[o.W1 + m];
+      w11[b] = params[o.W1 + W + m];
+      w3[b] = params[o.w3 + j0 + 16 * b + l16];
+    }
+    v4d acc[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; a++)
+#pragma unroll
+      for (int b = 0; b < 2; b++) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
+    float f0[4], f1[4], d[4], z[4][2];
+    auto load = [&](int64_t i0) {   // rows past the end read the last one and count as zero (dg)
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        const int64_t i = i0 + 4 * e + q, ic = min(i, r1 - 1);
+        f0[e] = x[ic * MLP_IN];
+        f1[e] = x[ic * MLP_IN + 1];
+        d[e] = i < r1 ? dg[ic] : 0.0f;
+#pragma unroll
+        for (int b = 0; b < 2; b++) z[e][b] = z2[ic * W + j0 + 16 * b + l16];
       }
-      As[ii][cc] = av;
-      Bs[ii][cc] = bv;
-    }
-    __syncthreads();
-    for (int ii = 0; ii < 32; ii++) {
-      const double bv = Bs[ii][tj];
+    };
+    load(r0);
+    for (int64_t i0 = r0; i0 < r1; i0 += 16) {
+      double av[4][2], bv[4][2];
 #pragma unroll
-      for (int q = 0; q < 4; q++) acc[q] += (double)As[ii][tm + 8 * q] * bv;
+      for (int e = 0; e < 4; e++)
+#pragma unroll
+        for (int b = 0; b < 2; b++) {
+          av[e][b] = (double)fmaxf(layer1(b1[b], w10[b], w11[b], f0[e], f1[e]), 0.0f);
+          bv[e][b] = (double)dz2_of(z[e][b], d[e], w3[b]);
+        }
+      load(min(i0 + 16, r1 - 1));
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+#pragma unroll
+        for (int a = 0; a < 2; a++)
+#pragma unroll
+          for (int b = 0; b < 2; b++)
+            acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av[e][a], bv[e][b], acc[a][b], 0, 0, 0);
     }
+    double *out = part + (int64_t)split * W * W;
+#pragma unroll
+    for (int a = 0; a < 2; a++)
+#pragma unroll
+      for (int b = 0; b < 2; b++)
+#pragma unroll
+        for (int r = 0; r < 4; r++)
+          out[(int64_t)(m0 + 16 * a + q + 4 * r) * W + j0 + 16 * b + l16] = acc[a][b][r];
+    return;
   }
-#pragma unroll
-  for (int q = 0; q < 4; q++) {
-    const int m = m0 + tm + 8 * q, j = j0 + tj;
-    if (m < M && j < N) out[(int64_t)m * N + j] = (float)acc[q];
+  const int split = (int)blockIdx.x - nb2;
+  const int64_t r0 = split * sp.rowsv, r1 = min(n, r0 + sp.rowsv);
+  double *out = part + (int64_t)sp.n2 * W * W + (int64_t)split * (5 * W + 1);
+  for (int c = threadIdx.x; c < W; c += NT) {
+    const float w3 = params[o.w3 + c];
+    double s0 = 0.0, s1 = 0.0, sb1 = 0.0, sb2 = 0.0, sw3 = 0.0, sb3 = 0.0;
+#pragma unroll 8
+    for (int64_t i = r0; i < r1; i++) {
+      const float d = dg[i], z = z2[i * W + c], e = dz1[i * W + c];
+      s0 += (double)x[i * MLP_IN] * (double)e;
+      s1 += (double)x[i * MLP_IN + 1] * (double)e;
+      sb1 += (double)e;
+      sb2 += (double)dz2_of(z, d, w3);
+      sw3 += (double)d * (double)fmaxf(z, 0.0f);
+      sb3 += (double)d;
+    }
+    out[c] = s0;
+    out[W + c] = s1;
+    out[2 * W + c] = sb1;
+    out[3 * W + c] = sb2;
+    out[4 * W + c] = sw3;
+    if (c == 0) out[5 * W] = sb3;
   }
 }
 
-// dz1[i][k] = (sum_j dz2[i][j] W2[k][j]) [z1[i][k] > 0], FP64 accumulation
-__global__ void __launch_bounds__(NT) nt_mask_kernel(const float *__restrict__ dz2, const float *__restrict__ W2,
-                                                     const float *__restrict__ z1, int64_t n, int W,
-                                                     float *__restrict__ dz1) {
-  __shared__ float As[32][33], Bs[32][33];
-  const int tid = threadIdx.x, tk = tid & 31, ti = tid >> 5;
-  const int64_t i0 = (int64_t)blockIdx.y * 32;
-  const int k0 = blockIdx.x * 32;
-  double acc[4] = {0.0, 0.0, 0.0, 0.0};
-  for (int j0 = 0; j0 < W; j0 += 32) {
-    __syncthreads();
-    for (int e = tid; e < 32 * 32; e += NT) {
-      const int rr = e >> 5, cc = e & 31;
-      As[rr][cc] = (i0 + rr < n) ? dz2[(i0 + rr) * W + j0 + cc] : 0.0f;
-      Bs[rr][cc] = W2[(int64_t)(k0 + rr) * W + j0 + cc];
-    }
-    __syncthreads();
-    for (int jj = 0; jj < 32; jj++) {
-      const double bv = Bs[tk][jj];
-#pragma unroll
-      for (int q = 0; q < 4; q++) acc[q] += (double)As[ti + 8 * q][jj] * bv;
-    }
+// gradient = sum of the partial sums in split order
+template <int W>
+__global__ void __launch_bounds__(NT) grad_sum_kernel(const double *__restrict__ part, int64_t n,
+                                                      float *__restrict__ grad) {
+  const POff o = poff(W);
+  const Splits sp = splits_of(n);
+  const int e = blockIdx.x * NT + threadIdx.x;
+  if (e < W * W) {
+    double s = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < sp.n2; k++) s += part[(int64_t)k * W * W + e];
+    grad[o.W2 + e] = (float)s;
+    return;
   }
-#pragma unroll
-  for (int q = 0; q < 4; q++) {
-    const int64_t i = i0 + ti + 8 * q;
-    const int k = k0 + tk;
-    if (i < n) dz1[i * W + k] = z1[i * W + k] > 0.0f ? (float)acc[q] : 0.0f;
-  }
+  const int v = e - W * W;
+  if (v > 5 * W) return;
+  const double *pv = part + (int64_t)sp.n2 * W * W + v;
+  double s = 0.0;
+#pragma unroll 8
+  for (int k = 0; k < sp.nv; k++) s += pv[(int64_t)k * (5 * W + 1)];
+  const int64_t at = v < 2 * W ? o.W1 + v : v < 3 * W ? o.b1 + v - 2 * W : v < 4 * W ? o.b2 + v - 3 * W
+                   : v < 5 * W ? o.w3 + v - 4 * W : o.b3;
+  grad[at] = (float)s;
 }
 
 // p -= lr mhat / (sqrt(vhat) + eps), mhat = m c1, vhat = v c2
@@ -319,37 +488,49 @@ inline dim3 grid1(int64_t n) { return dim3((unsigned)((n + NT - 1) / NT)); }
 
 bool mlp_width_ok(int W) { return W == 32 || W == 64 || W == 128 || W == 256; }
 
-void launch_mlp_forward(int W, int mode, const FwdArgs &A, void *stream) {
-  const dim3 grid((unsigned)((A.n + MR - 1) / MR));
+void launch_mlp_forward(int W, int mode, const FwdArgs &A, const FwdSegs &S, void *stream) {
   hipStream_t s = (hipStream_t)stream;
-#define FWD(w)                                                                                   \
-  case w:                                                                                        \
-    if (mode == 0) hipLaunchKernelGGL((mlp_fwd_kernel<w, 0>), grid, dim3(NT), 0, s, A);          \
-    else hipLaunchKernelGGL((mlp_fwd_kernel<w, 1>), grid, dim3(NT), 0, s, A);                    \
-    break;
-  switch (W) { FWD(32) FWD(64) FWD(128) FWD(256) default: break; }
+  // column groups where 64-row work groups would not give every CU two
+  const bool few = W >= 64 && A.n <= 64 * 512;
+  const dim3 grid((unsigned)(few ? (A.n + 15) / 16 : (A.n + 63) / 64));
+#define FWD(w, cs)                                                                                     \
+  {                                                                                                    \
+    if (mode == 0) hipLaunchKernelGGL((mlp_fwd_kernel<w, 0, cs>), grid, dim3(NT), 0, s, A, S);         \
+    else hipLaunchKernelGGL((mlp_fwd_kernel<w, 1, cs>), grid, dim3(NT), 0, s, A, S);                   \
+  }
+  switch (W) {
+    case 32: FWD(32, 1) break;
+    case 64: if (few) FWD(64, 4) else FWD(64, 1) break;
+    case 128: if (few) FWD(128, 4) else FWD(128, 1) break;
+    case 256: if (few) FWD(256, 4) else FWD(256, 1) break;
+    default: break;
+  }
 #undef FWD
 }
 
-void launch_mlp_backward(int W, const float *params, const float *x, const float *a, const float *b,
-                         int64_t n, const float *g, const float *z1, const float *z2, float *dg, float *dz2,
-                         float *dz1, double *lpart, float *grad, void *stream) {
+int64_t mlp_part_elems(int W, int64_t n) {
+  // splits_of grows with n up to its limits (64 and 256)
+  const int64_t n2 = std::min<int64_t>(64, (n + 255) / 256), nv = std::min<int64_t>(256, (n + 63) / 64);
+  return n2 * W * W + nv * (5 * W + 1);
+}
+
+void launch_mlp_backward(int W, const float *params, const float *x, const float *a, const float *b, int64_t n,
+                         const float *g, const float *z2, float *dg, float *dz1, double *lpart, double *part,
+                         float *grad, void *stream) {
   hipStream_t s = (hipStream_t)stream;
-  const POff o = poff(W);
+  const Splits sp = splits_of(n);
   hipLaunchKernelGGL(out_grad_kernel, grid1(n), dim3(NT), 0, s, g, a, b, n, dg, lpart);
-  hipLaunchKernelGGL(dz2_kernel, grid1(n * W), dim3(NT), 0, s, dg, z2, params + o.w3, n, W, dz2);
-  auto tn = [&](const float *A_, int64_t lda, int rA, const float *B_, int64_t ldb, int rB, int M, int N, float *out) {
-    dim3 grid((unsigned)((N + 31) / 32), (unsigned)((M + 31) / 32));
-    hipLaunchKernelGGL(tn_kernel, grid, dim3(NT), 0, s, A_, lda, rA, B_, ldb, rB, n, M, N, out);
-  };
-  tn(z1, W, 1, dz2, W, 0, W, W, grad + o.W2);          // dW2 = relu(z1)^T dz2
-  tn(nullptr, 0, 0, dz2, W, 0, 1, W, grad + o.b2);     // db2
-  tn(dg, 1, 0, z2, W, 1, 1, W, grad + o.w3);           // dw3 = dg^T relu(z2)
-  tn(nullptr, 0, 0, dg, 1, 0, 1, 1, grad + o.b3);      // db3
-  dim3 gnt((unsigned)(W / 32), (unsigned)((n + 31) / 32));
-  hipLaunchKernelGGL(nt_mask_kernel, gnt, dim3(NT), 0, s, dz2, params + o.W2, z1, n, W, dz1);
-  tn(x, MLP_IN, 0, dz1, W, 0, MLP_IN, W, grad + o.W1); // dW1 = x^T dz1
-  tn(nullptr, 0, 0, dz1, W, 0, 1, W, grad + o.b1);     // db1
+  const int t = W / 32, nb2 = (sp.n2 * t * t + 3) / 4;
+  const int64_t waves1 = (n + 15) / 16 * (W >= 64 ? W / 64 : 1);
+#define BWD(w)                                                                                             \
+  case w:                                                                                                  \
+    hipLaunchKernelGGL(dz1_kernel<w>, dim3((unsigned)((waves1 + 3) / 4)), dim3(NT), 0, s, params, x, dg, z2, n, dz1); \
+    hipLaunchKernelGGL(grad_part_kernel<w>, dim3((unsigned)(nb2 + sp.nv)), dim3(NT), 0, s, params, x, dg, z2, dz1, n, \
+                       nb2, part);                                                                         \
+    hipLaunchKernelGGL(grad_sum_kernel<w>, dim3((w * w + 5 * w + 1 + NT - 1) / NT), dim3(NT), 0, s, part, n, grad);   \
+    break;
+  switch (W) { BWD(32) BWD(64) BWD(128) BWD(256) default: break; }
+#undef BWD
 }
 
 void launch_adam(float *p, float *m, float *v, const float *gr, int64_t n, float lr, float b1, float b2, float eps,

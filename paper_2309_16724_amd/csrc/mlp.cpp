@@ -35,11 +35,11 @@ int dev_alloc(T **p, int64_t n) {
 }
 
 void release_scratch(dmrg_mlp *m) {
-  for (void *q : {(void *)m->xb, (void *)m->ab, (void *)m->bb, (void *)m->g, (void *)m->dg, (void *)m->z1,
-                  (void *)m->z2, (void *)m->dz2, (void *)m->dz1, (void *)m->lpart})
+  for (void *q : {(void *)m->xb, (void *)m->ab, (void *)m->bb, (void *)m->g, (void *)m->dg, (void *)m->z2,
+                  (void *)m->dz1, (void *)m->lpart, (void *)m->part})
     if (q) (void)hipFree(q);
-  m->xb = m->ab = m->bb = m->g = m->dg = m->z1 = m->z2 = m->dz2 = m->dz1 = nullptr;
-  m->lpart = nullptr;
+  m->xb = m->ab = m->bb = m->g = m->dg = m->z2 = m->dz1 = nullptr;
+  m->lpart = m->part = nullptr;
   m->cap = 0;
 }
 
@@ -49,9 +49,9 @@ int ensure_scratch(dmrg_mlp *m, int64_t rows) {
   const int64_t W = m->width;
   int rc;
   if ((rc = dev_alloc(&m->xb, rows * MLP_IN)) || (rc = dev_alloc(&m->ab, rows)) || (rc = dev_alloc(&m->bb, rows)) ||
-      (rc = dev_alloc(&m->g, rows)) || (rc = dev_alloc(&m->dg, rows)) || (rc = dev_alloc(&m->z1, rows * W)) ||
-      (rc = dev_alloc(&m->z2, rows * W)) || (rc = dev_alloc(&m->dz2, rows * W)) || (rc = dev_alloc(&m->dz1, rows * W)) ||
-      (rc = dev_alloc(&m->lpart, (rows + 255) / 256))) {
+      (rc = dev_alloc(&m->g, rows)) || (rc = dev_alloc(&m->dg, rows)) || (rc = dev_alloc(&m->z2, rows * W)) ||
+      (rc = dev_alloc(&m->dz1, rows * W)) || (rc = dev_alloc(&m->lpart, (rows + 255) / 256)) ||
+      (rc = dev_alloc(&m->part, mlp_part_elems((int)W, rows)))) {
     release_scratch(m);
     return rc;
   }
@@ -67,11 +67,9 @@ int loss_grad_rows(dmrg_mlp *m, const float *x, const float *a, const float *b, 
   A.n = n;
   A.x = x;
   A.g = m->g;
-  A.z1 = m->z1;
   A.z2 = m->z2;
-  launch_mlp_forward(m->width, 0, A, stream);
-  launch_mlp_backward(m->width, m->p, x, a, b, n, m->g, m->z1, m->z2, m->dg, m->dz2, m->dz1, m->lpart, m->grad,
-                      stream);
+  launch_mlp_forward(m->width, 0, A, FwdSegs{}, stream);
+  launch_mlp_backward(m->width, m->p, x, a, b, n, m->g, m->z2, m->dg, m->dz1, m->lpart, m->part, m->grad, stream);
   HIPCHK(hipGetLastError());
   return DMRG_OK;
 }
@@ -172,7 +170,7 @@ extern "C" int dmrg_mlp_forward(dmrg_mlp_t *m, const float *x, int64_t n, float 
   A.n = n;
   A.x = x;
   A.g = g;
-  launch_mlp_forward(m->width, 0, A, stream);
+  launch_mlp_forward(m->width, 0, A, FwdSegs{}, stream);
   HIPCHK(hipGetLastError());
   return mark_done(m, stream);
 }
@@ -192,7 +190,32 @@ extern "C" int dmrg_mlp_step(const dmrg_mlp_t *m, const double *diag, const doub
     }
   const int64_t n = seg_off[nseg];
   if (n == 0) return DMRG_OK;
-  // per-segment inputs of the fused kernel: theta, sigma, feature f1, absolute floor, offsets
+  hipStream_t s = (hipStream_t)stream;
+  FwdArgs A{};
+  A.params = m->p;
+  A.n = n;
+  A.d = diag;
+  A.r = r;
+  A.nseg = nseg;
+  A.t = t;
+  if (nseg <= MLP_SEGS) {
+    FwdSegs S{};
+    for (int k = 0; k < nseg; k++) {
+      S.off[k] = seg_off[k];
+      S.theta[k] = theta[k];
+      S.sigma[k] = sigma[k];
+      S.f1[k] = std::log10(rnorm[k]) / 8.0;
+      S.floor_[k] = floor * sigma[k];
+    }
+    S.off[nseg] = n;
+    launch_mlp_forward(m->width, 1, A, S, stream);
+    if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
+      set_error("learned-step kernel failed");
+      return DMRG_EHIP;
+    }
+    return DMRG_OK;
+  }
+  // more segments: theta, sigma, feature f1, absolute floor, offsets on the device
   std::vector<double> h((size_t)4 * nseg);
   for (int k = 0; k < nseg; k++) {
     h[k] = theta[k];
@@ -207,26 +230,18 @@ extern "C" int dmrg_mlp_step(const dmrg_mlp_t *m, const double *diag, const doub
   }
   double *dh = (double *)d;
   int64_t *doff = (int64_t *)(dh + h.size());
-  hipStream_t s = (hipStream_t)stream;
   int rc = DMRG_OK;
   if (hipMemcpyAsync(dh, h.data(), sizeof(double) * h.size(), hipMemcpyHostToDevice, s) != hipSuccess ||
       hipMemcpyAsync(doff, seg_off, sizeof(int64_t) * (nseg + 1), hipMemcpyHostToDevice, s) != hipSuccess) {
     set_error("copy failed in dmrg_mlp_step");
     rc = DMRG_EHIP;
   } else {
-    FwdArgs A{};
-    A.params = m->p;
-    A.n = n;
-    A.d = diag;
-    A.r = r;
     A.theta = dh;
     A.sigma = dh + nseg;
     A.f1 = dh + 2 * nseg;
     A.floor_ = dh + 3 * nseg;
     A.seg_off = doff;
-    A.nseg = nseg;
-    A.t = t;
-    launch_mlp_forward(m->width, 1, A, stream);
+    launch_mlp_forward(m->width, 1, A, FwdSegs{}, stream);
     if (hipGetLastError() != hipSuccess || hipStreamSynchronize(s) != hipSuccess) {
       set_error("learned-step kernel failed");
       rc = DMRG_EHIP;

@@ -15,7 +15,7 @@ struct FwdArgs {
   // mode 0
   const float *x;
   float *g;
-  float *z1, *z2;          // optional pre-activations [n][W]
+  float *z2;               // optional pre-activations of layer 2 [n][W]
   // mode 1 (Davidson): per-segment theta, sigma, f1 and absolute floor
   const double *d, *r;
   const double *theta, *sigma, *f1, *floor_;
@@ -23,12 +23,21 @@ struct FwdArgs {
   int nseg;
   double *t;
 };
+// the same per-segment inputs of mode 1 as kernel arguments (theta of FwdArgs
+// NULL): calls with few segments need no device copy of them
+constexpr int MLP_SEGS = 8;
+struct FwdSegs {
+  int64_t off[MLP_SEGS + 1];
+  double theta[MLP_SEGS], sigma[MLP_SEGS], f1[MLP_SEGS], floor_[MLP_SEGS];
+};
 
 bool mlp_width_ok(int W);
-void launch_mlp_forward(int W, int mode, const FwdArgs &A, void *stream);
+void launch_mlp_forward(int W, int mode, const FwdArgs &A, const FwdSegs &S, void *stream);
+// doubles of the backward pass's partial sums for up to n rows
+int64_t mlp_part_elems(int W, int64_t n);
 void launch_mlp_backward(int W, const float *params, const float *x, const float *a, const float *b, int64_t n,
-                         const float *g, const float *z1, const float *z2, float *dg, float *dz2, float *dz1,
-                         double *lpart, float *grad, void *stream);
+                         const float *g, const float *z2, float *dg, float *dz1, double *lpart, double *part,
+                         float *grad, void *stream);
 void launch_adam(float *p, float *m, float *v, const float *gr, int64_t n, float lr, float b1, float b2, float eps,
                  float c1, float c2, void *stream);
 void launch_gather(const float *x, const float *a, const float *b, int64_t n, uint64_t seed, uint64_t step, int batch,
@@ -48,8 +57,8 @@ struct dmrg_mlp {
   // training scratch, sized for `cap` rows
   int64_t cap = 0;
   float *xb = nullptr, *ab = nullptr, *bb = nullptr, *g = nullptr, *dg = nullptr;
-  float *z1 = nullptr, *z2 = nullptr, *dz2 = nullptr, *dz1 = nullptr;
-  double *lpart = nullptr;
+  float *z2 = nullptr, *dz1 = nullptr;
+  double *lpart = nullptr, *part = nullptr;   // partial sums of the loss and of the gradient
   // completion of the last launch sequence of the entry points that return
   // before their work is done (forward, step, adam_step): reading or freeing
   // the parameters waits for it instead of for the whole device
