@@ -36,119 +36,114 @@ __device__ constexpr float digit_weight(int t) {
                                                                                         : t == 5 ? 0x1p-40f : 0x1p-48f;
 }
 
-__global__ void __launch_bounds__(256) slice_kernel(const SliceJob *__restrict__ jobs, int njobs, int ns,
-                                                     const double *const *__restrict__ bases,
-                                                     const double *__restrict__ psi,
-                                                     const double *__restrict__ work, SliceBufs bufs) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  for (int jb = blockIdx.x; jb < njobs; jb += gridDim.x) {
-    const SliceJob J = jobs[jb];
-    const double *src = sbase_ptr(J.src_base, bases, psi, nullptr, work, nullptr) + J.src_off;
-    int32_t *exps = bufs.exps[J.dst_buf] + J.exp_off;
-    // line lengths fit in 32 bits (checked when the plan is built): the
-    // (position, offset) split of an index is a 32-bit division
-    const int len = J.npos * J.kbp;
-    const int nval = J.npos * J.kb;
-    const unsigned kb = (unsigned)J.kb, kbp = (unsigned)J.kbp;
-    for (int rho = wave; rho < J.nrho; rho += 4) {
-      const double *line = src + (int64_t)rho * J.s_rho;
-      // four independent loads in flight per lane
-      double m0 = 0.0, m1 = 0.0, m2 = 0.0, m3 = 0.0;
-      auto val = [&](int idx) {
-        const unsigned p = (unsigned)idx / kb, kk = (unsigned)idx - p * kb;
-        return fabs(line[(int64_t)p * J.s_pos + (int64_t)kk * J.s_k]);
-      };
-      int idx = lane;
-      for (; idx + 192 < nval; idx += 256) {
-        const double v0 = val(idx), v1 = val(idx + 64), v2 = val(idx + 128), v3 = val(idx + 192);
-        m0 = fmax(m0, v0);
-        m1 = fmax(m1, v1);
-        m2 = fmax(m2, v2);
-        m3 = fmax(m3, v3);
-      }
-      for (; idx < nval; idx += 64) m0 = fmax(m0, val(idx));
-      double m = fmax(fmax(m0, m1), fmax(m2, m3));
-      for (int off = 32; off > 0; off >>= 1) m = fmax(m, __shfl_xor(m, off));
-      int e = 0;
-      if (m > 0.0) {
-        int ex;
-        double mant = frexp(m, &ex);          // m = mant 2^ex, mant in [0.5, 1)
-        e = (mant == 0.5) ? ex - 1 : ex;      // smallest e with m <= 2^e
-      }
-      if (lane == 0) exps[rho] = e;
-      // the line starts at a multiple of 8: its slices start at ns times that
-      uint16_t *out = bufs.data[J.dst_buf] + (J.dst_off + (int64_t)rho * len) * ns;
-      auto slice_out = [&](int idx, double x) {
-        double yv = ldexp(x, -e);
-        for (int t = 0; t < ns; t++) {
-          double a = rint(yv * 256.0);
-          yv = yv * 256.0 - a;
-          const float af = (float)a * digit_weight(t);   // |a| <= 256 at weight 2^(-8t): exact in BF16
-          out[slice_index(idx, t, ns)] = (uint16_t)(__float_as_uint(af) >> 16);
-        }
-      };
-      auto raw = [&](int idx) {
-        const unsigned p = (unsigned)idx / kbp, kk = (unsigned)idx - p * kbp;
-        return kk < kb ? line[(int64_t)p * J.s_pos + (int64_t)kk * J.s_k] : 0.0;
-      };
-      int i2 = lane;
-      for (; i2 + 192 < len; i2 += 256) {
-        const double x0 = raw(i2), x1 = raw(i2 + 64), x2 = raw(i2 + 128), x3 = raw(i2 + 192);
-        slice_out(i2, x0);
-        slice_out(i2 + 64, x1);
-        slice_out(i2 + 128, x2);
-        slice_out(i2 + 192, x3);
-      }
-      for (; i2 < len; i2 += 64) slice_out(i2, raw(i2));
+// slices of the eight values at K index kk of one line (position block already
+// in `line`), scaled by 2^-e, to out + t hs: padding reads a valid entry and
+// slices zero
+__device__ __forceinline__ void slice_chunk(const double *__restrict__ line, int kk, int kb, int64_t s_k, int e, int ns,
+                                            uint16_t *__restrict__ out, int hs) {
+  typedef unsigned int v4u __attribute__((ext_vector_type(4)));
+  double yv[8];
+#pragma unroll
+  for (int i = 0; i < 8; i++) yv[i] = line[(int64_t)min(kk + i, kb - 1) * s_k];
+#pragma unroll
+  for (int i = 0; i < 8; i++) yv[i] = ldexp(kk + i < kb ? yv[i] : 0.0, -e);
+  for (int t = 0; t < ns; t++) {
+    uint32_t w[8];
+#pragma unroll
+    for (int i = 0; i < 8; i++) {
+      const double a = rint(yv[i] * 256.0);
+      yv[i] = yv[i] * 256.0 - a;
+      w[i] = __float_as_uint((float)a * digit_weight(t)) >> 16;   // |a| <= 256 at weight 2^(-8t): exact in BF16
     }
+    *(v4u *)(out + t * hs) = (v4u){w[0] | w[1] << 16, w[2] | w[3] << 16, w[4] | w[5] << 16, w[6] | w[7] << 16};
   }
 }
 
-// stripe slices, one work group per chunk of TSLICE_CHUNK elements, four
-// consecutive elements per thread.  Line lengths, position blocks (kbp), job
-// offsets and chunk starts are multiples of 8, so a group of four never
-// straddles a line, a position block or a chunk of 8, and the slices of a
-// work group's elements are one contiguous range of the slice buffer: they
-// are assembled in LDS and written out in whole 16-byte pieces.
-static_assert(TSLICE_CHUNK == 4 * 256, "one chunk is 256 threads x 4 elements");
-__global__ void __launch_bounds__(256) tslice_kernel(const SliceJob *__restrict__ jobs,
-                                                      const TSliceItem *__restrict__ items, int nitems, int ns,
-                                                      const double *__restrict__ work, SliceBufs bufs) {
-  __shared__ __attribute__((aligned(16))) uint16_t out[TSLICE_CHUNK * 7];
+// One work group per panel (slice_kernel: the line maxima first, then the
+// slices) or per K range of a panel (tslice_kernel: exponents in place):
+// thread (l, g) takes the chunks g, g + 8, ... of line l.  The 32 lines of a
+// panel are neighbours in memory for all sources but the transposed ones, and
+// their slices of one chunk are a run of 512 bytes, so neither the loads nor
+// the stores pass through LDS.
+struct PanelLine {
+  int h, l;              // lines of the panel, this thread's line in it
+  int64_t L;             // its line of the job
+  const double *line;    // its values
+  int64_t out;           // element of its first slice chunk
+};
+__device__ __forceinline__ PanelLine panel_line(const SliceJob &J, int panel, const double *src, int ns) {
+  PanelLine p;
+  p.h = min(SLICE_PANEL, J.nl - SLICE_PANEL * panel);
+  p.l = min((int)threadIdx.x & (SLICE_PANEL - 1), p.h - 1);
+  p.L = SLICE_PANEL * panel + p.l;
+  const unsigned q = (unsigned)p.L / (unsigned)J.nrho, rho = (unsigned)p.L - q * (unsigned)J.nrho;
+  p.line = src + J.src_off + (int64_t)q * J.s_q + (int64_t)rho * J.s_rho;
+  p.out = (J.dst_off + (int64_t)SLICE_PANEL * panel * J.npos * J.kbp) * ns + 8 * p.l;
+  return p;
+}
+
+__global__ void __launch_bounds__(256) slice_kernel(const SliceJob *__restrict__ jobs,
+                                                     const SliceItem *__restrict__ items, int nitems, int ns,
+                                                     const double *const *__restrict__ bases,
+                                                     const double *__restrict__ psi,
+                                                     const double *__restrict__ work, SliceBufs bufs) {
+  __shared__ double mx[256 / SLICE_PANEL][SLICE_PANEL];
+  const int g = threadIdx.x / SLICE_PANEL, l0 = threadIdx.x % SLICE_PANEL;
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
-    const TSliceItem I = items[it];
+    const SliceItem I = items[it];
     const SliceJob J = jobs[I.job];
-    const unsigned kb = (unsigned)J.kb, kbp = (unsigned)J.kbp, len = (unsigned)(J.npos * J.kbp);
-    const unsigned tot = len * (unsigned)J.nrho;
-    const unsigned n = min((unsigned)TSLICE_CHUNK, tot - (unsigned)I.e0);   // a multiple of 8
-    const unsigned el = 4u * threadIdx.x, e = (unsigned)I.e0 + el;
-    if (el < n) {
-      const unsigned rho = e / len, idx = e - rho * len;
-      const unsigned p = idx / kbp, kk = idx - p * kbp;
-      const double *line = work + J.src_off + (int64_t)rho * J.s_rho + (int64_t)p * J.s_pos;
-      const int ex = bufs.exps[SBUF_T][J.exp_off + rho];
-      double yv[4];
-      for (int i = 0; i < 4; i++) {
-        const unsigned k = kk + i;
-        const double x = line[(int64_t)min(k, kb - 1) * J.s_k];    // padding reads a valid entry ...
-        yv[i] = ldexp(k < kb ? x : 0.0, ex == INT_MIN ? 0 : -ex);  // ... and slices zero
-      }
-      for (int t = 0; t < ns; t++) {
-        uint64_t packed = 0;
-        for (int i = 0; i < 4; i++) {
-          const double a = rint(yv[i] * 256.0);
-          yv[i] = yv[i] * 256.0 - a;
-          const float af = (float)a * digit_weight(t);   // exact in BF16 (see slice_kernel)
-          packed |= (uint64_t)(__float_as_uint(af) >> 16) << (16 * i);
-        }
-        *(uint64_t *)(out + slice_index(el, t, ns)) = packed;
+    const double *src = sbase_ptr(J.src_base, bases, psi, nullptr, work, nullptr);
+    const PanelLine P = panel_line(J, I.panel, src, ns);
+    // line lengths fit in 31 bits (checked when the plan is built)
+    const int nch = J.npos * (J.kbp / 8), pch = J.kbp / 8;
+    double m = 0.0;
+    for (int c = g; c < nch; c += 256 / SLICE_PANEL) {
+      const int p = c / pch, kk = 8 * (c - p * pch);
+      const double *line = P.line + (int64_t)p * J.s_pos;
+      double v[8];
+#pragma unroll
+      for (int i = 0; i < 8; i++) v[i] = line[(int64_t)min(kk + i, J.kb - 1) * J.s_k];
+#pragma unroll
+      for (int i = 0; i < 8; i++) m = fmax(m, fabs(v[i]));
+    }
+    mx[g][l0] = m;
+    __syncthreads();
+    for (int i = 0; i < 256 / SLICE_PANEL; i++) m = fmax(m, mx[i][l0]);
+    int e = 0;
+    if (m > 0.0) {
+      int ex;
+      const double mant = frexp(m, &ex);    // m = mant 2^ex, mant in [0.5, 1)
+      e = (mant == 0.5) ? ex - 1 : ex;      // smallest e with m <= 2^e
+    }
+    if (l0 < P.h) {
+      if (g == 0) bufs.exps[J.dst_buf][J.exp_off + P.L] = e;
+      uint16_t *out = bufs.data[J.dst_buf] + P.out;
+      for (int c = g; c < nch; c += 256 / SLICE_PANEL) {
+        const int p = c / pch, kk = 8 * (c - p * pch);
+        slice_chunk(P.line + (int64_t)p * J.s_pos, kk, J.kb, J.s_k, e, ns, out + (int64_t)c * (8 * ns * P.h), 8 * P.h);
       }
     }
-    __syncthreads();
-    typedef unsigned int v4u __attribute__((ext_vector_type(4)));
-    v4u *dst = (v4u *)(bufs.data[SBUF_T] + slice_index(J.dst_off + I.e0, 0, ns));
-    for (unsigned u = threadIdx.x; u < n * ns / 8; u += blockDim.x) dst[u] = ((const v4u *)out)[u];
-    __syncthreads();   // out is reused by the next chunk
+    __syncthreads();   // mx is reused by the next panel
+  }
+}
+
+__global__ void __launch_bounds__(256) tslice_kernel(const SliceJob *__restrict__ jobs,
+                                                      const SliceItem *__restrict__ items, int nitems, int ns,
+                                                      const double *__restrict__ work, SliceBufs bufs) {
+  const int g = threadIdx.x / SLICE_PANEL, l0 = threadIdx.x % SLICE_PANEL;
+  for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
+    const SliceItem I = items[it];
+    const SliceJob J = jobs[I.job];
+    const PanelLine P = panel_line(J, I.panel, work, ns);
+    if (l0 >= P.h) continue;
+    const int e = bufs.exps[SBUF_T][J.exp_off + P.L];
+    const int pch = J.kbp / 8, c1 = min(J.npos * pch, (I.k0 + I.nk) * (SLICE_KBLOCK / 8));
+    uint16_t *out = bufs.data[SBUF_T] + P.out;
+    for (int c = I.k0 * (SLICE_KBLOCK / 8) + g; c < c1; c += 256 / SLICE_PANEL) {
+      const int p = c / pch, kk = 8 * (c - p * pch);
+      slice_chunk(P.line + (int64_t)p * J.s_pos, kk, J.kb, J.s_k, e == INT_MIN ? 0 : e, ns,
+                  out + (int64_t)c * (8 * ns * P.h), 8 * P.h);
+    }
   }
 }
 
@@ -157,7 +152,7 @@ __global__ void fill_int_kernel(int32_t *__restrict__ p, int64_t n, int32_t v) {
     p[i] = v;
 }
 
-void launch_tslices(const SliceJob *jobs, const TSliceItem *items, int nitems, int nslices, const double *work,
+void launch_tslices(const SliceJob *jobs, const SliceItem *items, int nitems, int nslices, const double *work,
                     SliceBufs bufs, void *stream) {
   if (nitems <= 0) return;
   hipLaunchKernelGGL(tslice_kernel, dim3(std::min(nitems, 65535)), dim3(256), 0, (hipStream_t)stream, jobs, items,
@@ -170,11 +165,11 @@ void launch_fill_int(int32_t *p, int64_t n, int32_t v, void *stream) {
                      (hipStream_t)stream, p, n, v);
 }
 
-void launch_slices(const SliceJob *jobs, int njobs, int nslices, const double *const *bases, const double *psi,
-                   const double *work, SliceBufs bufs, void *stream) {
-  if (njobs <= 0) return;
-  hipLaunchKernelGGL(slice_kernel, dim3(std::min(njobs, 8192)), dim3(256), 0, (hipStream_t)stream, jobs, njobs,
-                     nslices, bases, psi, work, bufs);
+void launch_slices(const SliceJob *jobs, const SliceItem *items, int nitems, int nslices, const double *const *bases,
+                   const double *psi, const double *work, SliceBufs bufs, void *stream) {
+  if (nitems <= 0) return;
+  hipLaunchKernelGGL(slice_kernel, dim3(std::min(nitems, 8192)), dim3(256), 0, (hipStream_t)stream, jobs, items,
+                     nitems, nslices, bases, psi, work, bufs);
 }
 
 // ------------------------------------------------------------------ split products
@@ -203,6 +198,17 @@ __device__ __forceinline__ double fold_groups(const V *q, int r) {
   double x = (double)q[0][r];
   for (int g = 1; g < G; g++) x += (double)q[g][r];
   return x;
+}
+
+// Byte offset of chunk 0, slice 0 of line L of nl lines of length ld, from the
+// first slice of its operand, and the stride hs between the slices of a chunk
+// (chunks follow at NS hs).  64-bit: the lines of a segment's operand begin
+// anywhere in the record's panels.
+template <int NS>
+__device__ __forceinline__ uint64_t line_offset(uint32_t L, uint32_t nl, uint32_t ld, uint32_t &hs) {
+  const uint32_t p = L / SLICE_PANEL;
+  hs = 16u * min((uint32_t)SLICE_PANEL, nl - SLICE_PANEL * p);
+  return (uint64_t)(SLICE_PANEL * 2u * NS * p) * ld + 16u * (L % SLICE_PANEL);
 }
 
 template <int MB, int NS>
@@ -239,21 +245,19 @@ __device__ __forceinline__ void item_split(const Tile &T, const Seg *__restrict_
         }
       continue;
     }
-    // segment offsets and line lengths are multiples of 8: a segment's slices
-    // start at NS times its offset, a line's at NS times its start
+    // the operand's slices start at NS times its offset
     const uint16_t *A = bufs.data[Q.a_buf] + Q.a_off * NS;
     const uint16_t *B = bufs.data[Q.b_buf] + Q.b_off * NS;
     const int32_t *ea = bufs.exps[Q.a_buf] + Q.a_exp;
     const int32_t *eb = bufs.exps[Q.b_buf] + Q.b_exp;
     // lanes past the last row / column read the last one: their outputs are
-    // never stored, so every operand load is unconditional.  Addresses are a
-    // wave-uniform slice base plus a 32-bit lane offset within the segment's
-    // lines (checked when the plan is built).
-    uint32_t arow[MB], bcol[NB];   // byte offsets
+    // never stored, so every operand load is unconditional.
+    uint64_t arow[MB], bcol[NB];   // byte offsets, and strides between slices
+    uint32_t ahs[MB], bhs[NB];
     for (int bi = 0; bi < MB; bi++)
-      arow[bi] = (uint32_t)(T.i0 + min(16 * bi + r16, mrem - 1)) * (uint32_t)Q.a_ld * (2u * NS);
+      arow[bi] = line_offset<NS>(Q.a_line0 + T.i0 + min(16 * bi + r16, mrem - 1), Q.a_nl, (uint32_t)Q.a_ld, ahs[bi]);
     for (int bj = 0; bj < NB; bj++)
-      bcol[bj] = (uint32_t)(T.j0 + min(16 * bj + r16, nrem - 1)) * (uint32_t)Q.b_ld * (2u * NS);
+      bcol[bj] = line_offset<NS>(Q.b_line0 + T.j0 + min(16 * bj + r16, nrem - 1), Q.b_nl, (uint32_t)Q.b_ld, bhs[bj]);
     // scale exponents of this lane's output elements
     int erow[MB][4], fcol[NB];
     for (int bi = 0; bi < MB; bi++)
@@ -271,13 +275,17 @@ __device__ __forceinline__ void item_split(const Tile &T, const Seg *__restrict_
     // loads of the next step fly while the MFMAs of this one run without
     // holding a second set of registers.
     auto dma = [&](int k0) {
-      const uint32_t kl = (2u * NS) * (uint32_t)min(k0 + 8 * q4, Q.K - 8);
-      for (int t = 0; t < NS; t++) {
-        const char *at = (const char *)A + 16 * t, *bt = (const char *)B + 16 * t;
-        for (int bi = 0; bi < MB; bi++)
-          __builtin_amdgcn_global_load_lds((gvptr)(at + (arow[bi] + kl)), (lvptr)(stage + (bi * NS + t) * 1024), 16, 0, 0);
-        for (int bj = 0; bj < NB; bj++)
-          __builtin_amdgcn_global_load_lds((gvptr)(bt + (bcol[bj] + kl)), (lvptr)(stage + ((MB + bj) * NS + t) * 1024),
+      const uint32_t kc = (uint32_t)min(k0 + 8 * q4, Q.K - 8) / 8;
+      const uint32_t ca = NS * (Q.a_k0 / 8 + kc), cb = NS * (Q.b_k0 / 8 + kc);
+      for (int bi = 0; bi < MB; bi++) {
+        const char *at = (const char *)A + (arow[bi] + (uint64_t)ca * ahs[bi]);
+        for (int t = 0; t < NS; t++)
+          __builtin_amdgcn_global_load_lds((gvptr)(at + t * ahs[bi]), (lvptr)(stage + (bi * NS + t) * 1024), 16, 0, 0);
+      }
+      for (int bj = 0; bj < NB; bj++) {
+        const char *bt = (const char *)B + (bcol[bj] + (uint64_t)cb * bhs[bj]);
+        for (int t = 0; t < NS; t++)
+          __builtin_amdgcn_global_load_lds((gvptr)(bt + t * bhs[bj]), (lvptr)(stage + ((MB + bj) * NS + t) * 1024),
                                            16, 0, 0);
       }
     };
@@ -463,15 +471,18 @@ __device__ __forceinline__ void macro_split(const Tile &T, const Seg *__restrict
     // lines are zero-padded to it: the chunk of 8 at min(k, K - 8) is inside
     // the operand; lanes whose chunk starts at or past K are zeroed at the MFMA)
     auto issue = [&](const SegS &Q, int k0, int b) {
-      const char *A = (const char *)(bufs.data[Q.a_buf] + Q.a_off * NS);   // slices interleaved (see item_split)
+      const char *A = (const char *)(bufs.data[Q.a_buf] + Q.a_off * NS);   // panels, see item_split
       const char *B = (const char *)(bufs.data[Q.b_buf] + Q.b_off * NS);
-      const uint32_t kl = (2u * NS) * (uint32_t)min(k0 + 8 * q4, Q.K - 8);
-      const uint32_t ao = lrow * (uint32_t)Q.a_ld * (2u * NS) + kl, bo = lcol * (uint32_t)Q.b_ld * (2u * NS) + kl;
+      const uint32_t kc = (uint32_t)min(k0 + 8 * q4, Q.K - 8) / 8;
+      uint32_t ah, bh;
+      A += line_offset<NS>(Q.a_line0 + lrow, Q.a_nl, (uint32_t)Q.a_ld, ah);
+      B += line_offset<NS>(Q.b_line0 + lcol, Q.b_nl, (uint32_t)Q.b_ld, bh);
+      A += (uint64_t)(NS * (Q.a_k0 / 8 + kc)) * ah;
+      B += (uint64_t)(NS * (Q.b_k0 / 8 + kc)) * bh;
       char *st = lds + b * STAGE;
       for (int t = 0; t < NS; t++) {
-        __builtin_amdgcn_global_load_lds((gvptr)(A + 16 * t + ao), (lvptr)(st + (wave * NS + t) * 1024), 16, 0, 0);
-        __builtin_amdgcn_global_load_lds((gvptr)(B + 16 * t + bo), (lvptr)(st + ((4 + wave) * NS + t) * 1024), 16,
-                                         0, 0);
+        __builtin_amdgcn_global_load_lds((gvptr)(A + t * ah), (lvptr)(st + (wave * NS + t) * 1024), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((gvptr)(B + t * bh), (lvptr)(st + ((4 + wave) * NS + t) * 1024), 16, 0, 0);
       }
     };
     v4f q[MB][NB][slice_groups(NS)];
@@ -658,11 +669,11 @@ MACRO_KERNELS(7)
 // ------------------------------------------------------------ wide work-group tiles
 // A 128 x 128 output tile (WIDE_MB) computed by the eight wavefronts of a
 // work group, two per SIMD: wave w owns rows 32 (w >> 1) .. + 32 and columns
-// 64 (w & 1) .. + 64 as two blocks of v_mfma_f32_32x32x16_bf16.  The MFMA
-// takes the B lines (output columns) as its first operand and the A lines
-// (output rows) as its second, so lane l holds output row l % 32 of a block
-// and its columns wcol(r) = 8 (r / 4) + 4 (l / 32) + r % 4: the column-major
-// stores of 32 lanes are contiguous 256-byte runs.  Each 32-wide K step of
+// 64 (w & 1) .. + 64 as two blocks of v_mfma_f32_32x32x16_bf16: lane l holds
+// output column l % 32 of a block and its rows wrow(r) = 8 (r / 4) + 4 (l / 32)
+// + r % 4, so the accesses of 32 lanes to the row-major stripes (first-stage
+// stores, identity segments) are contiguous 256-byte runs, and a column's
+// exponent takes one exchange between lanes.  Each 32-wide K step of
 // the operands (A: 4 row blocks of 32 lines, B: 4 column blocks, two K halves
 // of 16, NS slices; 1 KiB per block, half and slice) goes from global memory
 // through registers into one of two LDS stages -- wave w loads row block
@@ -670,7 +681,7 @@ MACRO_KERNELS(7)
 // on the other stage.  The stages are two separate LDS objects, so the
 // compiler knows that the stores into one never alias the reads of the other.
 constexpr int wstage_bytes(int ns) { return 16 * ns * 1024; }
-__device__ __forceinline__ int wcol(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
+__device__ __forceinline__ int wrow(int r, int h) { return 8 * (r >> 2) + 4 * h + (r & 3); }
 
 template <int NS>
 __device__ __forceinline__ void wide_split(const Tile &T, const Seg *__restrict__ segs,
@@ -704,19 +715,20 @@ __device__ __forceinline__ void wide_split(const Tile &T, const Seg *__restrict_
     if (cs[T.seg0 + si].K != 0) continue;
     CSeg &S = cg[T.seg0 + si];
     const double *B = sbase_ptr(S.b_base, bases, psi, y, work, part) + S.b_off;
-    if (c32 >= mrem) continue;
-    const int k = i0 + c32;
-    const int pk = k / S.b_kb;
-    const int64_t ko = (int64_t)pk * S.b_pk + (int64_t)(k - pk * S.b_kb) * S.b_k;
-    for (int bj = 0; bj < 2; bj++)
+    for (int bj = 0; bj < 2; bj++) {
+      if (32 * bj + c32 >= nrem) continue;
+      const int n = j0 + 32 * bj + c32;
+      const int pn = n / S.b_nb;
+      const int64_t bo = (int64_t)pn * S.b_pn + (int64_t)(n - pn * S.b_nb) * S.b_n;
       for (int r = 0; r < 16; r++) {
-        const int j = 32 * bj + wcol(r, h);
-        if (j < nrem) {
-          const int n = j0 + j;
-          const int pn = n / S.b_nb;
-          acc[bj][r] += S.s * B[ko + (int64_t)pn * S.b_pn + (int64_t)(n - pn * S.b_nb) * S.b_n];
+        const int i = wrow(r, h);
+        if (i < mrem) {
+          const int k = i0 + i;
+          const int pk = k / S.b_kb;
+          acc[bj][r] += S.s * B[(int64_t)pk * S.b_pk + (int64_t)(k - pk * S.b_kb) * S.b_k + bo];
         }
       }
+    }
   }
   int si = 0;
   while (si < T.nseg && cs[T.seg0 + si].K == 0) si++;
@@ -739,11 +751,13 @@ __device__ __forceinline__ void wide_split(const Tile &T, const Seg *__restrict_
       // across the K loop); lines past the output read the last one (never stored)
       int ln;
       asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
-      const uint32_t line = (uint32_t)(op ? min(T.j0 + 32 * lb + (ln & 31), T.n - 1)
-                                          : min(T.i0 + 32 * lb + (ln & 31), T.m - 1));
-      const uint32_t kl = (2u * NS) * (uint32_t)min(k0 + 16 * lkh + 8 * (ln >> 5), Q.K - 8);
-      const uint32_t xo = line * (uint32_t)(op ? Q.b_ld : Q.a_ld) * (2u * NS) + kl;
-      for (int t = 0; t < NS; t++) pre[t] = *(const v4u *)(X + xo + 16 * t);
+      const uint32_t line = (uint32_t)(op ? Q.b_line0 + min(T.j0 + 32 * lb + (ln & 31), T.n - 1)
+                                          : Q.a_line0 + min(T.i0 + 32 * lb + (ln & 31), T.m - 1));
+      const uint32_t kc = (uint32_t)((op ? Q.b_k0 : Q.a_k0) + min(k0 + 16 * lkh + 8 * (ln >> 5), Q.K - 8)) / 8;
+      uint32_t hs;
+      X += line_offset<NS>(line, op ? Q.b_nl : Q.a_nl, (uint32_t)(op ? Q.b_ld : Q.a_ld), hs);
+      X += (uint64_t)(NS * kc) * hs;
+      for (int t = 0; t < NS; t++) pre[t] = *(const v4u *)(X + t * hs);
     };
     // ... and from registers into LDS stage st, in the MFMA operand layout
     auto store = [&](int op, const v4u *pre, char *st) {
@@ -772,30 +786,31 @@ __device__ __forceinline__ void wide_split(const Tile &T, const Seg *__restrict_
           const v8bf bn = u + 1 < NS ? *(const lv8ptr)(bs + (u + 1) * 1024) : b;
 #pragma unroll
           for (int t = 0; t + u < NS; t++)
-            q[bj][sgroup<NS>(t + u)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b, a[t], q[bj][sgroup<NS>(t + u)], 0, 0, 0);
+            q[bj][sgroup<NS>(t + u)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t], b, q[bj][sgroup<NS>(t + u)], 0, 0, 0);
           b = bn;
         }
       }
     };
     // segment descriptors are read where needed (wave-uniform, scalar loads)
     // rather than copied, so that they never sit in scratch memory
-    // fold into FP64 with the scale exponents of this lane's row and its 32
-    // columns, read here (the exponent arrays hold WIDE_EDGE spare entries, so
+    // fold into FP64 with the scale exponents of this lane's two columns and 16
+    // rows, read here (the exponent arrays hold WIDE_EDGE spare entries, so
     // the lines past the output read in bounds; their outputs are never
     // stored).  Exponents are in [-1100, 1100] or the all-zero sentinel, which
     // only meets zero sums: int16 keeps every sum of two in range.
     auto fold = [&]() {
       CSegS &Q = cs[T.seg0 + si];
       const double sc = cg[T.seg0 + si].s;
-      const int32_t *ea = bufs.exps[Q.a_buf] + Q.a_exp + (i0 + c32);
-      const int32_t *eb = bufs.exps[Q.b_buf] + Q.b_exp + (j0 + 4 * h);
-      const int er = (int16_t)ea[0];
-      for (int bj = 0; bj < 2; bj++)
-        for (int r = 0; r < 16; r++) {
-          const int f = (int16_t)eb[32 * bj + 8 * (r >> 2) + (r & 3)];
+      const int32_t *ea = bufs.exps[Q.a_buf] + Q.a_exp + (i0 + 4 * h);
+      const int32_t *eb = bufs.exps[Q.b_buf] + Q.b_exp + (j0 + c32);
+      const int f0 = (int16_t)eb[0], f1 = (int16_t)eb[32];
+      for (int r = 0; r < 16; r++) {
+        const int er = (int16_t)ea[8 * (r >> 2) + (r & 3)];
+        for (int bj = 0; bj < 2; bj++) {
           const double x = fold_groups<slice_groups(NS)>(q[bj], r);
-          acc[bj][r] += sc * ldexp(x, er + f - 2 * SLICE_BITS);
+          acc[bj][r] += sc * ldexp(x, er + (bj ? f1 : f0) - 2 * SLICE_BITS);
         }
+      }
       for (int bj = 0; bj < 2; bj++)
         for (int g = 0; g < slice_groups(NS); g++) q[bj][g] = (v16f){};
     };
@@ -845,31 +860,29 @@ __device__ __forceinline__ void wide_split(const Tile &T, const Seg *__restrict_
   const int ci0 = T.ci0 + 32 * wr, cj0 = T.cj0 + 64 * wc;
   for (int bj = 0; bj < 2; bj++)
     for (int r = 0; r < 16; r++) {
-      const int i = c32, j = 32 * bj + wcol(r, h);
+      const int i = wrow(r, h), j = 32 * bj + c32;
       if (i < mrem && j < nrem) {
         double *c = T.rowmajor ? C + (int64_t)(ci0 + i) * T.ldc + (cj0 + j)
                                : C + (int64_t)(ci0 + i) + (int64_t)(cj0 + j) * T.ldc;
         *c = T.accumulate ? *c + acc[bj][r] : acc[bj][r];
       }
     }
-  // first-stage tiles: exponent of every stripe column written (see
-  // item_split), the maximum of the elements' exponents over the rows
+  // first-stage tiles: exponent of every stripe column written (see item_split)
   CSegS &Q0 = cs[T.seg0];
   if (Q0.t_exp >= 0) {
     int32_t *ex = bufs.exps[SBUF_T] + Q0.t_exp;
-    for (int bj = 0; bj < 2; bj++)
-      for (int r = 0; r < 16; r++) {
-        const int j = 32 * bj + wcol(r, h);
-        const double m = fabs(acc[bj][r]);
-        int e = INT_MIN;
-        if (c32 < mrem && j < nrem && m > 0.0) {
-          int e2;
-          const double mant = frexp(m, &e2);
-          e = mant == 0.5 ? e2 - 1 : e2;
-        }
-        for (int off = 16; off > 0; off >>= 1) e = max(e, __shfl_xor(e, off));
-        if (c32 == 0 && j < nrem && e != INT_MIN) atomicMax(ex + (cj0 + j) % Q0.t_nb, e);
+    for (int bj = 0; bj < 2; bj++) {
+      const int j = 32 * bj + c32;
+      double m = 0.0;
+      for (int r = 0; r < 16; r++)
+        if (wrow(r, h) < mrem && j < nrem) m = fmax(m, fabs(acc[bj][r]));
+      m = fmax(m, __shfl_xor(m, 32));
+      if (h == 0 && j < nrem && m > 0.0) {
+        int e2;
+        const double mant = frexp(m, &e2);
+        atomicMax(ex + (cj0 + j) % Q0.t_nb, mant == 0.5 ? e2 - 1 : e2);
       }
+    }
   }
 }
 

@@ -77,7 +77,9 @@ struct dmrg_plan {
   int precision = 0, n_slices = 0;
   // split precision
   std::vector<SliceJob> jobs_ops, jobs_psi;
+  std::vector<SliceItem> items_ops, items_psi;
   SliceJob *d_jobs_ops = nullptr, *d_jobs_psi = nullptr;
+  SliceItem *d_items_psi = nullptr;
   int64_t sb_elems[N_SBUF] = {0, 0, 0, 0}, sb_exps[N_SBUF] = {0, 0, 0, 0};
   SliceBufs sb{};
   std::vector<uint16_t> h_sb[N_SBUF];      // host copies (test emulation only)
@@ -243,7 +245,6 @@ int autotune(dmrg_plan *P, void *stream);
 int replan(dmrg_plan *P);
 
 int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
-  const bool trow = P->precision != DMRG_SPLIT_BF16;   // stripe layout, see the first stage
   P->wg_tiles = true;
   for (const auto &pp : P->probs)
     for (const auto *sec : {&pp->L.sec, &pp->R.sec})
@@ -309,10 +310,9 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
       woff += (int64_t)s.dL * s.dRout * s.slots.size();
       woff = (woff + 31) / 32 * 32;
       // first stage: T_h = X [op(D_s0) ... op(D_s1-1)] for each run of consecutive positions.
-      // FP64 plans store the stripe as a row-major d_L x (nslots d_R') matrix
-      // (slot s in columns [s d_R', (s+1) d_R')), so that both stages access
-      // it along rows; split plans slice it per column and store it
-      // column-major (slot s is the d_L x d_R' block at off + s d_L d_R').
+      // The stripe is a row-major d_L x (nslots d_R') matrix (slot s in columns
+      // [s d_R', (s+1) d_R')), so that both stages, and the slicer of split
+      // plans, access it along rows.
       const ProbPlan &pp = *P->probs[kv.first.prob];
       const PsiBlock &E = pp.T.blocks[kv.first.E];
       const dmrg_oprec_t &rec = pp.R.rec[kv.first.rec];
@@ -350,14 +350,9 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
             const int i0 = cell.i0, j0 = cell.j0, mb = cell.mb;
             Tile t{};
             t.c_base = BASE_WORK;
-            if (trow) {
-              t.c_off = s.off + (int64_t)s0 * s.dRout;
-              t.ldc = (int64_t)s.slots.size() * s.dRout;
-              t.rowmajor = 1;
-            } else {
-              t.c_off = s.off + (int64_t)s0 * s.dL * s.dRout;
-              t.ldc = s.dL;
-            }
+            t.c_off = s.off + (int64_t)s0 * s.dRout;
+            t.ldc = (int64_t)s.slots.size() * s.dRout;
+            t.rowmajor = 1;
             t.m = s.dL; t.n = N; t.i0 = i0; t.j0 = j0; t.ci0 = i0; t.cj0 = j0;
             t.mb = mb;
             t.seg0 = sidx; t.nseg = 1; t.accumulate = 0;
@@ -411,7 +406,7 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
         int run = (int)(q1 - q);
         Seg g{};
         g.s = tk.v * row.pos[q].alpha;
-        if (st && trow) {
+        if (st) {
           // B = [T_s; T_s+1; ...]: slot s of the row-major stripe in columns s d_R'..
           g.b_base = BASE_WORK;
           g.b_off = st->off + (int64_t)slot_of(row.pos[q].pD) * F.dR;
@@ -419,14 +414,6 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
           g.b_pk = F.dR;
           g.b_k = (int64_t)st->slots.size() * F.dR;
           g.b_n = 1;
-        } else if (st) {
-          // column-major stripe: slot s is the d_L x d_R' block at s d_L d_R'
-          g.b_base = BASE_WORK;
-          g.b_off = st->off + (int64_t)slot_of(row.pos[q].pD) * E.dL * F.dR;
-          g.b_kb = E.dL;
-          g.b_pk = (int64_t)E.dL * F.dR;
-          g.b_k = 1;
-          g.b_n = E.dL;
         } else {
           g.b_base = BASE_PSI;
           g.b_off = pp.psi_off + E.off;
@@ -765,7 +752,7 @@ int prepare_device(dmrg_plan *P) {
 // parallel to the FP64 segments (same tiles, parts and reduction).
 namespace {
 
-struct VarInfo { int64_t off, exp; int kbp; int64_t line_len; int lines_per_pos; };
+struct VarInfo { int64_t off, exp, line_len; int kbp, nl, lines_per_pos; };
 
 static int rup8(int x) { return (x + 7) / 8 * 8; }
 
@@ -773,6 +760,18 @@ static int rup8(int x) { return (x + 7) / 8 * 8; }
 static void check_jobs(const std::vector<SliceJob> &jobs) {
   for (const SliceJob &j : jobs)
     if ((int64_t)j.npos * j.kbp >= ((int64_t)1 << 31)) throw std::length_error("slice line longer than 2^31");
+}
+
+// work items of a job list: whole panels (the line maxima are taken first), or,
+// with the exponents in place, panels cut along K every `cut` blocks
+static void slice_items(const std::vector<SliceJob> &jobs, int cut, std::vector<SliceItem> &items) {
+  items.clear();
+  for (int j = 0; j < (int)jobs.size(); j++) {
+    const SliceJob &J = jobs[j];
+    const int nk = (int)(((int64_t)J.npos * J.kbp + SLICE_KBLOCK - 1) / SLICE_KBLOCK);
+    for (int p = 0; p < (J.nl + SLICE_PANEL - 1) / SLICE_PANEL; p++)
+      for (int k = 0; k < nk; k += cut > 0 ? cut : nk) items.push_back({j, p, k, cut > 0 ? std::min(cut, nk - k) : nk});
+  }
 }
 
 void build_split(dmrg_plan *P) {
@@ -802,36 +801,29 @@ void build_split(dmrg_plan *P) {
     VarInfo v{};
     v.off = P->sb_elems[SBUF_OPS];
     v.exp = P->sb_exps[SBUF_OPS];
-    int64_t bs = (int64_t)R0 * C0;
-    if (var == 0 || var == 1) {
-      int nrho = var == 0 ? R0 : C0, kb = var == 0 ? C0 : R0;
-      v.kbp = rup8(kb);
-      v.line_len = (int64_t)npos * v.kbp;
-      v.lines_per_pos = 0;
-      SliceJob j{};
-      j.src_base = base; j.src_off = src_off;
-      j.s_rho = var == 0 ? 1 : R0; j.s_pos = bs; j.s_k = var == 0 ? R0 : 1;
-      j.dst_buf = SBUF_OPS; j.dst_off = v.off; j.exp_off = v.exp;
-      j.nrho = nrho; j.npos = npos; j.kb = kb; j.kbp = v.kbp;
-      P->jobs_ops.push_back(j);
-      P->sb_elems[SBUF_OPS] += (int64_t)nrho * v.line_len;
-      P->sb_exps[SBUF_OPS] += nrho;
-    } else {
-      int nrho = var == 2 ? R0 : C0, kb = var == 2 ? C0 : R0;
-      v.kbp = rup8(kb);
-      v.line_len = v.kbp;
-      v.lines_per_pos = nrho;
-      for (int p = 0; p < npos; p++) {
-        SliceJob j{};
-        j.src_base = base; j.src_off = src_off + (int64_t)p * bs;
-        j.s_rho = var == 2 ? 1 : R0; j.s_pos = 0; j.s_k = var == 2 ? R0 : 1;
-        j.dst_buf = SBUF_OPS; j.dst_off = v.off + (int64_t)p * nrho * v.kbp; j.exp_off = v.exp + (int64_t)p * nrho;
-        j.nrho = nrho; j.npos = 1; j.kb = kb; j.kbp = v.kbp;
-        P->jobs_ops.push_back(j);
-      }
-      P->sb_elems[SBUF_OPS] += (int64_t)npos * nrho * v.kbp;
-      P->sb_exps[SBUF_OPS] += (int64_t)npos * nrho;
-    }
+    const int64_t bs = (int64_t)R0 * C0;
+    // lines over all positions along K (A operands: 0 rows, 1 columns), or one
+    // line per position and row or column (D operands: 2 rows, 3 columns)
+    const bool rows = var == 0 || var == 2, perpos = var >= 2;
+    SliceJob j{};
+    j.src_base = base; j.src_off = src_off;
+    j.nrho = rows ? R0 : C0;
+    j.kb = rows ? C0 : R0;
+    j.kbp = rup8(j.kb);
+    j.s_rho = rows ? 1 : R0;
+    j.s_k = rows ? R0 : 1;
+    j.npos = perpos ? 1 : npos;
+    j.s_pos = perpos ? 0 : bs;
+    j.s_q = perpos ? bs : 0;
+    j.nl = perpos ? npos * j.nrho : j.nrho;
+    j.dst_buf = SBUF_OPS; j.dst_off = v.off; j.exp_off = v.exp;
+    v.kbp = j.kbp;
+    v.nl = j.nl;
+    v.line_len = (int64_t)j.npos * j.kbp;
+    v.lines_per_pos = perpos ? j.nrho : 0;
+    P->jobs_ops.push_back(j);
+    P->sb_elems[SBUF_OPS] += (int64_t)j.nl * v.line_len;
+    P->sb_exps[SBUF_OPS] += j.nl;
     vars[key] = v;
     return v;
   };
@@ -845,7 +837,7 @@ void build_split(dmrg_plan *P) {
       SliceJob j{};
       j.src_base = BASE_PSI; j.src_off = pp.psi_off + E.off;
       j.s_rho = 1; j.s_pos = 0; j.s_k = E.dL;
-      j.nrho = E.dL; j.npos = 1; j.kb = E.dR; j.kbp = rup8(E.dR);
+      j.nl = j.nrho = E.dL; j.npos = 1; j.kb = E.dR; j.kbp = rup8(E.dR);
       j.dst_buf = SBUF_PSIR; j.dst_off = P->sb_elems[SBUF_PSIR]; j.exp_off = P->sb_exps[SBUF_PSIR];
       o[0] = j.dst_off; o[1] = j.exp_off;
       P->sb_elems[SBUF_PSIR] += (int64_t)E.dL * j.kbp;
@@ -854,7 +846,7 @@ void build_split(dmrg_plan *P) {
       SliceJob c{};
       c.src_base = BASE_PSI; c.src_off = pp.psi_off + E.off;
       c.s_rho = E.dL; c.s_pos = 0; c.s_k = 1;
-      c.nrho = E.dR; c.npos = 1; c.kb = E.dL; c.kbp = rup8(E.dL);
+      c.nl = c.nrho = E.dR; c.npos = 1; c.kb = E.dL; c.kbp = rup8(E.dL);
       c.dst_buf = SBUF_PSIC; c.dst_off = P->sb_elems[SBUF_PSIC]; c.exp_off = P->sb_exps[SBUF_PSIC];
       o[2] = c.dst_off; o[3] = c.exp_off;
       P->sb_elems[SBUF_PSIC] += (int64_t)E.dR * c.kbp;
@@ -875,17 +867,17 @@ void build_split(dmrg_plan *P) {
     for (const StripeInfo &si : ch.stripes) {
       SliceJob j{};
       j.src_base = BASE_WORK; j.src_off = si.off;
-      j.s_rho = si.dL; j.s_pos = (int64_t)si.dL * si.dRout; j.s_k = 1;   // column-major stripes
-      j.nrho = si.dRout; j.npos = si.nslots; j.kb = si.dL; j.kbp = rup8(si.dL);
+      j.s_rho = 1; j.s_pos = si.dRout; j.s_k = (int64_t)si.nslots * si.dRout;   // row-major stripes
+      j.nl = j.nrho = si.dRout; j.npos = si.nslots; j.kb = si.dL; j.kbp = rup8(si.dL);
       j.dst_buf = SBUF_T; j.dst_off = te; j.exp_off = tx;
       toff.push_back({te, tx, j.kbp});
       const int64_t tot = (int64_t)si.dRout * si.nslots * j.kbp;
       if (tot >= ((int64_t)1 << 31)) throw std::length_error("stripe slice job longer than 2^31");
-      for (int64_t e0 = 0; e0 < tot; e0 += TSLICE_CHUNK) ch.titems.push_back({(int32_t)ch.tjobs.size(), (int32_t)e0});
       te += tot;
       tx += si.dRout;
       ch.tjobs.push_back(j);
     }
+    slice_items(ch.tjobs, 8, ch.titems);
     ch.t_elems = te;
     ch.t_exps = tx;
     t_elems_max = std::max(t_elems_max, te);
@@ -901,10 +893,13 @@ void build_split(dmrg_plan *P) {
       q.a_off = psi_off[si.prob][si.E][0];
       q.a_ld = rup8(si.dRin);
       q.a_exp = psi_off[si.prob][si.E][1];
+      q.a_nl = si.dL;
       q.b_buf = SBUF_OPS;
-      q.b_off = v.off + (int64_t)inf.pD0 * v.lines_per_pos * v.kbp;
+      q.b_off = v.off;
       q.b_ld = v.kbp;
-      q.b_exp = v.exp + (int64_t)inf.pD0 * v.lines_per_pos;
+      q.b_line0 = inf.pD0 * v.lines_per_pos;
+      q.b_nl = v.nl;
+      q.b_exp = v.exp + q.b_line0;
       q.K = rup8(si.dRin);
       q.t_nb = si.dRout;
       q.t_exp = toff[inf.stripe][1];
@@ -923,18 +918,23 @@ void build_split(dmrg_plan *P) {
       }
       VarInfo v = variant(inf.prob, 0, inf.recA, inf.adjA ? 1 : 0);
       q.a_buf = SBUF_OPS;
-      q.a_off = v.off + (int64_t)inf.pA0 * v.kbp;
+      q.a_off = v.off;
+      q.a_k0 = inf.pA0 * v.kbp;
+      q.a_nl = v.nl;
       q.a_ld = v.line_len;
       q.a_exp = v.exp;
       if (inf.stripe >= 0) {
         const StripeInfo &si = ch.stripes[inf.stripe];
         q.b_buf = SBUF_T;
-        q.b_off = toff[inf.stripe][0] + (int64_t)inf.slot0 * toff[inf.stripe][2];
+        q.b_off = toff[inf.stripe][0];
+        q.b_k0 = (int)(inf.slot0 * toff[inf.stripe][2]);
+        q.b_nl = si.dRout;
         q.b_ld = (int64_t)si.nslots * toff[inf.stripe][2];
         q.b_exp = toff[inf.stripe][1];
       } else {
         q.b_buf = SBUF_PSIC;
         q.b_off = psi_off[inf.prob][inf.E][2];
+        q.b_nl = E.dR;
         q.b_ld = rup8(E.dL);
         q.b_exp = psi_off[inf.prob][inf.E][3];
       }
@@ -946,6 +946,8 @@ void build_split(dmrg_plan *P) {
   P->sb_exps[SBUF_T] = t_exps_max;
   check_jobs(P->jobs_ops);
   check_jobs(P->jobs_psi);
+  slice_items(P->jobs_ops, 0, P->items_ops);
+  slice_items(P->jobs_psi, 0, P->items_psi);
   for (auto &ch : P->chunks) check_jobs(ch.tjobs);
   // the split kernels address a segment's slice lines with 32-bit byte
   // offsets from the slice base: rows * ld * 2 s bytes must stay below 2^32
@@ -970,7 +972,10 @@ namespace {
 int upload_split(dmrg_plan *P) {
   build_split(P);
   int rc;
-  if ((rc = upload(P, P->jobs_ops, &P->d_jobs_ops)) || (rc = upload(P, P->jobs_psi, &P->d_jobs_psi))) return rc;
+  SliceItem *d_items_ops = nullptr;
+  if ((rc = upload(P, P->jobs_ops, &P->d_jobs_ops)) || (rc = upload(P, P->jobs_psi, &P->d_jobs_psi)) ||
+      (rc = upload(P, P->items_ops, &d_items_ops)) || (rc = upload(P, P->items_psi, &P->d_items_psi)))
+    return rc;
   for (auto &ch : P->chunks)
     if ((rc = upload(P, ch.sseg1, &ch.d_sseg1)) || (rc = upload(P, ch.sseg2, &ch.d_sseg2)) ||
         (rc = upload(P, ch.tjobs, &ch.d_tjobs)) || (rc = upload(P, ch.titems, &ch.d_titems)))
@@ -990,7 +995,7 @@ int upload_split(dmrg_plan *P) {
     P->sb.exps[b] = (int32_t *)e;
   }
   // operator slices: once per plan (the operators are constant during Davidson)
-  launch_slices(P->d_jobs_ops, (int)P->jobs_ops.size(), P->n_slices, P->d_bases, nullptr, nullptr, P->sb,
+  launch_slices(P->d_jobs_ops, d_items_ops, (int)P->items_ops.size(), P->n_slices, P->d_bases, nullptr, nullptr, P->sb,
                 P->build_stream);
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(P->build_stream));
@@ -1017,7 +1022,10 @@ void release_plan(dmrg_plan *P) {
   P->work_elems = P->part_elems = 0;
   P->jobs_ops.clear();
   P->jobs_psi.clear();
+  P->items_ops.clear();
+  P->items_psi.clear();
   P->d_jobs_ops = P->d_jobs_psi = nullptr;
+  P->d_items_psi = nullptr;
   P->sb = SliceBufs{};
   for (int b = 0; b < N_SBUF; b++) P->sb_elems[b] = P->sb_exps[b] = 0;
   P->stats.n_stage1 = P->stats.n_segments = 0;
@@ -1373,7 +1381,7 @@ int enqueue_with(dmrg_plan *p, const double *psi, double *hpsi, void *stream, bo
   launch_zero(hpsi, p->psi_len, qs.cur(), stream);
   const bool split = p->precision == DMRG_SPLIT_BF16;
   if (split)
-    launch_slices(p->d_jobs_psi, (int)p->jobs_psi.size(), p->n_slices, p->d_bases, psi, B.work, B.sb, stream);
+    launch_slices(p->d_jobs_psi, p->d_items_psi, (int)p->items_psi.size(), p->n_slices, p->d_bases, psi, B.work, B.sb, stream);
   size_t ev = p->ev_marks.empty() ? 0 : (size_t)p->ev_marks.back().second.second + 1;
   for (auto &ch : p->chunks) {
     for (int stage = 1; stage <= 2; stage++) {
@@ -1651,9 +1659,9 @@ static void host_slices(const std::vector<SliceJob> &jobs, int ns, const std::ve
   };
   for (const SliceJob &J : jobs) {
     const double *src = base(J.src_base) + J.src_off;
-    int64_t len = (int64_t)J.npos * J.kbp;
-    for (int rho = 0; rho < J.nrho; rho++) {
-      const double *line = src + (int64_t)rho * J.s_rho;
+    const int64_t len = (int64_t)J.npos * J.kbp;
+    for (int L = 0; L < J.nl; L++) {
+      const double *line = src + (int64_t)(L / J.nrho) * J.s_q + (int64_t)(L % J.nrho) * J.s_rho;
       double m = 0.0;
       for (int p = 0; p < J.npos; p++)
         for (int kk = 0; kk < J.kb; kk++) m = std::max(m, std::fabs(line[(int64_t)p * J.s_pos + (int64_t)kk * J.s_k]));
@@ -1663,7 +1671,7 @@ static void host_slices(const std::vector<SliceJob> &jobs, int ns, const std::ve
         double mant = std::frexp(m, &ex);
         e = (mant == 0.5) ? ex - 1 : ex;
       }
-      sbe[J.dst_buf][J.exp_off + rho] = e;
+      sbe[J.dst_buf][J.exp_off + L] = e;
       for (int64_t idx = 0; idx < len; idx++) {
         int p = (int)(idx / J.kbp), kk = (int)(idx - (int64_t)p * J.kbp);
         double x = kk < J.kb ? line[(int64_t)p * J.s_pos + (int64_t)kk * J.s_k] : 0.0;
@@ -1674,7 +1682,7 @@ static void host_slices(const std::vector<SliceJob> &jobs, int ns, const std::ve
           float af = (float)std::ldexp(a, -SLICE_BITS * t);   // digit t at its weight 2^(-8t)
           uint32_t bits;
           std::memcpy(&bits, &af, 4);
-          sbd[J.dst_buf][slice_index(J.dst_off + (int64_t)rho * len + idx, t, ns)] = (uint16_t)(bits >> 16);
+          sbd[J.dst_buf][slice_index(J.dst_off, len, J.nl, L, idx, t, ns)] = (uint16_t)(bits >> 16);
         }
       }
     }
@@ -1715,21 +1723,30 @@ static void host_tiles_split(const std::vector<Tile> &tiles, const std::vector<S
           }
         continue;
       }
-      const uint16_t *A = sbd[Q.a_buf].data(), *B = sbd[Q.b_buf].data();   // slices interleaved
+      // the tile's operand lines out of their panels: slice t, K index k of line l at (l ns + t) K + k
+      auto unpack = [&](int buf, int64_t off, int64_t ld, int nl, int line0, int k0, int lines) {
+        std::vector<double> u((size_t)lines * ns * Q.K);
+        for (int l = 0; l < lines; l++)
+          for (int k = 0; k < Q.K; k++)
+            for (int t = 0; t < ns; t++)
+              u[((size_t)l * ns + t) * Q.K + k] = bf16v(sbd[buf][slice_index(off, ld, nl, line0 + l, k0 + k, t, ns)]);
+        return u;
+      };
+      const auto A = unpack(Q.a_buf, Q.a_off, Q.a_ld, Q.a_nl, Q.a_line0 + T.i0, Q.a_k0, mt);
+      const auto B = unpack(Q.b_buf, Q.b_off, Q.b_ld, Q.b_nl, Q.b_line0 + T.j0, Q.b_k0, nt);
       const int32_t *ea = sbe[Q.a_buf].data() + Q.a_exp;
       const int32_t *eb = sbe[Q.b_buf].data() + Q.b_exp;
       for (int j = 0; j < nt; j++)
         for (int i = 0; i < mt; i++) {
-          const int64_t ar = Q.a_off + (int64_t)(T.i0 + i) * Q.a_ld;   // line starts (unsliced layout)
-          const int64_t bc = Q.b_off + (int64_t)(T.j0 + j) * Q.b_ld;
           double tot = 0.0;
           for (int k0 = 0; k0 < Q.K; k0 += split_fold_k(ns)) {
             double x = 0.0;
             for (int d = 0; d < ns; d++) {
               double qd = 0.0;
-              for (int t = 0; t <= d; t++)
-                for (int k = k0; k < std::min(Q.K, k0 + split_fold_k(ns)); k++)
-                  qd += bf16v(A[slice_index(ar + k, t, ns)]) * bf16v(B[slice_index(bc + k, d - t, ns)]);
+              for (int t = 0; t <= d; t++) {
+                const double *a = A.data() + ((size_t)i * ns + t) * Q.K, *b = B.data() + ((size_t)j * ns + d - t) * Q.K;
+                for (int k = k0; k < std::min(Q.K, k0 + split_fold_k(ns)); k++) qd += a[k] * b[k];
+              }
               x += std::ldexp(qd, -2 * SLICE_BITS);   // slices carry their digit weights
             }
             tot += S.s * std::ldexp(x, ea[T.i0 + i] + eb[T.j0 + j]);

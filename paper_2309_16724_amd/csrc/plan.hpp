@@ -252,12 +252,16 @@ struct DressItem {
 // bits, x = 2^e sum_t a_t 2^(-8(t+1)) + O(2^(e-8s)), |a_0| <= 256, |a_t| <= 128.
 // Slice t stores a_t 2^(-8t), exact in BF16 (at most 8 significant bits), so
 // that a product of slices t and u already carries the relative weight
-// 2^(-8(t+u)) of its group d = t + u and every group folds with 2^-16.  Lines
-// are stored K-contiguous (operand-ready), each position block of K padded to
-// a multiple of 8 with zeros, and the s slices interleaved per chunk of 8: the
-// element at index e of the unsliced layout (offsets, line lengths: multiples
-// of 8) has slice t at (e - e % 8) s + 8 t + e % 8 (slice_index), so that the
-// s slices of a K step of a line are one contiguous run of memory.
+// 2^(-8(t+u)) of its group d = t + u and every group folds with 2^-16.  A line's
+// K range is cut into position blocks padded to a multiple of 8 with zeros.
+// Lines are stored in panels of SLICE_PANEL: inside a panel of h lines (the last
+// one may have fewer), chunk c of eight K values, slice t and line l lie at
+// ((c s + t) h + l) 8 -- the operand order of the MFMAs, so that the 32 lines a
+// wavefront loads for one chunk and slice are one run of 512 bytes.  Stored line
+// by line, such a load took 64 pieces of 16 bytes from as many cache lines, and
+// these requests bound the tiles: H.psi at L = 54, D = 768, s = 5 took 96.7 ms,
+// of which 37.2 in the first stage's wide tiles (18.1 now; in all 69.2 ms), and
+// slicing its operators at plan creation took 137 ms (11 now).
 constexpr int SLICE_BITS = 8;
 // Slice products accumulate in slice_groups(s) FP32 sums: groups d = t + u
 // below s - 3 each in its own sum, exact, and all groups d >= s - 3 in one
@@ -271,33 +275,36 @@ constexpr int SLICE_BITS = 8;
 constexpr int slice_groups(int ns) { return ns <= 3 ? 1 : ns - 2; }
 constexpr int split_fold_k(int ns) { return ns <= 5 ? 256 : 128; }
 
-// One slicing job: lines rho < nrho, position blocks p < npos of kb valid
-// entries (padded to kbp);  source x(rho, p, kk) at src[src_off + rho*s_rho + p*s_pos + kk*s_k];
-// slice t of the element at e = dst_off + rho*npos*kbp + p*kbp + kk at dst[slice_index(e, t, s)];
-// exponent of line rho at exps[exp_off + rho].
+// One slicing job: lines L < nl, position blocks p < npos of kb valid entries
+// (padded to kbp); with rho = L % nrho and q = L / nrho the source x(L, p, kk)
+// is at src[src_off + q*s_q + rho*s_rho + p*s_pos + kk*s_k]; the slices start
+// at element dst_off s (panel layout, slice_index), the exponent of line L is
+// at exps[exp_off + L].
 struct SliceJob {
-  int64_t src_off, s_rho, s_pos, s_k;
+  int64_t src_off, s_q, s_rho, s_pos, s_k;
   int64_t dst_off, exp_off;
   int32_t src_base, dst_buf;
-  int32_t nrho, npos, kb, kbp;
+  int32_t nl, nrho, npos, kb, kbp, pad;
+};
+constexpr int SLICE_PANEL = 32;
+constexpr int SLICE_KBLOCK = 64;     // K values of a panel sliced at a time
+// Slicing work item: K blocks [k0, k0 + nk) of panel `panel` of job `job`.
+struct SliceItem {
+  int32_t job, panel, k0, nk;
 };
 
 // Split segment (same role as Seg): A lines are operand rows, B lines operand
-// columns, both K-contiguous in slice buffers.
+// columns.  The output's row i is line a_line0 + i of a_nl, its K index k is a_k0 + k
+// of lines of a_ld; exponents at a_exp + i.
 struct SegS {
   int64_t a_off, a_ld, a_exp;
   int64_t b_off, b_ld, b_exp;
   int32_t a_buf, b_buf;
+  int32_t a_line0, a_nl, a_k0;
+  int32_t b_line0, b_nl, b_k0;
   int32_t K;          // padded K (multiple of 8); 0 for an identity segment
   int32_t t_nb;       // first-stage segments: stripe columns per slot (line = column mod t_nb)
   int64_t t_exp;      // first-stage segments: exponent offset of the stripe's lines, else -1
-};
-
-// Stripe slicing work item: elements [e0, e0 + TSLICE_CHUNK) of job `job`,
-// flattened line by line (line rho, then padded index along its K range).
-constexpr int TSLICE_CHUNK = 1024;
-struct TSliceItem {
-  int32_t job, e0;
 };
 
 // slice buffers: 0 operator records (plan), 1 psi rows, 2 psi columns, 3 stripes
@@ -307,8 +314,13 @@ struct SliceBufs {
   uint16_t *data[N_SBUF];     // bf16 bit patterns, slices interleaved (slice_index)
   int32_t *exps[N_SBUF];
 };
-// position of slice t of element e (index in the unsliced layout) for s slices
-__host__ __device__ inline int64_t slice_index(int64_t e, int t, int s) { return (e - (e & 7)) * s + 8 * t + (e & 7); }
+// position of slice t of K index k of line L, for lines of length ld (a multiple
+// of 8), nl of them, stored from element off s on
+__host__ __device__ inline int64_t slice_index(int64_t off, int64_t ld, int nl, int64_t L, int64_t k, int t, int s) {
+  const int64_t p0 = L - L % SLICE_PANEL;
+  const int64_t h = nl - p0 < SLICE_PANEL ? nl - p0 : SLICE_PANEL;
+  return (off + p0 * ld) * s + ((k / 8 * s + t) * h + (L - p0)) * 8 + k % 8;
+}
 
 
 // bookkeeping that lets the split-precision plan mirror the FP64 segments
@@ -344,10 +356,10 @@ struct Chunk {
   // split precision (filled only for split plans)
   std::vector<SegS> sseg1, sseg2;
   std::vector<SliceJob> tjobs;          // stripe slicing after the first stage
-  std::vector<TSliceItem> titems;       // its element chunks
+  std::vector<SliceItem> titems;        // its work items
   SegS *d_sseg1 = nullptr, *d_sseg2 = nullptr;
   SliceJob *d_tjobs = nullptr;
-  TSliceItem *d_titems = nullptr;
+  SliceItem *d_titems = nullptr;
   int64_t t_elems = 0, t_exps = 0;
 };
 
@@ -432,11 +444,11 @@ void launch_diag(const DiagBlock *blocks, const DiagTerm *terms, int nblocks,
 }  // namespace dmrg
 
 namespace dmrg {
-void launch_slices(const SliceJob *jobs, int njobs, int nslices, const double *const *bases, const double *psi,
-                   const double *work, SliceBufs bufs, void *stream);
+void launch_slices(const SliceJob *jobs, const SliceItem *items, int nitems, int nslices, const double *const *bases,
+                   const double *psi, const double *work, SliceBufs bufs, void *stream);
 // stripe slicing with line exponents already in place (the first stage's
 // epilogue takes their maxima with atomicMax; sentinel INT_MIN = all zero)
-void launch_tslices(const SliceJob *jobs, const TSliceItem *items, int nitems, int nslices, const double *work,
+void launch_tslices(const SliceJob *jobs, const SliceItem *items, int nitems, int nslices, const double *work,
                     SliceBufs bufs, void *stream);
 void launch_fill_int(int32_t *p, int64_t n, int32_t v, void *stream);
 // scratch memory of one H.psi: byte offsets of the stripe workspace, partial
