@@ -668,9 +668,10 @@ MACRO_KERNELS(7)
 
 // ------------------------------------------------------------ wide work-group tiles
 // A 128 x 128 output tile (WIDE_MB) computed by the eight wavefronts of a
-// work group, two per SIMD: wave w owns rows 32 (w >> 1) .. + 32 and columns
-// 64 (w & 1) .. + 64 as two blocks of v_mfma_f32_32x32x16_bf16: lane l holds
-// output column l % 32 of a block and its rows wrow(r) = 8 (r / 4) + 4 (l / 32)
+// work group, two per SIMD, in blocks of v_mfma_f32_32x32x16_bf16: the blocks
+// that lie inside the output (up to 16) are dealt to the waves, so a part-filled
+// tile costs what its blocks cost (outputs of 48 to 127 lines; 42 % of the wide
+// tiles' products at L = 54, D = 768 fell outside).  Lane l holds output column l % 32 of a block and its rows wrow(r) = 8 (r / 4) + 4 (l / 32)
 // + r % 4, so the accesses of 32 lanes to the row-major stripes (first-stage
 // stores, identity segments) are contiguous 256-byte runs, and a column's
 // exponent takes one exchange between lanes.  Each 32-wide K step of
@@ -701,31 +702,38 @@ __device__ __forceinline__ void wide_split(const Tile &T, const Seg *__restrict_
   // out of the tile loop into registers that the K loop needs
   asm volatile("" : "+v"(lane));
   const int c32 = lane & 31, h = lane >> 5;
-  const int wr = wave >> 1, wc = wave & 1;
-  const int i0 = T.i0 + 32 * wr, j0 = T.j0 + 64 * wc;    // this wave's part
-  const int mrem = T.m - i0, nrem = T.n - j0;             // <= 0: part outside the output
+  // the 32 x 32 blocks inside the output, row by row: the first nblk - 8 waves
+  // take two neighbours each, the others one
+  const int nc = min(4, (T.n - T.j0 + 31) >> 5), nblk = nc * min(4, (T.m - T.i0 + 31) >> 5);
+  const int two = max(0, nblk - WIDE_WAVES);
+  const int nb = wave < two ? 2 : wave < nblk ? 1 : 0;
+  int br[2], bc[2];
+  for (int b = 0; b < 2; b++) {
+    const int id = min(wave < two ? 2 * wave + b : two + wave, nblk - 1);
+    br[b] = id / nc;
+    bc[b] = id - br[b] * nc;
+  }
   // operand lines this lane loads: row block / column block wave % 4, K half
   // wave / 4 (see issue)
   const int lb = wave & 3, lkh = wave >> 2;
   double acc[2][16];
-  for (int bj = 0; bj < 2; bj++)
-    for (int r = 0; r < 16; r++) acc[bj][r] = 0.0;
+  for (int b = 0; b < 2; b++)
+    for (int r = 0; r < 16; r++) acc[b][r] = 0.0;
   // identity left operators: exact FP64 additions of the FP64 operand
   for (int si = 0; si < T.nseg; si++) {
     if (cs[T.seg0 + si].K != 0) continue;
     CSeg &S = cg[T.seg0 + si];
     const double *B = sbase_ptr(S.b_base, bases, psi, y, work, part) + S.b_off;
-    for (int bj = 0; bj < 2; bj++) {
-      if (32 * bj + c32 >= nrem) continue;
-      const int n = j0 + 32 * bj + c32;
+    for (int b = 0; b < 2; b++) {
+      const int n = T.j0 + 32 * bc[b] + c32, i0 = T.i0 + 32 * br[b];
+      if (b >= nb || n >= T.n) continue;
       const int pn = n / S.b_nb;
       const int64_t bo = (int64_t)pn * S.b_pn + (int64_t)(n - pn * S.b_nb) * S.b_n;
       for (int r = 0; r < 16; r++) {
-        const int i = wrow(r, h);
-        if (i < mrem) {
-          const int k = i0 + i;
+        const int k = i0 + wrow(r, h);
+        if (k < T.m) {
           const int pk = k / S.b_kb;
-          acc[bj][r] += S.s * B[(int64_t)pk * S.b_pk + (int64_t)(k - pk * S.b_kb) * S.b_k + bo];
+          acc[b][r] += S.s * B[(int64_t)pk * S.b_pk + (int64_t)(k - pk * S.b_kb) * S.b_k + bo];
         }
       }
     }
@@ -744,6 +752,7 @@ __device__ __forceinline__ void wide_split(const Tile &T, const Seg *__restrict_
     // loads straight into LDS.
     typedef unsigned int v4u __attribute__((ext_vector_type(4)));
     auto load = [&](int qi, int k0, int op, v4u *pre) {
+      if (32 * lb >= (op ? T.n - T.j0 : T.m - T.i0)) return;   // block outside the output
       CSegS &Q = cs[T.seg0 + qi];
       const int buf = op ? Q.b_buf : Q.a_buf;
       const char *X = (const char *)(bufs.data[buf] + (op ? Q.b_off : Q.a_off) * NS);   // see item_split
@@ -761,58 +770,64 @@ __device__ __forceinline__ void wide_split(const Tile &T, const Seg *__restrict_
     };
     // ... and from registers into LDS stage st, in the MFMA operand layout
     auto store = [&](int op, const v4u *pre, char *st) {
+      if (32 * lb >= (op ? T.n - T.j0 : T.m - T.i0)) return;
       int ln;
       asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(ln));
       for (int t = 0; t < NS; t++)
         *(v4u *)(st + (8 * NS * op + (2 * lb + lkh) * NS + t) * 1024 + 16 * ln) = pre[t];
     };
     v16f q[2][slice_groups(NS)];
-    for (int bj = 0; bj < 2; bj++)
-      for (int g = 0; g < slice_groups(NS); g++) q[bj][g] = (v16f){};
-    // one K half kh of this step's products from stage st: the row block's A
-    // slices, then per column block its B slices one at a time (slice u
+    for (int b = 0; b < 2; b++)
+      for (int g = 0; g < slice_groups(NS); g++) q[b][g] = (v16f){};
+    // one K half kh of this step's products from stage st: per block the row
+    // block's A slices (those of the block before if it is the same), then
+    // the column block's B slices one at a time (slice u
     // meets A slices t <= NS - 1 - u), the next one read while the MFMAs of
     // the current one run; so only five A and two B operands are in registers
     auto compute = [&](const char *st, int k0, int K, int kh) {
       v8bf a[NS];
-      for (int t = 0; t < NS; t++) a[t] = *(const lv8ptr)(st + ((2 * wr + kh) * NS + t) * 1024 + 16 * lane);
-      if (k0 + 32 > K && k0 + 16 * kh + 8 * h >= K)   // only a segment's last step has such lanes
-        for (int t = 0; t < NS; t++) a[t] = (v8bf){};
-      for (int bj = 0; bj < 2; bj++) {
-        const char *bs = st + (8 * NS + (2 * (2 * wc + bj) + kh) * NS) * 1024 + 16 * lane;
-        v8bf b = *(const lv8ptr)bs;
+#pragma unroll
+      for (int b = 0; b < 2; b++) {
+        if (b >= nb) continue;
+        if (b == 0 || br[1] != br[0]) {
+          for (int t = 0; t < NS; t++) a[t] = *(const lv8ptr)(st + ((2 * br[b] + kh) * NS + t) * 1024 + 16 * lane);
+          if (k0 + 32 > K && k0 + 16 * kh + 8 * h >= K)   // only a segment's last step has such lanes
+            for (int t = 0; t < NS; t++) a[t] = (v8bf){};
+        }
+        const char *bs = st + (8 * NS + (2 * bc[b] + kh) * NS) * 1024 + 16 * lane;
+        v8bf x = *(const lv8ptr)bs;
 #pragma unroll
         for (int u = 0; u < NS; u++) {
-          const v8bf bn = u + 1 < NS ? *(const lv8ptr)(bs + (u + 1) * 1024) : b;
+          const v8bf xn = u + 1 < NS ? *(const lv8ptr)(bs + (u + 1) * 1024) : x;
 #pragma unroll
           for (int t = 0; t + u < NS; t++)
-            q[bj][sgroup<NS>(t + u)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t], b, q[bj][sgroup<NS>(t + u)], 0, 0, 0);
-          b = bn;
+            q[b][sgroup<NS>(t + u)] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[t], x, q[b][sgroup<NS>(t + u)], 0, 0, 0);
+          x = xn;
         }
       }
     };
     // segment descriptors are read where needed (wave-uniform, scalar loads)
     // rather than copied, so that they never sit in scratch memory
-    // fold into FP64 with the scale exponents of this lane's two columns and 16
-    // rows, read here (the exponent arrays hold WIDE_EDGE spare entries, so
+    // fold into FP64 with the scale exponents of this lane's column and 16 rows
+    // per block, read here (the exponent arrays hold WIDE_EDGE spare entries, so
     // the lines past the output read in bounds; their outputs are never
     // stored).  Exponents are in [-1100, 1100] or the all-zero sentinel, which
     // only meets zero sums: int16 keeps every sum of two in range.
     auto fold = [&]() {
       CSegS &Q = cs[T.seg0 + si];
       const double sc = cg[T.seg0 + si].s;
-      const int32_t *ea = bufs.exps[Q.a_buf] + Q.a_exp + (i0 + 4 * h);
-      const int32_t *eb = bufs.exps[Q.b_buf] + Q.b_exp + (j0 + c32);
-      const int f0 = (int16_t)eb[0], f1 = (int16_t)eb[32];
-      for (int r = 0; r < 16; r++) {
-        const int er = (int16_t)ea[8 * (r >> 2) + (r & 3)];
-        for (int bj = 0; bj < 2; bj++) {
-          const double x = fold_groups<slice_groups(NS)>(q[bj], r);
-          acc[bj][r] += sc * ldexp(x, er + (bj ? f1 : f0) - 2 * SLICE_BITS);
+#pragma unroll
+      for (int b = 0; b < 2; b++) {
+        if (b >= nb) continue;
+        const int32_t *ea = bufs.exps[Q.a_buf] + Q.a_exp + (T.i0 + 32 * br[b] + 4 * h);
+        const int f = (int16_t)bufs.exps[Q.b_buf][Q.b_exp + (T.j0 + 32 * bc[b] + c32)];
+        for (int r = 0; r < 16; r++) {
+          const int er = (int16_t)ea[8 * (r >> 2) + (r & 3)];
+          const double x = fold_groups<slice_groups(NS)>(q[b], r);
+          acc[b][r] += sc * ldexp(x, er + f - 2 * SLICE_BITS);
         }
+        for (int g = 0; g < slice_groups(NS); g++) q[b][g] = (v16f){};
       }
-      for (int bj = 0; bj < 2; bj++)
-        for (int g = 0; g < slice_groups(NS); g++) q[bj][g] = (v16f){};
     };
     {
       v4u pre[NS];
@@ -857,30 +872,31 @@ __device__ __forceinline__ void wide_split(const Tile &T, const Seg *__restrict_
     }
   }
   double *C = const_cast<double *>(sbase_ptr(T.c_base, bases, psi, y, work, part)) + T.c_off;
-  const int ci0 = T.ci0 + 32 * wr, cj0 = T.cj0 + 64 * wc;
-  for (int bj = 0; bj < 2; bj++)
+  for (int b = 0; b < nb; b++) {
+    const int i0 = T.i0 + 32 * br[b], j = T.j0 + 32 * bc[b] + c32;
+    const int ci0 = T.ci0 + 32 * br[b], cj = T.cj0 + 32 * bc[b] + c32;
     for (int r = 0; r < 16; r++) {
-      const int i = wrow(r, h), j = 32 * bj + c32;
-      if (i < mrem && j < nrem) {
-        double *c = T.rowmajor ? C + (int64_t)(ci0 + i) * T.ldc + (cj0 + j)
-                               : C + (int64_t)(ci0 + i) + (int64_t)(cj0 + j) * T.ldc;
-        *c = T.accumulate ? *c + acc[bj][r] : acc[bj][r];
+      const int i = wrow(r, h);
+      if (i0 + i < T.m && j < T.n) {
+        double *c = T.rowmajor ? C + (int64_t)(ci0 + i) * T.ldc + cj : C + (int64_t)(ci0 + i) + (int64_t)cj * T.ldc;
+        *c = T.accumulate ? *c + (b ? acc[1][r] : acc[0][r]) : b ? acc[1][r] : acc[0][r];
       }
     }
+  }
   // first-stage tiles: exponent of every stripe column written (see item_split)
   CSegS &Q0 = cs[T.seg0];
   if (Q0.t_exp >= 0) {
     int32_t *ex = bufs.exps[SBUF_T] + Q0.t_exp;
-    for (int bj = 0; bj < 2; bj++) {
-      const int j = 32 * bj + c32;
+    for (int b = 0; b < nb; b++) {
+      const int i0 = T.i0 + 32 * br[b], j = T.j0 + 32 * bc[b] + c32;
       double m = 0.0;
       for (int r = 0; r < 16; r++)
-        if (wrow(r, h) < mrem && j < nrem) m = fmax(m, fabs(acc[bj][r]));
+        if (i0 + wrow(r, h) < T.m && j < T.n) m = fmax(m, fabs(b ? acc[1][r] : acc[0][r]));
       m = fmax(m, __shfl_xor(m, 32));
-      if (h == 0 && j < nrem && m > 0.0) {
+      if (h == 0 && j < T.n && m > 0.0) {
         int e2;
         const double mant = frexp(m, &e2);
-        atomicMax(ex + (cj0 + j) % Q0.t_nb, mant == 0.5 ? e2 - 1 : e2);
+        atomicMax(ex + (T.cj0 + 32 * bc[b] + c32) % Q0.t_nb, mant == 0.5 ? e2 - 1 : e2);
       }
     }
   }
