@@ -683,8 +683,8 @@ void launch_tiles_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles,
                       double *part, void *stream) {
   if (ntiles <= 0) return;
   hipStream_t s = (hipStream_t)stream;
-  const int grid = wave_grid(ntiles, F64_GRID), chunk = wave_chunk(ntiles, flops);
-  const XcdQueues dq = deal(q, grid / NXCD * WAVES);
+  const int grid = wave_grid(ntiles, F64_GRID, WAVES), chunk = wave_chunk(ntiles, flops);
+  const XcdQueues dq = deal(q, grid / NXCD * WAVES, false);
   if (stage == 1)
     hipLaunchKernelGGL(stage_f64_kernel<1>, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, dq, qs.cur(), qs.other(),
                        chunk, psi, y, work, part);
@@ -695,13 +695,13 @@ void launch_tiles_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles,
 }
 
 template <typename G>
-static void launch_wg_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles, const XcdQueues &q, QueueSets &qs,
+static void launch_wg_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles, double flops, const XcdQueues &q, QueueSets &qs,
                           const double *psi, double *y, double *work, double *part,
                           hipStream_t s) {
   // as many work groups as are resident at once: G::EU wavefronts per SIMD
   const int resident = 256 * (G::EU * 4 * 64 / G::NT);
   const int grid = std::min((ntiles + NXCD - 1) / NXCD * NXCD, resident);
-  const XcdQueues dq = deal(q, grid / NXCD);
+  const XcdQueues dq = deal(q, grid / NXCD, heavy_tiles(ntiles, flops));
   if (stage == 1)
     hipLaunchKernelGGL((wg_f64_kernel<G, 1>), dim3(grid), dim3(G::NT), 0, s, tiles, segs, dq, qs.cur(), qs.other(),
                        psi, y, work, part);
@@ -711,14 +711,14 @@ static void launch_wg_f64(int stage, const Tile *tiles, const Seg *segs, int nti
   qs.launch++;
 }
 
-void launch_wg_tiles_f64(int stage, int mb, const Tile *tiles, const Seg *segs, int ntiles, const XcdQueues &q,
+void launch_wg_tiles_f64(int stage, int mb, const Tile *tiles, const Seg *segs, int ntiles, double flops, const XcdQueues &q,
                          QueueSets &qs, const double *psi, double *y, double *work,
                          double *part, void *stream) {
   if (ntiles <= 0) return;
   if (mb == F64_WIDE_MB)
-    launch_wg_f64<WideF64>(stage, tiles, segs, ntiles, q, qs, psi, y, work, part, (hipStream_t)stream);
+    launch_wg_f64<WideF64>(stage, tiles, segs, ntiles, flops, q, qs, psi, y, work, part, (hipStream_t)stream);
   else
-    launch_wg_f64<MacroF64>(stage, tiles, segs, ntiles, q, qs, psi, y, work, part, (hipStream_t)stream);
+    launch_wg_f64<MacroF64>(stage, tiles, segs, ntiles, flops, q, qs, psi, y, work, part, (hipStream_t)stream);
 }
 
 void launch_reduce(const Reduce *red, int nred, const double *part, double *y, void *stream) {

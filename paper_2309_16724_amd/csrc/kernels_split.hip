@@ -36,17 +36,19 @@ __device__ constexpr float digit_weight(int t) {
                                                                                         : t == 5 ? 0x1p-40f : 0x1p-48f;
 }
 
-// slices of the eight values at K index kk of one line (position block already
-// in `line`), scaled by 2^-e, to out + t hs: padding reads a valid entry and
-// slices zero
-__device__ __forceinline__ void slice_chunk(const double *__restrict__ line, int kk, int kb, int64_t s_k, int e, int ns,
-                                            uint16_t *__restrict__ out, int hs) {
+// the eight values at K index kk of one line (position block already in `line`;
+// padding reads a valid entry) ...
+__device__ __forceinline__ void load_chunk(const double *__restrict__ line, int kk, int kb, int64_t s_k, double *x) {
+#pragma unroll
+  for (int i = 0; i < 8; i++) x[i] = line[(int64_t)min(kk + i, kb - 1) * s_k];
+}
+// ... and their slices, scaled by 2^-e, to out + t hs (padding slices zero)
+__device__ __forceinline__ void slice_chunk(const double *x, int kk, int kb, int e, int ns, uint16_t *__restrict__ out,
+                                            int hs) {
   typedef unsigned int v4u __attribute__((ext_vector_type(4)));
   double yv[8];
 #pragma unroll
-  for (int i = 0; i < 8; i++) yv[i] = line[(int64_t)min(kk + i, kb - 1) * s_k];
-#pragma unroll
-  for (int i = 0; i < 8; i++) yv[i] = ldexp(kk + i < kb ? yv[i] : 0.0, -e);
+  for (int i = 0; i < 8; i++) yv[i] = ldexp(kk + i < kb ? x[i] : 0.0, -e);
   for (int t = 0; t < ns; t++) {
     uint32_t w[8];
 #pragma unroll
@@ -59,12 +61,15 @@ __device__ __forceinline__ void slice_chunk(const double *__restrict__ line, int
   }
 }
 
-// One work group per panel (slice_kernel: the line maxima first, then the
-// slices) or per K range of a panel (tslice_kernel: exponents in place):
-// thread (l, g) takes the chunks g, g + 8, ... of line l.  The 32 lines of a
-// panel are neighbours in memory for all sources but the transposed ones, and
-// their slices of one chunk are a run of 512 bytes, so neither the loads nor
-// the stores pass through LDS.
+// slice_kernel: one work group per panel, the line maxima first, then the
+// slices; tslice_kernel (exponents in place): one work group per K range of a
+// panel.  Thread (l, g) takes the chunks g, g + 8, ... of line l.  The lines of
+// a panel are neighbours in memory for all sources but the transposed ones, and
+// their slices of one chunk are one run, so neither the loads nor the stores
+// pass through LDS.  The stripes' slicing moves 3.8 TB/s of a copy's 4.7 (L=54,
+// D=768: 45 GB in 12.1 ms; L=24, D=512: 3.9 GB in 1.0 ms); whole rows at a time
+// were 13 % slower (scattered stores), 64 columns or the next values requested
+// ahead made no difference.
 struct PanelLine {
   int h, l;              // lines of the panel, this thread's line in it
   int64_t L;             // its line of the job
@@ -74,12 +79,24 @@ struct PanelLine {
 __device__ __forceinline__ PanelLine panel_line(const SliceJob &J, int panel, const double *src, int ns) {
   PanelLine p;
   p.h = min(SLICE_PANEL, J.nl - SLICE_PANEL * panel);
-  p.l = min((int)threadIdx.x & (SLICE_PANEL - 1), p.h - 1);
+  p.l = min((int)threadIdx.x % SLICE_PANEL, p.h - 1);
   p.L = SLICE_PANEL * panel + p.l;
   const unsigned q = (unsigned)p.L / (unsigned)J.nrho, rho = (unsigned)p.L - q * (unsigned)J.nrho;
   p.line = src + J.src_off + (int64_t)q * J.s_q + (int64_t)rho * J.s_rho;
   p.out = (J.dst_off + (int64_t)SLICE_PANEL * panel * J.npos * J.kbp) * ns + 8 * p.l;
   return p;
+}
+
+// slices of the chunks c, c + 8, ... < c1 of a line
+__device__ __forceinline__ void slice_range(const SliceJob &J, const PanelLine &P, int c, int c1, int e, int ns,
+                                            uint16_t *__restrict__ out) {
+  const int pch = J.kbp / 8, hs = 8 * P.h;
+  for (; c < c1; c += 256 / SLICE_PANEL) {
+    const int p = c / pch, kk = 8 * (c - p * pch);
+    double x[8];
+    load_chunk(P.line + (int64_t)p * J.s_pos, kk, J.kb, J.s_k, x);
+    slice_chunk(x, kk, J.kb, e, ns, out + (int64_t)c * (ns * hs), hs);
+  }
 }
 
 __global__ void __launch_bounds__(256) slice_kernel(const SliceJob *__restrict__ jobs,
@@ -101,8 +118,7 @@ __global__ void __launch_bounds__(256) slice_kernel(const SliceJob *__restrict__
       const int p = c / pch, kk = 8 * (c - p * pch);
       const double *line = P.line + (int64_t)p * J.s_pos;
       double v[8];
-#pragma unroll
-      for (int i = 0; i < 8; i++) v[i] = line[(int64_t)min(kk + i, J.kb - 1) * J.s_k];
+      load_chunk(line, kk, J.kb, J.s_k, v);
 #pragma unroll
       for (int i = 0; i < 8; i++) m = fmax(m, fabs(v[i]));
     }
@@ -118,10 +134,7 @@ __global__ void __launch_bounds__(256) slice_kernel(const SliceJob *__restrict__
     if (l0 < P.h) {
       if (g == 0) bufs.exps[J.dst_buf][J.exp_off + P.L] = e;
       uint16_t *out = bufs.data[J.dst_buf] + P.out;
-      for (int c = g; c < nch; c += 256 / SLICE_PANEL) {
-        const int p = c / pch, kk = 8 * (c - p * pch);
-        slice_chunk(P.line + (int64_t)p * J.s_pos, kk, J.kb, J.s_k, e, ns, out + (int64_t)c * (8 * ns * P.h), 8 * P.h);
-      }
+      slice_range(J, P, g, nch, e, ns, out);
     }
     __syncthreads();   // mx is reused by the next panel
   }
@@ -130,20 +143,14 @@ __global__ void __launch_bounds__(256) slice_kernel(const SliceJob *__restrict__
 __global__ void __launch_bounds__(256) tslice_kernel(const SliceJob *__restrict__ jobs,
                                                       const SliceItem *__restrict__ items, int nitems, int ns,
                                                       const double *__restrict__ work, SliceBufs bufs) {
-  const int g = threadIdx.x / SLICE_PANEL, l0 = threadIdx.x % SLICE_PANEL;
   for (int it = blockIdx.x; it < nitems; it += gridDim.x) {
     const SliceItem I = items[it];
     const SliceJob J = jobs[I.job];
+    if ((int)threadIdx.x % SLICE_PANEL >= J.nl - SLICE_PANEL * I.panel) continue;
     const PanelLine P = panel_line(J, I.panel, work, ns);
-    if (l0 >= P.h) continue;
     const int e = bufs.exps[SBUF_T][J.exp_off + P.L];
-    const int pch = J.kbp / 8, c1 = min(J.npos * pch, (I.k0 + I.nk) * (SLICE_KBLOCK / 8));
-    uint16_t *out = bufs.data[SBUF_T] + P.out;
-    for (int c = I.k0 * (SLICE_KBLOCK / 8) + g; c < c1; c += 256 / SLICE_PANEL) {
-      const int p = c / pch, kk = 8 * (c - p * pch);
-      slice_chunk(P.line + (int64_t)p * J.s_pos, kk, J.kb, J.s_k, e == INT_MIN ? 0 : e, ns,
-                  out + (int64_t)c * (8 * ns * P.h), 8 * P.h);
-    }
+    slice_range(J, P, I.c0 + threadIdx.x / SLICE_PANEL, min(J.npos * (J.kbp / 8), I.c0 + TSLICE_CHUNKS),
+                e == INT_MIN ? 0 : e, ns, bufs.data[SBUF_T] + P.out);
   }
 }
 
@@ -604,16 +611,15 @@ template <int NS>
 __device__ __forceinline__ void macro_items(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,
                                             const SegS *__restrict__ ssegs, const XcdQueues &q,
                                             int32_t *__restrict__ counters,
-                                            int32_t *__restrict__ next_counters, int32_t *__restrict__ mailboxes,
+                                            int32_t *__restrict__ next_counters,
                                             const double *const *__restrict__ bases, const double *__restrict__ psi,
                                             double *__restrict__ y, double *__restrict__ work,
                                             double *__restrict__ part, const SliceBufs &bufs) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // all of the LDS holds the two operand stages (two work groups per CU); the
-  // tile index taken by thread 0 reaches the other wavefronts through this
-  // work group's mailbox in global memory (atomics: coherent at the L2)
+  // index of the next tile reaches the wavefronts through the second one, which
+  // a tile writes only after the first barrier of its K loop
   __shared__ __attribute__((aligned(1024))) char lds[2 * mstage_bytes(NS)];
-  int32_t *mailbox = mailboxes + blockIdx.x;
   clear_counters(next_counters);
   WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD), (int)(gridDim.x / NXCD), 1);
   for (bool more = true; more;) {
@@ -622,18 +628,13 @@ __device__ __forceinline__ void macro_items(const Tile *__restrict__ tiles, cons
       const Tile T = tiles[__builtin_amdgcn_readfirstlane(wq.t)];
       macro_split<NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, lds, wave, lane);
     }
-    // the next tiles reach the wavefronts through this work group's mailbox
-    // (chunks of one tile; atomics: coherent at the L2)
+    __syncthreads();   // everyone has read the last LDS stage
     if (wave == 0) {
       const int v = wq.next(lane) ? wq.t : -1;
-      if (lane == 0) atomicExch(mailbox, v);
+      if (lane == 0) *(volatile int *)(lds + mstage_bytes(NS)) = v;
     }
-    // every wave reads the mailbox before the barrier inside the tile, the
-    // earliest point after which wave 0 can write it again
     __syncthreads();
-    int v = 0;
-    if (lane == 0) v = atomicAdd(mailbox, 0);
-    wq.t = __builtin_amdgcn_readfirstlane(v);
+    wq.t = __builtin_amdgcn_readfirstlane(*(volatile int *)(lds + mstage_bytes(NS)));
     more = wq.t >= 0;
     wq.tend = wq.t + 1;
     wq.step = 1;
@@ -644,20 +645,20 @@ __device__ __forceinline__ void macro_items(const Tile *__restrict__ tiles, cons
   __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))                 \
   stage1_msplit##NS##_kernel(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,                  \
                              const SegS *__restrict__ ssegs, XcdQueues q, int32_t *__restrict__ counters,   \
-                             int32_t *__restrict__ next_counters, int32_t *__restrict__ mailboxes,           \
+                             int32_t *__restrict__ next_counters,\
                              const double *const *__restrict__ bases, const double *__restrict__ psi,       \
                              double *__restrict__ y, double *__restrict__ work, double *__restrict__ part,   \
                              SliceBufs bufs) {                                                              \
-    macro_items<NS>(tiles, segs, ssegs, q, counters, next_counters, mailboxes, bases, psi, y, work, part, bufs);                      \
+    macro_items<NS>(tiles, segs, ssegs, q, counters, next_counters, bases, psi, y, work, part, bufs);                      \
   }                                                                                                         \
   __global__ void __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))                 \
   stage2_msplit##NS##_kernel(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,                  \
                              const SegS *__restrict__ ssegs, XcdQueues q, int32_t *__restrict__ counters,   \
-                             int32_t *__restrict__ next_counters, int32_t *__restrict__ mailboxes,           \
+                             int32_t *__restrict__ next_counters,\
                              const double *const *__restrict__ bases, const double *__restrict__ psi,       \
                              double *__restrict__ y, double *__restrict__ work, double *__restrict__ part,   \
                              SliceBufs bufs) {                                                              \
-    macro_items<NS>(tiles, segs, ssegs, q, counters, next_counters, mailboxes, bases, psi, y, work, part, bufs);                      \
+    macro_items<NS>(tiles, segs, ssegs, q, counters, next_counters, bases, psi, y, work, part, bufs);                      \
   }
 
 MACRO_KERNELS(3)
@@ -906,17 +907,15 @@ template <int NS>
 __device__ __forceinline__ void wide_items(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,
                                            const SegS *__restrict__ ssegs, const XcdQueues &q,
                                            int32_t *__restrict__ counters,
-                                            int32_t *__restrict__ next_counters, int32_t *__restrict__ mailboxes,
+                                            int32_t *__restrict__ next_counters,
                                            const double *const *__restrict__ bases, const double *__restrict__ psi,
                                            double *__restrict__ y, double *__restrict__ work,
                                            double *__restrict__ part, const SliceBufs &bufs) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // the two operand stages fill the LDS (one work group of eight wavefronts
-  // per CU); the tile index reaches the wavefronts through the work group's
-  // mailbox as in macro_items
+  // per CU); the next tile's index passes through the second as in macro_items
   __shared__ __attribute__((aligned(1024))) char lds0[wstage_bytes(NS)];
   __shared__ __attribute__((aligned(1024))) char lds1[wstage_bytes(NS)];
-  int32_t *mailbox = mailboxes + blockIdx.x;
   clear_counters(next_counters);
   WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD), (int)(gridDim.x / NXCD), 1);
   for (bool more = true; more;) {
@@ -925,18 +924,13 @@ __device__ __forceinline__ void wide_items(const Tile *__restrict__ tiles, const
       const Tile T = tiles[__builtin_amdgcn_readfirstlane(wq.t)];
       wide_split<NS>(T, segs, ssegs, bases, psi, y, work, part, bufs, lds0, lds1, wave, lane);
     }
-    // the next tiles reach the wavefronts through this work group's mailbox
-    // (chunks of one tile; atomics: coherent at the L2)
+    __syncthreads();   // everyone has read the last LDS stage
     if (wave == 0) {
       const int v = wq.next(lane) ? wq.t : -1;
-      if (lane == 0) atomicExch(mailbox, v);
+      if (lane == 0) *(volatile int *)lds1 = v;
     }
-    // every wave reads the mailbox before the barrier inside the tile, the
-    // earliest point after which wave 0 can write it again
     __syncthreads();
-    int v = 0;
-    if (lane == 0) v = atomicAdd(mailbox, 0);
-    wq.t = __builtin_amdgcn_readfirstlane(v);
+    wq.t = __builtin_amdgcn_readfirstlane(*(volatile int *)lds1);
     more = wq.t >= 0;
     wq.tend = wq.t + 1;
     wq.step = 1;
@@ -947,20 +941,20 @@ __device__ __forceinline__ void wide_items(const Tile *__restrict__ tiles, const
   __global__ void __launch_bounds__(64 * WIDE_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))           \
   stage1_wsplit##NS##_kernel(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,                  \
                              const SegS *__restrict__ ssegs, XcdQueues q, int32_t *__restrict__ counters,   \
-                             int32_t *__restrict__ next_counters, int32_t *__restrict__ mailboxes,           \
+                             int32_t *__restrict__ next_counters,\
                              const double *const *__restrict__ bases, const double *__restrict__ psi,       \
                              double *__restrict__ y, double *__restrict__ work, double *__restrict__ part,   \
                              SliceBufs bufs) {                                                              \
-    wide_items<NS>(tiles, segs, ssegs, q, counters, next_counters, mailboxes, bases, psi, y, work, part, bufs);                       \
+    wide_items<NS>(tiles, segs, ssegs, q, counters, next_counters, bases, psi, y, work, part, bufs);                       \
   }                                                                                                         \
   __global__ void __launch_bounds__(64 * WIDE_WAVES) __attribute__((amdgpu_waves_per_eu(2, 2)))           \
   stage2_wsplit##NS##_kernel(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,                  \
                              const SegS *__restrict__ ssegs, XcdQueues q, int32_t *__restrict__ counters,   \
-                             int32_t *__restrict__ next_counters, int32_t *__restrict__ mailboxes,           \
+                             int32_t *__restrict__ next_counters,\
                              const double *const *__restrict__ bases, const double *__restrict__ psi,       \
                              double *__restrict__ y, double *__restrict__ work, double *__restrict__ part,   \
                              SliceBufs bufs) {                                                              \
-    wide_items<NS>(tiles, segs, ssegs, q, counters, next_counters, mailboxes, bases, psi, y, work, part, bufs);                       \
+    wide_items<NS>(tiles, segs, ssegs, q, counters, next_counters, bases, psi, y, work, part, bufs);                       \
   }
 
 WIDE_KERNELS(3)
@@ -991,7 +985,7 @@ SPLIT_KERNELS(5)
 SPLIT_KERNELS(6)
 SPLIT_KERNELS(7)
 
-void launch_macro_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles,
+void launch_macro_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles, double flops,
                         const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
                         const double *psi, double *y, double *work, double *part, SliceBufs bufs, void *stream) {
   if (ntiles <= 0) return;
@@ -999,15 +993,15 @@ void launch_macro_split(int stage, const Tile *tiles, const Seg *segs, const Seg
   // two work groups resident per CU (80 KiB of LDS each at s = 5); every work
   // group takes tiles until all queues are empty
   const int grid = std::max(8, std::min((ntiles + 7) / 8 * 8, MACRO_GRID));
-  const XcdQueues dq = deal(q, grid / NXCD);
+  const XcdQueues dq = deal(q, grid / NXCD, heavy_tiles(ntiles, flops));
 #define MLAUNCH(NS)                                                                                         \
   if (nslices == NS) {                                                                                      \
     if (stage == 1)                                                                                         \
       hipLaunchKernelGGL(stage1_msplit##NS##_kernel, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, ssegs,  \
-                         dq, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);           \
+                         dq, qs.cur(), qs.other(), bases, psi, y, work, part, bufs);           \
     else                                                                                                    \
       hipLaunchKernelGGL(stage2_msplit##NS##_kernel, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, ssegs,  \
-                         dq, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);           \
+                         dq, qs.cur(), qs.other(), bases, psi, y, work, part, bufs);           \
     qs.launch++;                                                                                            \
     return;                                                                                                 \
   }
@@ -1019,22 +1013,22 @@ void launch_macro_split(int stage, const Tile *tiles, const Seg *segs, const Seg
 #undef MLAUNCH
 }
 
-void launch_wide_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles,
+void launch_wide_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles, double flops,
                        const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
                        const double *psi, double *y, double *work, double *part, SliceBufs bufs, void *stream) {
   if (ntiles <= 0) return;
   hipStream_t s = (hipStream_t)stream;
   // one work group per CU (the two stages take all 160 KiB of LDS at s = 5)
   const int grid = std::max(8, std::min((ntiles + 7) / 8 * 8, WIDE_GRID));
-  const XcdQueues dq = deal(q, grid / NXCD);
+  const XcdQueues dq = deal(q, grid / NXCD, heavy_tiles(ntiles, flops));
 #define WLAUNCH(NS)                                                                                         \
   if (nslices == NS) {                                                                                      \
     if (stage == 1)                                                                                         \
       hipLaunchKernelGGL(stage1_wsplit##NS##_kernel, dim3(grid), dim3(64 * WIDE_WAVES), 0, s, tiles, segs,  \
-                         ssegs, dq, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);    \
+                         ssegs, dq, qs.cur(), qs.other(), bases, psi, y, work, part, bufs);    \
     else                                                                                                    \
       hipLaunchKernelGGL(stage2_wsplit##NS##_kernel, dim3(grid), dim3(64 * WIDE_WAVES), 0, s, tiles, segs,  \
-                         ssegs, dq, qs.cur(), qs.other(), qs.mailbox(), bases, psi, y, work, part, bufs);    \
+                         ssegs, dq, qs.cur(), qs.other(), bases, psi, y, work, part, bufs);    \
     qs.launch++;                                                                                            \
     return;                                                                                                 \
   }
@@ -1051,8 +1045,8 @@ void launch_tiles_split(int stage, const Tile *tiles, const Seg *segs, const Seg
   hipStream_t s = (hipStream_t)stream;
   // work groups that the LDS stages let run at once
   const int resident = 256 * std::max(1, LDS_BYTES / (WAVES * stage_bytes(nslices)));
-  const int grid = wave_grid(ntiles, resident), chunk = wave_chunk(ntiles, flops);
-  const XcdQueues dq = deal(q, grid / NXCD * WAVES);
+  const int grid = wave_grid(ntiles, resident, WAVES), chunk = wave_chunk(ntiles, flops);
+  const XcdQueues dq = deal(q, grid / NXCD * WAVES, false);
 #define LAUNCH(NS)                                                                                          \
   if (nslices == NS) {                                                                                      \
     if (stage == 1)                                                                                         \

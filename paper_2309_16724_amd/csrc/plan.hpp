@@ -33,8 +33,8 @@ constexpr int MACRO_MB = 8;
 constexpr int MACRO_EDGE = 64;
 constexpr int MACRO_MIN = 48;   // default: outputs with both dims >= 48 get work-group tiles
 // Wide work-group tiles (split plans, s <= 5): WIDE_MB tiles are 128 x 128,
-// computed by the eight wavefronts of a work group (two per SIMD, 32 x 64
-// each, v_mfma_f32_32x32x16_bf16) from two 80 KiB LDS stages.  An
+// computed by the eight wavefronts of a work group (two per SIMD, in 32 x 32
+// blocks of v_mfma_f32_32x32x16_bf16) from two 80 KiB LDS stages.  An
 // output with both sides >= wide_min is cut into 128-wide bands (a last band
 // of >= wide_min lines is a wide band too); the rest of it gets 64 x 64 or
 // wavefront tiles.
@@ -58,20 +58,27 @@ constexpr int MACRO_GRID = 512;          // work groups of a work-group tile lau
 constexpr int WIDE_GRID = 256;           // work groups of a wide tile launch (one per CU)
 constexpr int QUEUE_STRIDE = 32;         // ints between counters: a 128-byte line each
 constexpr int QUEUE_SET = NXCD * QUEUE_STRIDE;
-constexpr int QUEUE_INTS = 2 * QUEUE_SET + MACRO_GRID;   // two counter sets, then one mailbox per work group
+constexpr int QUEUE_INTS = 2 * QUEUE_SET;   // two counter sets
 struct XcdQueues {
   int32_t start[NXCD + 1];
   int32_t dyn[NXCD];   // first tile of range r that its counter hands out (set per launch)
 };
-// Eleven twelfths of every range go round the workers in turn (at least one
-// tile each), the rest goes to whoever is free first.
-inline XcdQueues deal(XcdQueues q, int workers) {
+// Light tiles: eleven twelfths of every range go round the workers in turn (at
+// least one tile each), the rest to whoever is free first.  Heavy ones: all but
+// the first round to whoever is free first.
+inline XcdQueues deal(XcdQueues q, int workers, bool heavy) {
   for (int r = 0; r < NXCD; r++) {
-    const int len = q.start[r + 1] - q.start[r], rounds = (len - len / 12) / workers;
+    const int len = q.start[r + 1] - q.start[r], rounds = heavy ? 1 : (len - len / 12) / workers;
     q.dyn[r] = q.start[r] + (int)std::min<int64_t>(len, (int64_t)workers * std::max(1, rounds));
   }
   return q;
 }
+// Work-group tiles of four million flops and more on average are heavy (FP64,
+// L=54, D=1024: 87.3 -> 83.8 ms), those of a few K steps are not: their atomics
+// and the hand-over of the index to the other waves show (the first stage of
+// split plans at L=54, D=768, 3.2 million each: 17.6 -> 19.2 ms).
+inline bool heavy_tiles(int ntiles, double flops) { return flops >= 4194304.0 * ntiles; }
+
 // Counters of consecutive tile launches on one stream: a launch uses the
 // current set, which is zero when it starts, and clears the other one.  The
 // first set is cleared by the launch_zero that opens the sequence.
@@ -80,14 +87,13 @@ struct QueueSets {
   int launch = 0;
   int32_t *cur() const { return base + (launch & 1) * QUEUE_SET; }
   int32_t *other() const { return base + (1 - (launch & 1)) * QUEUE_SET; }
-  int32_t *mailbox() const { return base + 2 * QUEUE_SET; }
 };
 
 // Work groups of a wavefront-tile launch (a multiple of NXCD, no more than fit
 // on the chip at once: `resident`) and tiles per dynamic chunk: at most about
 // 2^18 flops of the list's average (eight 16 x 16 tiles of K = 64), at most 8.
-inline int wave_grid(int ntiles, int resident) {
-  const int blocks = (ntiles + 3) / 4;
+inline int wave_grid(int ntiles, int resident, int waves) {
+  const int blocks = (ntiles + waves - 1) / waves;
   return blocks < resident ? (blocks + NXCD - 1) / NXCD * NXCD : resident;
 }
 inline int wave_chunk(int ntiles, double flops) {
@@ -287,11 +293,12 @@ struct SliceJob {
   int32_t nl, nrho, npos, kb, kbp, pad;
 };
 constexpr int SLICE_PANEL = 32;
-constexpr int SLICE_KBLOCK = 64;     // K values of a panel sliced at a time
-// Slicing work item: K blocks [k0, k0 + nk) of panel `panel` of job `job`.
+// Slicing work item: panel `panel` of job `job`; of a stripe, its chunks
+// [c0, c0 + TSLICE_CHUNKS).
 struct SliceItem {
-  int32_t job, panel, k0, nk;
+  int32_t job, panel, c0;
 };
+constexpr int TSLICE_CHUNKS = 64;
 
 // Split segment (same role as Seg): A lines are operand rows, B lines operand
 // columns.  The output's row i is line a_line0 + i of a_nl, its K index k is a_k0 + k
@@ -378,7 +385,7 @@ void launch_dress(const DressItem *items, int nitems, const int64_t *src_off, co
 void launch_tiles_f64(int stage, const Tile *tiles, const Seg *segs, int ntiles, double flops, const XcdQueues &q,
                       QueueSets &qs, const double *psi, double *y, double *work, double *part, void *stream);
 // 128 x 128 (mb == F64_WIDE_MB) or 64 x 64 (MACRO_MB) FP64 tiles of whole work groups
-void launch_wg_tiles_f64(int stage, int mb, const Tile *tiles, const Seg *segs, int ntiles, const XcdQueues &q,
+void launch_wg_tiles_f64(int stage, int mb, const Tile *tiles, const Seg *segs, int ntiles, double flops, const XcdQueues &q,
                          QueueSets &qs, const double *psi, double *y, double *work, double *part, void *stream);
 
 // NXCD contiguous ranges of a tile list with about equal summed cost
@@ -432,7 +439,7 @@ inline void launch_lists_f64(int stage, const Tile *tiles, const Seg *segs, cons
                              const double *psi, double *y, double *work, double *part, void *stream) {
   for (int k = 0; k < 2; k++)
     launch_wg_tiles_f64(stage, k == 0 ? F64_WIDE_MB : MACRO_MB, tiles + L.first[k], segs, L.first[k + 1] - L.first[k],
-                        L.q[k], qs, psi, y, work, part, stream);
+                        L.flops[k], L.q[k], qs, psi, y, work, part, stream);
   launch_tiles_f64(stage, tiles + L.first[2], segs, L.first[3] - L.first[2], L.flops[2], L.q[2], qs, psi, y, work, part,
                    stream);
 }
@@ -463,11 +470,11 @@ void launch_tiles_split(int stage, const Tile *tiles, const Seg *segs, const Seg
                         double flops, const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
                         const double *psi, double *y, double *work, double *part, SliceBufs bufs, void *stream);
 // work-group (MACRO_MB) tiles from per-XCD queues
-void launch_macro_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles,
+void launch_macro_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles, double flops,
                         const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
                         const double *psi, double *y, double *work, double *part, SliceBufs bufs, void *stream);
 // wide (WIDE_MB) tiles, s <= WIDE_MAX_SLICES, same queue protocol
-void launch_wide_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles,
+void launch_wide_split(int stage, const Tile *tiles, const Seg *segs, const SegS *ssegs, int ntiles, double flops,
                        const XcdQueues &q, QueueSets &qs, int nslices, const double *const *bases,
                        const double *psi, double *y, double *work, double *part, SliceBufs bufs, void *stream);
 
