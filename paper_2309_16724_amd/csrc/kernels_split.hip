@@ -218,93 +218,129 @@ __device__ __forceinline__ uint64_t line_offset(uint32_t L, uint32_t nl, uint32_
   return (uint64_t)(SLICE_PANEL * 2u * NS * p) * ld + 16u * (L % SLICE_PANEL);
 }
 
+// One wavefront tile.  The K steps of all segments are one sequence: the
+// operands of a step go straight from global memory into this wave's LDS stage
+// (one 1 KiB chunk per operand row block and slice, 16 bytes per lane), and the
+// loads of the next step, also across a segment boundary, fly while the MFMAs
+// of this one run without holding a second set of registers.  What bounds it is
+// the latency of that round trip, so as many waves run per CU as their stages
+// fit (SPLIT_WAVES).
 template <int MB, int NS>
 __device__ __forceinline__ void item_split(const Tile &T, const Seg *__restrict__ segs,
                                            const SegS *__restrict__ ssegs, const double *const *bases,
                                            const double *psi, double *y, double *work, double *part,
                                            const SliceBufs &bufs, char *stage, int r16, int q4) {
   constexpr int NB = 4 / MB;
+  constexpr int FOLD = split_fold_k(NS);
+  static_assert(FOLD % 32 == 0, "the K loop folds after whole 32-wide steps");
+  // descriptors: scalar loads
+  const CSegS *cs = (const CSegS *)ssegs + T.seg0;
+  const CSeg *cg = (const CSeg *)segs + T.seg0;
+  asm volatile("" : "+v"(r16), "+v"(q4));   // nothing derived from the lane is kept across tiles
   v4d acc[MB][NB];
   for (int a = 0; a < MB; a++)
     for (int b = 0; b < NB; b++) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
   const int mrem = T.m - T.i0, nrem = T.n - T.j0;
-  for (int si = 0; si < T.nseg; si++) {
-    const Seg S = segs[T.seg0 + si];
-    const SegS Q = ssegs[T.seg0 + si];
-    if (Q.K == 0) {
-      // identity left operator: exact FP64 addition of the FP64 operand
-      const double *B = sbase_ptr(S.b_base, bases, psi, y, work, part) + S.b_off;
-      for (int bi = 0; bi < MB; bi++)
-        for (int bj = 0; bj < NB; bj++) {
-          int jj = 16 * bj + r16;
-          if (jj >= nrem) continue;
-          int n = T.j0 + jj;
-          int pn = n / S.b_nb;
-          int64_t bo = (int64_t)pn * S.b_pn + (int64_t)(n - pn * S.b_nb) * S.b_n;
-          for (int r = 0; r < 4; r++) {
-            int i = 16 * bi + 4 * q4 + r;
-            if (i < mrem) {
-              int k = T.i0 + i;
-              int pk = k / S.b_kb;
-              acc[bi][bj][r] += S.s * B[(int64_t)pk * S.b_pk + (int64_t)(k - pk * S.b_kb) * S.b_k + bo];
-            }
+  // identity left operators (first in the list): exact FP64 additions of the FP64 operand
+  for (int si = 0; si < T.nid; si++) {
+    CSeg &S = cg[si];
+    const double *B = sbase_ptr(S.b_base, bases, psi, y, work, part) + S.b_off;
+    for (int bi = 0; bi < MB; bi++)
+      for (int bj = 0; bj < NB; bj++) {
+        int jj = 16 * bj + r16;
+        if (jj >= nrem) continue;
+        int n = T.j0 + jj;
+        int pn = n / S.b_nb;
+        int64_t bo = (int64_t)pn * S.b_pn + (int64_t)(n - pn * S.b_nb) * S.b_n;
+        for (int r = 0; r < 4; r++) {
+          int i = 16 * bi + 4 * q4 + r;
+          if (i < mrem) {
+            int k = T.i0 + i;
+            int pk = k / S.b_kb;
+            acc[bi][bj][r] += S.s * B[(int64_t)pk * S.b_pk + (int64_t)(k - pk * S.b_kb) * S.b_k + bo];
           }
         }
-      continue;
-    }
-    // the operand's slices start at NS times its offset
-    const uint16_t *A = bufs.data[Q.a_buf] + Q.a_off * NS;
-    const uint16_t *B = bufs.data[Q.b_buf] + Q.b_off * NS;
-    const int32_t *ea = bufs.exps[Q.a_buf] + Q.a_exp;
-    const int32_t *eb = bufs.exps[Q.b_buf] + Q.b_exp;
-    // lanes past the last row / column read the last one: their outputs are
-    // never stored, so every operand load is unconditional.
-    uint64_t arow[MB], bcol[NB];   // byte offsets, and strides between slices
+      }
+  }
+  if (T.nid < T.nseg) {
+    // chunk 0 of this lane's operand lines in segment si, and the strides
+    // between slices.  Lanes past the last row / column read the last one: their
+    // outputs are never stored, so every operand load is unconditional.
+    const char *arow[MB], *bcol[NB];
     uint32_t ahs[MB], bhs[NB];
-    for (int bi = 0; bi < MB; bi++)
-      arow[bi] = line_offset<NS>(Q.a_line0 + T.i0 + min(16 * bi + r16, mrem - 1), Q.a_nl, (uint32_t)Q.a_ld, ahs[bi]);
-    for (int bj = 0; bj < NB; bj++)
-      bcol[bj] = line_offset<NS>(Q.b_line0 + T.j0 + min(16 * bj + r16, nrem - 1), Q.b_nl, (uint32_t)Q.b_ld, bhs[bj]);
-    // scale exponents of this lane's output elements
-    int erow[MB][4], fcol[NB];
-    for (int bi = 0; bi < MB; bi++)
-      for (int r = 0; r < 4; r++) erow[bi][r] = ea[T.i0 + min(16 * bi + 4 * q4 + r, mrem - 1)];
-    for (int bj = 0; bj < NB; bj++) fcol[bj] = eb[T.j0 + min(16 * bj + r16, nrem - 1)];
-    v4f q[MB][NB][slice_groups(NS)];
-    for (int bi = 0; bi < MB; bi++)
-      for (int bj = 0; bj < NB; bj++)
-        for (int g = 0; g < slice_groups(NS); g++) q[bi][bj][g] = (v4f){0.f, 0.f, 0.f, 0.f};
-    // K is a multiple of 8 and the lines are zero-padded to it, so the chunk
-    // of 8 at min(k, K - 8) is always inside the operand; a lane whose chunk
-    // starts at or past K multiplies a zeroed A operand.  The operands of a
-    // step go straight from global memory into this wave's LDS stage (one
-    // 1 KiB chunk per operand row block and slice, 16 bytes per lane), so the
-    // loads of the next step fly while the MFMAs of this one run without
-    // holding a second set of registers.
-    auto dma = [&](int k0) {
-      const uint32_t kc = (uint32_t)min(k0 + 8 * q4, Q.K - 8) / 8;
-      const uint32_t ca = NS * (Q.a_k0 / 8 + kc), cb = NS * (Q.b_k0 / 8 + kc);
+    auto lines = [&](int si) {
+      CSegS &Q = cs[si];
+      const char *A = (const char *)(bufs.data[Q.a_buf] + Q.a_off * NS);   // the slices start at NS times the offset
+      const char *B = (const char *)(bufs.data[Q.b_buf] + Q.b_off * NS);
       for (int bi = 0; bi < MB; bi++) {
-        const char *at = (const char *)A + (arow[bi] + (uint64_t)ca * ahs[bi]);
+        arow[bi] = A + line_offset<NS>(Q.a_line0 + T.i0 + min(16 * bi + r16, mrem - 1), Q.a_nl, (uint32_t)Q.a_ld, ahs[bi]);
+        arow[bi] += (uint64_t)(NS * (Q.a_k0 / 8)) * ahs[bi];
+      }
+      for (int bj = 0; bj < NB; bj++) {
+        bcol[bj] = B + line_offset<NS>(Q.b_line0 + T.j0 + min(16 * bj + r16, nrem - 1), Q.b_nl, (uint32_t)Q.b_ld, bhs[bj]);
+        bcol[bj] += (uint64_t)(NS * (Q.b_k0 / 8)) * bhs[bj];
+      }
+    };
+    // scale exponents of this lane's output elements
+    auto exps = [&](int si, int (*er)[4], int *fc) {
+      CSegS &Q = cs[si];
+      const int32_t *ea = bufs.exps[Q.a_buf] + Q.a_exp;
+      const int32_t *eb = bufs.exps[Q.b_buf] + Q.b_exp;
+      for (int bi = 0; bi < MB; bi++)
+        for (int r = 0; r < 4; r++) er[bi][r] = ea[T.i0 + min(16 * bi + 4 * q4 + r, mrem - 1)];
+      for (int bj = 0; bj < NB; bj++) fc[bj] = eb[T.j0 + min(16 * bj + r16, nrem - 1)];
+    };
+    // one K step into the stage.  K is a multiple of 8 and the lines are
+    // zero-padded to it, so the chunk of 8 at min(k, K - 8) is always inside the
+    // operand; a lane whose chunk starts at or past K multiplies a zeroed A operand.
+    auto dma = [&](int k0, int K) {
+      const uint32_t kc = NS * ((uint32_t)min(k0 + 8 * q4, K - 8) / 8);
+      for (int bi = 0; bi < MB; bi++) {
+        const char *at = arow[bi] + (uint64_t)kc * ahs[bi];
         for (int t = 0; t < NS; t++)
           __builtin_amdgcn_global_load_lds((gvptr)(at + t * ahs[bi]), (lvptr)(stage + (bi * NS + t) * 1024), 16, 0, 0);
       }
       for (int bj = 0; bj < NB; bj++) {
-        const char *bt = (const char *)B + (bcol[bj] + (uint64_t)cb * bhs[bj]);
+        const char *bt = bcol[bj] + (uint64_t)kc * bhs[bj];
         for (int t = 0; t < NS; t++)
           __builtin_amdgcn_global_load_lds((gvptr)(bt + t * bhs[bj]), (lvptr)(stage + ((MB + bj) * NS + t) * 1024),
                                            16, 0, 0);
       }
     };
-    auto rd = [&](v8bf (*as)[NS], v8bf (*bs)[NS]) {
+    v4f q[MB][NB][slice_groups(NS)];
+    for (int bi = 0; bi < MB; bi++)
+      for (int bj = 0; bj < NB; bj++)
+        for (int g = 0; g < slice_groups(NS); g++) q[bi][bj][g] = (v4f){0.f, 0.f, 0.f, 0.f};
+    int si = T.nid, k0 = 0, K = cs[si].K;
+    double sc = cg[si].s;
+    lines(si);
+    dma(0, K);
+    for (;;) {
+      __builtin_amdgcn_s_waitcnt(WAIT_VM0);      // this step's chunks are in LDS
+      __builtin_amdgcn_sched_barrier(0);
+      v8bf as[MB][NS], bs[NB][NS];
       const int lo = 16 * (r16 + 16 * q4);
       for (int t = 0; t < NS; t++) {
         for (int bi = 0; bi < MB; bi++) as[bi][t] = *(const lv8ptr)(stage + (bi * NS + t) * 1024 + lo);
         for (int bj = 0; bj < NB; bj++) bs[bj][t] = *(const lv8ptr)(stage + ((MB + bj) * NS + t) * 1024 + lo);
       }
-    };
-    auto mma = [&](int k0, v8bf (*as)[NS], v8bf (*bs)[NS]) {
-      if (k0 + 32 > Q.K && k0 + 8 * q4 >= Q.K)   // only the last step of a line has such lanes
+      const bool newseg = k0 + 32 >= K;
+      const int nsi = newseg ? si + 1 : si, nk0 = newseg ? 0 : k0 + 32;
+      const bool more = nsi < T.nseg;
+      const bool fold = newseg || (k0 + 32) % FOLD == 0;
+      int nK = K, erow[MB][4], fcol[NB];
+      double nsc = sc;
+      if (newseg && more) {
+        nK = cs[nsi].K;
+        nsc = cg[nsi].s;
+        lines(nsi);
+      }
+      __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);    // ... and in registers: the stage is free
+      __builtin_amdgcn_sched_barrier(0);
+      if (fold) exps(si, erow, fcol);
+      if (more) dma(nk0, nK);
+      __builtin_amdgcn_sched_barrier(0);
+      if (k0 + 32 > K && k0 + 8 * q4 >= K)   // only the last step of a segment has such lanes
         for (int bi = 0; bi < MB; bi++)
           for (int t = 0; t < NS; t++) as[bi][t] = (v8bf){};
 #pragma unroll
@@ -315,32 +351,22 @@ __device__ __forceinline__ void item_split(const Tile &T, const Seg *__restrict_
             for (int bj = 0; bj < NB; bj++)
               q[bi][bj][sgroup<NS>(d)] =
                   __builtin_amdgcn_mfma_f32_16x16x32_bf16(as[bi][t], bs[bj][d - t], q[bi][bj][sgroup<NS>(d)], 0, 0, 0);
-    };
-    auto fold = [&]() {
-      for (int bi = 0; bi < MB; bi++)
-        for (int bj = 0; bj < NB; bj++)
-          for (int r = 0; r < 4; r++) {
-            const double x = fold_groups<slice_groups(NS)>(q[bi][bj], r);
-            acc[bi][bj][r] += S.s * ldexp(x, erow[bi][r] + fcol[bj] - 2 * SLICE_BITS);
-          }
-      for (int bi = 0; bi < MB; bi++)
-        for (int bj = 0; bj < NB; bj++)
-          for (int g = 0; g < slice_groups(NS); g++) q[bi][bj][g] = (v4f){0.f, 0.f, 0.f, 0.f};
-    };
-    constexpr int FOLD = split_fold_k(NS);
-    static_assert(FOLD % 32 == 0, "the K loop folds after whole 32-wide steps");
-    v8bf as[MB][NS], bs[NB][NS];
-    dma(0);
-    for (int k0 = 0; k0 < Q.K; k0 += 32) {
-      __builtin_amdgcn_s_waitcnt(WAIT_VM0);      // this step's chunks are in LDS
-      __builtin_amdgcn_sched_barrier(0);
-      rd(as, bs);
-      __builtin_amdgcn_s_waitcnt(WAIT_LGKM0);    // ... and in registers: the stage is free
-      __builtin_amdgcn_sched_barrier(0);
-      if (k0 + 32 < Q.K) dma(k0 + 32);
-      __builtin_amdgcn_sched_barrier(0);
-      mma(k0, as, bs);
-      if (k0 + 32 >= Q.K || (k0 + 32) % FOLD == 0) fold();
+      if (fold) {
+        for (int bi = 0; bi < MB; bi++)
+          for (int bj = 0; bj < NB; bj++)
+            for (int r = 0; r < 4; r++) {
+              const double x = fold_groups<slice_groups(NS)>(q[bi][bj], r);
+              acc[bi][bj][r] += sc * ldexp(x, erow[bi][r] + fcol[bj] - 2 * SLICE_BITS);
+            }
+        for (int bi = 0; bi < MB; bi++)
+          for (int bj = 0; bj < NB; bj++)
+            for (int g = 0; g < slice_groups(NS); g++) q[bi][bj][g] = (v4f){0.f, 0.f, 0.f, 0.f};
+      }
+      if (!more) break;
+      K = nK;
+      sc = nsc;
+      si = nsi;
+      k0 = nk0;
     }
   }
   double *C = const_cast<double *>(sbase_ptr(T.c_base, bases, psi, y, work, part)) + T.c_off;
@@ -380,6 +406,9 @@ __device__ __forceinline__ void item_split(const Tile &T, const Seg *__restrict_
 
 // Wavefront tiles: every wavefront takes its next tile from the per-XCD
 // queues (one lane takes it, the index is wave-uniform).
+// waves of a work group: 25 KiB of LDS each at s = 5, so three work groups of
+// two fit a CU, where one of four did
+constexpr int SPLIT_WAVES = 2;
 template <int NS>
 __device__ __forceinline__ void items_split(const Tile *__restrict__ tiles, const Seg *__restrict__ segs,
                                             const SegS *__restrict__ ssegs, const XcdQueues &q,
@@ -390,10 +419,10 @@ __device__ __forceinline__ void items_split(const Tile *__restrict__ tiles, cons
                                             double *__restrict__ part, const SliceBufs &bufs) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int r16 = lane & 15, q4 = lane >> 4;
-  __shared__ __attribute__((aligned(1024))) char lds[WAVES * stage_bytes(NS)];
+  __shared__ __attribute__((aligned(1024))) char lds[SPLIT_WAVES * stage_bytes(NS)];
   char *stage = lds + wave * stage_bytes(NS);
   clear_counters(next_counters);
-  WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD) * WAVES + wave, (int)(gridDim.x / NXCD) * WAVES, chunk);
+  WorkQueue wq(q, counters, (int)(blockIdx.x / NXCD) * SPLIT_WAVES + wave, (int)(gridDim.x / NXCD) * SPLIT_WAVES, chunk);
   do {
     for (; wq.t < wq.tend; wq.t += wq.step) {
       if (wq.last()) wq.request(lane == 0);
@@ -962,7 +991,7 @@ WIDE_KERNELS(4)
 WIDE_KERNELS(5)
 
 #define SPLIT_KERNELS(NS)                                                                                   \
-  __global__ void __launch_bounds__(64 * WAVES) stage1_split##NS##_kernel(                                  \
+  __global__ void __launch_bounds__(64 * SPLIT_WAVES, 2) stage1_split##NS##_kernel(                                  \
       const Tile *__restrict__ tiles, const Seg *__restrict__ segs, const SegS *__restrict__ ssegs,         \
       XcdQueues q, int32_t *__restrict__ counters, int32_t *__restrict__ next_counters, int chunk,               \
       const double *const *__restrict__ bases,                 \
@@ -970,7 +999,7 @@ WIDE_KERNELS(5)
       double *__restrict__ part, SliceBufs bufs) {                                                          \
     items_split<NS>(tiles, segs, ssegs, q, counters, next_counters, chunk, bases, psi, y, work, part, bufs);                      \
   }                                                                                                         \
-  __global__ void __launch_bounds__(64 * WAVES) stage2_split##NS##_kernel(                                  \
+  __global__ void __launch_bounds__(64 * SPLIT_WAVES, 2) stage2_split##NS##_kernel(                                  \
       const Tile *__restrict__ tiles, const Seg *__restrict__ segs, const SegS *__restrict__ ssegs,         \
       XcdQueues q, int32_t *__restrict__ counters, int32_t *__restrict__ next_counters, int chunk,               \
       const double *const *__restrict__ bases,                 \
@@ -1044,16 +1073,16 @@ void launch_tiles_split(int stage, const Tile *tiles, const Seg *segs, const Seg
   if (ntiles <= 0) return;
   hipStream_t s = (hipStream_t)stream;
   // work groups that the LDS stages let run at once
-  const int resident = 256 * std::max(1, LDS_BYTES / (WAVES * stage_bytes(nslices)));
-  const int grid = wave_grid(ntiles, resident, WAVES), chunk = wave_chunk(ntiles, flops);
-  const XcdQueues dq = deal(q, grid / NXCD * WAVES, false);
+  const int resident = 256 * std::max(1, LDS_BYTES / (SPLIT_WAVES * stage_bytes(nslices)));
+  const int grid = wave_grid(ntiles, resident, SPLIT_WAVES), chunk = wave_chunk(ntiles, flops);
+  const XcdQueues dq = deal(q, grid / NXCD * SPLIT_WAVES, false);
 #define LAUNCH(NS)                                                                                          \
   if (nslices == NS) {                                                                                      \
     if (stage == 1)                                                                                         \
-      hipLaunchKernelGGL(stage1_split##NS##_kernel, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, ssegs,   \
+      hipLaunchKernelGGL(stage1_split##NS##_kernel, dim3(grid), dim3(64 * SPLIT_WAVES), 0, s, tiles, segs, ssegs,   \
                          dq, qs.cur(), qs.other(), chunk, bases, psi, y, work, part, bufs);           \
     else                                                                                                    \
-      hipLaunchKernelGGL(stage2_split##NS##_kernel, dim3(grid), dim3(64 * WAVES), 0, s, tiles, segs, ssegs,   \
+      hipLaunchKernelGGL(stage2_split##NS##_kernel, dim3(grid), dim3(64 * SPLIT_WAVES), 0, s, tiles, segs, ssegs,   \
                          dq, qs.cur(), qs.other(), chunk, bases, psi, y, work, part, bufs);           \
     qs.launch++;                                                                                            \
     return;                                                                                                 \
