@@ -52,14 +52,19 @@ __global__ void __launch_bounds__(VB) sdots_kernel(const VChunk *__restrict__ ch
   }
 }
 
-// out[k * m + j] = sum of the partials of segment k's chunks, in chunk order
-__global__ void sdots_finish_kernel(const int32_t *__restrict__ seg_chunk0, int nseg, int m,
-                                    const double *__restrict__ part, double *__restrict__ out) {
-  for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < nseg * m; t += gridDim.x * blockDim.x) {
-    int k = t / m, j = t - k * m;
+// out[k * m + j] = sum of the partials of segment k's chunks, in a fixed order:
+// a wavefront per sum (one thread each made it a chain of nchunks loads: 33 us
+// for the 350 chunks of L=24, D=512, twice the dots themselves)
+__global__ void __launch_bounds__(256) sdots_finish_kernel(const int32_t *__restrict__ seg_chunk0, int nseg, int m,
+                                                           const double *__restrict__ part,
+                                                           double *__restrict__ out) {
+  const int lane = threadIdx.x & 63;
+  for (int t = blockIdx.x * 4 + (threadIdx.x >> 6); t < nseg * m; t += gridDim.x * 4) {
+    const int k = t / m, j = t - k * m;
     double s = 0.0;
-    for (int c = seg_chunk0[k]; c < seg_chunk0[k + 1]; c++) s += part[(int64_t)c * m + j];
-    out[t] = s;
+    for (int c = seg_chunk0[k] + lane; c < seg_chunk0[k + 1]; c += 64) s += part[(int64_t)c * m + j];
+    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    if (lane == 0) out[t] = s;
   }
 }
 
@@ -145,7 +150,7 @@ void vec_dots(const VecCtx &X, const double *V, int64_t ldv, int m, const double
   hipLaunchKernelGGL(sdots_kernel, dim3(cgrid(X.nchunks)), dim3(VB), 0, (hipStream_t)stream, X.chunks, X.nchunks,
                      V, ldv, m, x, X.part);
   int tot = X.nseg * m;
-  hipLaunchKernelGGL(sdots_finish_kernel, dim3(std::max(1, (tot + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
+  hipLaunchKernelGGL(sdots_finish_kernel, dim3(std::min(std::max(1, (tot + 3) / 4), 16384)), dim3(256), 0, (hipStream_t)stream,
                      X.seg_chunk0, X.nseg, m, X.part, out);
 }
 
