@@ -860,11 +860,11 @@ __device__ __forceinline__ void wide_split(const Tile &T, const Seg *__restrict_
       }
     };
     {
-      v4u pre[NS];
-      load(si, 0, 0, pre);
-      store(0, pre, lds0);
-      load(si, 0, 1, pre);
-      store(1, pre, lds0);
+      v4u pa[NS], pb[NS];
+      load(si, 0, 0, pa);
+      load(si, 0, 1, pb);
+      store(0, pa, lds0);
+      store(1, pb, lds0);
     }
     int k0 = 0;
     // one step on stage cur; the next one (across segment boundaries) goes
