@@ -1,15 +1,15 @@
 // FP64 MFMA kernels for the grouped stripe products of H.psi.
 //
-// Every H.psi is two launches of one work-item routine.  The first stage
-// computes, for each wavefunction block X and run of right-block operator
-// positions, T = X [op(D_1) ... op(D_c)] (positions concatenated along N).
-// The second stage accumulates Y_F += sum v [A_1 ... A_c] [T_1; ...; T_c] for
-// every output block F.  Output tiles are owned by work items; a tile whose
-// segment list is long is split into parts (split K) that write partial
-// tiles, summed afterwards in a fixed order, so no atomics are used and the
-// result is bitwise reproducible.  A wavefront handles one work item: a
-// (16 mb) x (64/mb) tile as mb x (4/mb) v_mfma_f64_16x16x4 products with
-// operands loaded into registers one K step ahead.
+// Every H.psi is two stages.  The first computes, for each wavefunction block X
+// and run of right-block operator positions, T = X [op(D_1) ... op(D_c)]
+// (positions concatenated along N).  The second accumulates
+// Y_F += sum v [A_1 ... A_c] [T_1; ...; T_c] for every output block F.  Output
+// tiles are owned by work items; a tile whose segment list is long is split
+// into parts (split K) that write partial tiles, summed afterwards in a fixed
+// order, so the result is bitwise reproducible.  Large outputs are cut into
+// tiles of whole work groups, staged through LDS (wg_f64_kernel); the rest into
+// tiles of one wavefront (stage_f64_kernel), (16 mb) x (64/mb) as mb x (4/mb)
+// v_mfma_f64_16x16x4 products with operands in registers several K steps ahead.
 // Lane layout of v_mfma_f64_16x16x4f64 (lane l, accumulator element r):
 // A[l%16][l/16], B[l/16][l%16], D[l/16 + 4r][l%16].
 #include <hip/hip_runtime.h>
@@ -735,24 +735,50 @@ void launch_diag(const DiagBlock *blocks, const DiagTerm *terms, int nblocks, co
                      bases, diag);
 }
 
-// dst block (c, r) = src block (r, c) for every position of every job
+// dst block (c, r) = src block (r, c) for every position of every job.  The
+// blocks along y share a job's 32 x 32 pieces, which pass through LDS so that
+// both sides are runs of 256 bytes; blocks of fewer than 16 rows or columns go
+// element by element.  One work group per job, writing 8 bytes at a time, took
+// 190 ms for the operators of L=54, D=768 (4.9 now) and 87 us for the
+// transpose of U before a renormalization at L=24, D=512 (5 now).
+constexpr int TRANS_EDGE = 32;
 __global__ void __launch_bounds__(256) transpose_kernel(const TransJob *__restrict__ jobs, int njobs,
                                                         const double *__restrict__ src, double *__restrict__ dst) {
+  __shared__ double piece[TRANS_EDGE][TRANS_EDGE + 1];
+  const int tx = threadIdx.x % TRANS_EDGE, ty = threadIdx.x / TRANS_EDGE;
   for (int j = blockIdx.x; j < njobs; j += gridDim.x) {
     const TransJob J = jobs[j];
-    const int64_t bs = (int64_t)J.rows * J.cols, tot = bs * J.npos;
-    for (int64_t e = threadIdx.x; e < tot; e += 256) {
-      const int64_t p = e / bs, rem = e - p * bs;
-      const int64_t c = rem / J.rows, r = rem - c * J.rows;
-      dst[J.off + p * bs + c + r * J.cols] = src[J.off + e];
+    const int64_t bs = (int64_t)J.rows * J.cols;
+    if (J.rows < 16 || J.cols < 16) {
+      const int64_t tot = bs * J.npos;
+      for (int64_t e = (int64_t)blockIdx.y * 256 + threadIdx.x; e < tot; e += (int64_t)gridDim.y * 256) {
+        const int64_t p = e / bs, rem = e - p * bs;
+        const int64_t c = rem / J.rows, r = rem - c * J.rows;
+        dst[J.off + p * bs + c + r * J.cols] = src[J.off + e];
+      }
+      continue;
+    }
+    const int nr = (J.rows + TRANS_EDGE - 1) / TRANS_EDGE, nc = (J.cols + TRANS_EDGE - 1) / TRANS_EDGE;
+    for (int u = blockIdx.y; u < nr * nc * J.npos; u += gridDim.y) {
+      const int p = u / (nr * nc), t = u - p * (nr * nc);
+      const int c0 = t / nr * TRANS_EDGE, r0 = (t - t / nr * nr) * TRANS_EDGE;
+      const double *s = src + J.off + p * bs;
+      double *d = dst + J.off + p * bs;
+      for (int i = ty; i < TRANS_EDGE; i += 256 / TRANS_EDGE)
+        if (c0 + i < J.cols && r0 + tx < J.rows) piece[i][tx] = s[(int64_t)(c0 + i) * J.rows + r0 + tx];
+      __syncthreads();
+      for (int i = ty; i < TRANS_EDGE; i += 256 / TRANS_EDGE)
+        if (r0 + i < J.rows && c0 + tx < J.cols) d[(int64_t)(r0 + i) * J.cols + c0 + tx] = piece[tx][i];
+      __syncthreads();   // the piece is reused
     }
   }
 }
 
 void launch_transpose(const TransJob *jobs, int njobs, const double *src, double *dst, void *stream) {
   if (njobs <= 0) return;
-  hipLaunchKernelGGL(transpose_kernel, dim3(std::min(njobs, 65535)), dim3(256), 0, (hipStream_t)stream, jobs, njobs,
-                     src, dst);
+  const int share = std::min(64, std::max(1, 16384 / njobs));
+  hipLaunchKernelGGL(transpose_kernel, dim3(std::min(njobs, 65535), share), dim3(256), 0, (hipStream_t)stream, jobs,
+                     njobs, src, dst);
 }
 
 }  // namespace dmrg
