@@ -319,8 +319,10 @@ def time_hpsi(torch, plan, x, y, steps, warmup):
 
 KERNEL_NAMES = {
     # profile code -> kernel (split s=5 plans, FP64 plans)
-    31: ("stage1_wsplit5_kernel", None), 32: ("stage2_wsplit5_kernel", None),
-    11: ("stage1_msplit5_kernel", None), 12: ("stage2_msplit5_kernel", None),
+    31: ("stage1_wsplit5_kernel", "wg_f64_kernel<WgTile<2, 4, 4, 2, 4>, 1>"),
+    32: ("stage2_wsplit5_kernel", "wg_f64_kernel<WgTile<2, 4, 4, 2, 4>, 2>"),
+    11: ("stage1_msplit5_kernel", "wg_f64_kernel<WgTile<2, 2, 2, 2, 4>, 1>"),
+    12: ("stage2_msplit5_kernel", "wg_f64_kernel<WgTile<2, 2, 2, 2, 4>, 2>"),
     21: ("stage1_split5_kernel", "stage_f64_kernel<1>"), 22: ("stage2_split5_kernel", "stage_f64_kernel<2>"),
 }
 
