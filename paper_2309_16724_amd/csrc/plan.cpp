@@ -67,8 +67,6 @@ struct dmrg_plan {
   int64_t work_elems = 0;
   double *d_part = nullptr;
   int64_t part_elems = 0;
-  bool fine = false;                  // kpart may be lowered for plans of few tiles (see fine_kpart)
-  int64_t fine_elems = 0;             // what part_elems has grown by that
   int32_t *d_counters = nullptr;      // per-XCD queue counters of the work-group launches
   std::vector<Chunk> chunks;
   std::vector<DiagBlock> dblocks;
@@ -242,98 +240,12 @@ std::vector<Cell> output_cells(const dmrg_plan *P, int m, int n) {
   });
 }
 
-// Second-stage segments of the outputs of a chunk: by (problem, row, output).
-using SegList = std::vector<std::pair<Seg, Seg2Info>>;
-using OutputSegs = std::map<std::array<int, 3>, SegList>;
-
-// The segments of one output in pieces of at most kpart along K, cut at
-// position boundaries, and the pieces in parts of summed K up to kpart
-// (identity pieces count as a quarter).
-void cut_parts(const SegList &segs, int kpart, std::vector<Seg> &pieces, std::vector<Seg2Info> &pinfo,
-               std::vector<std::pair<int, int>> &parts, std::vector<double> &pcost) {
-  for (auto &gi : segs) {
-    const Seg &g = gi.first;
-    if (g.a_base < 0 || g.K <= kpart) { pieces.push_back(g); pinfo.push_back(gi.second); continue; }
-    int npos = g.K / g.a_kb;
-    int per = std::max(1, kpart / g.a_kb);
-    for (int p0 = 0; p0 < npos; p0 += per) {
-      int p1 = std::min(npos, p0 + per);
-      Seg h = g;
-      h.a_off += (int64_t)p0 * g.a_p;
-      h.b_off += (int64_t)p0 * g.b_pk;
-      h.K = (p1 - p0) * g.a_kb;
-      pieces.push_back(h);
-      Seg2Info hi = gi.second;
-      hi.pA0 += p0;
-      hi.slot0 += p0;
-      hi.run = p1 - p0;
-      pinfo.push_back(hi);
-    }
-  }
-  int b0 = 0;
-  double cost = 0.0;
-  for (int i = 0; i < (int)pieces.size(); i++) {
-    double c = pieces[i].a_base < 0 ? 0.25 * pieces[i].K : (double)pieces[i].K;
-    if (i > b0 && cost + c > kpart) {
-      parts.push_back({b0, i});
-      pcost.push_back(cost);
-      b0 = i;
-      cost = 0.0;
-    }
-    cost += c;
-  }
-  parts.push_back({b0, (int)pieces.size()});
-  pcost.push_back(cost);
-}
-
-// partial-tile elements of the outputs at kpart
-int64_t part_elems_at(const dmrg_plan *P, const OutputSegs &byF, int kpart) {
-  int64_t n = 0;
-  for (auto &kv : byF) {
-    const PsiBlock &F = P->probs[kv.first[0]]->T.blocks[kv.first[2]];
-    std::vector<Seg> pieces;
-    std::vector<Seg2Info> pinfo;
-    std::vector<std::pair<int, int>> parts;
-    std::vector<double> pcost;
-    cut_parts(kv.second, kpart, pieces, pinfo, parts, pcost);
-    if (parts.size() > 1) n += (int64_t)parts.size() * F.dL * F.dR;
-  }
-  return n;
-}
-
-// Summed K of a part.  A chunk whose tiles occupy fewer than FINE_TILES
-// wavefronts leaves the rest idle behind a chain of a hundred segments, so its
-// parts are cut finer, down to FINE_KPART, unless the caller set kpart, and
-// within FINE_ELEMS partial elements.  H.psi: L=8 in the exact spaces (106
-// tiles -> 1,500) 210 -> 119 us, L=16, D=128 (931 -> 2,100) 361 -> 274 us;
-// 1,024 wavefronts give 112 and 343 us, 4,096 119 and 277.
-constexpr int FINE_TILES = 2048, FINE_KPART = 64;
-constexpr int64_t FINE_ELEMS = (int64_t)1 << 19;
-int fine_kpart(const dmrg_plan *P, const OutputSegs &byF) {
-  if (!P->fine) return P->kpart;
-  double tiles = 0.0, ksum = 0.0;
-  for (auto &kv : byF) {
-    const PsiBlock &F = P->probs[kv.first[0]]->T.blocks[kv.first[2]];
-    double cells = 0.0, k = 0.0;   // wavefronts of its tiles
-    for (const Cell &c : output_cells(P, F.dL, F.dR))
-      cells += c.mb == WIDE_MB || c.mb == F64_WIDE_MB ? WIDE_WAVES : c.mb == MACRO_MB ? WAVES : 1;
-    for (auto &gi : kv.second) k += gi.first.a_base < 0 ? 0.25 * gi.first.K : (double)gi.first.K;
-    tiles += cells * std::max(1.0, k / P->kpart);
-    ksum += cells * k;
-  }
-  if (tiles >= FINE_TILES) return P->kpart;
-  int kp = (int)std::min((double)P->kpart, std::max((double)FINE_KPART, ksum / FINE_TILES));
-  while (kp < P->kpart && part_elems_at(P, byF, kp) > FINE_ELEMS) kp = std::min(2 * kp, P->kpart);
-  return kp;
-}
-
 int prepare_device(dmrg_plan *P);
 int autotune(dmrg_plan *P, void *stream);
 int replan(dmrg_plan *P);
 
 int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
   P->wg_tiles = true;
-  int64_t part_default = 0;   // partial elements without finer parts
   for (const auto &pp : P->probs)
     for (const auto *sec : {&pp->L.sec, &pp->R.sec})
       for (const dmrg_sector_t &s : *sec) P->wg_tiles = P->wg_tiles && s.dim < WG_MAX_DIM;
@@ -534,16 +446,48 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
     }
     std::vector<std::pair<double, Tile>> tiles2, tiles2m, tiles2x;
     int64_t npart = 0;   // partial-tile elements
-    const int kpart = fine_kpart(P, byF);
-    if (kpart < P->kpart) ch.part_default = part_elems_at(P, byF, P->kpart);
     for (auto &kv : byF) {
       const ProbPlan &pp = *P->probs[kv.first[0]];
       const PsiBlock &F = pp.T.blocks[kv.first[2]];
+      // pieces of at most KPART along K, cut at position boundaries
       std::vector<Seg> pieces;
       std::vector<Seg2Info> pinfo;
+      for (auto &gi : kv.second) {
+        const Seg &g = gi.first;
+        if (g.a_base < 0 || g.K <= P->kpart) { pieces.push_back(g); pinfo.push_back(gi.second); continue; }
+        int npos = g.K / g.a_kb;
+        int per = std::max(1, P->kpart / g.a_kb);
+        for (int p0 = 0; p0 < npos; p0 += per) {
+          int p1 = std::min(npos, p0 + per);
+          Seg h = g;
+          h.a_off += (int64_t)p0 * g.a_p;
+          h.b_off += (int64_t)p0 * g.b_pk;
+          h.K = (p1 - p0) * g.a_kb;
+          pieces.push_back(h);
+          Seg2Info hi = gi.second;
+          hi.pA0 += p0;
+          hi.slot0 += p0;
+          hi.run = p1 - p0;
+          pinfo.push_back(hi);
+        }
+      }
+      // parts: consecutive pieces with summed K up to KPART (identity pieces count as d_L)
       std::vector<std::pair<int, int>> parts;   // [begin, end) into pieces
       std::vector<double> pcost;
-      cut_parts(kv.second, kpart, pieces, pinfo, parts, pcost);
+      int b0 = 0;
+      double cost = 0.0;
+      for (int i = 0; i < (int)pieces.size(); i++) {
+        double c = pieces[i].a_base < 0 ? 0.25 * pieces[i].K : (double)pieces[i].K;
+        if (i > b0 && cost + c > P->kpart) {
+          parts.push_back({b0, i});
+          pcost.push_back(cost);
+          b0 = i;
+          cost = 0.0;
+        }
+        cost += c;
+      }
+      parts.push_back({b0, (int)pieces.size()});
+      pcost.push_back(cost);
       // identity pieces first within a part
       std::vector<int> pnid;
       for (const auto &pt : parts) {
@@ -614,7 +558,6 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
     }
     ch.part_elems = npart;
     P->part_elems = std::max(P->part_elems, ch.part_elems);
-    part_default = std::max(part_default, ch.part_default >= 0 ? ch.part_default : npart);
     // by falling cost within a factor of two: a full sort would take the tiles
     // that share stripes apart.  The wide tiles of one output and K range go by
     // their common cost and stay neighbours: they read the same operand lines
@@ -660,7 +603,6 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
     ch.q2x = xcd_queues(cost2x.data(), (int)cost2x.size());
     P->chunks.push_back(std::move(ch));
   }
-  P->fine_elems = std::max<int64_t>(0, P->part_elems - part_default);
   P->stats.flops = P->stats.stage1_flops + P->stats.stage2_flops;
   P->stats.n_chunks = (int)P->chunks.size();
   P->stats.workspace_bytes = max_work * 8;
@@ -1086,7 +1028,7 @@ void release_plan(dmrg_plan *P) {
   P->d_work = nullptr;
   P->d_part = nullptr;
   P->d_counters = nullptr;
-  P->work_elems = P->part_elems = P->fine_elems = 0;
+  P->work_elems = P->part_elems = 0;
   P->jobs_ops.clear();
   P->jobs_psi.clear();
   P->items_ops.clear();
@@ -1199,7 +1141,6 @@ void append_tune_file(const std::string &path, uint64_t key, const TuneChoice &c
 
 void apply_choice(dmrg_plan *P, const TuneChoice &c) {
   P->kpart = (int)c[0];
-  P->fine = false;
   P->tile_policy = (int)c[1];
   P->budget = c[2];
   P->macro_min = (int)c[3];
@@ -1396,7 +1337,6 @@ extern "C" int dmrg_build_tasks(const dmrg_problem_t *probs, int32_t n_probs, co
     P->flags = opts ? opts->flags : 0;
     P->xcd = (P->flags & DMRG_PLAN_XCD) ? 1 : 0;
     P->kpart = (opts && opts->kpart > 0) ? opts->kpart : KPART;
-    P->fine = !(opts && opts->kpart > 0);
     P->tile_policy = opts ? opts->tile_policy : 0;
     P->macro_min = !opts || opts->macro_min == 0 ? MACRO_MIN : std::max(0, opts->macro_min);
     P->wide_min = !opts || opts->wide_min == 0 ? WIDE_MIN : std::max(0, opts->wide_min);
@@ -1555,13 +1495,6 @@ int64_t plan_scratch_layout(const dmrg_plan_t *p, int64_t off[SCRATCH_REGIONS]) 
   off[3] = o; if (split) o = up(o + 4 * (p->sb_exps[SBUF_T] + WIDE_EDGE));   // spare entries: see upload_split
   off[4] = o; o = up(o + 4 * QUEUE_INTS);
   return o;
-}
-
-// bytes of that total due to finer parts than kpart asks for
-int64_t plan_scratch_fine(const dmrg_plan_t *p) {
-  auto up = [](int64_t x) { return (x + 255) / 256 * 256; };
-  auto part = [&](int64_t n) { return up(8 * std::max<int64_t>(n, 1)); };
-  return part(p->part_elems) - part(p->part_elems - p->fine_elems);
 }
 
 // One H.psi with the scratch memory at `base` (laid out by
@@ -1861,7 +1794,6 @@ extern "C" int dmrg_debug_plan_host_apply(const dmrg_problem_t *prob, const doub
   P->precision = opts ? opts->precision : DMRG_FP64;
   P->n_slices = opts ? opts->n_slices : 0;
   P->kpart = (opts && opts->kpart > 0) ? opts->kpart : KPART;
-  P->fine = !(opts && opts->kpart > 0);
   P->tile_policy = opts ? opts->tile_policy : 0;
   P->macro_min = !opts || opts->macro_min == 0 ? MACRO_MIN : std::max(0, opts->macro_min);
   P->wide_min = !opts || opts->wide_min == 0 ? WIDE_MIN : std::max(0, opts->wide_min);
@@ -1961,7 +1893,6 @@ extern "C" int64_t dmrg_debug_plan_tiles(const dmrg_problem_t *prob, const dmrg_
   P->precision = opts ? opts->precision : DMRG_FP64;
   P->n_slices = opts ? opts->n_slices : 0;
   P->kpart = (opts && opts->kpart > 0) ? opts->kpart : KPART;
-  P->fine = !(opts && opts->kpart > 0);
   P->tile_policy = opts ? opts->tile_policy : 0;
   P->macro_min = !opts || opts->macro_min == 0 ? MACRO_MIN : std::max(0, opts->macro_min);
   P->wide_min = !opts || opts->wide_min == 0 ? WIDE_MIN : std::max(0, opts->wide_min);

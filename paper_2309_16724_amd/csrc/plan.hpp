@@ -101,17 +101,16 @@ inline int wave_chunk(int ntiles, double flops) {
   return c < 1.0 ? 1 : c > 8.0 ? 8 : (int)c;
 }
 
-// FP64 outputs with both sides >= F64_WIDE_MIN, one of them >= F64_WIDE_MAX,
-// take 128 x 128 work-group tiles; other outputs (and the strips beyond the
-// bands) with both sides >= F64_MACRO_MIN 64 x 64 ones.  A 32 x 32 wavefront
-// tile fetches 0.125 B per flop, 4.5 TB/s at the 36 TF/s it reached on large
-// outputs; a 128 x 128 one a quarter of that.  L=54, D=1024: 138.8 ms with
-// wavefront tiles alone, 87.6 ms with 64/48, 89.7 ms with 48/33, 92 ms with
-// 96/48 or 64 x 64 tiles alone (84.0 now, see heavy_tiles).  L=24, D=512
-// (sectors up to 83): 128-wide tiles of which both sides are half empty cost
-// 0.87 ms where 64 x 64 ones take 0.63, hence F64_WIDE_MAX.  Sectors of
-// WG_MAX_DIM states and more stay with wavefront tiles (the work-group tiles
-// address an operand's lines by 32-bit byte offsets).
+// FP64 outputs with both sides >= F64_WIDE_MIN, one of them at least a whole
+// band, take 128 x 128 work-group tiles; other outputs (and the strips beyond
+// the bands) with both sides >= F64_MACRO_MIN 64 x 64 ones.  A 32 x 32
+// wavefront tile fetches 0.125 B per flop, 4.5 TB/s at the 36 TF/s it reached
+// on large outputs; a 128 x 128 one a quarter of that.  L=54, D=1024: 138.8 ms
+// with wavefront tiles alone, 87.6 ms with 64/48, 89.7 ms with 48/33, 92 ms
+// with 96/48 or 64 x 64 tiles alone.  L=24, D=512 (sectors up to 83): 128-wide
+// tiles of which one side is half empty cost 0.87 ms where 64 x 64 ones take
+// 0.63, so a whole band is asked for.  Sectors of WG_MAX_DIM states and more stay with wavefront tiles (the
+// work-group tiles address an operand's lines by 32-bit byte offsets).
 constexpr int F64_WIDE_MIN = 64, F64_WIDE_MAX = 96, F64_MACRO_MIN = 48, WG_MAX_DIM = 1 << 14;
 
 // A cell of an output's tiling: top-left corner and tile kind.
@@ -361,7 +360,6 @@ struct Chunk {
   double flops1x = 0.0, flops2x = 0.0;  // ... of its wide tiles
   double flops1w = 0.0, flops2w = 0.0;  // ... of its wavefront tiles
   int64_t part_elems = 0;               // partial-tile buffer needed
-  int64_t part_default = -1;            // ... without finer parts (-1: there are none)
   // split precision (filled only for split plans)
   std::vector<SegS> sseg1, sseg2;
   std::vector<SliceJob> tjobs;          // stripe slicing after the first stage
@@ -465,7 +463,6 @@ void launch_fill_int(int32_t *p, int64_t n, int32_t v, void *stream);
 // total bytes
 constexpr int SCRATCH_REGIONS = 5;
 int64_t plan_scratch_layout(const dmrg_plan_t *p, int64_t off[SCRATCH_REGIONS]);
-int64_t plan_scratch_fine(const dmrg_plan_t *p);
 // one H.psi with that scratch memory at base (device address)
 int enqueue_scratch(dmrg_plan_t *p, const double *psi, double *hpsi, void *stream, char *base);
 // wavefront tiles (one tile per wavefront) from per-XCD queues
