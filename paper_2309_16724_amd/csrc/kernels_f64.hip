@@ -171,6 +171,32 @@ __device__ __forceinline__ void item2_f64(const Tile &T, const Seg *__restrict__
     for (int b = 0; b < NB; b++) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
   const int mrem = T.m - T.i0, nrem = T.n - T.j0;
   const CSegF *cs = (const CSegF *)segs + T.seg0;
+  // identity left operators (the first segments): tile += s * B restricted to
+  // the tile (one position, K == rows).  (The lane's coordinates pass through
+  // an empty asm so that offsets derived from them are not kept in registers
+  // during the loop below.)
+  asm volatile("" : "+v"(r16), "+v"(q4));
+  for (int si = 0; si < T.nid; si++) {
+    CSegF &S = cs[si];
+    const double *B = seg_ptr(S.b_base, psi, work) + S.b_off + T.i0 * S.b_k + T.j0 * S.b_n;
+    const double s = S.s;
+    double v[MB][NB][4];
+#pragma unroll
+    for (int bi = 0; bi < MB; bi++)
+#pragma unroll
+      for (int r = 0; r < 4; r++) {
+        const double *row = mad(B, min(16 * bi + q4 + 4 * r, mrem - 1), S.b_k);
+#pragma unroll
+        for (int bj = 0; bj < NB; bj++) v[bi][bj][r] = gld(mad(row, min(16 * bj + r16, nrem - 1), S.b_n));
+      }
+#pragma unroll
+    for (int bi = 0; bi < MB; bi++)
+#pragma unroll
+      for (int bj = 0; bj < NB; bj++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) acc[bi][bj][r] += s * v[bi][bj][r];
+  }
+  asm volatile("" : "+v"(r16), "+v"(q4));
   if (T.nid < T.nseg) {
     // uniform state of the walk ...
     int si = T.nid, K = 0, kb = 1, dk = 0, k0 = 0;
@@ -259,31 +285,6 @@ __device__ __forceinline__ void item2_f64(const Tile &T, const Seg *__restrict__
         __builtin_amdgcn_sched_barrier(0);
       }
     } while (rem[0] > 0);
-  }
-  // identity left operators (the first segments): tile += s * B restricted to
-  // the tile (one position, K == rows).  (The lane's coordinates pass through
-  // an empty asm so that offsets derived from them are computed here, not kept
-  // in registers during the loop above.)
-  asm volatile("" : "+v"(r16), "+v"(q4));
-  for (int si = 0; si < T.nid; si++) {
-    CSegF &S = cs[si];
-    const double *B = seg_ptr(S.b_base, psi, work) + S.b_off + T.i0 * S.b_k + T.j0 * S.b_n;
-    const double s = S.s;
-    double v[MB][NB][4];
-#pragma unroll
-    for (int bi = 0; bi < MB; bi++)
-#pragma unroll
-      for (int r = 0; r < 4; r++) {
-        const double *row = mad(B, min(16 * bi + q4 + 4 * r, mrem - 1), S.b_k);
-#pragma unroll
-        for (int bj = 0; bj < NB; bj++) v[bi][bj][r] = gld(mad(row, min(16 * bj + r16, nrem - 1), S.b_n));
-      }
-#pragma unroll
-    for (int bi = 0; bi < MB; bi++)
-#pragma unroll
-      for (int bj = 0; bj < NB; bj++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) acc[bi][bj][r] += s * v[bi][bj][r];
   }
   double *C = out_ptr<2>(T.c_base, y, work, part) + T.c_off;
 #pragma unroll
@@ -381,6 +382,34 @@ __device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict
   for (int a = 0; a < G::MBW; a++)
 #pragma unroll
     for (int b = 0; b < G::NBW; b++) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
+  // identity left operators: tile += s * B restricted to the tile (one
+  // position, K == rows).  Lanes outside the output read its last row or
+  // column, so that no load waits for another.
+  // (the lane index passes through an empty asm, here and below, so that the
+  // offsets derived from it are not kept in registers during the K loop)
+  asm volatile("" : "+v"(lane));
+  for (int e = 0; STAGE == 2 && e < T.nid; e++) {
+    CSegF &S = cs[e];
+    const double *B = seg_ptr(S.b_base, psi, work) + S.b_off;
+    const double s = S.s;
+#pragma unroll
+    for (int bi = 0; bi < G::MBW; bi++) {
+      double v[G::NBW][4];
+#pragma unroll
+      for (int bj = 0; bj < G::NBW; bj++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+          const int i = T.i0 + min(16 * (wr + G::WM * bi) + (lane >> 4) + 4 * r, mt - 1);
+          const int j = T.j0 + min(16 * (wc + G::WN * bj) + (lane & 15), nt - 1);
+          v[bj][r] = gld(B + i * S.b_k + j * S.b_n);
+        }
+#pragma unroll
+      for (int bj = 0; bj < G::NBW; bj++)
+#pragma unroll
+        for (int r = 0; r < 4; r++) acc[bi][bj][r] += s * v[bj][r];
+    }
+  }
+  asm volatile("" : "+v"(lane));
   int si = T.nid;   // identity segments come first
   if (si < T.nseg) {
     // this thread's line of each operand (lines past the output read the last
@@ -522,33 +551,6 @@ __device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict
       store(nsi, nk0, lds + cur * G::STAGE);
       si = nsi;
       k0 = nk0;
-    }
-  }
-  // identity left operators: tile += s * B restricted to the tile (one
-  // position, K == rows).  Lanes outside the output read its last row or
-  // column, so that no load waits for another.
-  // (the lane index passes through an empty asm, here and below, so that the
-  // offsets derived from it are not kept in registers during the K loop)
-  asm volatile("" : "+v"(lane));
-  for (si = 0; STAGE == 2 && si < T.nid; si++) {
-    CSegF &S = cs[si];
-    const double *B = seg_ptr(S.b_base, psi, work) + S.b_off;
-    const double s = S.s;
-#pragma unroll
-    for (int bi = 0; bi < G::MBW; bi++) {
-      double v[G::NBW][4];
-#pragma unroll
-      for (int bj = 0; bj < G::NBW; bj++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-          const int i = T.i0 + min(16 * (wr + G::WM * bi) + (lane >> 4) + 4 * r, mt - 1);
-          const int j = T.j0 + min(16 * (wc + G::WN * bj) + (lane & 15), nt - 1);
-          v[bj][r] = gld(B + i * S.b_k + j * S.b_n);
-        }
-#pragma unroll
-      for (int bj = 0; bj < G::NBW; bj++)
-#pragma unroll
-        for (int r = 0; r < 4; r++) acc[bi][bj][r] += s * v[bj][r];
     }
   }
   asm volatile("" : "+v"(lane));
