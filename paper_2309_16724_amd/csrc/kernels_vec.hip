@@ -52,18 +52,25 @@ __global__ void __launch_bounds__(VB) sdots_kernel(const VChunk *__restrict__ ch
   }
 }
 
-// out[k * m + j] = sum of the partials of segment k's chunks, in a fixed order:
-// a wavefront per sum (one thread each made it a chain of nchunks loads: 33 us
-// for the 350 chunks of L=24, D=512, twice the dots themselves)
+// out[k * m + j] = sum of the partials of segment k's chunks, in chunk order.  A
+// wavefront per sum: its lanes load 64 partials at once and the sum takes them
+// one after the other out of the lanes.  One thread per sum made it a chain of
+// loads, 33 us for the 350 chunks of L=24, D=512, twice the dots themselves.  The
+// order stays: an unconverged solve multiplies a change of rounding here, by
+// another order 9e-9 of the vector after 30 iterations.
 __global__ void __launch_bounds__(256) sdots_finish_kernel(const int32_t *__restrict__ seg_chunk0, int nseg, int m,
                                                            const double *__restrict__ part,
                                                            double *__restrict__ out) {
   const int lane = threadIdx.x & 63;
   for (int t = blockIdx.x * 4 + (threadIdx.x >> 6); t < nseg * m; t += gridDim.x * 4) {
     const int k = t / m, j = t - k * m;
+    const int c1 = seg_chunk0[k + 1];
     double s = 0.0;
-    for (int c = seg_chunk0[k] + lane; c < seg_chunk0[k + 1]; c += 64) s += part[(int64_t)c * m + j];
-    for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
+    for (int c0 = seg_chunk0[k]; c0 < c1; c0 += 64) {
+      const double v = c0 + lane < c1 ? part[(int64_t)(c0 + lane) * m + j] : 0.0;   // s + 0.0 is s
+#pragma unroll
+      for (int i = 0; i < 64; i++) s += __shfl(v, i);
+    }
     if (lane == 0) out[t] = s;
   }
 }
