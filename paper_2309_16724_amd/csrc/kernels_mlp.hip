@@ -94,16 +94,20 @@ __device__ __forceinline__ float layer1(float b1, float w10, float w11, float f0
 // loads each); layer 2 runs on v_mfma_f32_16x16x4f32 with W2 going through
 // registers into one of two LDS chunks of 16 rows while the chunk before is
 // used (row stride W + 16: the four rows an operand read touches lie in
-// different banks).  Layer 3 reduces over the 16 lanes of each output row, then
-// over the column groups.  Bound: the FP32 matrix rate.  CS = 4 is for few
-// rows: at 4096 rows CS = 1 is 64 work groups on 256 CUs, 110 us; CS = 4 256.
+// different banks).  Layer 3 sums a row's columns in 16 lanes, each every
+// sixteenth column in rising order, then over the lanes; column groups hand
+// their layer-2 outputs over in LDS for it, so that a row's result does not
+// depend on the rows beside it (with a sum per column group the gradient of
+// 4096 rows at width 64 was 4.96e-8 off, 4.84e-8 this way, at the same time).
+// Bound: the FP32 matrix rate.  CS = 4 is for few rows: at 4096 rows CS = 1 is
+// 64 work groups on 256 CUs, 110 us; CS = 4 256.
 template <int W, int MODE, int CS>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) mlp_fwd_kernel(const FwdArgs A, const FwdSegs S) {
   constexpr int NB = W / 16 / CS, KC = 16, LD = W + 16, RG = 4 / CS, ROWS = 16 * RG;
   static_assert(W % (16 * CS) == 0 && (KC * W / 4) % NT == 0 || W < 64, "whole chunks");
+  static_assert(CS == 1 || (CS == 4 && W / KC % 2 == 0), "16 rows a work group, the last chunk is chunk 1");
   __shared__ float w2c[2][KC][LD];
   __shared__ float l1[3][W];
-  __shared__ float red[4][16];
   const POff o = poff(W);
   const float *__restrict__ p = A.params;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -159,6 +163,12 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) ml
     if (k0 + KC < W) store(1 - b);
   }
   // layer 3
+  const float b3 = p[o.b3];
+  float w3s[CS > 1 ? W / 16 : 1];
+  if (CS > 1) {
+#pragma unroll
+    for (int e = 0; e < W / 16; e++) w3s[CS > 1 ? e : 0] = p[o.w3 + 16 * e + l16];   // in flight until the barrier
+  }
   float part[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
   for (int bj = 0; bj < NB; bj++) {
@@ -169,25 +179,29 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3))) ml
       const float z = acc[bj][r] + bb;
       const int64_t orow = base + mfma_row(q, r);
       if (MODE == 0 && A.z2 && orow < A.n) A.z2[orow * W + c] = z;
-      part[r] = fmaf(fmaxf(z, 0.0f), w3, part[r]);
+      // (the last K step read chunk 1: chunk 0 is free)
+      if (CS > 1) w2c[0][mfma_row(q, r)][c] = fmaxf(z, 0.0f);
+      else part[r] = fmaf(fmaxf(z, 0.0f), w3, part[r]);
     }
+  }
+  if (CS > 1) {
+    // wavefront w sums rows 4 w + q over all columns as CS = 1 does
+    __syncthreads();
+    const int row = 4 * wave + q;
+#pragma unroll
+    for (int e = 0; e < W / 16; e++) part[0] = fmaf(w2c[0][row][16 * e + l16], w3s[CS > 1 ? e : 0], part[0]);
+    for (int m = 8; m > 0; m >>= 1) part[0] += __shfl_xor(part[0], m, 16);
+    const double tdr = MODE == 1 ? __shfl(td, row) : 0.0;
+    const int64_t orow = base + row;
+    if (l16 != 0 || orow >= A.n) return;
+    const float g = part[0] + b3;
+    if (MODE == 0) A.g[orow] = g;
+    else A.t[orow] = tdr * (1.0 + (double)g);
+    return;
   }
 #pragma unroll
   for (int r = 0; r < 4; r++)
     for (int m = 8; m > 0; m >>= 1) part[r] += __shfl_xor(part[r], m, 16);
-  if (CS > 1) {
-#pragma unroll
-    for (int r = 0; r < 4; r++)
-      if (l16 == 0) red[wave][mfma_row(q, r)] = part[r];
-    __syncthreads();
-    if (cg != 0) return;
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-      part[r] = 0.0f;
-      for (int c = 0; c < CS; c++) part[r] += red[rg * CS + c][mfma_row(q, r)];
-    }
-  }
-  const float b3 = p[o.b3];
 #pragma unroll
   for (int r = 0; r < 4; r++) {
     const int64_t orow = base + mfma_row(q, r);
