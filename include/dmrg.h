@@ -571,6 +571,10 @@ int dmrg_debug_plan_host_apply(const dmrg_problem_t *prob, const double *psi, do
  * of tiles (call with out = NULL to size) or a negative status. */
 int64_t dmrg_debug_plan_tiles(const dmrg_problem_t *prob, const dmrg_plan_opts_t *opts, int32_t stage,
                               int64_t *out, int64_t cap);
+/* Test-only: element offset at which the FP64 wavefront tiles address line
+ * `line` of row `row` of position `pos` of an operand with these strides. */
+int64_t dmrg_debug_operand_offset(int32_t pos, int64_t pos_stride, int32_t row, int64_t row_stride, int32_t line,
+                                  int64_t line_stride);
 /* Test-only: the renormalization lists built as by dmrg_renorm_create for a
  * problem whose ldata is a HOST array, executed on the CPU with the kernels'
  * addressing (u, out HOST; out = NULL: statistics only); rec (may be NULL)

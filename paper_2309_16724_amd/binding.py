@@ -162,6 +162,8 @@ def load(path=None):
                                                  ctypes.POINTER(PlanOpts), ctypes.POINTER(PlanStats)]
         L.dmrg_debug_plan_tiles.argtypes = [ctypes.POINTER(ProblemT), ctypes.POINTER(PlanOpts), c_i32, c_vp, c_i64]
         L.dmrg_debug_plan_tiles.restype = c_i64
+        L.dmrg_debug_operand_offset.argtypes = [c_i32, c_i64, c_i32, c_i64, c_i32, c_i64]
+        L.dmrg_debug_operand_offset.restype = c_i64
         c_f = ctypes.c_float
         L.dmrg_mlp_create.argtypes = [c_i32, ctypes.c_uint64, ctypes.POINTER(c_vp)]
         L.dmrg_mlp_num_params.argtypes = [c_vp]

@@ -82,11 +82,6 @@ __device__ __forceinline__ void mma_f64(v4d (&acc)[MB][NB], const StepF64<MB, NB
       acc[bi][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[bi], b[bj], acc[bi][bj], 0, 0, 0);
 }
 
-// offsets of up to 2^32 elements: one multiply-add each
-__device__ __forceinline__ const double *mad(const double *p, unsigned n, int64_t stride) {
-  return p + (uint64_t)n * (uint32_t)stride;
-}
-
 // first stage: T = X op(D), one segment
 template <int MB, int NB>
 __device__ __forceinline__ void item1_f64(const Tile &T, const Seg *__restrict__ segs, const double *psi, double *y,
@@ -103,16 +98,16 @@ __device__ __forceinline__ void item1_f64(const Tile &T, const Seg *__restrict__
   const double s = S.s;
   int k = min(q4, K - 1);
   const double *pa[MB], *pb[NB];
-  const double *A = mad(seg_ptr(S.a_base, psi, work) + S.a_off, k, S.a_k);
-  const double *B = mad(seg_ptr(S.b_base, psi, work) + S.b_off, k, S.b_k);
+  const double *A = seg_ptr(S.a_base, psi, work) + S.a_off, *B = seg_ptr(S.b_base, psi, work) + S.b_off;
 #pragma unroll
-  for (int bi = 0; bi < MB; bi++) pa[bi] = mad(A, T.i0 + min(16 * bi + r16, mrem - 1), S.a_i);
+  for (int bi = 0; bi < MB; bi++)
+    pa[bi] = A + operand_offset(0, 0, k, S.a_k, T.i0 + min(16 * bi + r16, mrem - 1), S.a_i);
 #pragma unroll
   for (int bj = 0; bj < NB; bj++) {
     const unsigned n = T.j0 + min(16 * bj + r16, nrem - 1);
     unsigned pn = 0;
     if (S.b_nb < T.n) pn = n / (unsigned)S.b_nb;
-    pb[bj] = mad(mad(B, pn, S.b_pn), n - pn * S.b_nb, S.b_n);
+    pb[bj] = B + operand_offset(pn, S.b_pn, k, S.b_k, n - pn * S.b_nb, S.b_n);
   }
   k = q4;
   const int64_t da = 4 * S.a_k, db = 4 * S.b_k;
@@ -185,9 +180,10 @@ __device__ __forceinline__ void item2_f64(const Tile &T, const Seg *__restrict__
     for (int bi = 0; bi < MB; bi++)
 #pragma unroll
       for (int r = 0; r < 4; r++) {
-        const double *row = mad(B, min(16 * bi + q4 + 4 * r, mrem - 1), S.b_k);
+        const uint32_t row = min(16 * bi + q4 + 4 * r, mrem - 1);
 #pragma unroll
-        for (int bj = 0; bj < NB; bj++) v[bi][bj][r] = gld(mad(row, min(16 * bj + r16, nrem - 1), S.b_n));
+        for (int bj = 0; bj < NB; bj++)
+          v[bi][bj][r] = gld(B + operand_offset(0, 0, row, S.b_k, min(16 * bj + r16, nrem - 1), S.b_n));
       }
 #pragma unroll
     for (int bi = 0; bi < MB; bi++)
@@ -208,15 +204,15 @@ __device__ __forceinline__ void item2_f64(const Tile &T, const Seg *__restrict__
     uint32_t ao[MB], bo[NB];   // lines of the further blocks, elements past the first one's
     const unsigned i0 = min(r16, mrem - 1), j0 = min(r16, nrem - 1);
     struct {
-      int64_t a_off, b_off, da, ea, db, eb;
+      int64_t a_off, b_off, a_p, da, ea, db, eb;
       double s;
-      uint32_t a_p, a_i, a_k, b_pk, b_k, b_n;   // strides below 2^32 (see mad)
+      uint32_t a_i, a_k, b_pk, b_k, b_n;   // strides below 2^32 (see operand_offset)
       int a_base, b_base, K, kb;
     } nx;   // descriptor of segment si
     auto fetch_desc = [&]() {
       CSegF &S = cs[si];
       nx.a_off = S.a_off; nx.b_off = S.b_off;
-      nx.a_p = (uint32_t)S.a_p; nx.a_i = (uint32_t)S.a_i; nx.a_k = (uint32_t)S.a_k;
+      nx.a_p = S.a_p; nx.a_i = (uint32_t)S.a_i; nx.a_k = (uint32_t)S.a_k;
       nx.b_pk = (uint32_t)S.b_pk; nx.b_k = (uint32_t)S.b_k; nx.b_n = (uint32_t)S.b_n;
       nx.da = S.da; nx.ea = S.ea; nx.db = S.db; nx.eb = S.eb;
       nx.s = S.s;
@@ -236,10 +232,8 @@ __device__ __forceinline__ void item2_f64(const Tile &T, const Seg *__restrict__
       k = min(q4, K - 1);
       const unsigned p = kb >= 4 ? 0 : kb == 3 ? (k == 3) : kb == 2 ? k >> 1 : k;
       kk = k - p * kb;
-      pa = seg_ptr(nx.a_base, psi, work) + nx.a_off;
-      pb = seg_ptr(nx.b_base, psi, work) + nx.b_off;
-      pa = mad(mad(mad(pa, p, nx.a_p), kk, nx.a_k), T.i0 + i0, nx.a_i);
-      pb = mad(mad(mad(pb, p, nx.b_pk), kk, nx.b_k), T.j0 + j0, nx.b_n);
+      pa = seg_ptr(nx.a_base, psi, work) + nx.a_off + operand_offset(p, nx.a_p, kk, nx.a_k, T.i0 + i0, nx.a_i);
+      pb = seg_ptr(nx.b_base, psi, work) + nx.b_off + operand_offset(p, nx.b_pk, kk, nx.b_k, T.j0 + j0, nx.b_n);
       k = q4;
 #pragma unroll
       for (int bi = 1; bi < MB; bi++) ao[bi] = (uint32_t)(min(16 * bi + r16, mrem - 1) - i0) * nx.a_i;

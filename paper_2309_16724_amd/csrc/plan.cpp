@@ -1930,3 +1930,8 @@ extern "C" int64_t dmrg_debug_plan_tiles(const dmrg_problem_t *prob, const dmrg_
   delete P;
   return n;
 }
+
+extern "C" int64_t dmrg_debug_operand_offset(int32_t pos, int64_t pos_stride, int32_t row, int64_t row_stride,
+                                             int32_t line, int64_t line_stride) {
+  return operand_offset(pos, pos_stride, row, row_stride, line, line_stride);
+}

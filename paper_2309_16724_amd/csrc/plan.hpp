@@ -26,6 +26,16 @@ struct Seg {
   int64_t da, ea, db, eb;
 };
 
+// Element offset of a line of row `row` of position `pos` of an operand, as the
+// FP64 wavefront tiles compute it.  Rows and lines have strides below 2^32 (the
+// width of a block or a stripe): one multiply-add each.  Positions are whole
+// blocks, 2^32 elements and more from sectors of 65536 states on: 64 bits.
+__host__ __device__ inline int64_t operand_offset(uint32_t pos, int64_t pos_stride, uint32_t row, int64_t row_stride,
+                                                  uint32_t line, int64_t line_stride) {
+  return (int64_t)pos * pos_stride + (int64_t)((uint64_t)row * (uint32_t)row_stride) +
+         (int64_t)((uint64_t)line * (uint32_t)line_stride);
+}
+
 // Work-group tiles: a tile with mb == MACRO_MB is a 64 x 64 tile computed by
 // the four wavefronts of a work group together from operand tiles they stage
 // in LDS once; the other tiles belong to one wavefront each.
