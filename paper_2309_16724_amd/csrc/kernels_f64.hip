@@ -33,10 +33,11 @@ __device__ __forceinline__ double gld(const double *p) { return *(gcptr)p; }
 
 
 // Operands lie in psi, in the stripe workspace or in operator arrays, which are
-// addressed absolutely (resolve_bases).  First-stage tiles are stored in the
-// workspace, second-stage ones in the output or among the partial tiles.
-__device__ __forceinline__ const double *seg_ptr(int id, const double *psi, const double *work) {
-  return id == BASE_PSI ? psi : id == BASE_WORK ? work : nullptr;
+// addressed absolutely (resolve_bases; off in bytes).  First-stage tiles are
+// stored in the workspace, second-stage ones in the output or among the partial
+// tiles.
+__device__ __forceinline__ const double *seg_ptr(int id, int64_t off, const double *psi, const double *work) {
+  return (const double *)((const char *)(id == BASE_PSI ? psi : id == BASE_WORK ? work : nullptr) + off);
 }
 template <int STAGE>
 __device__ __forceinline__ double *out_ptr(int id, double *y, double *work, double *part) {
@@ -98,7 +99,7 @@ __device__ __forceinline__ void item1_f64(const Tile &T, const Seg *__restrict__
   const double s = S.s;
   int k = min(q4, K - 1);
   const double *pa[MB], *pb[NB];
-  const double *A = seg_ptr(S.a_base, psi, work) + S.a_off, *B = seg_ptr(S.b_base, psi, work) + S.b_off;
+  const double *A = seg_ptr(S.a_base, S.a_off, psi, work), *B = seg_ptr(S.b_base, S.b_off, psi, work);
 #pragma unroll
   for (int bi = 0; bi < MB; bi++)
     pa[bi] = A + operand_offset(0, 0, k, S.a_k, T.i0 + min(16 * bi + r16, mrem - 1), S.a_i);
@@ -173,7 +174,7 @@ __device__ __forceinline__ void item2_f64(const Tile &T, const Seg *__restrict__
   asm volatile("" : "+v"(r16), "+v"(q4));
   for (int si = 0; si < T.nid; si++) {
     CSegF &S = cs[si];
-    const double *B = seg_ptr(S.b_base, psi, work) + S.b_off + T.i0 * S.b_k + T.j0 * S.b_n;
+    const double *B = seg_ptr(S.b_base, S.b_off, psi, work) + T.i0 * S.b_k + T.j0 * S.b_n;
     const double s = S.s;
     double v[MB][NB][4];
 #pragma unroll
@@ -232,8 +233,8 @@ __device__ __forceinline__ void item2_f64(const Tile &T, const Seg *__restrict__
       k = min(q4, K - 1);
       const unsigned p = kb >= 4 ? 0 : kb == 3 ? (k == 3) : kb == 2 ? k >> 1 : k;
       kk = k - p * kb;
-      pa = seg_ptr(nx.a_base, psi, work) + nx.a_off + operand_offset(p, nx.a_p, kk, nx.a_k, T.i0 + i0, nx.a_i);
-      pb = seg_ptr(nx.b_base, psi, work) + nx.b_off + operand_offset(p, nx.b_pk, kk, nx.b_k, T.j0 + j0, nx.b_n);
+      pa = seg_ptr(nx.a_base, nx.a_off, psi, work) + operand_offset(p, nx.a_p, kk, nx.a_k, T.i0 + i0, nx.a_i);
+      pb = seg_ptr(nx.b_base, nx.b_off, psi, work) + operand_offset(p, nx.b_pk, kk, nx.b_k, T.j0 + j0, nx.b_n);
       k = q4;
 #pragma unroll
       for (int bi = 1; bi < MB; bi++) ao[bi] = (uint32_t)(min(16 * bi + r16, mrem - 1) - i0) * nx.a_i;
@@ -384,7 +385,7 @@ __device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict
   asm volatile("" : "+v"(lane));
   for (int e = 0; STAGE == 2 && e < T.nid; e++) {
     CSegF &S = cs[e];
-    const double *B = seg_ptr(S.b_base, psi, work) + S.b_off;
+    const double *B = seg_ptr(S.b_base, S.b_off, psi, work);
     const double s = S.s;
 #pragma unroll
     for (int bi = 0; bi < G::MBW; bi++) {
@@ -441,8 +442,8 @@ __device__ __forceinline__ void wg_tile_f64(const Tile &T, const Seg *__restrict
       const int p0 = STAGE == 2 || T.j0 < S.b_nb ? 0 : T.j0 / S.b_nb;
       const int row = min(kr, wK - 1);
       wk = row;
-      wa = seg_ptr(S.a_base, psi, work) + S.a_off + (int64_t)T.i0 * S.a_i + row * ak;
-      wb = seg_ptr(S.b_base, psi, work) + S.b_off + (int64_t)p0 * S.b_pn + row * bk;
+      wa = seg_ptr(S.a_base, S.a_off, psi, work) + (int64_t)T.i0 * S.a_i + row * ak;
+      wb = seg_ptr(S.b_base, S.b_off, psi, work) + (int64_t)p0 * S.b_pn + row * bk;
       if (wk >= wkb) {   // kr < R <= 4, positions of at least two rows
         wk -= wkb;
         wa += ea;

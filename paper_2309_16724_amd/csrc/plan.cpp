@@ -1614,12 +1614,13 @@ extern "C" int dmrg_plan_stats(const dmrg_plan_t *p, dmrg_plan_stats_t *st) {
 // Test-only: build the plan for one problem whose operator data are HOST
 // arrays and execute its tile and segment lists on the CPU with the kernels'
 // addressing (no GPU use).  Checks the plan layout without a device.
-static void host_tiles(const std::vector<Tile> &tiles, const std::vector<Seg> &segs,
+static void host_tiles(const std::vector<Tile> &tiles, const std::vector<Seg> &plan_segs,
                        const std::vector<const double *> &bases, const double *psi, double *y,
                        double *work, double *part) {
-  auto base = [&](int id) -> const double * {
-    return id == BASE_PSI ? psi : id == BASE_Y ? y : id == BASE_WORK ? work : id == BASE_PART ? part
-                                                                                               : bases[id - BASE_OPS];
+  const std::vector<Seg> segs = resolve_bases(plan_segs, bases.data());   // the kernels' copy
+  auto operand = [&](int id, int64_t off) {
+    const double *p = id == BASE_PSI ? psi : id == BASE_WORK ? work : nullptr;
+    return (const double *)((uintptr_t)p + (uintptr_t)off);
   };
   auto Bel = [](const Seg &S, const double *B, int64_t k, int64_t n) {
     int64_t pk = k / S.b_kb, pn = n / S.b_nb;
@@ -1631,13 +1632,13 @@ static void host_tiles(const std::vector<Tile> &tiles, const std::vector<Seg> &s
     std::vector<double> acc((size_t)mt * nt, 0.0);
     for (int si = 0; si < T.nseg; si++) {
       const Seg &S = segs[T.seg0 + si];
-      const double *B = base(S.b_base) + S.b_off;
+      const double *B = operand(S.b_base, S.b_off);
       if (S.a_base < 0) {
         for (int j = 0; j < nt; j++)
           for (int i = 0; i < mt; i++) acc[i + (size_t)j * mt] += S.s * Bel(S, B, T.i0 + i, T.j0 + j);
         continue;
       }
-      const double *A = base(S.a_base) + S.a_off;
+      const double *A = operand(S.a_base, S.a_off);
       for (int j = 0; j < nt; j++)
         for (int i = 0; i < mt; i++) {
           double a = 0.0;
@@ -1649,7 +1650,7 @@ static void host_tiles(const std::vector<Tile> &tiles, const std::vector<Seg> &s
           acc[i + (size_t)j * mt] += a;
         }
     }
-    double *C = const_cast<double *>(base(T.c_base)) + T.c_off;
+    double *C = (T.c_base == BASE_Y ? y : T.c_base == BASE_WORK ? work : part) + T.c_off;
     for (int j = 0; j < nt; j++)
       for (int i = 0; i < mt; i++) {
         double &c = T.rowmajor ? C[(int64_t)(T.ci0 + i) * T.ldc + (T.cj0 + j)]

@@ -21,8 +21,9 @@ struct Seg {
   double s;
   int32_t a_base, b_base;
   int32_t K, a_kb, b_kb, b_nb;
-  // FP64 device copies (resolve_bases): the operands' strides over four K rows,
-  // and the extra one when that crosses a position boundary (a_kb == b_kb)
+  // FP64 device copies (resolve_bases; a_off and b_off are in bytes there): the
+  // operands' strides over four K rows, and the extra one when that crosses a
+  // position boundary (a_kb == b_kb)
   int64_t da, ea, db, eb;
 };
 
@@ -193,19 +194,22 @@ inline std::vector<Cell> f64_cells(int m, int n, int policy, bool wg) {
                     });
 }
 
-// Device copy of FP64 segments: operands in operator arrays (base BASE_OPS + k
-// at bases[k]) get the absolute element address as their offset, so that the
-// kernels need no look-up between a descriptor and its loads, and the strides
-// of the walk along K are filled in.
+// Device copy of FP64 segments: offsets in bytes, absolute addresses where the
+// operand lies in an operator array (base BASE_OPS + k at bases[k], whatever
+// its alignment), so that the kernels need no look-up between a descriptor and
+// its loads; the strides of the walk along K are filled in.
 inline std::vector<Seg> resolve_bases(std::vector<Seg> segs, const double *const *bases) {
+  auto bytes = [&](int base, int64_t off) {
+    return (int64_t)sizeof(double) * off + (base >= BASE_OPS ? (int64_t)(uintptr_t)bases[base - BASE_OPS] : 0);
+  };
   for (Seg &S : segs) {
-    if (S.a_base >= BASE_OPS) S.a_off += (int64_t)((uintptr_t)bases[S.a_base - BASE_OPS] / sizeof(double));
+    S.a_off = bytes(S.a_base, S.a_off);
+    S.b_off = bytes(S.b_base, S.b_off);
     const int64_t dp = 4 / S.a_kb, dk = 4 % S.a_kb;
     S.da = dp * S.a_p + dk * S.a_k;
     S.ea = S.a_p - S.a_kb * S.a_k;
     S.db = dp * S.b_pk + dk * S.b_k;
     S.eb = S.b_pk - S.b_kb * S.b_k;
-    if (S.b_base >= BASE_OPS) S.b_off += (int64_t)((uintptr_t)bases[S.b_base - BASE_OPS] / sizeof(double));
   }
   return segs;
 }
