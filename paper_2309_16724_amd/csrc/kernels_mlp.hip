@@ -345,13 +345,13 @@ __global__ void __launch_bounds__(NT) grad_part_kernel(const float *__restrict__
 #pragma unroll
       for (int b = 0; b < 2; b++) acc[a][b] = (v4d){0.0, 0.0, 0.0, 0.0};
     float f0[4], f1[4], d[4], z[4][2];
-    auto load = [&](int64_t i0) {   // rows past the end read the last one and count as zero (dg)
+    auto load = [&](int64_t i0) {   // rows past the end read the last one
 #pragma unroll
       for (int e = 0; e < 4; e++) {
         const int64_t i = i0 + 4 * e + q, ic = min(i, r1 - 1);
         f0[e] = x[ic * MLP_IN];
         f1[e] = x[ic * MLP_IN + 1];
-        d[e] = i < r1 ? dg[ic] : 0.0f;
+        d[e] = dg[ic];
 #pragma unroll
         for (int b = 0; b < 2; b++) z[e][b] = z2[ic * W + j0 + 16 * b + l16];
       }
@@ -366,6 +366,15 @@ __global__ void __launch_bounds__(NT) grad_part_kernel(const float *__restrict__
           av[e][b] = (double)fmaxf(layer1(b1[b], w10[b], w11[b], f0[e], f1[e]), 0.0f);
           bv[e][b] = (double)dz2_of(z[e][b], d[e], w3[b]);
         }
+      // ... and are zeros in both operands: zero times what the last row holds
+      // would make an infinite sum a NaN
+      if (i0 + 16 > r1) {
+#pragma unroll
+        for (int e = 0; e < 4; e++)
+#pragma unroll
+          for (int b = 0; b < 2; b++)
+            if (i0 + 4 * e + q >= r1) av[e][b] = bv[e][b] = 0.0;
+      }
       load(min(i0 + 16, r1 - 1));
 #pragma unroll
       for (int e = 0; e < 4; e++)
