@@ -571,6 +571,11 @@ int dmrg_debug_plan_host_apply(const dmrg_problem_t *prob, const double *psi, do
  * of tiles (call with out = NULL to size) or a negative status. */
 int64_t dmrg_debug_plan_tiles(const dmrg_problem_t *prob, const dmrg_plan_opts_t *opts, int32_t stage,
                               int64_t *out, int64_t cap);
+/* Test-only: the tiles that an m x n FP64 output is cut into (default policy,
+ * sectors below 2^14 states): (first row, first column, kind as above) written
+ * to out[3 * i ..] for i < cap; returns the number of tiles (out = NULL to
+ * size) or a negative status. */
+int32_t dmrg_debug_f64_cells(int32_t m, int32_t n, int32_t *out, int32_t cap);
 /* Test-only: element offset at which the FP64 wavefront tiles address line
  * `line` of row `row` of position `pos` of an operand with these strides. */
 int64_t dmrg_debug_operand_offset(int32_t pos, int64_t pos_stride, int32_t row, int64_t row_stride, int32_t line,

@@ -162,6 +162,7 @@ def load(path=None):
                                                  ctypes.POINTER(PlanOpts), ctypes.POINTER(PlanStats)]
         L.dmrg_debug_plan_tiles.argtypes = [ctypes.POINTER(ProblemT), ctypes.POINTER(PlanOpts), c_i32, c_vp, c_i64]
         L.dmrg_debug_plan_tiles.restype = c_i64
+        L.dmrg_debug_f64_cells.argtypes = [c_i32, c_i32, c_vp, c_i32]
         L.dmrg_debug_operand_offset.argtypes = [c_i32, c_i64, c_i32, c_i64, c_i32, c_i64]
         L.dmrg_debug_operand_offset.restype = c_i64
         c_f = ctypes.c_float
@@ -279,6 +280,17 @@ def debug_plan_tiles(prob, stage, lib=None, precision=0, n_slices=0, kpart=0, ti
     out = np.zeros((max(n, 1), 7), dtype=np.int64)
     L.dmrg_debug_plan_tiles(ctypes.byref(args.s), ctypes.byref(opts), stage, out.ctypes.data, n)
     return out[:n]
+
+
+def debug_f64_cells(m, n, lib=None):
+    """Test-only: the tiles of an m x n FP64 output, rows (first row, first
+    column, kind) -- see dmrg_debug_f64_cells."""
+    L = lib or load()
+    count = L.dmrg_debug_f64_cells(m, n, None, 0)
+    check(min(count, 0), L)
+    out = np.zeros((count, 3), dtype=np.int32)
+    L.dmrg_debug_f64_cells(m, n, out.ctypes.data, count)
+    return out
 
 
 def debug_jacobi(A, lib=None, sweeps=False):

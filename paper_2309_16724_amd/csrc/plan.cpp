@@ -1936,3 +1936,14 @@ extern "C" int64_t dmrg_debug_operand_offset(int32_t pos, int64_t pos_stride, in
                                              int32_t line, int64_t line_stride) {
   return operand_offset(pos, pos_stride, row, row_stride, line, line_stride);
 }
+
+extern "C" int32_t dmrg_debug_f64_cells(int32_t m, int32_t n, int32_t *out, int32_t cap) {
+  if (m <= 0 || n <= 0 || m >= WG_MAX_DIM || n >= WG_MAX_DIM) { set_error("output size out of range"); return DMRG_EINVAL; }
+  const std::vector<Cell> v = f64_cells(m, n, 0, true);
+  for (int i = 0; out && i < std::min<int>(cap, (int)v.size()); i++) {
+    out[3 * i] = v[i].i0;
+    out[3 * i + 1] = v[i].j0;
+    out[3 * i + 2] = v[i].mb;
+  }
+  return (int32_t)v.size();
+}
