@@ -567,8 +567,9 @@ int dmrg_debug_plan_host_apply(const dmrg_problem_t *prob, const double *psi, do
  * defaults, FP64) give for one problem (operator data not read): rows (tile
  * rows and columns inside the output, segments, summed K, rows and columns of
  * the whole output block, tile kind: 1, 2, 4 wavefront, 8 work-group 64 x 64,
- * 16 wide 128 x 128 of split plans, 32 the 128 x 128 of FP64 plans) written to out[7 * i ..] for i < cap; returns the number
- * of tiles (call with out = NULL to size) or a negative status. */
+ * 16 wide 128 x 128 of split plans, 32 the 128 x 128 of FP64 plans) written to
+ * out[7 * i ..] for i < cap; returns the number of tiles (call with out = NULL
+ * to size) or a negative status. */
 int64_t dmrg_debug_plan_tiles(const dmrg_problem_t *prob, const dmrg_plan_opts_t *opts, int32_t stage,
                               int64_t *out, int64_t cap);
 /* Test-only: the tiles that an m x n FP64 output is cut into (default policy,

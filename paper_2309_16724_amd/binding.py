@@ -265,7 +265,7 @@ def debug_plan_host_apply(prob, psi, workspace_bytes=0, lib=None, precision=0, n
 
 
 def debug_plan_tiles(prob, stage, lib=None, precision=0, n_slices=0, kpart=0, tile_policy=0, macro_min=0,
-                     wide_min=0):
+                     wide_min=0, workspace_bytes=0):
     """Test-only: the tiles of one stage of the plan for one problem, an
     array of rows (rows, columns, segments, summed K, output rows, output
     columns, kind) -- see dmrg_debug_plan_tiles."""
@@ -273,7 +273,7 @@ def debug_plan_tiles(prob, stage, lib=None, precision=0, n_slices=0, kpart=0, ti
     ld = np.ascontiguousarray(prob.left.data)
     rd = np.ascontiguousarray(prob.right.data)
     args = ProblemArgs(prob, ld.ctypes.data, rd.ctypes.data)
-    opts = PlanOpts(precision, n_slices, 0, 0, kpart, tile_policy, macro_min, wide_min, 0, None, None, None, None)
+    opts = PlanOpts(precision, n_slices, workspace_bytes, 0, kpart, tile_policy, macro_min, wide_min, 0, None, None, None, None)
     n = L.dmrg_debug_plan_tiles(ctypes.byref(args.s), ctypes.byref(opts), stage, None, 0)
     if n < 0:
         check(int(n), L)

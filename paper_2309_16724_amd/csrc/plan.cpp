@@ -207,6 +207,13 @@ struct Stripe {
   int index = 0;
 };
 
+// end of the run of consecutive positions that begins at slot s0
+size_t run_end(const std::vector<int> &slots, size_t s0) {
+  size_t s1 = s0 + 1;
+  while (s1 < slots.size() && slots[s1] == slots[s1 - 1] + 1) s1++;
+  return s1;
+}
+
 struct TaskRef { int prob; int task; };
 
 // algorithmic flops of a tile list: 2 (tile rows) (tile columns) K over its
@@ -233,8 +240,8 @@ bool use_wide(const dmrg_plan *P, int m, int n) {
 
 // Tiles of an m x n output (see cut_output); split plans take wide and 64 x 64
 // tiles by their own thresholds.
-std::vector<Cell> output_cells(const dmrg_plan *P, int m, int n) {
-  if (P->precision == DMRG_FP64) return f64_cells(m, n, P->tile_policy, P->wg_tiles);
+std::vector<Cell> output_cells(const dmrg_plan *P, int m, int n, int level) {
+  if (P->precision == DMRG_FP64) return f64_cells(m, n, P->tile_policy, level);
   return cut_output(m, n, use_wide(P, m, n) ? WIDE_MB : 0, std::min(P->wide_min, WIDE_EDGE), [&](int rows, int cols) {
     return use_macro(P, rows, cols) ? MACRO_MB : wave_mb(rows, cols, P->tile_policy);
   });
@@ -297,12 +304,22 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
       s.dRout = T.blocks[tk.F].dR;
       for (const auto &pa : T.rows[tk.row].pos) s.slots.push_back(pa.pD);
     }
-    int64_t woff = 0;
-    std::vector<double> cost1, cost1m, cost1x;   // K of every stage-1 tile
+    // positions of the stripes, and what the first stage's tiles cost
+    TileLevel est1;
     for (auto &kv : stripes) {
       Stripe &s = kv.second;
       std::sort(s.slots.begin(), s.slots.end());
       s.slots.erase(std::unique(s.slots.begin(), s.slots.end()), s.slots.end());
+      for (size_t s0 = 0, s1; s0 < s.slots.size(); s0 = s1) {
+        s1 = run_end(s.slots, s0);
+        est1.add(s.dL, (int)(s1 - s0) * s.dRout, 1, s.dRin, 1.0, P->tile_policy);
+      }
+    }
+    const int level1 = P->wg_tiles ? est1.level() : 0;
+    int64_t woff = 0;
+    std::vector<double> cost1, cost1m, cost1x;   // tile_cost of every stage-1 tile
+    for (auto &kv : stripes) {
+      Stripe &s = kv.second;
       s.off = woff;
       s.index = (int)ch.stripes.size();
       ch.stripes.push_back({kv.first.prob, kv.first.E, kv.first.rec, kv.first.adj, kv.first.dress, woff, s.dL,
@@ -319,8 +336,7 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
       int rows = pp.R.sec[rec.row_sec].dim, cols = pp.R.sec[rec.col_sec].dim;
       size_t s0 = 0;
       while (s0 < s.slots.size()) {
-        size_t s1 = s0 + 1;
-        while (s1 < s.slots.size() && s.slots[s1] == s.slots[s1 - 1] + 1) s1++;
+        const size_t s1 = run_end(s.slots, s0);
         Seg g{};
         g.a_base = BASE_PSI;
         g.a_off = pp.psi_off + E.off;
@@ -346,7 +362,7 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
         double fl = 2.0 * s.dL * s.dRin * N;
         P->stats.stage1_flops += fl;
         ch.flops1 += fl;
-        for (const Cell &cell : output_cells(P, s.dL, N)) {
+        for (const Cell &cell : output_cells(P, s.dL, N, level1)) {
             const int i0 = cell.i0, j0 = cell.j0, mb = cell.mb;
             Tile t{};
             t.c_base = BASE_WORK;
@@ -444,6 +460,15 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
         q = q1;
       }
     }
+    TileLevel est2;
+    for (auto &kv : byF) {
+      const PsiBlock &F = P->probs[kv.first[0]]->T.blocks[kv.first[2]];
+      double k = 0.0;
+      for (auto &gi : kv.second) k += gi.first.a_base < 0 ? 0.25 * gi.first.K : (double)gi.first.K;
+      const double parts = std::ceil(std::max(k, 1.0) / P->kpart);
+      est2.add(F.dL, F.dR, (int)(kv.second.size() / parts), std::min(k, (double)P->kpart), parts, P->tile_policy);
+    }
+    const int level2 = P->wg_tiles ? est2.level() : 0;
     std::vector<std::pair<double, Tile>> tiles2, tiles2m, tiles2x;
     int64_t npart = 0;   // partial-tile elements
     for (auto &kv : byF) {
@@ -506,7 +531,7 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
       int seg0 = (int)ch.seg2.size();
       for (auto &g : pieces) ch.seg2.push_back(g);
       for (auto &gi : pinfo) ch.s2info.push_back(gi);
-      const auto cells = output_cells(P, F.dL, F.dR);
+      const auto cells = output_cells(P, F.dL, F.dR, level2);
       const int np = (int)parts.size();
       // partial tiles of cell c, part p at npart + coff[c] + p tm tn (tm x tn
       // the tile's part inside the output); the list runs over parts (outer) and cells in
@@ -1904,7 +1929,7 @@ extern "C" int64_t dmrg_debug_plan_tiles(const dmrg_problem_t *prob, const dmrg_
   P->bases_h = {prob->ldata, prob->rdata, nullptr};
   P->psi_len = pp->T.size;
   P->probs.push_back(std::move(pp));
-  int rc = build_plan(P, DEFAULT_WORKSPACE, false);
+  int rc = build_plan(P, opts && opts->workspace_bytes > 0 ? opts->workspace_bytes : DEFAULT_WORKSPACE, false);
   if (rc) { delete P; return rc; }
   int64_t n = 0;
   for (auto &ch : P->chunks) {
@@ -1939,7 +1964,7 @@ extern "C" int64_t dmrg_debug_operand_offset(int32_t pos, int64_t pos_stride, in
 
 extern "C" int32_t dmrg_debug_f64_cells(int32_t m, int32_t n, int32_t *out, int32_t cap) {
   if (m <= 0 || n <= 0 || m >= WG_MAX_DIM || n >= WG_MAX_DIM) { set_error("output size out of range"); return DMRG_EINVAL; }
-  const std::vector<Cell> v = f64_cells(m, n, 0, true);
+  const std::vector<Cell> v = f64_cells(m, n, 0, 2);
   for (int i = 0; out && i < std::min<int>(cap, (int)v.size()); i++) {
     out[3 * i] = v[i].i0;
     out[3 * i + 1] = v[i].j0;

@@ -157,6 +157,11 @@ inline std::vector<std::pair<int, int>> patch_order(int nr, int nc) {
   return v;
 }
 
+// Lines of the 128-wide bands of `len` lines, a last band of at least `tail`
+// lines included.
+inline int wide_bands(int len, int tail) { return len / WIDE_EDGE + (len % WIDE_EDGE >= tail ? 1 : 0); }
+inline int wide_lines(int len, int tail) { return std::min(len, wide_bands(len, tail) * WIDE_EDGE); }
+
 // Tiles of an m x n output.  With `wide` it is cut into 128-wide row and
 // column bands (a last band of at least `tail` lines is wide too): the wide x
 // wide cells in patch order, then the columns beyond the bands, then the rows
@@ -176,23 +181,74 @@ std::vector<Cell> cut_output(int m, int n, int wide, int tail, F &&small) {
     grid(0, 0, m, n);
     return v;
   }
-  auto bands = [&](int len) { return len / WIDE_EDGE + (len % WIDE_EDGE >= tail ? 1 : 0); };
-  const int nr = bands(m), nc = bands(n);
-  const int mw = std::min(m, nr * WIDE_EDGE), nw = std::min(n, nc * WIDE_EDGE);
-  for (const auto &c : patch_order(nr, nc)) v.push_back({c.first * WIDE_EDGE, c.second * WIDE_EDGE, wide});
+  const int mw = wide_lines(m, tail), nw = wide_lines(n, tail);
+  for (const auto &c : patch_order(wide_bands(m, tail), wide_bands(n, tail))) v.push_back({c.first * WIDE_EDGE, c.second * WIDE_EDGE, wide});
   grid(0, nw, mw, n - nw);
   grid(mw, 0, m - mw, n);
   return v;
 }
 
-// ... of an FP64 output; wg: work-group tiles allowed
-inline std::vector<Cell> f64_cells(int m, int n, int policy, bool wg) {
-  const bool wide = wg && std::min(m, n) >= F64_WIDE_MIN && std::max(m, n) >= F64_WIDE_MAX;
-  return cut_output(m, n, wide ? F64_WIDE_MB : 0, F64_WIDE_MIN,
-                    [&](int rows, int cols) {
-                      return wg && std::min(rows, cols) >= F64_MACRO_MIN ? MACRO_MB : wave_mb(rows, cols, policy);
-                    });
+// ... of an FP64 output; level: the largest kind allowed (0 wavefront tiles,
+// 1 64 x 64, 2 128 x 128)
+inline bool f64_wide(int m, int n) { return std::min(m, n) >= F64_WIDE_MIN && std::max(m, n) >= F64_WIDE_MAX; }
+inline int f64_small(int rows, int cols, int policy, int level) {
+  return level > 0 && std::min(rows, cols) >= F64_MACRO_MIN ? MACRO_MB : wave_mb(rows, cols, policy);
 }
+inline std::vector<Cell> f64_cells(int m, int n, int policy, int level) {
+  return cut_output(m, n, level > 1 && f64_wide(m, n) ? F64_WIDE_MB : 0, F64_WIDE_MIN,
+                    [&](int rows, int cols) { return f64_small(rows, cols, policy, level); });
+}
+
+// The level for a stage of an FP64 plan.  The three kinds of a stage run one
+// after the other, each at least as long as its longest tile, so a stage of few
+// outputs (a plan cut into many small chunks, or long parts along K) is sooner
+// done with smaller tiles that run side by side.  Estimated from the tiles'
+// costs (tile_cost) at the times measured for a K row of a whole tile, alone and
+// with all work groups that fit on the chip at once.  Second stage of L=36,
+// D=512 (sectors up to 137): in 64 MiB chunks 36.3 ms with all kinds, 13.8 with
+// wavefront tiles (estimated 38.0 and 14.2); in one chunk 5.1 and 7.0 (5.0, 7.8).
+// Sums are in the same order either way.
+class TileLevel {
+ public:
+  // `copies` outputs of m x n, each summing nseg segments of k rows in all
+  void add(int m, int n, int nseg, double k, double copies, int policy) {
+    for (int level = 0; level < 3; level++) {
+      auto part = [&](int rows, int cols, int mb) {
+        if (rows <= 0 || cols <= 0) return;
+        const int tr = tile_rows(mb), tc = tile_cols(mb);
+        const double tiles = (double)((rows + tr - 1) / tr) * ((cols + tc - 1) / tc);
+        const double blocks = (double)((rows + 15) / 16) * ((cols + 15) / 16) / (tiles * (tr * tc / 256));
+        Kind &x = kinds[level][mb == F64_WIDE_MB ? 0 : mb == MACRO_MB ? 1 : 2];
+        x.sum += copies * tiles * (32.0 + 4.0 * nseg + k * (0.5 + 0.5 * blocks));
+        x.top = std::max(x.top, tile_cost(mb, std::min(rows, tr), std::min(cols, tc), nseg, k));
+      };
+      if (level < 2 || !f64_wide(m, n)) {
+        part(m, n, f64_small(m, n, policy, level));
+        continue;
+      }
+      const int mw = wide_lines(m, F64_WIDE_MIN), nw = wide_lines(n, F64_WIDE_MIN);
+      part(mw, nw, F64_WIDE_MB);
+      part(mw, n - nw, f64_small(mw, n - nw, policy, level));
+      part(m - mw, n, f64_small(m - mw, n, policy, level));
+    }
+  }
+  // the usual level 2 unless another one is expected to take less than three
+  // quarters of its time
+  int level() const {
+    // us per K row: a tile alone, and all together: 512 wide tiles at once take
+    // 0.30, 1024 64 x 64 ones 0.17, 4096 wavefront ones 0.34; 8 us a launch
+    constexpr double ALONE[3] = {0.16, 0.07, 0.076}, BUSY[3] = {0.30 / 512, 0.17 / 1024, 0.34 / 4096};
+    double t[3] = {0.0, 0.0, 0.0};
+    for (int l = 0; l < 3; l++)
+      for (int k = 0; k < 3; k++)
+        if (kinds[l][k].sum > 0.0) t[l] += 8.0 + std::max(kinds[l][k].top * ALONE[k], kinds[l][k].sum * BUSY[k]);
+    const int best = t[0] < t[1] ? 0 : 1;
+    return t[best] < 0.75 * t[2] ? best : 2;
+  }
+
+ private:
+  struct Kind { double sum = 0.0, top = 0.0; } kinds[3][3];   // by level; wide, 64 x 64, wavefront
+};
 
 // Device copy of FP64 segments: offsets in bytes, absolute addresses where the
 // operand lies in an operator array (base BASE_OPS + k at bases[k], whatever

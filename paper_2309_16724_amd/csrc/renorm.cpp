@@ -1126,7 +1126,7 @@ int build_renorm(const dmrg_problem_t *prob, const dmrg_rkeep_t *keep, int n_kee
   for (int k = 0; k < n_keep; k++) wg = wg && kept(k) < WG_MAX_DIM;
   auto add_tiles = [&](std::vector<Tile> &tiles, std::vector<double> &cost, int m, int n, int c_base,
                        int64_t c_off, int64_t ldc, int seg0, int nseg, double ksum, int rowmajor) {
-    for (const Cell &c : f64_cells(m, n, 0, wg)) {
+    for (const Cell &c : f64_cells(m, n, 0, wg ? 2 : 0)) {
       Tile T{};
       T.c_off = c_off; T.ldc = ldc; T.c_base = c_base;
       T.m = m; T.n = n; T.i0 = c.i0; T.j0 = c.j0; T.ci0 = c.i0; T.cj0 = c.j0;

@@ -147,7 +147,7 @@ int build_rho(const dmrg_problem_t *prob, int32_t flags, RhoLists &RL) {
         const int nseg = (int)segs.size() - seg0;
         if (nseg == 0) continue;
         const int m = ca.dim, n = cb.dim;
-        for (const Cell &c : f64_cells(m, n, 0, wg)) {
+        for (const Cell &c : f64_cells(m, n, 0, wg ? 2 : 0)) {
           Tile T{};
           T.c_off = roff[si] + ca.row0 + (int64_t)cb.row0 * P.rows;
           T.ldc = P.rows; T.c_base = BASE_Y;

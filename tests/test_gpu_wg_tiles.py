@@ -1,6 +1,8 @@
-"""Density matrices and renormalizations whose sectors reach the work-group
-tiles (64 x 64 from 48 states on, 128 x 128 from 64 x 96 on), both sides, against
-the oracle.  That the sizes reach both kinds is asserted."""
+"""H.psi plans, density matrices and renormalizations whose sectors reach the
+work-group tiles (64 x 64 from 48 states on, 128 x 128 from 64 x 96 on), both
+sides, against the oracle.  That the sizes reach both kinds is asserted."""
+import ctypes
+
 import numpy as np
 import pytest
 
@@ -16,6 +18,51 @@ pytestmark = pytest.mark.gpu
 
 def _kinds(sizes):
     return {int(k) for m in sizes for n in sizes for k in B.debug_f64_cells(m, n)[:, 2]}
+
+
+def _launches(plan, code):
+    n = ctypes.c_int64()
+    B.check(plan.lib.dmrg_get_profile(plan.handle, code, ctypes.byref(n), None, None), plan.lib)
+    return n.value
+
+
+@pytest.mark.parametrize("D,Dr,codes", [(340, 700, (11, 12, 31, 32)), (620, 150, (11, 12, 31, 32)),
+                                        (160, 640, (11, 31, 32))])
+def test_batches_use_work_group_tiles(D, Dr, codes):
+    """Sixteen copies of a problem give both stages enough outputs for work-group
+    tiles (their launches are counted: 1 for 64 x 64, 3 for 128 x 128, then the
+    stage; the last shape has no second-stage output between them); each copy, with a vector of its own, against the
+    oracle.  FP64 sums in another order: 1e-12 of the largest element."""
+    import torch
+    from oracle.hpsi import HEff
+    from paper_2309_16724_amd.hpsi import Plan
+    prob = random_problem(6, 6, 0, 5, D=D, D_right=Dr, cap=False)
+    he = HEff(prob)
+    x = np.random.default_rng(3).standard_normal((16, he.size))
+    plan = Plan([prob] * 16)
+    B.check(plan.lib.dmrg_set_profiling(plan.handle, 1), plan.lib)
+    y = plan.apply(torch.from_numpy(x.reshape(-1)).cuda()).cpu().numpy().reshape(x.shape)
+    counts = {code: _launches(plan, code) for code in codes}
+    plan.free()
+    assert all(counts.values()), counts
+    for k in (0, 5, 15):
+        ref = he.apply(x[k])
+        assert np.abs(y[k] - ref).max() <= 1e-12 * np.abs(ref).max(), k
+
+
+@pytest.mark.parametrize("opts", [dict(workspace_bytes=2 << 20), dict(workspace_bytes=8 << 20), dict(kpart=16384)])
+def test_plans_of_few_tiles_match_oracle(opts):
+    import torch
+    from oracle.hpsi import HEff
+    from paper_2309_16724_amd.hpsi import Plan
+    prob = random_problem(6, 6, 0, 5, D=340, D_right=300, cap=False)
+    he = HEff(prob)
+    x = np.random.default_rng(4).standard_normal(he.size)
+    ref = he.apply(x)
+    plan = Plan(prob, **opts)
+    y = plan.apply(torch.from_numpy(x).cuda()).cpu().numpy()
+    plan.free()
+    assert np.abs(y - ref).max() <= 1e-12 * np.abs(ref).max()
 
 
 @pytest.mark.parametrize("right", [False, True])

@@ -32,8 +32,26 @@ def test_tile_kinds(m, n, kinds):
 
 def test_plans_of_the_gpu_tests_have_every_kind():
     """The shapes that test_gpu_tile_edges.py compares with the oracle reach
-    all five kinds in the second stage."""
+    all five kinds (the 128 x 128 one in the first stage; the second stage's are
+    in test_gpu_wg_tiles.py)."""
     seen = set()
     for D, Dr in ((300, 300), (340, 700), (620, 150), (160, 640)):
-        seen |= set(B.debug_plan_tiles(random_problem(6, 6, 0, 5, D=D, D_right=Dr, cap=False), 2)[:, 6])
+        prob = random_problem(6, 6, 0, 5, D=D, D_right=Dr, cap=False)
+        first = set(B.debug_plan_tiles(prob, 1)[:, 6])
+        assert 32 in first, (D, Dr, first)
+        seen |= first | set(B.debug_plan_tiles(prob, 2)[:, 6])
     assert seen == {1, 2, 4, 8, 32}
+
+
+def test_small_chunks_and_long_parts_take_small_tiles():
+    """Few outputs at a time leave no room for large tiles: a plan in one chunk
+    has 128 x 128 tiles in both stages, in chunks of 8 MiB none (64 x 64 ones in a
+    few chunks), and with parts of 16384 along K none in the second stage."""
+    prob = random_problem(6, 6, 0, 1, D=600, cap=False)
+
+    def kinds(stage, **kw):
+        return set(B.debug_plan_tiles(prob, stage, **kw)[:, 6])
+
+    assert 32 in kinds(1) and 32 in kinds(2)
+    assert 32 not in kinds(1, workspace_bytes=8 << 20) | kinds(2, workspace_bytes=8 << 20)
+    assert 32 in kinds(1, kpart=16384) and 32 not in kinds(2, kpart=16384)
