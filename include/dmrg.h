@@ -344,15 +344,15 @@ int dmrg_mlp_collect(dmrg_plan_t *p, const double *psi0, const dmrg_dav_opts_t *
 void dmrg_mlp_free(dmrg_mlp_t *m);
 
 /* Profiling: when on, dmrg_apply_H records a hipEvent pair on its stream
- * around each tile launch of the first (1) and second (2) stage -- the wide
- * and the 64 x 64 work-group tile launches of split plans and the wavefront
- * tile launch, each with the algorithmic flops of its tiles (slicing launches
- * fall outside the pairs).  dmrg_get_profile waits for the recorded events
+ * around each tile launch of the first (1) and second (2) stage -- the
+ * 128 x 128 and the 64 x 64 work-group tile launches and the wavefront tile
+ * launch, of plans of either precision, each with the algorithmic flops of its
+ * tiles (slicing launches fall outside the pairs).  dmrg_get_profile waits for the recorded events
  * and returns the number of launches, their summed duration and summed
  * algorithmic flops since the last dmrg_set_profiling call, for stage 1 or 2
  * (all its tile launches), 11 or 12 (its 64 x 64 work-group tile launches
- * only), 21 or 22 (its wavefront tile launches only) or 31 or 32 (its wide
- * tile launches only). */
+ * only), 21 or 22 (its wavefront tile launches only) or 31 or 32 (its
+ * 128 x 128 tile launches only). */
 int dmrg_set_profiling(dmrg_plan_t *p, int32_t on);
 int dmrg_get_profile(dmrg_plan_t *p, int32_t stage, int64_t *n_launches, double *total_ms,
                      double *total_flops);
@@ -455,9 +455,9 @@ int dmrg_renorm_records(const dmrg_renorm_t *r, dmrg_oprec_t *rec, int64_t cap, 
 int dmrg_renorm_apply(dmrg_renorm_t *r, const double *u, double *out, void *stream);
 int dmrg_renorm_stats(const dmrg_renorm_t *r, dmrg_renorm_stats_t *st);
 /* Profiling as for plans: when on, dmrg_renorm_apply records a hipEvent pair
- * on its stream around the first-stage (1) and the second-stage (2) product
- * launch; dmrg_renorm_get_profile waits for them and returns the number of
- * launches, their summed duration and algorithmic flops since the last
+ * on its stream around the first-stage (1) and around the second-stage (2)
+ * product launches, up to three kinds of tiles each; dmrg_renorm_get_profile
+ * waits for them and returns the number of recorded stages, their summed duration and algorithmic flops since the last
  * dmrg_renorm_set_profiling call. */
 int dmrg_renorm_set_profiling(dmrg_renorm_t *r, int32_t on);
 int dmrg_renorm_get_profile(dmrg_renorm_t *r, int32_t stage, int64_t *n_launches, double *total_ms,

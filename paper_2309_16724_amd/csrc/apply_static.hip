@@ -12,14 +12,15 @@ namespace {
 
 constexpr int64_t SCRATCH_BYTES = DMRG_STATIC_SCRATCH_BYTES;
 constexpr int MAX_DEVICES = 64;
-// The work queues take one line per counter and two counter sets; the limit
-// on a plan's scratch memory counts them as the 2304 bytes of one packed set.
-constexpr int64_t QUEUE_EXTRA = (4 * (int64_t)dmrg::QUEUE_INTS + 255) / 256 * 256 - 2304;
+// The limit counts the queue counters as the 2304 bytes they took when it was
+// set (2048 now), so that the same plans pass it.
+constexpr int64_t QUEUE_COUNTED = 2304 - (4 * (int64_t)dmrg::QUEUE_INTS + 255) / 256 * 256;
+static_assert(QUEUE_COUNTED >= 0, "what the limit accepts fits the array");
 
 // Every GPU the library runs on holds its own copy until the process ends.
 // In host code the name is a host-side stand-in: only the address returned by
 // hipGetSymbolAddress (per device) may be passed to kernels.
-__device__ __align__(256) unsigned char scratch[SCRATCH_BYTES + QUEUE_EXTRA];
+__device__ __align__(256) unsigned char scratch[SCRATCH_BYTES];
 
 std::mutex g_mu;
 void *g_scratch[MAX_DEVICES] = {};
@@ -52,7 +53,7 @@ extern "C" int dmrg_apply_H_static(dmrg_plan_t *p, const double *psi, double *hp
   if (!p || !psi || !hpsi) { dmrg::set_error("null argument"); return DMRG_EINVAL; }
   if (psi == hpsi) { dmrg::set_error("psi and hpsi must not alias"); return DMRG_EINVAL; }
   int64_t off[dmrg::SCRATCH_REGIONS];
-  const int64_t need = dmrg::plan_scratch_layout(p, off) - QUEUE_EXTRA;
+  const int64_t need = dmrg::plan_scratch_layout(p, off) + QUEUE_COUNTED;
   if (need > SCRATCH_BYTES) {
     dmrg::set_error("dmrg_apply_H_static: the plan needs " + std::to_string(need) +
                     " bytes of scratch memory, more than the static " + std::to_string(SCRATCH_BYTES) +

@@ -983,8 +983,10 @@ void build_split(dmrg_plan *P) {
   slice_items(P->jobs_ops, 0, P->items_ops);
   slice_items(P->jobs_psi, 0, P->items_psi);
   for (auto &ch : P->chunks) check_jobs(ch.tjobs);
-  // the split kernels address a segment's slice lines with 32-bit byte
-  // offsets from the slice base: rows * ld * 2 s bytes must stay below 2^32
+  // operands whose lines span 4 GiB of slices or more (large sectors times many
+  // positions) are refused, as they were when lines lay one after the other and
+  // were addressed in 32 bits.  The panels' kernels need less: line lengths below
+  // 2^31 (check_jobs).
   for (auto &ch : P->chunks)
     for (int st = 0; st < 6; st++) {
       const auto &tiles = st == 0 ? ch.tile1 : st == 1 ? ch.tile1m : st == 2 ? ch.tile1x

@@ -112,17 +112,19 @@ inline int wave_chunk(int ntiles, double flops) {
   return c < 1.0 ? 1 : c > 8.0 ? 8 : (int)c;
 }
 
-// FP64 outputs with both sides >= F64_WIDE_MIN, one of them at least a whole
-// band, take 128 x 128 work-group tiles; other outputs (and the strips beyond
-// the bands) with both sides >= F64_MACRO_MIN 64 x 64 ones.  A 32 x 32
-// wavefront tile fetches 0.125 B per flop, 4.5 TB/s at the 36 TF/s it reached
-// on large outputs; a 128 x 128 one a quarter of that.  L=54, D=1024: 138.8 ms
-// with wavefront tiles alone, 87.6 ms with 64/48, 89.7 ms with 48/33, 92 ms
-// with 96/48 or 64 x 64 tiles alone.  L=24, D=512 (sectors up to 83): 128-wide
-// tiles of which one side is half empty cost 0.87 ms where 64 x 64 ones take
-// 0.63, so a whole band is asked for.  Sectors of WG_MAX_DIM states and more stay with wavefront tiles (the
-// work-group tiles address an operand's lines by 32-bit byte offsets).
-constexpr int F64_WIDE_MIN = 64, F64_WIDE_MAX = 96, F64_MACRO_MIN = 48, WG_MAX_DIM = 1 << 14;
+// FP64 outputs with both sides >= F64_WIDE_MIN, the longer >= F64_WIDE_LONG,
+// take 128 x 128 work-group tiles; other outputs (and the strips beyond the
+// bands) with both sides >= F64_MACRO_MIN 64 x 64 ones (see TileLevel for
+// stages of few outputs).  A 32 x 32 wavefront tile fetches 0.125 B per flop,
+// 4.5 TB/s at the 36 TF/s it reached on large outputs; a 128 x 128 one a
+// quarter of that.  L=54, D=1024: 138.8 ms with wavefront tiles alone, 87.6 ms
+// with 64/48, 89.7 ms with 48/33, 92 ms with 96/48 or 64 x 64 tiles alone (84
+// now, see heavy_tiles).  L=24, D=512 (sectors up to 83): 128-wide tiles of
+// which both sides are half empty cost 0.87 ms where 64 x 64 ones take 0.63,
+// hence F64_WIDE_LONG.  Sectors of WG_MAX_DIM states and more stay with
+// wavefront tiles (the work-group tiles address an operand's lines by 32-bit
+// byte offsets).
+constexpr int F64_WIDE_MIN = 64, F64_WIDE_LONG = 96, F64_MACRO_MIN = 48, WG_MAX_DIM = 1 << 14;
 
 // A cell of an output's tiling: top-left corner and tile kind.
 struct Cell { int i0, j0, mb; };
@@ -190,7 +192,7 @@ std::vector<Cell> cut_output(int m, int n, int wide, int tail, F &&small) {
 
 // ... of an FP64 output; level: the largest kind allowed (0 wavefront tiles,
 // 1 64 x 64, 2 128 x 128)
-inline bool f64_wide(int m, int n) { return std::min(m, n) >= F64_WIDE_MIN && std::max(m, n) >= F64_WIDE_MAX; }
+inline bool f64_wide(int m, int n) { return std::min(m, n) >= F64_WIDE_MIN && std::max(m, n) >= F64_WIDE_LONG; }
 inline int f64_small(int rows, int cols, int policy, int level) {
   return level > 0 && std::min(rows, cols) >= F64_MACRO_MIN ? MACRO_MB : wave_mb(rows, cols, policy);
 }

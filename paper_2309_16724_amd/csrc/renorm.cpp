@@ -13,7 +13,7 @@
 // identity) and B a site operator (or the identity); coef = alpha C~
 // <s_b||B||s_a> (-1)^(parity(B) N_a) (and the adjoint phase when A is
 // applied as an adjoint).  The products run on the FP64 stripe engine of
-// H.psi in two launches: T = op(A) U_a'[rows] for every distinct
+// H.psi in two stages: T = op(A) U_a'[rows] for every distinct
 // (member, ket component) and O' = sum coef U_b'[rows]^T T, every output
 // tile summing its terms in a fixed order (no atomics, reproducible).
 //
@@ -1259,7 +1259,7 @@ int build_renorm(const dmrg_problem_t *prob, const dmrg_rkeep_t *keep, int n_kee
     add_tiles(B.t2, cost2, m, n, BASE_Y, off, m, seg0, (int)B.s2.size() - seg0, ksum, 0);
   }
   // every element a kernel lane may touch lies inside its array (lanes past
-  // the tile or K read inside the operand: row 0, column 0, element K - 1)
+  // the output or K read the operand's last row, column or element)
   auto inside = [&](const std::vector<Tile> &tiles, const std::vector<Seg> &segs) {
     auto len = [&](int base) { return base == BASE_PSI ? u_len : base == BASE_Y ? B.out_len
                                     : base == BASE_WORK ? B.work_len : base == BASE_OPS + 2 ? B.dress_len

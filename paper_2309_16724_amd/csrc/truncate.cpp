@@ -158,8 +158,8 @@ int build_rho(const dmrg_problem_t *prob, int32_t flags, RhoLists &RL) {
         }
       }
   }
-  // every lane's reads stay inside psi (lanes past the tile or K read row 0,
-  // column 0 or element K - 1 of their operand)
+  // every lane's reads stay inside psi (lanes past the output or K read their
+  // operand's last row, column or element)
   for (const Tile &T : tiles)
     for (int i = 0; i < T.nseg; i++) {
       const Seg &S = segs[T.seg0 + i];
