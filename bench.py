@@ -130,7 +130,8 @@ def cpu_baseline(flops_bench, bench_workload):
     }
 
 
-# HBM bytes per launch of the stage kernels at L54_D2048 from the FETCH_SIZE
+# HBM bytes per launch of the stage kernels (renormalizations: of a stage's
+# launches together) at L54_D2048 from the FETCH_SIZE
 # and WRITE_SIZE runs summarised in profiles/hpsi_L54_D2048_split5.md and
 # profiles/hpsi_L54_D2048_fp64.md: FETCH scaled by 2.000 and WRITE by 1.000,
 # what the same counters read for a plain 256 MiB device copy in the same
@@ -138,18 +139,19 @@ def cpu_baseline(flops_bench, bench_workload):
 # traffic are the ones it was taken on (their hash); else null.
 _SPLIT_SRC = ("kernels_split.hip", "plan.cpp", "plan.hpp", "model.cpp")
 _F64_SRC = ("kernels_f64.hip", "plan.cpp", "plan.hpp", "model.cpp")
-_REN_SRC = ("renorm.cpp", "kernels_f64.hip")
+_REN_SRC = ("renorm.cpp", "kernels_f64.hip", "plan.hpp")
+_SPLIT_HASH, _F64_HASH, _REN_HASH = "2faf80d9bd82fcc3", "775e1157fd1c7a63", "26e8904f973e60e9"
 MEASURED_TRAFFIC = {
-    ("L54_D2048", "stage1_wsplit5_kernel"): (1.6826e11, _SPLIT_SRC, "fd14f25f69d6d718"),
-    ("L54_D2048", "stage2_wsplit5_kernel"): (2.2778e11, _SPLIT_SRC, "fd14f25f69d6d718"),
-    ("L54_D2048", "stage_f64_kernel<1>"): (3.5086e11, _F64_SRC, "69c8d5cbc4f75ca9"),
-    ("L54_D2048", "stage_f64_kernel<2>"): (1.0639e12, _F64_SRC, "69c8d5cbc4f75ca9"),
+    ("L54_D2048", "stage1_wsplit5_kernel"): (1.8150e11, _SPLIT_SRC, _SPLIT_HASH),
+    ("L54_D2048", "stage2_wsplit5_kernel"): (2.7840e11, _SPLIT_SRC, _SPLIT_HASH),
+    ("L54_D2048", "wg_f64_kernel<WgTile<2, 4, 4, 2, 4>, 1>"): (1.6990e11, _F64_SRC, _F64_HASH),
+    ("L54_D2048", "wg_f64_kernel<WgTile<2, 4, 4, 2, 4>, 2>"): (2.6319e11, _F64_SRC, _F64_HASH),
     # renormalization of the L54_D2048 left block (profiles/renorm_left_L54_D2048_fp64.md)
-    ("L54_D2048", "renorm:stage_f64_kernel<1>"): (1.3855e11, _REN_SRC, "7150222daa7f2493"),
-    ("L54_D2048", "renorm:stage_f64_kernel<2>"): (1.7818e11, _REN_SRC, "7150222daa7f2493"),
+    ("L54_D2048", "renorm:1"): (6.420e10, _REN_SRC, _REN_HASH),
+    ("L54_D2048", "renorm:2"): (5.239e10, _REN_SRC, _REN_HASH),
     # the right block through the right site (profiles/renorm_right_L54_D2048_fp64.md)
-    ("L54_D2048", "renorm_right:stage_f64_kernel<1>"): (3.1297e11, _REN_SRC, "7150222daa7f2493"),
-    ("L54_D2048", "renorm_right:stage_f64_kernel<2>"): (5.3775e11, _REN_SRC, "7150222daa7f2493"),
+    ("L54_D2048", "renorm_right:1"): (1.5735e11, _REN_SRC, _REN_HASH),
+    ("L54_D2048", "renorm_right:2"): (1.1877e11, _REN_SRC, _REN_HASH),
 }
 
 
@@ -530,7 +532,8 @@ def renorm_run(torch, workload, steps, warmup, prob=None, all_pairs=False, right
     dom = max((1, 2), key=lambda s_: prof[s_][1])
     n_d, ms_d, fl_d = prof[dom]
     ach = (fl_d / n_d) / (ms_d / n_d * 1e-3) / 1e12
-    kname = "stage_f64_kernel<%d>" % dom
+    # the stage's launches together: 128 x 128, 64 x 64 and wavefront tiles
+    kname = "stage %d: wg_f64_kernel, stage_f64_kernel" % dom
     return {"ms": ms, "tflops": tf, "flops": flops, "flops_stage1": st["flops1"], "flops_stage2": st["flops2"],
             "kept_states": int(sum(u.shape[1] for _, _, u in keep)),
             "product_states": int(sum(u.shape[0] for _, _, u in keep)),
@@ -543,7 +546,8 @@ def renorm_run(torch, workload, steps, warmup, prob=None, all_pairs=False, right
             "stages_ms": {str(k): v[1] / max(v[0], 1) for k, v in prof.items()},
             "roofline": {"bound": "mfma", "kernel": kname, "achieved": ach, "peak": FP64_PEAK_TFLOPS,
                          "unit": "TFLOP/s", "frac": ach / FP64_PEAK_TFLOPS,
-                         "traffic": measured_traffic(workload, ("renorm_right:" if right else "renorm:") + kname)}}
+                         "traffic": None if all_pairs else
+                         measured_traffic(workload, "renorm%s:%d" % ("_right" if right else "", dom))}}
 
 
 def truncation_run(torch, prob, D, reps=3):
