@@ -118,7 +118,7 @@ struct dmrg_plan {
   int kpart = KPART, tile_policy = 0, xcd = 0, flags = 0;
   int macro_min = MACRO_MIN;          // split plans: work-group tiles for outputs >= this (0: none)
   int wide_min = WIDE_MIN;            // split plans, s <= 5: wide tiles for outputs >= this (0: none)
-  bool wg_tiles = true;               // FP64 plans: work-group tiles (set by build_plan)
+  bool wg_tiles = true;               // FP64 plans: work-group tiles possible (set by build_plan)
   int64_t budget = DEFAULT_WORKSPACE;
   int tuned = 0;
   double tune_ms = 0.0;
@@ -252,10 +252,14 @@ int autotune(dmrg_plan *P, void *stream);
 int replan(dmrg_plan *P);
 
 int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
-  P->wg_tiles = true;
-  for (const auto &pp : P->probs)
+  P->wg_tiles = P->precision == DMRG_FP64;
+  int left = 0;   // outputs have the rows of a left sector
+  for (const auto &pp : P->probs) {
     for (const auto *sec : {&pp->L.sec, &pp->R.sec})
       for (const dmrg_sector_t &s : *sec) P->wg_tiles = P->wg_tiles && s.dim < WG_MAX_DIM;
+    for (const dmrg_sector_t &s : pp->L.sec) left = std::max(left, s.dim);
+  }
+  P->wg_tiles = P->wg_tiles && left >= F64_MACRO_MIN;
   // ---- split tasks into chunks whose stripes fit the workspace budget
   std::vector<std::vector<TaskRef>> chunk_tasks(1);
   std::map<StripeKey, std::set<int>> cur;
@@ -312,7 +316,7 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
       s.slots.erase(std::unique(s.slots.begin(), s.slots.end()), s.slots.end());
       for (size_t s0 = 0, s1; s0 < s.slots.size(); s0 = s1) {
         s1 = run_end(s.slots, s0);
-        est1.add(s.dL, (int)(s1 - s0) * s.dRout, 1, s.dRin, 1.0, P->tile_policy);
+        if (P->wg_tiles) est1.add(s.dL, (int)(s1 - s0) * s.dRout, 1, s.dRin, 1.0, P->tile_policy);
       }
     }
     const int level1 = P->wg_tiles ? est1.level() : 0;
@@ -462,6 +466,7 @@ int build_plan(dmrg_plan *P, int64_t budget_bytes, bool device) {
     }
     TileLevel est2;
     for (auto &kv : byF) {
+      if (!P->wg_tiles) break;
       const PsiBlock &F = P->probs[kv.first[0]]->T.blocks[kv.first[2]];
       double k = 0.0;
       for (auto &gi : kv.second) k += gi.first.a_base < 0 ? 0.25 * gi.first.K : (double)gi.first.K;

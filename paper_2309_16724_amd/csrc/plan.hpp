@@ -213,26 +213,34 @@ inline std::vector<Cell> f64_cells(int m, int n, int policy, int level) {
 class TileLevel {
  public:
   // `copies` outputs of m x n, each summing nseg segments of k rows in all
+  // (plans have some 10^5 first-stage outputs: shifts only, and outputs too
+  // narrow for work-group tiles are counted once for all levels)
   void add(int m, int n, int nseg, double k, double copies, int policy) {
-    for (int level = 0; level < 3; level++) {
-      auto part = [&](int rows, int cols, int mb) {
-        if (rows <= 0 || cols <= 0) return;
-        const int tr = tile_rows(mb), tc = tile_cols(mb);
-        const double tiles = (double)((rows + tr - 1) / tr) * ((cols + tc - 1) / tc);
-        const double blocks = (double)((rows + 15) / 16) * ((cols + 15) / 16) / (tiles * (tr * tc / 256));
-        Kind &x = kinds[level][mb == F64_WIDE_MB ? 0 : mb == MACRO_MB ? 1 : 2];
-        x.sum += copies * tiles * (32.0 + 4.0 * nseg + k * (0.5 + 0.5 * blocks));
-        x.top = std::max(x.top, tile_cost(mb, std::min(rows, tr), std::min(cols, tc), nseg, k));
-      };
-      if (level < 2 || !f64_wide(m, n)) {
-        part(m, n, f64_small(m, n, policy, level));
-        continue;
-      }
-      const int mw = wide_lines(m, F64_WIDE_MIN), nw = wide_lines(n, F64_WIDE_MIN);
-      part(mw, nw, F64_WIDE_MB);
-      part(mw, n - nw, f64_small(mw, n - nw, policy, level));
-      part(m - mw, n, f64_small(m - mw, n, policy, level));
-    }
+    const double each = 32.0 + 4.0 * nseg;
+    auto part = [&](Kind &x, int rows, int cols, int r, int c) {   // tiles of 2^r x 2^c
+      if (rows <= 0 || cols <= 0) return;
+      auto blocks = [](int rows_, int cols_) { return (double)((rows_ + 15) >> 4) * ((cols_ + 15) >> 4); };
+      const double share = 0.5 * k / (1 << (r + c - 8));
+      const double tiles = (double)((rows + (1 << r) - 1) >> r) * ((cols + (1 << c) - 1) >> c);
+      x.sum += copies * (tiles * (each + 0.5 * k) + share * blocks(rows, cols));
+      x.top = std::max(x.top, each + 0.5 * k + share * blocks(std::min(rows, 1 << r), std::min(cols, 1 << c)));
+    };
+    auto wave = [&](Kind &x, int rows, int cols) {
+      const int mb = wave_mb(rows, cols, policy);
+      part(x, rows, cols, mb == 1 ? 4 : mb == 2 ? 5 : 6, mb == 1 ? 6 : mb == 2 ? 5 : 4);
+    };
+    if (std::min(m, n) < F64_MACRO_MIN) return wave(narrow, m, n);
+    auto small = [&](int level, int rows, int cols) {
+      if (std::min(rows, cols) >= F64_MACRO_MIN) part(kinds[level][1], rows, cols, 6, 6);
+      else if (rows > 0 && cols > 0) wave(kinds[level][2], rows, cols);
+    };
+    wave(kinds[0][2], m, n);
+    small(1, m, n);
+    if (!f64_wide(m, n)) return small(2, m, n);
+    const int mw = wide_lines(m, F64_WIDE_MIN), nw = wide_lines(n, F64_WIDE_MIN);
+    part(kinds[2][0], mw, nw, 7, 7);
+    small(2, mw, n - nw);
+    small(2, m - mw, n);
   }
   // the usual level 2 unless another one is expected to take less than three
   // quarters of its time
@@ -242,14 +250,17 @@ class TileLevel {
     constexpr double ALONE[3] = {0.16, 0.07, 0.076}, BUSY[3] = {0.30 / 512, 0.17 / 1024, 0.34 / 4096};
     double t[3] = {0.0, 0.0, 0.0};
     for (int l = 0; l < 3; l++)
-      for (int k = 0; k < 3; k++)
-        if (kinds[l][k].sum > 0.0) t[l] += 8.0 + std::max(kinds[l][k].top * ALONE[k], kinds[l][k].sum * BUSY[k]);
+      for (int k = 0; k < 3; k++) {
+        const double sum = kinds[l][k].sum + (k == 2 ? narrow.sum : 0.0);
+        const double top = k == 2 ? std::max(kinds[l][2].top, narrow.top) : kinds[l][k].top;
+        if (sum > 0.0) t[l] += 8.0 + std::max(top * ALONE[k], sum * BUSY[k]);
+      }
     const int best = t[0] < t[1] ? 0 : 1;
     return t[best] < 0.75 * t[2] ? best : 2;
   }
 
  private:
-  struct Kind { double sum = 0.0, top = 0.0; } kinds[3][3];   // by level; wide, 64 x 64, wavefront
+  struct Kind { double sum = 0.0, top = 0.0; } kinds[3][3], narrow;   // by level; wide, 64 x 64, wavefront
 };
 
 // Device copy of FP64 segments: offsets in bytes, absolute addresses where the
