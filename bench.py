@@ -131,8 +131,8 @@ def cpu_baseline(flops_bench, bench_workload):
 
 
 # HBM bytes per launch of the stage kernels (renormalizations: of a stage's
-# launches together) at L54_D2048 from the FETCH_SIZE
-# and WRITE_SIZE runs summarised in profiles/hpsi_L54_D2048_split5.md and
+# launches together) at L54_D2048 from the FETCH_SIZE and WRITE_SIZE runs
+# summarised in profiles/hpsi_L54_D2048_split5.md and
 # profiles/hpsi_L54_D2048_fp64.md: FETCH scaled by 2.000 and WRITE by 1.000,
 # what the same counters read for a plain 256 MiB device copy in the same
 # runs.  A figure holds only while the sources that decide the kernel's memory
@@ -140,18 +140,18 @@ def cpu_baseline(flops_bench, bench_workload):
 _SPLIT_SRC = ("kernels_split.hip", "plan.cpp", "plan.hpp", "model.cpp")
 _F64_SRC = ("kernels_f64.hip", "plan.cpp", "plan.hpp", "model.cpp")
 _REN_SRC = ("renorm.cpp", "kernels_f64.hip", "plan.hpp")
-_SPLIT_HASH, _F64_HASH, _REN_HASH = "2faf80d9bd82fcc3", "775e1157fd1c7a63", "26e8904f973e60e9"
+_SPLIT_HASH, _F64_HASH, _REN_HASH = "6aa173f5b60f2535", "f4f1a8260e536ca0", "2a19cb27913c383b"
 MEASURED_TRAFFIC = {
-    ("L54_D2048", "stage1_wsplit5_kernel"): (1.8150e11, _SPLIT_SRC, _SPLIT_HASH),
-    ("L54_D2048", "stage2_wsplit5_kernel"): (2.7840e11, _SPLIT_SRC, _SPLIT_HASH),
-    ("L54_D2048", "wg_f64_kernel<WgTile<2, 4, 4, 2, 4>, 1>"): (1.6990e11, _F64_SRC, _F64_HASH),
-    ("L54_D2048", "wg_f64_kernel<WgTile<2, 4, 4, 2, 4>, 2>"): (2.6319e11, _F64_SRC, _F64_HASH),
+    ("L54_D2048", "stage1_wsplit5_kernel"): (1.8085e11, _SPLIT_SRC, _SPLIT_HASH),
+    ("L54_D2048", "stage2_wsplit5_kernel"): (2.7743e11, _SPLIT_SRC, _SPLIT_HASH),
+    ("L54_D2048", "wg_f64_kernel<WgTile<2, 4, 4, 2, 4>, 1>"): (1.6908e11, _F64_SRC, _F64_HASH),
+    ("L54_D2048", "wg_f64_kernel<WgTile<2, 4, 4, 2, 4>, 2>"): (2.6309e11, _F64_SRC, _F64_HASH),
     # renormalization of the L54_D2048 left block (profiles/renorm_left_L54_D2048_fp64.md)
-    ("L54_D2048", "renorm:1"): (6.420e10, _REN_SRC, _REN_HASH),
-    ("L54_D2048", "renorm:2"): (5.239e10, _REN_SRC, _REN_HASH),
+    ("L54_D2048", "renorm:1"): (6.397e10, _REN_SRC, _REN_HASH),
+    ("L54_D2048", "renorm:2"): (5.240e10, _REN_SRC, _REN_HASH),
     # the right block through the right site (profiles/renorm_right_L54_D2048_fp64.md)
-    ("L54_D2048", "renorm_right:1"): (1.5735e11, _REN_SRC, _REN_HASH),
-    ("L54_D2048", "renorm_right:2"): (1.1877e11, _REN_SRC, _REN_HASH),
+    ("L54_D2048", "renorm_right:1"): (1.5649e11, _REN_SRC, _REN_HASH),
+    ("L54_D2048", "renorm_right:2"): (1.1777e11, _REN_SRC, _REN_HASH),
 }
 
 
