@@ -347,12 +347,12 @@ void dmrg_mlp_free(dmrg_mlp_t *m);
  * around each tile launch of the first (1) and second (2) stage -- the
  * 128 x 128 and the 64 x 64 work-group tile launches and the wavefront tile
  * launch, of plans of either precision, each with the algorithmic flops of its
- * tiles (slicing launches fall outside the pairs).  dmrg_get_profile waits for the recorded events
- * and returns the number of launches, their summed duration and summed
- * algorithmic flops since the last dmrg_set_profiling call, for stage 1 or 2
- * (all its tile launches), 11 or 12 (its 64 x 64 work-group tile launches
- * only), 21 or 22 (its wavefront tile launches only) or 31 or 32 (its
- * 128 x 128 tile launches only). */
+ * tiles (slicing launches fall outside the pairs).  dmrg_get_profile waits for
+ * the recorded events and returns the number of launches, their summed duration
+ * and summed algorithmic flops since the last dmrg_set_profiling call, for stage
+ * 1 or 2 (all its tile launches), 11 or 12 (its 64 x 64 work-group tile launches
+ * only), 21 or 22 (its wavefront tile launches only) or 31 or 32 (its 128 x 128
+ * tile launches only). */
 int dmrg_set_profiling(dmrg_plan_t *p, int32_t on);
 int dmrg_get_profile(dmrg_plan_t *p, int32_t stage, int64_t *n_launches, double *total_ms,
                      double *total_flops);
